@@ -1,0 +1,45 @@
+"""The fp32 GEMM at the edges of its tiles: all three workgroup tiles, ragged rows, columns and contraction lengths
+(K = 8 leaves half of the only 16-deep chunk empty, K = 136 gives the contraction-splitting waves unequal shares)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_2510_27257_amd as stp
+from harness import rel_err, to_dev, to_host
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = stp.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+@pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(8, 40, 8), (136, 256, 136), (1000, 840, 72), (1032, 776, 264), (2056, 1800, 40), (2048, 1536, 144)])
+def test_gemm_f32(ctx, M, N, K, a_trans, b_trans):
+    rng = np.random.default_rng(M + N + K)
+    A, B = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    R, bias = rng.standard_normal((M, N), dtype=np.float32), rng.standard_normal(N, dtype=np.float32)
+    Ad = to_dev(np.ascontiguousarray(A.T) if a_trans else A, "f32")
+    Bd = to_dev(np.ascontiguousarray(B.T) if b_trans else B, "f32")
+    Rd, bd = to_dev(R, "f32"), to_dev(bias, "f32")
+    Cd = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+    base = dict(dtype=stp.F32, M=M, N=N, K=K, A=Ad.data_ptr(), lda=M if a_trans else K, a_trans=a_trans, B=Bd.data_ptr(),
+                ldb=K if b_trans else N, b_trans=b_trans, C=Cd.data_ptr(), ldc=N, bias_scale=1.0, resid_scale=1.0)
+    AB = A.astype(np.float64) @ B.astype(np.float64)
+    # a sum of K products of unit variance has standard deviation sqrt(K); its rounding error grows like
+    # sqrt(K) * 2^-24 of that: well below 2e-6 of the largest of M * N such values
+    ctx.gemm(stp.GemmArgs(**base))
+    torch.cuda.synchronize()
+    assert rel_err(to_host(Cd), AB) < 2e-6
+    ctx.gemm(stp.GemmArgs(**base | dict(bias=bd.data_ptr(), bias_scale=0.5, resid=Rd.data_ptr(), ldr=N, resid_scale=0.25)))
+    torch.cuda.synchronize()
+    assert rel_err(to_host(Cd), AB + 0.5 * bias + 0.25 * R) < 2e-6
+    before = Cd.clone()
+    ctx.gemm(stp.GemmArgs(**base | dict(c_f32_accum=1)))
+    torch.cuda.synchronize()
+    assert rel_err(to_host(Cd), to_host(before) + AB) < 2e-6
