@@ -1,0 +1,316 @@
+// Attention forward / backward of the fp32 configuration on the fp32 matrix instruction v_mfma_f32_32x32x2_f32
+// (true fp32 products and sums; any head dimension that is a multiple of 8, up to 128).
+//
+// A workgroup owns 32 queries of one head (forward, dQ) or 32 keys of one key / value head (dK, dV); its waves
+// share out the 32-row blocks of the other index (for dK / dV: the pairs of a query head of the group and a query
+// block) and their results are merged through LDS in wave order, so every sum has a fixed order.
+// Scores are formed transposed in the forward and dQ (S^T = K Q^T: a lane's accumulator column is one query, the
+// softmax statistics are per-lane scalars) and straight for dK / dV (the column is one key).  Either way the
+// accumulator is the B operand of the following product as it stands: with the pair of contraction indices
+// (8 j + r, 8 j + 4 + r) given to the two lane halves, its register 4 j + r is the value instruction 4 j + r wants.
+// Operands come straight from L2, as in the fp32 GEMM: 8 consecutive floats per lane where the contraction runs along
+// the row, one float per lane (32 lanes contiguous) where it runs across rows.
+//
+// What bounds it: latency.  At 128 tokens and 4 heads of 64 there are 16 workgroups, and a wave works through one or
+// two 32 x 32 blocks (32 + 32 matrix instructions of 64 clocks each in the forward).  One wave per row with a
+// cross-lane reduction per score was a chain of 128 such reductions: forward / dQ / dK dV 91 / 56 / 46 us against
+// 14 / 11 / 15 us now, the training pass of two microbatches over that layer 554 against 401 us.
+#include "common.h"
+
+int stp_launch_rowdot(stp_ctx *ctx, const stp_layer_desc *d, const void *a, const void *b, float *delta, hipStream_t s);
+
+namespace {
+
+constexpr int RB = 32;      // rows (queries or keys) of a workgroup and of a step
+
+__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+// 8 values of a row for contraction chunk c (16 deep): index 16 c + 8 (lane / 32) .. +7, zero past d (a multiple of 8)
+__device__ __forceinline__ void row_chunk(float (&f)[8], const float *__restrict__ row, int c, int lg, int d) {
+  const int k = 16 * c + 8 * lg;
+  const bool ok = k < d;
+  const float *q = row + (ok ? k : 0);
+  const float4 u = *reinterpret_cast<const float4 *>(q), v = *reinterpret_cast<const float4 *>(q + 4);
+  f[0] = u.x; f[1] = u.y; f[2] = u.z; f[3] = u.w; f[4] = v.x; f[5] = v.y; f[6] = v.z; f[7] = v.w;
+#pragma unroll
+  for (int i = 0; i < 8; i++) f[i] = ok ? f[i] : 0.f;
+}
+__device__ __forceinline__ void zero(f32x16_t &a) {
+#pragma unroll
+  for (int v = 0; v < 16; v++) a[v] = 0.f;
+}
+// row of accumulator register v within its 32 x 32 block
+__device__ __forceinline__ int acc_row(int v, int lg) { return 8 * (v >> 2) + 4 * lg + (v & 3); }
+
+// acc^T[column][.] += X^T p over 32 rows of X: instruction v takes rows acc_row(v, 0) and acc_row(v, 1); rows past the
+// end are read from the last one (their p is zero), columns past d land in accumulator rows that are never stored
+template <int DB>
+__device__ __forceinline__ void add_rows(f32x16_t (&acc)[DB], const float *__restrict__ x, size_t ld, int row0, int last, const f32x16_t &p,
+                                         int lr, int lg, int d) {
+#pragma unroll
+  for (int v = 0; v < 16; v++) {
+    const float *r = x + (size_t)min(row0 + acc_row(v, lg), last) * ld;
+#pragma unroll
+    for (int i = 0; i < DB; i++) acc[i] = mfma_f32(r[min(32 * i + lr, d - 1)], p[v], acc[i]);
+  }
+}
+
+// The waves' accumulators to LDS, then their sum in wave order with a factor per wave and column, four consecutive
+// columns of one row at a time: put(row 0..31, first of four columns, values).
+template <int DB, int NW, typename Factor, typename Put>
+__device__ __forceinline__ void merge_waves(const f32x16_t (&acc)[DB], float *red, int wave, int lane, int d, Factor factor, Put put) {
+#pragma unroll
+  for (int i = 0; i < DB; i++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) red[((wave * DB + i) * 16 + v) * 64 + lane] = acc[i][v];
+  __syncthreads();
+  for (int q = wave; q < 4 * DB; q += NW) {        // group q: block q / 4, registers 4 (q % 4) .. +3
+    const int col = 32 * (q >> 2) + 8 * (q & 3) + 4 * (lane >> 5);
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      const float fw = factor(w);
+#pragma unroll
+      for (int r = 0; r < 4; r++) s[r] += red[(w * DB * 16 + 4 * q + r) * 64 + lane] * fw;
+    }
+    if (col < d) put(lane & 31, col, make_float4(s[0], s[1], s[2], s[3]));
+  }
+}
+
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, float *__restrict__ lse,
+                                                               int seq, int n, int nk, int d, int causal, float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];      // [NW][DB * 16][64], then m [NW][32], l [NW][32]
+  float *red_m = red + NW * DB * 1024, *red_l = red_m + NW * 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * RB;        // the late blocks, which see the most keys, first
+  const int head = blockIdx.y % n, b = blockIdx.y / n;
+  const int a = n * d;
+  const size_t ld = (size_t)(n + 2 * nk) * d;
+  const float *base = qkv + (size_t)b * seq * ld;
+  const float *kp = base + a + (head / (n / nk)) * d, *vp = kp + nk * d;
+  const int qg = q0 + lr;
+  const float *qrow = base + (size_t)min(qg, seq - 1) * ld + head * d;
+  float qf[2 * DB][8];
+#pragma unroll
+  for (int c = 0; c < 2 * DB; c++) row_chunk(qf[c], qrow, c, lg, d);
+  f32x16_t o[DB];
+#pragma unroll
+  for (int i = 0; i < DB; i++) zero(o[i]);
+  float m = -INFINITY, l = 0.f;
+  const int kend = causal ? min(seq, q0 + RB) : seq;
+  for (int k0 = wave * RB; k0 < kend; k0 += NW * RB) {
+    const float *krow = kp + (size_t)min(k0 + lr, seq - 1) * ld;
+    f32x16_t sc;
+    zero(sc);
+#pragma unroll
+    for (int c = 0; c < 2 * DB; c++) {
+      float kf[8];
+      row_chunk(kf, krow, c, lg, d);
+#pragma unroll
+      for (int e = 0; e < 8; e++) sc = mfma_f32(kf[e], qf[c][e], sc);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int key = k0 + acc_row(v, lg);
+      sc[v] = (key >= seq || (causal && key > qg)) ? -INFINITY : sc[v] * scale;
+      mx = fmaxf(mx, sc[v]);
+    }
+    mx = fmaxf(mx, other_half(mx));
+    const float mn = fmaxf(m, mx);                 // finite: key k0 is admissible for every query of the block
+    const float corr = expf(m - mn);
+    float rs = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v++) { sc[v] = expf(sc[v] - mn); rs += sc[v]; }
+    l = l * corr + rs + other_half(rs);
+    m = mn;
+#pragma unroll
+    for (int i = 0; i < DB; i++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) o[i][v] *= corr;
+    add_rows<DB>(o, vp, ld, k0, seq - 1, sc, lr, lg, d);
+  }
+  if (lg == 0) { red_m[wave * 32 + lr] = m; red_l[wave * 32 + lr] = l; }
+  __syncthreads();
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; w++) M = fmaxf(M, red_m[w * 32 + lr]);
+#pragma unroll
+  for (int w = 0; w < NW; w++) L += red_l[w * 32 + lr] * expf(red_m[w * 32 + lr] - M);     // a wave without keys: exp(-inf) = 0
+  const float inv = 1.0f / L;
+  merge_waves<DB, NW>(o, red, wave, lane, d, [&](int w) { return expf(red_m[w * 32 + lr] - M) * inv; },
+                      [&](int r, int col, float4 s) {
+                        if (q0 + r < seq) *reinterpret_cast<float4 *>(out + ((size_t)b * seq + q0 + r) * a + head * d + col) = s;
+                      });
+  if (wave == 0 && lg == 0 && qg < seq) lse[((size_t)b * n + head) * seq + qg] = M + logf(L);
+}
+
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                                  const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                  float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal,
+                                                                  float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * RB;
+  const int head = blockIdx.y % n, b = blockIdx.y / n;
+  const int a = n * d;
+  const size_t ld = (size_t)(n + 2 * nk) * d;
+  const float *base = qkv + (size_t)b * seq * ld;
+  const float *kp = base + a + (head / (n / nk)) * d, *vp = kp + nk * d;
+  const int qg = q0 + lr, qc = min(qg, seq - 1);
+  const float *qrow = base + (size_t)qc * ld + head * d, *grow = dout + ((size_t)b * seq + qc) * a + head * d;
+  const float L = lse[((size_t)b * n + head) * seq + qc], D = delta[((size_t)b * n + head) * seq + qc];
+  float qf[2 * DB][8], gf[2 * DB][8];
+#pragma unroll
+  for (int c = 0; c < 2 * DB; c++) { row_chunk(qf[c], qrow, c, lg, d); row_chunk(gf[c], grow, c, lg, d); }
+  f32x16_t dq[DB];
+#pragma unroll
+  for (int i = 0; i < DB; i++) zero(dq[i]);
+  const int kend = causal ? min(seq, q0 + RB) : seq;
+  for (int k0 = wave * RB; k0 < kend; k0 += NW * RB) {
+    const size_t off = (size_t)min(k0 + lr, seq - 1) * ld;
+    f32x16_t sc, dp;
+    zero(sc);
+    zero(dp);
+#pragma unroll
+    for (int c = 0; c < 2 * DB; c++) {
+      float kf[8], vf[8];
+      row_chunk(kf, kp + off, c, lg, d);
+      row_chunk(vf, vp + off, c, lg, d);
+#pragma unroll
+      for (int e = 0; e < 8; e++) { sc = mfma_f32(kf[e], qf[c][e], sc); dp = mfma_f32(vf[e], gf[c][e], dp); }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int key = k0 + acc_row(v, lg);
+      sc[v] = (key >= seq || (causal && key > qg)) ? 0.f : expf(sc[v] * scale - L) * (dp[v] - D) * scale;
+    }
+    add_rows<DB>(dq, kp, ld, k0, seq - 1, sc, lr, lg, d);
+  }
+  merge_waves<DB, NW>(dq, red, wave, lane, d, [](int) { return 1.0f; },
+                      [&](int r, int col, float4 s) {
+                        if (q0 + r < seq) *reinterpret_cast<float4 *>(dqkv + ((size_t)b * seq + q0 + r) * ld + head * d + col) = s;
+                      });
+}
+
+// sums over the query heads of the key / value head's group
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                                   const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal,
+                                                                   float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
+  const int k0 = (int)blockIdx.x * RB;                               // the early blocks, which most queries see, first
+  const int kh = blockIdx.y % nk, b = blockIdx.y / nk;
+  const int a = n * d, group = n / nk;
+  const size_t ld = (size_t)(n + 2 * nk) * d;
+  const float *base = qkv + (size_t)b * seq * ld;
+  const int key = k0 + lr;
+  const float *krow = base + (size_t)min(key, seq - 1) * ld + a + kh * d, *vrow = krow + nk * d;
+  float kf[2 * DB][8], vf[2 * DB][8];
+#pragma unroll
+  for (int c = 0; c < 2 * DB; c++) { row_chunk(kf[c], krow, c, lg, d); row_chunk(vf[c], vrow, c, lg, d); }
+  f32x16_t dk[DB], dv[DB];
+#pragma unroll
+  for (int i = 0; i < DB; i++) { zero(dk[i]); zero(dv[i]); }
+  const int first = causal ? k0 / RB : 0, nblk = (seq + RB - 1) / RB - first;
+  for (int u = wave; u < group * nblk; u += NW) {
+    const int head = kh * group + u / nblk, q0 = (first + u % nblk) * RB;
+    const float *qp = base + head * d, *gp = dout + (size_t)b * seq * a + head * d;
+    const size_t row = min(q0 + lr, seq - 1);
+    const float *Lr = lse + ((size_t)b * n + head) * seq, *Dr = delta + ((size_t)b * n + head) * seq;
+    f32x16_t p, ds;
+    zero(p);
+    zero(ds);
+#pragma unroll
+    for (int c = 0; c < 2 * DB; c++) {
+      float qf[8], gf[8];
+      row_chunk(qf, qp + row * ld, c, lg, d);
+      row_chunk(gf, gp + row * a, c, lg, d);
+#pragma unroll
+      for (int e = 0; e < 8; e++) { p = mfma_f32(qf[e], kf[c][e], p); ds = mfma_f32(gf[e], vf[c][e], ds); }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int i = q0 + acc_row(v, lg), ic = min(i, seq - 1);
+      const bool masked = i >= seq || (causal && key > i);
+      const float e = masked ? 0.f : expf(p[v] * scale - Lr[ic]);
+      ds[v] = masked ? 0.f : e * (ds[v] - Dr[ic]) * scale;
+      p[v] = e;
+    }
+    add_rows<DB>(dv, gp, a, q0, seq - 1, p, lr, lg, d);
+    add_rows<DB>(dk, qp, ld, q0, seq - 1, ds, lr, lg, d);
+  }
+  float *dkp = dqkv + (size_t)b * seq * ld + a + kh * d, *dvp = dkp + nk * d;
+  merge_waves<DB, NW>(dk, red, wave, lane, d, [](int) { return 1.0f; },
+                      [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dkp + (size_t)(k0 + r) * ld + col) = s; });
+  __syncthreads();
+  merge_waves<DB, NW>(dv, red, wave, lane, d, [](int) { return 1.0f; },
+                      [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dvp + (size_t)(k0 + r) * ld + col) = s; });
+}
+
+// head dimensions up to 64 run 8 waves per workgroup (64 KB of merge area), wider ones 4
+template <int DB> constexpr int waves_of = DB <= 2 ? 8 : 4;
+template <int DB> constexpr size_t lds_of = (size_t)waves_of<DB> * (DB * 1024 + 64) * sizeof(float);
+
+template <int DB>
+int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, float *out, float *lse, hipStream_t s) {
+  constexpr int NW = waves_of<DB>;
+  auto kern = attn_fwd_f32_kernel<DB, NW>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((d->seq + RB - 1) / RB, d->heads_local * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, out, lse, d->seq,
+                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, 1.0f / sqrtf((float)d->head_dim));
+  STP_LAUNCH_CHECK(ctx);
+  return STP_OK;
+}
+
+template <int DB>
+int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, const float *lse, const float *dout, const float *delta, float *dqkv,
+               hipStream_t s) {
+  constexpr int NW = waves_of<DB>;
+  auto kq = attn_bwd_dq_f32_kernel<DB, NW>;
+  auto kkv = attn_bwd_dkv_f32_kernel<DB, NW>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kq), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
+    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
+    attr_set = true;
+  }
+  const int nblk = (d->seq + RB - 1) / RB;
+  const float scale = 1.0f / sqrtf((float)d->head_dim);
+  hipLaunchKernelGGL(kq, dim3(nblk, d->heads_local * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
+                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, scale);
+  STP_LAUNCH_CHECK(ctx);
+  hipLaunchKernelGGL(kkv, dim3(nblk, stp_kv_heads(d) * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
+                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, scale);
+  STP_LAUNCH_CHECK(ctx);
+  return STP_OK;
+}
+
+}  // namespace
+
+int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s) {
+  const float *x = (const float *)qkv;
+  float *o = (float *)out;
+  if (d->head_dim <= 32) return launch_fwd<1>(ctx, d, x, o, lse, s);
+  if (d->head_dim <= 64) return launch_fwd<2>(ctx, d, x, o, lse, s);
+  return launch_fwd<4>(ctx, d, x, o, lse, s);
+}
+
+int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse, const void *dout,
+                            float *delta, void *dqkv, hipStream_t s) {
+  int rc = stp_launch_rowdot(ctx, d, dout, out, delta, s);
+  if (rc != STP_OK) return rc;
+  const float *x = (const float *)qkv, *g = (const float *)dout;
+  float *dx = (float *)dqkv;
+  if (d->head_dim <= 32) return launch_bwd<1>(ctx, d, x, lse, g, delta, dx, s);
+  if (d->head_dim <= 64) return launch_bwd<2>(ctx, d, x, lse, g, delta, dx, s);
+  return launch_bwd<4>(ctx, d, x, lse, g, delta, dx, s);
+}

@@ -223,8 +223,8 @@ const stp_attn_plan *stp_attn_bwd_plan_for(stp_ctx *ctx, const stp_layer_desc *d
 
 size_t stp_attn_fwd_ws_bytes(const stp_layer_desc *d);   // workspace the bf16 attention kernels need (chunk partials)
 size_t stp_attn_bwd_ws_bytes(const stp_layer_desc *d);
-int stp_launch_attn_fwd_generic(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s);
-int stp_launch_attn_bwd_generic(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse,
+int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s);
+int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse,
                                 const void *dout, float *delta, void *dqkv, hipStream_t s);
 // device address of the fixed scratch array of stp_colsum_noalloc on `device` (the current device); a lookup, no allocation
 int stp_noalloc_init(stp_ctx *ctx, int device);

@@ -241,7 +241,7 @@ extern "C" int stp_attention_forward(stp_ctx *ctx, const stp_layer_desc *d, cons
     char *ws = stp_ws_lane(ctx, lane, &lane_bytes);
     return stp_launch_attn_fwd_bf16(ctx, d, qkv, out, lse, (float *)ws, lane_bytes, s);
   }
-  return stp_launch_attn_fwd_generic(ctx, d, qkv, out, lse, s);
+  return stp_launch_attn_fwd_f32(ctx, d, qkv, out, lse, s);
 }
 
 extern "C" int stp_attention_backward(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out,
@@ -261,7 +261,7 @@ extern "C" int stp_attention_backward(stp_ctx *ctx, const stp_layer_desc *d, con
     char *ws = stp_ws_lane(ctx, lane, &lane_bytes);
     return stp_launch_attn_bwd_bf16(ctx, d, qkv, out, lse, dout, delta, dqkv, (float *)ws, lane_bytes, s);
   }
-  return stp_launch_attn_bwd_generic(ctx, d, qkv, out, lse, dout, delta, dqkv, s);
+  return stp_launch_attn_bwd_f32(ctx, d, qkv, out, lse, dout, delta, dqkv, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -43,3 +43,12 @@ def test_gemm_f32(ctx, M, N, K, a_trans, b_trans):
     ctx.gemm(stp.GemmArgs(**base | dict(c_f32_accum=1)))
     torch.cuda.synchronize()
     assert rel_err(to_host(Cd), to_host(before) + AB) < 2e-6
+
+
+# head dimensions at and between the kernels' 32-column blocks; sequences below, at and past a 32-row block and with more
+# blocks than waves; groups; several sequences whose length is not a multiple of 8
+@pytest.mark.parametrize("seq,mbsz,n,d,causal,nk", [(8, 1, 1, 8, True, 0), (32, 1, 2, 40, False, 0), (33, 8, 2, 96, True, 1), (200, 1, 2, 128, True, 1),
+                                                    (164, 2, 3, 72, False, 0), (328, 1, 3, 64, True, 1), (296, 1, 1, 24, False, 0)])
+def test_attention_f32(ctx, seq, mbsz, n, d, causal, nk):
+    import test_gpu_kernels
+    test_gpu_kernels.test_attention_forward_backward(ctx, "f32", seq, mbsz, n, d, causal, nk)
