@@ -1,0 +1,49 @@
+"""The bf16 GEMM at contraction lengths that are not a multiple of the 32-deep K-tile: the last tile is partly empty.
+What lies past K in memory (the padding of the rows, the rows after the last one) is NaN and must not reach a result."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_2510_27257_amd as stp
+from harness import rel_err, to_host
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = stp.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def operand(g, rows, K, std, k_outer):
+    """[rows, K] bf16 stored with a NaN surround; returns (storage, leading dimension, values as fp32)."""
+    x = (torch.randn((rows, K), generator=g, device="cuda") * std).to(torch.bfloat16)
+    if k_outer:
+        store = torch.full((K + 32, rows + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+        store[:K, :rows] = x.t()
+    else:
+        store = torch.full((rows + 1, K + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+        store[:rows, :K] = x
+    return store, store.stride(0), x.float()
+
+
+# (8, 8): one tile, K-tiles 1 .. 5 around the four-stage ring; then shapes that take each of the workgroup tiles
+@pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (8, 8, 40), (136, 264, 72), (264, 136, 120), (520, 776, 152), (1032, 2744, 1000), (3000, 1032, 328),
+                                   (6144, 2048, 1048), (6144, 4096, 88)])
+def test_k_tail(ctx, M, N, K, a_trans, b_trans):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, lda, a = operand(g, M, K, 1.0, a_trans)
+    B, ldb, b = operand(g, N, K, 0.05, not b_trans)
+    ref = a @ b.t()
+    base = dict(dtype=stp.BF16, M=M, N=N, K=K, A=A.data_ptr(), lda=lda, a_trans=a_trans, B=B.data_ptr(), ldb=ldb, b_trans=b_trans, ldc=N,
+                bias_scale=1.0, resid_scale=1.0)
+    C = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+    ctx.gemm(stp.GemmArgs(**base, C=C.data_ptr()))
+    acc = torch.ones((M, N), dtype=torch.float32, device="cuda")
+    ctx.gemm(stp.GemmArgs(**base, C=acc.data_ptr(), c_f32_accum=1))
+    torch.cuda.synchronize()
+    assert rel_err(to_host(C), to_host(ref)) < 4e-3
+    assert rel_err(to_host(acc), to_host(ref) + 1.0) < 1e-5
