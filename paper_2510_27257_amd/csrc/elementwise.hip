@@ -211,34 +211,52 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(const T *__restrict__ x, 
 
 // Column c of the partials belongs to segment c / seg_w, column c % seg_w of that segment's output:
 //   out_k[c % seg_w] += scale_k * sum_{p < nparts} partial[p*stride + c]      (a NULL out_k skips the segment)
-// in a fixed order: a 256-thread group owns 64 columns; thread (c, g) adds up rows g, g+4, g+8, ... (8 independent
-// loads in flight), then the four row-group sums are combined 0+1+2+3 through LDS.  The gain, bias and
-// residual-sum partials of a norm lie side by side (three segments of h columns) and are reduced by one launch;
-// a plain column sum is one segment.
+// in a fixed order.  The gain, bias and residual-sum partials of a norm lie side by side (three segments of h columns)
+// and are reduced by one launch; a plain column sum is one segment.
+// Bound by load latency: the partials of a column are a few hundred values a stride apart.  A 256-thread group owns 32
+// columns as 8 lanes of 4 by 32 row-lanes; a row-lane adds rows g, g + 32, ... in batches of 16 independent 16-byte
+// loads, so the usual 512 partials are one batch; then the 8 row-lanes of a wave are added by cross-lane exchanges and
+// the four waves through LDS.  (4 row-lanes with 8 four-byte loads in flight each took 16 batches: on average 7.6 us over
+// the norm and bias reductions of a 1024-token layer of hidden 1024 against 4.9 us now, 6.6 against 5.9 us over those of
+// [6144, 4096].)
 struct ReduceOut { float *out[3]; float scale[3]; };
 __global__ __launch_bounds__(256) void partial_reduce_kernel(const float *__restrict__ partial, int nparts,
                                                             size_t stride, int n, int seg_w, ReduceOut ro) {
-  __shared__ float red[4][64];
-  const int cl = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
+  __shared__ float4 red[4][8];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, cl = lane & 7, g = wv * 8 + (lane >> 3);
+  const int c = (blockIdx.x * 8 + cl) * 4;                  // n and seg_w are multiples of 4
   const int seg = c < n ? c / seg_w : 0;
   float *const dst = seg == 0 ? ro.out[0] : (seg == 1 ? ro.out[1] : ro.out[2]);
   const float scale = seg == 0 ? ro.scale[0] : (seg == 1 ? ro.scale[1] : ro.scale[2]);
-  float s = 0.f;
-  if (c < n && dst) {
-    int p = g;
-    for (; p + 28 < nparts; p += 32) {
-      float v[8];
+  const bool live = c < n && dst;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  if (live) {
+    constexpr int U = 16;
+    for (int p0 = g; p0 < nparts; p0 += 32 * U) {
+      float4 v[U];
 #pragma unroll
-      for (int u = 0; u < 8; u++) v[u] = partial[(size_t)(p + 4 * u) * stride + c];
+      for (int u = 0; u < U; u++) {
+        const int p = p0 + 32 * u;
+        v[u] = p < nparts ? *reinterpret_cast<const float4 *>(partial + (size_t)p * stride + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
 #pragma unroll
-      for (int u = 0; u < 8; u++) s += v[u];
+      for (int u = 0; u < U; u++) { s[0] += v[u].x; s[1] += v[u].y; s[2] += v[u].z; s[3] += v[u].w; }
     }
-    for (; p < nparts; p += 4) s += partial[(size_t)p * stride + c];
   }
-  red[g][cl] = s;
+#pragma unroll
+  for (int m = 8; m < 64; m <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; e++) s[e] += __shfl_xor(s[e], m);
+  if (lane < 8) red[wv][cl] = make_float4(s[0], s[1], s[2], s[3]);
   __syncthreads();
-  if (g == 0 && c < n && dst) dst[c - seg * seg_w] += scale * (((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl]);
+  if (threadIdx.x < 8 && live) {
+    const float4 a = red[0][cl], b = red[1][cl], d = red[2][cl], e = red[3][cl];
+    float *o = dst + (c - seg * seg_w);
+    o[0] += scale * ((a.x + b.x) + (d.x + e.x));
+    o[1] += scale * ((a.y + b.y) + (d.y + e.y));
+    o[2] += scale * ((a.z + b.z) + (d.z + e.z));
+    o[3] += scale * ((a.w + b.w) + (d.w + e.w));
+  }
 }
 
 // ======================================================================
@@ -639,7 +657,7 @@ extern "C" int stp_norm_backward(stp_ctx *ctx, int dtype, int norm, int32_t T, i
   if (partial) {   // the partials of a row group lie side by side: [gain | bias | residual sum]
     const int segs = rsum ? 3 : 2;
     ReduceOut ro = {{dgamma, want_beta ? dbeta : nullptr, d_resid_sum}, {1.0f, 1.0f, d_resid_sum_scale}};
-    hipLaunchKernelGGL(partial_reduce_kernel, dim3((segs * h + 63) / 64), dim3(256), 0, s, partial, blocks, (size_t)segs * h, segs * h, h, ro);
+    hipLaunchKernelGGL(partial_reduce_kernel, dim3((segs * h + 31) / 32), dim3(256), 0, s, partial, blocks, (size_t)segs * h, segs * h, h, ro);
     STP_LAUNCH_CHECK(ctx);
   }
   return STP_OK;
@@ -653,7 +671,7 @@ static int colsum_launch(stp_ctx *ctx, int dtype, int T, int N, const void *x, f
   else hipLaunchKernelGGL((colsum_kernel<float, 8>), grid, block, 0, s, (const float *)x, T, N, partial);
   STP_LAUNCH_CHECK(ctx);
   ReduceOut ro = {{out, nullptr, nullptr}, {scale, 0.f, 0.f}};
-  hipLaunchKernelGGL(partial_reduce_kernel, dim3((N + 63) / 64), dim3(256), 0, s, partial, slabs, (size_t)N, N, N, ro);
+  hipLaunchKernelGGL(partial_reduce_kernel, dim3((N + 31) / 32), dim3(256), 0, s, partial, slabs, (size_t)N, N, N, ro);
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }
