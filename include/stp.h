@@ -311,13 +311,15 @@ typedef struct {
   void *C2; const void *aux; int32_t ld2;
   int32_t tile_m, tile_n;  /* 0, 0: the library picks the workgroup tile from the shape.  Otherwise each
                             * 128 or 256, or 192 x 256 with a_trans = 0 (bf16 with K a multiple of 32
-                            * only): forces that tile, for tuning and tests; anything else is STP_EINVAL */
+                            * only): forces that tile, for tuning and tests (where the library would split the
+                            * contraction of a small output over waves, the last bits may differ); anything else is STP_EINVAL */
 } stp_gemm_args;
 int stp_gemm(stp_ctx *ctx, const stp_gemm_args *args, void *hip_stream);
 /* A measured tile preference for the bf16 GEMM of one shape and operand order, used for launches that
  * stp_braid_step issues on concurrent streams (Section 3: the units of a block share the GPU).  Which tile is
  * fastest there depends on the kernels of the other streams; the library's own choice models the GEMM alone.
- * Results do not depend on the tile (every element is summed over K in the same order).  tile_m = tile_n = 0
+ * Results do not depend on the tile (every element is summed over K in the same order; outputs of at most 256 tiles of
+ * 64 x 64, whose contraction is split over the waves of a workgroup, take no preference).  tile_m = tile_n = 0
  * forgets the preference for that shape.  Host only; at most 96 shapes per context (STP_ENOSPACE);
  * STP_EINVAL for a tile stp_gemm_args.tile_m / tile_n would not take. */
 int stp_gemm_tile_hint(stp_ctx *ctx, int32_t M, int32_t N, int32_t K, int a_trans, int b_trans,

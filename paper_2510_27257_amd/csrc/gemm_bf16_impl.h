@@ -136,6 +136,70 @@ __device__ __forceinline__ void map_tile(int tiles_m, int tiles_n, int &tm, int 
   tn = (pid % (GROUP_M * tiles_n)) / gsize;
 }
 
+// What the epilogue of 8 consecutive columns of one row reads from global memory: residual / aux in lo (8 bf16), the fp32
+// accumulator in lo and hi.  Rows / columns past M / N are read from a clamped address and never stored.
+struct EpiPre { uint4 lo, hi; };
+template <int EPI>
+__device__ __forceinline__ void epi_fetch(EpiPre &f, int row_, int col_, int M, int N, const Epi &ep) {
+  const size_t row = (size_t)min(row_, M - 1);
+  const int col = min(col_, N - 8);
+  if (EPI == EPI_F32_ACCUM) {
+    const uint4 *cp = reinterpret_cast<const uint4 *>(reinterpret_cast<const float *>(ep.C) + row * ep.ldc + col);
+    f.lo = cp[0];
+    f.hi = cp[1];
+  } else if (EPI == EPI_GELU_BWD) {
+    f.lo = *reinterpret_cast<const uint4 *>(ep.aux + row * ep.ld2 + col);
+  } else if (ep.resid != nullptr) {
+    f.lo = *reinterpret_cast<const uint4 *>(ep.resid + row * ep.ldr + col);
+  }
+}
+__device__ __forceinline__ void epi_bias(float (&bias)[8], int col, int N, const Epi &ep) {
+#pragma unroll
+  for (int e = 0; e < 8; e++) bias[e] = 0.f;
+  if (ep.bias != nullptr) {
+    Vec8<bf16_t>::load(ep.bias + min(col, N - 8), bias);
+#pragma unroll
+    for (int e = 0; e < 8; e++) bias[e] *= ep.bias_scale;
+  }
+}
+// val: the 8 sums; applies the epilogue and stores
+template <int EPI>
+__device__ __forceinline__ void epi_store(float (&val)[8], const float (&bias)[8], const EpiPre &f, int row, int col, int M, int N, const Epi &ep) {
+#pragma unroll
+  for (int e = 0; e < 8; e++) val[e] += bias[e];
+  if (EPI == EPI_F32_ACCUM) {
+    float old[8];
+    old[0] = __builtin_bit_cast(float, f.lo.x); old[1] = __builtin_bit_cast(float, f.lo.y);
+    old[2] = __builtin_bit_cast(float, f.lo.z); old[3] = __builtin_bit_cast(float, f.lo.w);
+    old[4] = __builtin_bit_cast(float, f.hi.x); old[5] = __builtin_bit_cast(float, f.hi.y);
+    old[6] = __builtin_bit_cast(float, f.hi.z); old[7] = __builtin_bit_cast(float, f.hi.w);
+#pragma unroll
+    for (int e = 0; e < 8; e++) old[e] += val[e];
+    if (row < M && col < N) Vec8<float>::store(reinterpret_cast<float *>(ep.C) + (size_t)row * ep.ldc + col, old);
+  } else {
+    if (EPI == EPI_GELU_BWD || ep.resid != nullptr) {
+      const bf16x8_t h8 = __builtin_bit_cast(bf16x8_t, f.lo);
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        if (EPI == EPI_GELU_BWD) val[e] *= gelu_grad_t<bf16_t>((float)h8[e]);
+        else val[e] += (float)h8[e] * ep.resid_scale;
+      }
+    }
+    bf16x8_t o;
+#pragma unroll
+    for (int e = 0; e < 8; e++) o[e] = (bf16_t)val[e];
+    if (row < M && col < N) {
+      *reinterpret_cast<bf16x8_t *>(reinterpret_cast<bf16_t *>(ep.C) + (size_t)row * ep.ldc + col) = o;
+      if (EPI == EPI_GELU_DUAL) {
+        float gv[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) gv[e] = gelu_t<bf16_t>((float)o[e]);
+        Vec8<bf16_t>::store(ep.C2 + (size_t)row * ep.ld2 + col, gv);
+      }
+    }
+  }
+}
+
 // Epilogue.  Accumulator v of lane l is C[32*i + 8*(v/4) + 4*(l/32) + v%4][32*j + l%32].
 // Each wave stages one 32 x WN strip at a time in its own LDS area (fp32, pitch WN + 8 keeps the two
 // lane halves on different banks) and reads it back row-wise, 8 consecutive columns per lane, so
@@ -143,17 +207,15 @@ __device__ __forceinline__ void map_tile(int tiles_m, int tiles_n, int &tm, int 
 // The staging area is private to the wave (LDS operations of a wave complete in order), so no barrier
 // is needed.  What the epilogue reads from global memory (residual, aux, the fp32 accumulator) is
 // fetched one strip ahead, all passes of a strip at once, so that its latency is paid once per tile
-// and not once per pass.  Rows / columns past M / N are read from a clamped address and never stored.
+// and not once per pass.
 // The caller guarantees that the operand stages in LDS are dead (barrier after the last K-tile).
 template <int MI, int NI, int WN, int EPI>
 __device__ __forceinline__ void store_tile(f32x16_t (&acc)[MI][NI], float *stage, int row_base, int col_base, int M, int N,
                                            const Epi &ep, int lane) {
   constexpr int SP = WN + 8;
   const int lr = lane & 31, lg = lane >> 5;
-  const bool has_bias = ep.bias != nullptr, has_resid = ep.resid != nullptr;
   constexpr int LPR = WN / 8;             // lanes per staged row
   constexpr int PASSES = 32 * LPR / 64;
-  constexpr bool ACC = EPI == EPI_F32_ACCUM, AUX = EPI == EPI_GELU_BWD;
   // pass p of a strip: staged row r_p, columns c_p .. c_p+7 (the same for every strip)
   int pr[PASSES], pc[PASSES];
   float bias[PASSES][8];
@@ -162,84 +224,27 @@ __device__ __forceinline__ void store_tile(f32x16_t (&acc)[MI][NI], float *stage
     const int idx = p * 64 + lane;
     pr[p] = idx / LPR;
     pc[p] = col_base + (idx % LPR) * 8;
-#pragma unroll
-    for (int e = 0; e < 8; e++) bias[p][e] = 0.f;
-    if (has_bias) {
-      Vec8<bf16_t>::load(ep.bias + min(pc[p], N - 8), bias[p]);
-#pragma unroll
-      for (int e = 0; e < 8; e++) bias[p][e] *= ep.bias_scale;
-    }
+    epi_bias(bias[p], pc[p], N, ep);
   }
   // what strip i needs from global memory
-  struct Pre { uint4 lo[PASSES], hi[PASSES]; };   // resid / aux: lo (8 bf16); fp32 accumulator: lo, hi (8 floats)
-  auto fetch = [&](int i, Pre &f) {
+  auto fetch = [&](int i, EpiPre (&f)[PASSES]) {
 #pragma unroll
-    for (int p = 0; p < PASSES; p++) {
-      const size_t row = (size_t)min(row_base + i * 32 + pr[p], M - 1);
-      const int col = min(pc[p], N - 8);
-      if (ACC) {
-        const uint4 *cp = reinterpret_cast<const uint4 *>(reinterpret_cast<const float *>(ep.C) + row * ep.ldc + col);
-        const uint4 a = cp[0], b = cp[1];
-        f.lo[p].x = a.x; f.lo[p].y = a.y; f.lo[p].z = a.z; f.lo[p].w = a.w;
-        f.hi[p].x = b.x; f.hi[p].y = b.y; f.hi[p].z = b.z; f.hi[p].w = b.w;
-      } else if (AUX) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(ep.aux + row * ep.ld2 + col);
-        f.lo[p].x = a.x; f.lo[p].y = a.y; f.lo[p].z = a.z; f.lo[p].w = a.w;
-      } else if (has_resid) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(ep.resid + row * ep.ldr + col);
-        f.lo[p].x = a.x; f.lo[p].y = a.y; f.lo[p].z = a.z; f.lo[p].w = a.w;
-      }
-    }
+    for (int p = 0; p < PASSES; p++) epi_fetch<EPI>(f[p], row_base + i * 32 + pr[p], pc[p], M, N, ep);
   };
-  auto strip = [&](int i, const Pre &f) {
+  auto strip = [&](int i, const EpiPre (&f)[PASSES]) {
 #pragma unroll
     for (int j = 0; j < NI; j++)
 #pragma unroll
       for (int v = 0; v < 16; v++) stage[(8 * (v >> 2) + 4 * lg + (v & 3)) * SP + 32 * j + lr] = acc[i][j][v];
 #pragma unroll
     for (int p = 0; p < PASSES; p++) {
-      const int row = row_base + i * 32 + pr[p], col = pc[p];
       float val[8];
-      Vec8<float>::load(stage + pr[p] * SP + (col - col_base), val);
-#pragma unroll
-      for (int e = 0; e < 8; e++) val[e] += bias[p][e];
-      if (ACC) {
-        float old[8];
-        old[0] = __builtin_bit_cast(float, f.lo[p].x); old[1] = __builtin_bit_cast(float, f.lo[p].y);
-        old[2] = __builtin_bit_cast(float, f.lo[p].z); old[3] = __builtin_bit_cast(float, f.lo[p].w);
-        old[4] = __builtin_bit_cast(float, f.hi[p].x); old[5] = __builtin_bit_cast(float, f.hi[p].y);
-        old[6] = __builtin_bit_cast(float, f.hi[p].z); old[7] = __builtin_bit_cast(float, f.hi[p].w);
-#pragma unroll
-        for (int e = 0; e < 8; e++) old[e] += val[e];
-        if (row < M && col < N) Vec8<float>::store(reinterpret_cast<float *>(ep.C) + (size_t)row * ep.ldc + col, old);
-      } else {
-        if (AUX || has_resid) {
-          uint4 raw;
-          raw.x = f.lo[p].x; raw.y = f.lo[p].y; raw.z = f.lo[p].z; raw.w = f.lo[p].w;
-          const bf16x8_t h8 = __builtin_bit_cast(bf16x8_t, raw);
-#pragma unroll
-          for (int e = 0; e < 8; e++) {
-            if (AUX) val[e] *= gelu_grad_t<bf16_t>((float)h8[e]);
-            else val[e] += (float)h8[e] * ep.resid_scale;
-          }
-        }
-        bf16x8_t o;
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = (bf16_t)val[e];
-        if (row < M && col < N) {
-          *reinterpret_cast<bf16x8_t *>(reinterpret_cast<bf16_t *>(ep.C) + (size_t)row * ep.ldc + col) = o;
-          if (EPI == EPI_GELU_DUAL) {
-            float gv[8];
-#pragma unroll
-            for (int e = 0; e < 8; e++) gv[e] = gelu_t<bf16_t>((float)o[e]);
-            Vec8<bf16_t>::store(ep.C2 + (size_t)row * ep.ld2 + col, gv);
-          }
-        }
-      }
+      Vec8<float>::load(stage + pr[p] * SP + (pc[p] - col_base), val);
+      epi_store<EPI>(val, bias[p], f[p], row_base + i * 32 + pr[p], pc[p], M, N, ep);
     }
   };
-  // strips alternate between two prefetch buffers; MI is 2 or 4
-  Pre f0, f1;
+  // strips alternate between two prefetch buffers
+  EpiPre f0[PASSES], f1[PASSES];
   fetch(0, f0);
 #pragma unroll
   for (int i = 0; i < MI; i += 2) {
@@ -332,7 +337,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 // side and undone in the fragment address):
 //   k-contiguous operand : tile [rows][32], 4 chunks per row; chunk c of row r sits in slot c ^ ((r>>2)&3)
 //   row-contiguous operand: tile [32][rows], rows/8 chunks per k-row; chunk c of k-row k sits in slot
-//                           c ^ (4*(k&3))   (read back with ds_read_b64_tr_b16)
+//                           c ^ (4*(k&3))   (read back with ds_read_b64_tr_b16); tiles of 64 rows, whose k-row is
+//                           half of the 64 banks: c ^ (4*((k>>1)&1))
 //
 // Schedule.  Two waves per SIMD run freely (no phase lock); each wave software-pipelines its fragments:
 // the LDS reads of the next 16-deep step are issued before the 8..16 MFMAs of the current one, so LDS
@@ -353,33 +359,39 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 constexpr int DK = 32;         // K-tile depth of the DMA kernel
 constexpr int DSTAGES = 4;
 
-template <int ROWS, bool KC, int NWAVES>
+template <int ROWS, bool KC, int NWAVES, int DEPTH = DK>
 struct DmaOp {
+  static_assert(DEPTH == 32 || DEPTH == 64, "K-tile depth");
   static_assert(ROWS % 16 == 0, "a tile is a whole number of 1 KB pieces per K-tile");
-  static_assert(KC || (ROWS / 8) % 16 == 0, "the chunk permutation of a row-contiguous tile works on blocks of 16 chunks");
-  static constexpr int PIECES = ROWS / 16;                               // 1 KB pieces (wave instructions) per K-tile
+  static_assert(KC || (ROWS / 8) % 8 == 0, "the chunk permutation of a row-contiguous tile works on blocks of 8 or 16 chunks");
+  static constexpr int PIECES = ROWS * DEPTH / 512;                      // 1 KB pieces (wave instructions) per K-tile
   static constexpr int NINST = (PIECES + NWAVES - 1) / NWAVES;           // issue slots per wave per K-tile
   static constexpr bool EVEN = PIECES % NWAVES == 0;                     // every slot of every wave has a piece
-  static constexpr int bytes = ROWS * DK * 2;
-  static constexpr int CPR = ROWS / 8;                   // 16-byte chunks per k-row (row-contiguous operand)
+  static constexpr int bytes = ROWS * DEPTH * 2;
+  static constexpr int CPR = KC ? DEPTH / 8 : ROWS / 8;                  // 16-byte chunks per tile row (k-contiguous) or k-row
   static constexpr int LDS_OPS_PER_FRAG = KC ? 1 : 2;
+  // chunk permutation of row r (k-contiguous) or k-row r (row-contiguous)
+  static __device__ __forceinline__ int swz(int r) {
+    if (KC) return DEPTH == 32 ? (r >> 2) & 3 : (r >> 1) & 7;
+    return CPR % 16 == 0 ? 4 * (r & 3) : 4 * ((r >> 1) & 1);
+  }
   // piece that slot j of wave `wave` loads; pieces >= PIECES do not exist (the slot then loads piece 0 again,
   // into a dump area: every wave issues the same number of loads per K-tile, which the vmcnt waits rely on)
   static __device__ __forceinline__ int piece(int j, int wave) { return wave + NWAVES * j; }
   // byte offset (from the operand base, K-tile 0) of the chunk that lane `lane` of this wave's j-th
   // instruction must fetch; a chunk at or past k_lim (within the K-tile) is replaced by one at its beginning
-  static __device__ __forceinline__ unsigned chunk_offset(int j, int wave, int lane, int ld, int row0, int row_lim, int k_lim = DK) {
+  static __device__ __forceinline__ unsigned chunk_offset(int j, int wave, int lane, int ld, int row0, int row_lim, int k_lim = DEPTH) {
     const int pc = piece(j, wave);
     const int p = (pc < PIECES ? pc : 0) * 64 + lane;
     if (KC) {
-      const int r = p >> 2;
-      int c = (p & 3) ^ ((r >> 2) & 3);
+      const int r = p / CPR;
+      int c = (p % CPR) ^ swz(r);
       if (c * 8 >= k_lim) c = 0;
       const int row = min(row0 + r, row_lim - 1);
       return ((unsigned)row * (unsigned)ld + c * 8) * 2u;
     } else {
       int k = p / CPR;
-      const int c = (p % CPR) ^ (4 * (k & 3));
+      const int c = (p % CPR) ^ swz(k);
       if (k >= k_lim) k = 0;
       int col = row0 + c * 8;
       col = col < row_lim ? col : 0;
@@ -387,33 +399,33 @@ struct DmaOp {
     }
   }
   // LDS byte offsets (within a tile) from which the fragments of rows row .. row + 32*NF - 1 are read:
-  // k-contiguous: one address per 16-deep half (fragment i adds 32 rows = 2048 bytes as an immediate);
-  // row-contiguous: one address per fragment (the half adds 16 k-rows as an immediate).
+  // k-contiguous: one address per 16-deep step (fragment i adds 32 rows as an immediate);
+  // row-contiguous: one address per fragment (a step adds 16 k-rows as an immediate).
   template <int NF>
-  static __device__ __forceinline__ void frag_bases(unsigned (&ad)[KC ? 2 : NF], int row, int lane) {
+  static __device__ __forceinline__ void frag_bases(unsigned (&ad)[KC ? DEPTH / 16 : NF], int row, int lane) {
     if (KC) {
       const int r = row + (lane & 31);
 #pragma unroll
-      for (int h = 0; h < 2; h++) {
+      for (int h = 0; h < DEPTH / 16; h++) {
         const int c = 2 * h + (lane >> 5);
-        ad[h] = (r * 4 + (c ^ ((r >> 2) & 3))) * 16;
+        ad[h] = (r * CPR + (c ^ swz(r))) * 16;
       }
     } else {
       const int k = 8 * (lane >> 5) + ((lane & 15) >> 2);
 #pragma unroll
       for (int i = 0; i < NF; i++) {
         const int col = row + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        ad[i] = (k * CPR + ((col >> 3) ^ (4 * (k & 3)))) * 16 + (col & 7) * 2;
+        ad[i] = (k * CPR + ((col >> 3) ^ swz(k))) * 16 + (col & 7) * 2;
       }
     }
   }
-  // issues the reads of the NF fragments of half H (k = 16*H .. 16*H+15) of the tile at LDS address `tile`
+  // issues the reads of the NF fragments of step H (k = 16*H .. 16*H+15) of the tile at LDS address `tile`
   template <int H, int NF, int... I>
-  static __device__ __forceinline__ void frag_issue(u32x4_t (&f)[NF], const unsigned (&ad)[KC ? 2 : NF], unsigned tile,
+  static __device__ __forceinline__ void frag_issue(u32x4_t (&f)[NF], const unsigned (&ad)[KC ? DEPTH / 16 : NF], unsigned tile,
                                                     std::integer_sequence<int, I...>) {
     if constexpr (KC) {
       const unsigned a = ad[H] + tile;
-      ((f[I] = lds_read_b128<I * 2048>(a)), ...);
+      ((f[I] = lds_read_b128<I * 32 * DEPTH * 2>(a)), ...);
     } else {
       ((f[I] = lds_read_tr16<H * 16 * CPR * 16, 4 * CPR * 16>(ad[I] + tile)), ...);
     }
@@ -591,6 +603,173 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
 #endif
 }
 
+// =====================================================================================================
+// Few output tiles: a 64 x 64 tile whose contraction is shared out over the four waves of a workgroup.
+//
+// For outputs of so few 128 x 128 tiles that most of the 256 compute units would idle ([1024, 1024]: 64 tiles, each a
+// chain of K / 32 K-tiles behind barriers).  Wave w takes the WK-deep K-tiles w, w + 4, ... of the whole tile through a
+// ring of its own, so there is no barrier until the four partial sums are added (in wave order, through LDS); a
+// fragment feeds two MFMAs instead of one, and four K-tiles advance at a time.  (The same tile as 2 x 2 waves with a
+// barrier per 64-deep stage spent 350 clocks per 32-deep K-tile on barrier, LDS and load-issue latency one after the
+// other, whatever the depth of the ring: 18.6 us for [1024, 1024] K = 4096 against 15.5.)
+// Bound by what a compute unit takes in: 41 B per clock at K = 4096.  Rows of a k-contiguous operand are fetched 128 bytes
+// at a time (WK = 64): with 64-byte pieces L2 delivers half as much per request and the same shape takes 18 us.  Without
+// such an operand a row-contiguous tile has 128-byte rows anyway and 32-deep K-tiles, more of them in flight, are the
+// faster (weight gradient [320, 784] K = 1824: 8.0 against 9.2 us).
+// The sum over K is taken in another order than in the tiles above, so who takes this kernel is a question of the
+// shape alone (never of other streams or tile preferences): see wavek_shape.
+// =====================================================================================================
+template <int WK, bool A_KC, bool B_KC, int EPI, bool KTAIL>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_wavek_kernel(const bf16_t *__restrict__ A, int lda, int a_bytes, const bf16_t *__restrict__ B,
+                                                                 int ldb, int b_bytes, int M, int N, int K, int tiles_m, int tiles_n, Epi ep) {
+  constexpr int BM = 64, BN = 64, KS = 4, NSTG = 128 / WK, MI = 2, NI = 2;
+  using OA = DmaOp<BM, A_KC, 1, WK>;
+  using OB = DmaOp<BN, B_KC, 1, WK>;
+  constexpr int STAGE_BYTES = OA::bytes + OB::bytes;
+  constexpr int LOADS = OA::NINST + OB::NINST;                       // per K-tile
+  constexpr int READS = MI * OA::LDS_OPS_PER_FRAG + NI * OB::LDS_OPS_PER_FRAG;   // per 16-deep step
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  map_tile(tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A), 0, a_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(B), 0, b_bytes, 0x00020000);
+  const int k_rem = KTAIL ? K % WK : WK;
+  unsigned offa[OA::NINST], offb[OB::NINST], taila[OA::NINST], tailb[OB::NINST];
+#pragma unroll
+  for (int j = 0; j < OA::NINST; j++) {
+    offa[j] = OA::chunk_offset(j, 0, lane, lda, m0, M);
+    taila[j] = KTAIL ? OA::chunk_offset(j, 0, lane, lda, m0, M, k_rem) : offa[j];
+  }
+#pragma unroll
+  for (int j = 0; j < OB::NINST; j++) {
+    offb[j] = OB::chunk_offset(j, 0, lane, ldb, n0, N);
+    tailb[j] = KTAIL ? OB::chunk_offset(j, 0, lane, ldb, n0, N, k_rem) : offb[j];
+  }
+  const unsigned stepa = (A_KC ? (unsigned)WK : (unsigned)WK * lda) * 2u, stepb = (B_KC ? (unsigned)WK : (unsigned)WK * ldb) * 2u;
+  unsigned ada[A_KC ? WK / 16 : MI], adb[B_KC ? WK / 16 : NI];
+  OA::template frag_bases<MI>(ada, 0, lane);
+  OB::template frag_bases<NI>(adb, 0, lane);
+  char *const ring = smem_raw + wave * NSTG * STAGE_BYTES;
+  const unsigned lds0 = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)ring;
+
+  f32x16_t acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; i++)
+#pragma unroll
+    for (int j = 0; j < NI; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+
+  const int KT = KTAIL ? K / WK + 1 : K / WK, NT = (KT - wave + KS - 1) / KS;      // this wave's K-tiles: wave, wave + KS, ...
+  auto issue = [&](int t) {
+    const int kt = t * KS + wave;
+    const bool last = KTAIL && kt == KT - 1;
+    char *st = ring + (t % NSTG) * STAGE_BYTES;
+#pragma unroll
+    for (int q = 0; q < OA::NINST; q++) dma_load16(ra, st + q * 1024, last ? taila[q] : offa[q], kt * stepa);
+#pragma unroll
+    for (int q = 0; q < OB::NINST; q++) dma_load16(rb, st + OA::bytes + q * 1024, last ? tailb[q] : offb[q], kt * stepb);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Seq2 = std::make_integer_sequence<int, 2>;
+  u32x4_t fa[2][MI], fb[2][NI];                  // fragments of two consecutive 16-deep steps
+#define STP_READ(H, t)                                                               \
+  do {                                                                               \
+    const unsigned t_ = lds0 + (unsigned)((t) % NSTG) * STAGE_BYTES;                 \
+    OA::template frag_issue<H>(fa[(H) & 1], ada, t_, Seq2{});                        \
+    OB::template frag_issue<H>(fb[(H) & 1], adb, t_ + OA::bytes, Seq2{});            \
+    __builtin_amdgcn_sched_barrier(0);                                               \
+  } while (0)
+#define STP_MFMAS(H, t)                                                              \
+  do {                                                                               \
+    lds_tie(fa[(H) & 1]);                                                            \
+    lds_tie(fb[(H) & 1]);                                                            \
+    if (KTAIL && (t) * KS + wave == KT - 1) {                                        \
+      const unsigned keep = 16 * (H) + 8 * (lane >> 5) < k_rem ? ~0u : 0u;           \
+      _Pragma("unroll") for (int i = 0; i < 2; i++) { fa[(H) & 1][i] &= keep; fb[(H) & 1][i] &= keep; } \
+    }                                                                                \
+    _Pragma("unroll") for (int i = 0; i < MI; i++)                                   \
+      _Pragma("unroll") for (int j = 0; j < NI; j++)                                 \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[(H) & 1][i]),                \
+                                                            __builtin_bit_cast(bf16x8_t, fb[(H) & 1][j]), acc[i][j], 0, 0, 0); \
+    __builtin_amdgcn_sched_barrier(0);                                               \
+  } while (0)
+  // waits until at most n of this wave's K-tiles are still on their way
+  auto wait_tiles = [&](int n) {
+    if (n >= NSTG - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTG - 1) * LOADS) : "memory");
+    else if (NSTG > 2 && n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
+    else if (NSTG > 2 && n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int t = 0; t < NSTG; t++)
+    if (t < NT) issue(t);
+  if (NT > 0) {
+    wait_tiles(NT - 1);
+    STP_READ(0, 0);
+  }
+  for (int t = 0; t < NT; t++) {
+    STP_READ(1, t);
+    lds_wait<READS>();
+    STP_MFMAS(0, t);
+    if constexpr (WK == 64) {
+      STP_READ(2, t);
+      lds_wait<READS>();
+      STP_MFMAS(1, t);
+      STP_READ(3, t);
+      lds_wait<READS>();
+      STP_MFMAS(2, t);
+    }
+    // this wave's reads of K-tile t are complete: its slot takes K-tile t + NSTG; K-tile t+1 has to land
+    lds_wait<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + NSTG < NT) issue(t + NSTG);
+    wait_tiles(NT - 2 - t);
+    if (t + 1 < NT) STP_READ(0, t + 1);
+    STP_MFMAS(WK / 16 - 1, t);
+  }
+#undef STP_READ
+#undef STP_MFMAS
+  // ---- partial sums to LDS (pitch 72: the lane halves, 4 rows apart, use different banks), added in wave order
+  constexpr int RP = BN + 8;
+  float *red = reinterpret_cast<float *>(smem_raw);                  // [KS][64][RP]
+  int pr[2], pc;
+  EpiPre pre[2];
+  float bias[8];
+  pc = n0 + (tid & 7) * 8;
+  epi_bias(bias, pc, N, ep);
+#pragma unroll
+  for (int p = 0; p < 2; p++) {
+    pr[p] = p * 32 + (tid >> 3);
+    epi_fetch<EPI>(pre[p], m0 + pr[p], pc, M, N, ep);
+  }
+  __syncthreads();                                                   // every wave is done with its ring
+  const int lr = lane & 31, lg = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < MI; i++)
+#pragma unroll
+    for (int j = 0; j < NI; j++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) red[(wave * BM + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3)) * RP + 32 * j + lr] = acc[i][j][v];
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 2; p++) {
+    float val[8], part[8];
+    Vec8<float>::load(red + pr[p] * RP + (tid & 7) * 8, val);
+#pragma unroll
+    for (int w = 1; w < KS; w++) {
+      Vec8<float>::load(red + (w * BM + pr[p]) * RP + (tid & 7) * 8, part);
+#pragma unroll
+      for (int e = 0; e < 8; e++) val[e] += part[e];
+    }
+    epi_store<EPI>(val, bias, pre[p], m0 + pr[p], pc, M, N, ep);
+  }
+}
+
 // extent in bytes of a K x rows operand as the kernel addresses it; 0 if it does not fit a 31-bit offset
 inline long operand_bytes(bool kc, long rows, long K, long ld) {
   long el = kc ? (rows - 1) * ld + K : (K - 1) * ld + rows;
@@ -611,6 +790,24 @@ int launch_dma(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t 
   const long ab = operand_bytes(A_KC, a->M, a->K, a->lda), bb = operand_bytes(B_KC, a->N, a->K, a->ldb);
   hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * WAVES_M * WAVES_N), smem, s, (const bf16_t *)a->A, a->lda, (int)ab, (const bf16_t *)a->B,
                      a->ldb, (int)bb, a->M, a->N, a->K, tiles_m, tiles_n, ep);
+  STP_LAUNCH_CHECK(ctx);
+  return STP_OK;
+}
+
+template <int WK, bool A_KC, bool B_KC, int EPI, bool KTAIL>
+int launch_wavek(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t s) {
+  constexpr size_t smem = (size_t)4 * 128 * (64 + 64) * 2;               // four rings of K-tiles, 128 deep together
+  static_assert(smem <= 160 * 1024 && smem >= (size_t)4 * 64 * (64 + 8) * sizeof(float), "LDS budget");
+  auto kern = gemm_bf16_wavek_kernel<WK, A_KC, B_KC, EPI, KTAIL>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    attr_set = true;
+  }
+  const int tiles_m = (a->M + 63) / 64, tiles_n = (a->N + 63) / 64;
+  const long ab = operand_bytes(A_KC, a->M, a->K, a->lda), bb = operand_bytes(B_KC, a->N, a->K, a->ldb);
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(256), smem, s, (const bf16_t *)a->A, a->lda, (int)ab, (const bf16_t *)a->B, a->ldb,
+                     (int)bb, a->M, a->N, a->K, tiles_m, tiles_n, ep);
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }
@@ -689,6 +886,14 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool s
   return best;
 }
 
+// Outputs of at most 256 tiles of 64 x 64 (one per compute unit) go to the contraction-splitting kernel, measured against
+// the best of the larger tiles (us): [1024, 1024] with K = 1024 / 3072 / 4096: 8.0 -> 6.0, 25.5 -> 12.7, 29 -> 15.5;
+// [1136, 512] K = 2816: 27 -> 11; [384, 1032] K = 3000 (weight gradient): 23 -> 13; [128, 2128] K = 456: 7.1 -> 4.9.  With
+// more tiles a compute unit works through two of them and the gain shrinks to nothing ([1080, 1344] K = 1792: 15.6 ->
+// 14.9, [2608, 576] K = 1664: none), and it costs more compute-unit time, which counts beside other streams; below K = 256
+// the extra reduction outweighs the shorter chain.
+inline bool wavek_shape(long M, long N, long K) { return ((M + 63) / 64) * ((N + 63) / 64) <= 256 && K >= 256; }
+
 template <bool A_KC, bool B_KC, int EPI, bool KTAIL>
 int launch_dma_tile(stp_ctx *ctx, const stp_gemm_args *a, TileChoice c, const Epi &ep, hipStream_t s) {
   if constexpr (A_KC) {
@@ -705,6 +910,10 @@ template <bool A_KC, bool B_KC, int EPI>
 int launch_tile(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t s) {
   const bool dma_ok = a->K > 0 && operand_bytes(A_KC, a->M, a->K, a->lda) > 0 && operand_bytes(B_KC, a->N, a->K, a->ldb) > 0;
   if (!dma_ok) return launch_cfg<128, 128, 2, 2, A_KC, B_KC, EPI>(ctx, a, ep, s);
+  if (!a->tile_m && wavek_shape(a->M, a->N, a->K)) {
+    constexpr int WK = A_KC || B_KC ? 64 : 32;
+    return a->K % WK ? launch_wavek<WK, A_KC, B_KC, EPI, true>(ctx, a, ep, s) : launch_wavek<WK, A_KC, B_KC, EPI, false>(ctx, a, ep, s);
+  }
   TileChoice c = pick_tile(a->M, a->N, a->K, A_KC, B_KC, ctx && ctx->concurrent);
   if (ctx && ctx->concurrent)       // a measured preference for this shape beside other streams' kernels
     for (int i = 0; i < ctx->n_tile_hints; i++) {
