@@ -5,7 +5,7 @@
 // transposed-weight forms in B; the token-contracting forms in W).
 //
 // Two kernels share the fragment scheme, the tile map and the epilogue:
-//   * gemm_bf16_dma_kernel (further down): direct-to-LDS loads, 4-stage ring of 32-deep K-tiles, the path of
+//   * gemm_bf16_dma_kernel (further down): direct-to-LDS loads, rings of 64-deep K-tiles, the path of
 //     every problem whose operands it can address;
 //   * gemm_bf16_kernel: the fallback for operands of 2 GiB and more, described here.
 //
@@ -30,6 +30,7 @@
 #include "lds_dma.h"
 #include <utility>
 #include <stdlib.h>
+#include <math.h>
 
 namespace {
 
@@ -324,40 +325,48 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const
 
 
 // =====================================================================================================
-// Kernel with direct-to-LDS loads and a 4-stage pipeline (the path every large GEMM takes).
+// Kernel with direct-to-LDS loads and rings of 64-deep K-tiles (the path every large GEMM takes).
 //
 // buffer_load_dwordx4 ... lds moves 16 bytes per lane from global memory straight into LDS (lane i of a
-// wave instruction lands at M0 + 16*i): no staging registers, no ds_write, and the loads of three
-// K-tiles (32 deep each) stay in flight behind the MFMAs of the current one.  The buffer form (resource
+// wave instruction lands at M0 + 16*i): no staging registers, no ds_write, and the loads of one to three
+// K-tiles stay in flight behind the MFMAs of the current one.  The buffer form (resource
 // descriptor in SGPRs, one 32-bit byte offset per lane, the K position in a scalar offset) is used
 // because the issue of a load with 64-bit per-lane addresses holds the SIMD's vector register ports
 // long enough to stall the MFMAs of the other wave on that SIMD (measured: about 15 % of a K-tile).
 // A wave instruction fills 1 KB of LDS contiguously, so padding is impossible; bank conflicts are
 // avoided by permuting WHICH global chunk each lane fetches (an XOR swizzle applied on the global
 // side and undone in the fragment address):
-//   k-contiguous operand : tile [rows][32], 4 chunks per row; chunk c of row r sits in slot c ^ ((r>>2)&3)
-//   row-contiguous operand: tile [32][rows], rows/8 chunks per k-row; chunk c of k-row k sits in slot
+//   k-contiguous operand : tile [rows][64], 8 chunks per row; chunk c of row r sits in slot c ^ ((r>>1)&7)
+//   row-contiguous operand: tile [64][rows], rows/8 chunks per k-row; chunk c of k-row k sits in slot
 //                           c ^ (4*(k&3))   (read back with ds_read_b64_tr_b16); tiles of 64 rows, whose k-row is
 //                           half of the 64 banks: c ^ (4*((k>>1)&1))
 //
+// Depth and rings.  What bounds the kernel besides the matrix pipes is what a compute unit takes in from L2.  A row of a
+// 64-deep k-contiguous tile is a whole 128-byte line; with 32-deep tiles each request used half a line and the other half
+// was fetched again one K-tile later.  A and B have rings of their own: A's is a stage longer where LDS has room for it
+// but not for a third stage of both (256 x 256: 3 x 32 + 2 x 32 KB), and A's part of a K-tile is then loaded a whole
+// K-tile ahead of B's.  Against one ring of four 32-deep tiles (us, 8192^3, both operands k-contiguous): 256 x 256 tile
+// 867 -> 790, 128 x 256 1143 -> 886, 128 x 128 1276 -> 968; forward layout 854 / 991 / 1166 -> 799 / 882 / 972; weight gradient
+// 862 / 927 / 1062 -> 796 / 908 / 1018.  [4096, 1792] K = 7168, k-contiguous: 127 -> 94; [3072, 640] K = 5120: 45 -> 34.  Two
+// stages of both operands are worth less (256 x 256: 860, 128 x 256: 1097: the last loads have half a K-tile to arrive).
+//
 // Schedule.  Two waves per SIMD run freely (no phase lock); each wave software-pipelines its fragments:
-// the LDS reads of the next 16-deep step are issued before the 8..16 MFMAs of the current one, so LDS
+// the LDS reads of the next 16-deep step are issued before the MFMAs of the current one, so LDS
 // latency hides behind the wave's own MFMAs and the other wave on the SIMD fills what is left.  All
 // fragment reads are inline assembly with explicit lgkmcnt waits: the compiler neither tracks the
 // direct-to-LDS loads nor may it order LDS reads behind them (through builtins it would wait for
-// vmcnt(0) before every transposing read).  One s_barrier per K-tile, between its two steps:
-//     s_waitcnt vmcnt(2 tiles' worth) lgkmcnt(0) ; s_barrier
-// after it tile kt+1 has landed for every wave, and no wave has a read of stage kt outstanding (both
-// fragment sets of tile kt are in registers), so stage kt is refilled with tile kt+4 right there.
+// vmcnt(0) before every transposing read).  One s_barrier per K-tile, between its last two steps:
+//     s_waitcnt vmcnt(IN_FLIGHT) lgkmcnt(0) ; s_barrier
+// after it tile kt+1 has landed for every wave, and no wave has a read of tile kt outstanding (the
+// fragments of its last step are in registers), so its stages are refilled right there.
 // Rows past M / N are fetched from a clamped (valid) address and never stored; each operand must span less than
-// 2 GiB.  K is a multiple of 8; when it is not one of 32 (KTAIL) the last K-tile is partly empty: lanes whose 8-deep
+// 2 GiB.  K is a multiple of 8; when it is not one of 64 (KTAIL) the last K-tile is partly empty: lanes whose 8-deep
 // chunk lies past K fetch the tile's first chunk instead (in bounds, any value) and the fragments of that tile are
 // zeroed in registers, both operands, where k >= K (a chunk of 8 is exactly a fragment's lane half).  Against the
-// register-staged kernel, which such K took before: 37 - 45 -> 23 - 34 us for [3000, 1032] x [1032, 2744] and its backward
+// register-staged kernel, which such K took before: 37 - 45 -> 23 - 31 us for [3000, 1032] x [1032, 2744] and its backward
 // forms.
 // =====================================================================================================
-constexpr int DK = 32;         // K-tile depth of the DMA kernel
-constexpr int DSTAGES = 4;
+constexpr int DK = 64;         // K-tile depth of the DMA kernel
 
 template <int ROWS, bool KC, int NWAVES, int DEPTH = DK>
 struct DmaOp {
@@ -365,8 +374,8 @@ struct DmaOp {
   static_assert(ROWS % 16 == 0, "a tile is a whole number of 1 KB pieces per K-tile");
   static_assert(KC || (ROWS / 8) % 8 == 0, "the chunk permutation of a row-contiguous tile works on blocks of 8 or 16 chunks");
   static constexpr int PIECES = ROWS * DEPTH / 512;                      // 1 KB pieces (wave instructions) per K-tile
-  static constexpr int NINST = (PIECES + NWAVES - 1) / NWAVES;           // issue slots per wave per K-tile
-  static constexpr bool EVEN = PIECES % NWAVES == 0;                     // every slot of every wave has a piece
+  static_assert(PIECES % NWAVES == 0, "every wave issues the same number of loads per K-tile, which the vmcnt waits rely on");
+  static constexpr int NINST = PIECES / NWAVES;                          // loads per wave per K-tile
   static constexpr int bytes = ROWS * DEPTH * 2;
   static constexpr int CPR = KC ? DEPTH / 8 : ROWS / 8;                  // 16-byte chunks per tile row (k-contiguous) or k-row
   static constexpr int LDS_OPS_PER_FRAG = KC ? 1 : 2;
@@ -375,14 +384,12 @@ struct DmaOp {
     if (KC) return DEPTH == 32 ? (r >> 2) & 3 : (r >> 1) & 7;
     return CPR % 16 == 0 ? 4 * (r & 3) : 4 * ((r >> 1) & 1);
   }
-  // piece that slot j of wave `wave` loads; pieces >= PIECES do not exist (the slot then loads piece 0 again,
-  // into a dump area: every wave issues the same number of loads per K-tile, which the vmcnt waits rely on)
+  // piece that load j of wave `wave` fetches
   static __device__ __forceinline__ int piece(int j, int wave) { return wave + NWAVES * j; }
   // byte offset (from the operand base, K-tile 0) of the chunk that lane `lane` of this wave's j-th
   // instruction must fetch; a chunk at or past k_lim (within the K-tile) is replaced by one at its beginning
   static __device__ __forceinline__ unsigned chunk_offset(int j, int wave, int lane, int ld, int row0, int row_lim, int k_lim = DEPTH) {
-    const int pc = piece(j, wave);
-    const int p = (pc < PIECES ? pc : 0) * 64 + lane;
+    const int p = piece(j, wave) * 64 + lane;
     if (KC) {
       const int r = p / CPR;
       int c = (p % CPR) ^ swz(r);
@@ -432,15 +439,17 @@ struct DmaOp {
   }
 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTG, bool A_KC, bool B_KC, int EPI, bool KTAIL>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTA, int NSTB, bool A_KC, bool B_KC, int EPI, bool KTAIL>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(const bf16_t *__restrict__ A, int lda, int a_bytes,
                                                             const bf16_t *__restrict__ B, int ldb, int b_bytes, int M, int N, int K,
                                                             int tiles_m, int tiles_n, Epi ep) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 32, NI = WN / 32;
-  using OA = DmaOp<BM, A_KC, NWAVES>;
-  using OB = DmaOp<BN, B_KC, NWAVES>;
-  constexpr int STAGE_BYTES = OA::bytes + OB::bytes;
+  using OA = DmaOp<BM, A_KC, NWAVES, DK>;
+  using OB = DmaOp<BN, B_KC, NWAVES, DK>;
+  constexpr int STEPS = DK / 16;
+  static_assert(NSTA >= NSTB && NSTB >= 2, "the loads of a K-tile's B part go ahead of those of a later one's A part");
+  constexpr int RING_B = NSTA * OA::bytes;      // LDS: ring of A, then ring of B
   constexpr int LOADS_PER_TILE = OA::NINST + OB::NINST;
   constexpr int READS_PER_STEP = MI * OA::LDS_OPS_PER_FRAG + NI * OB::LDS_OPS_PER_FRAG;
   // lgkmcnt is a 4-bit counter: with 16 reads per step the wait for "the previous step's reads" also waits for
@@ -476,7 +485,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
   const unsigned stepa = (A_KC ? (unsigned)DK : (unsigned)DK * lda) * 2u;
   const unsigned stepb = (B_KC ? (unsigned)DK : (unsigned)DK * ldb) * 2u;
 
-  unsigned ada[A_KC ? 2 : MI], adb[B_KC ? 2 : NI];
+  unsigned ada[A_KC ? STEPS : MI], adb[B_KC ? STEPS : NI];
   OA::template frag_bases<MI>(ada, wm * WM, lane);
   OB::template frag_bases<NI>(adb, wn * WN, lane);
   const unsigned lds0 = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)smem_raw;
@@ -490,46 +499,41 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
   const int KT = KTAIL ? K / DK + 1 : K / DK;
-  // The direct-to-LDS loads form one stream, tile after tile, each tile as A's instructions then B's.
+  // The direct-to-LDS loads form one stream of groups: group g (issued from K-tile g on) is B's part of tile g + NSTB, then
+  // A's part of tile g + NSTA, the stages that tile g occupied.
   // Issuing a load holds the wave until the address unit takes it, so the loads are placed one at a time
   // between MFMAs (whose execution covers the hold) instead of in a burst behind the barrier, where the
-  // eight waves would queue on the address FIFO with the matrix pipes idle.  Per K-tile kt the first
-  // LF loads of tile kt+4 go into the MFMA block that follows the barrier (stage kt is free from there on)
-  // and the remaining LS loads into the MFMA block before the next barrier.
-#define STP_ISSUE(q, ktile, stage)                                                                               \
+  // eight waves would queue on the address FIFO with the matrix pipes idle.  The first LF loads of a group, B's, go into the
+  // MFMA block that follows the barrier (the stages are free from there on), the rest into the next two.
+#define STP_ISSUE(q, g, sta, stb)                                                                                \
   do {                                                                                                           \
-    const int kt_ = min((ktile), KT - 1);                                                                        \
-    char *st_ = smem_raw + (stage) * STAGE_BYTES;                                                                \
-    if ((q) < OA::NINST) {                                                                                       \
-      const int pc_ = OA::piece((q), wave_s);                                                                    \
-      char *dst_ = (OA::EVEN || pc_ < OA::PIECES) ? st_ + pc_ * 1024 : smem_raw + NSTG * STAGE_BYTES;            \
-      const int j_ = (q) < OA::NINST ? (q) : 0;                                                                  \
-      dma_load16(ra, dst_, KTAIL && kt_ == KT - 1 ? taila[j_] : offa[j_], kt_ * stepa);                          \
+    if ((q) < OB::NINST) {                                                                                       \
+      const int kt_ = min((g) + NSTB, KT - 1), j_ = (q) < OB::NINST ? (q) : 0;                                   \
+      dma_load16(rb, smem_raw + RING_B + (stb) * OB::bytes + OB::piece(j_, wave_s) * 1024,                       \
+                 KTAIL && kt_ == KT - 1 ? tailb[j_] : offb[j_], kt_ * stepb);                                    \
     } else {                                                                                                     \
-      const int pc_ = OB::piece((q) - OA::NINST, wave_s);                                                        \
-      char *dst_ = (OB::EVEN || pc_ < OB::PIECES) ? st_ + OA::bytes + pc_ * 1024 : smem_raw + NSTG * STAGE_BYTES; \
-      const int j_ = (q) >= OA::NINST ? (q) - OA::NINST : 0;                                                     \
-      dma_load16(rb, dst_, KTAIL && kt_ == KT - 1 ? tailb[j_] : offb[j_], kt_ * stepb);                          \
+      const int kt_ = min((g) + NSTA, KT - 1), j_ = (q) >= OB::NINST ? (q) - OB::NINST : 0;                      \
+      dma_load16(ra, smem_raw + (sta) * OA::bytes + OA::piece(j_, wave_s) * 1024,                                \
+                 KTAIL && kt_ == KT - 1 ? taila[j_] : offa[j_], kt_ * stepa);                                    \
     }                                                                                                            \
   } while (0)
   u32x4_t fa0[MI], fb0[NI], fa1[MI], fb1[NI];
-  constexpr int LF = (LOADS_PER_TILE + 1) / 2, LS = LOADS_PER_TILE - LF;
-  // prologue: tiles 0 .. NSTG-2 and the first LF loads of tile NSTG-1
+  constexpr int LF = (LOADS_PER_TILE + 1) / 2, L0 = (LOADS_PER_TILE - LF + 1) / 2;
+  // prologue: groups -NSTA .. -2 and the first LF loads of group -1 (a group's B part does not exist below -NSTB)
 #pragma unroll
-  for (int t = 0; t < NSTG; t++)
+  for (int g = -NSTA; g < 0; g++)
 #pragma unroll
-    for (int q = 0; q < (t < NSTG - 1 ? LOADS_PER_TILE : LF); q++) STP_ISSUE(q, t, t);
+    for (int q = g < -NSTB ? OB::NINST : 0; q < (g < -1 ? LOADS_PER_TILE : LF); q++) STP_ISSUE(q, g, g + NSTA, g + NSTB);
 
   using SeqM = std::make_integer_sequence<int, MI>;
   using SeqN = std::make_integer_sequence<int, NI>;
-#define STP_READ(H, FA, FB, stage)                                                   \
+#define STP_READ(H, FA, FB, sta, stb)                                                \
   do {                                                                               \
-    const unsigned t_ = lds0 + (unsigned)(stage) * STAGE_BYTES;                      \
-    OA::template frag_issue<H>(FA, ada, t_, SeqM{});                                 \
-    OB::template frag_issue<H>(FB, adb, t_ + OA::bytes, SeqN{});                     \
+    OA::template frag_issue<H>(FA, ada, lds0 + (unsigned)(sta) * OA::bytes, SeqM{}); \
+    OB::template frag_issue<H>(FB, adb, lds0 + RING_B + (unsigned)(stb) * OB::bytes, SeqN{}); \
     __builtin_amdgcn_sched_barrier(0);                                               \
   } while (0)
-  // zeroes the fragments of half H of the last K-tile in the lanes whose k lies past K (after their lds_tie)
+  // zeroes the fragments of step H of the last K-tile in the lanes whose k lies past K (after their lds_tie)
   auto mask_tail = [&](u32x4_t (&fa)[MI], u32x4_t (&fb)[NI], int H) {
     const unsigned keep = 16 * H + 8 * (lane >> 5) < k_rem ? ~0u : 0u;
 #pragma unroll
@@ -537,8 +541,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
 #pragma unroll
     for (int j = 0; j < NI; j++) fb[j] &= keep;
   };
-  // MI*NI MFMAs with loads Q0 .. Q0+NQ-1 of tile `ktile` spread evenly between them
-#define STP_MFMAS(H, FA, FB, Q0, NQ, ktile, stage)                                   \
+  // MI*NI MFMAs with loads Q0 .. Q0+NQ-1 of group g spread evenly between them
+#define STP_MFMAS(H, FA, FB, Q0, NQ, g, sta, stb)                                   \
   do {                                                                               \
     lds_tie(FA);                                                                     \
     lds_tie(FB);                                                                     \
@@ -550,31 +554,43 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
         _Pragma("unroll") for (int r = 0; r < (NQ); r++)                             \
           if (i * NI + j == max(0, ((r + 1) * MI * NI) / ((NQ) + 1) - 1)) {          \
             __builtin_amdgcn_sched_barrier(0);                                       \
-            STP_ISSUE((Q0) + r, ktile, stage);                                       \
+            STP_ISSUE((Q0) + r, g, sta, stb);                                        \
             __builtin_amdgcn_sched_barrier(0);                                       \
           }                                                                          \
       }                                                                              \
     __builtin_amdgcn_sched_barrier(0);                                               \
   } while (0)
 
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NSTG - 2) * LOADS_PER_TILE + LF) : "memory");
+  // loads that may still be on their way where K-tile kt+1 is needed: the groups behind the one with its B part and, if A
+  // runs ahead, that group's own A part
+  constexpr int IN_FLIGHT = (NSTB - 2) * LOADS_PER_TILE + (NSTA > NSTB ? OA::NINST : 0);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(IN_FLIGHT + LF) : "memory");
 #ifdef STP_GEMM_TRACE
   const long long tr1 = wall_clock64();
 #endif
-  STP_READ(0, fa0, fb0, 0);
+  STP_READ(0, fa0, fb0, 0, 0);
 
+  int sa = 0, sb = 0;                    // kt % NSTA, kt % NSTB
   for (int kt = 0; kt < KT; kt++) {
-    const int st = kt % NSTG;
-    STP_READ(1, fa1, fb1, st);
-    lds_wait<READS_WAIT>();              // the reads of half 0 (issued one step ago) have returned
-    STP_MFMAS(0, fa0, fb0, LF, LS, kt + NSTG - 1, (kt + NSTG - 1) % NSTG);
-    // tile kt+1 has landed once at most (NSTG-2) tiles' worth of this wave's loads remain in flight;
-    // lgkmcnt(0): this wave's reads of stage st are complete, so after the barrier the stage is free
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NSTG - 2) * LOADS_PER_TILE) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    STP_READ(0, fa0, fb0, (kt + 1) % NSTG);   // past the last tile this reads a stale stage; never used
+    const int na = sa + 1 == NSTA ? 0 : sa + 1, nb = sb + 1 == NSTB ? 0 : sb + 1;
+    STP_READ(1, fa1, fb1, sa, sb);
+    lds_wait<READS_WAIT>();              // the reads of step 0 (issued one step ago) have returned
+    STP_MFMAS(0, fa0, fb0, LF, L0, kt - 1, sa == 0 ? NSTA - 1 : sa - 1, sb == 0 ? NSTB - 1 : sb - 1);
+    STP_READ(2, fa0, fb0, sa, sb);
     lds_wait<READS_WAIT>();
-    STP_MFMAS(1, fa1, fb1, 0, LF, kt + NSTG, st);
+    STP_MFMAS(1, fa1, fb1, LF + L0, LOADS_PER_TILE - LF - L0, kt - 1, sa == 0 ? NSTA - 1 : sa - 1, sb == 0 ? NSTB - 1 : sb - 1);
+    STP_READ(3, fa1, fb1, sa, sb);
+    lds_wait<READS_WAIT>();
+    STP_MFMAS(2, fa0, fb0, 0, 0, 0, 0, 0);
+    // tile kt+1 has landed once at most IN_FLIGHT of this wave's loads remain on their way;
+    // lgkmcnt(0): this wave's reads of tile kt are complete, so after the barrier its stages are free
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(IN_FLIGHT) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    STP_READ(0, fa0, fb0, na, nb);   // past the last tile this reads a stale stage; never used
+    lds_wait<READS_WAIT>();
+    STP_MFMAS(3, fa1, fb1, 0, LF, kt, sa, sb);
+    sa = na;
+    sb = nb;
   }
 #undef STP_READ
 #undef STP_MFMAS
@@ -776,11 +792,11 @@ inline long operand_bytes(bool kc, long rows, long K, long ld) {
   return el * 2 < 0x7fffffffL ? el * 2 : 0;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTG, bool A_KC, bool B_KC, int EPI, bool KTAIL>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTA, int NSTB, bool A_KC, bool B_KC, int EPI, bool KTAIL>
 int launch_dma(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t s) {
-  constexpr size_t smem = (size_t)NSTG * (BM + BN) * DK * 2 + 1024;      // stages, then the dump area of unused load slots
+  constexpr size_t smem = (size_t)(NSTA * BM + NSTB * BN) * DK * 2;
   static_assert(smem <= 160 * 1024 && smem >= (size_t)WAVES_M * WAVES_N * 32 * (BN / WAVES_N + 8) * sizeof(float), "LDS budget");
-  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, NSTG, A_KC, B_KC, EPI, KTAIL>;
+  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, NSTA, NSTB, A_KC, B_KC, EPI, KTAIL>;
   static bool attr_set = false;
   if (!attr_set) {
     STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -834,12 +850,12 @@ int launch_cfg(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t 
 // Tile choice.  A launch runs in rounds of as many workgroups as the 256 CUs hold at once (one per CU; two
 // for the 128 x 128 tile, whose LDS and registers allow it), so a shape that leaves the last round
 // nearly empty with big tiles can finish sooner with smaller, less efficient ones.  The estimate is
-//   sum over rounds of (K/32 x t_ktile x (0.8 + 0.2 x fill) + t_fixed)
-// with t_ktile the measured time of one 32-deep K-tile step of a resident workgroup on a full chip
+//   sum over rounds of (K/32 x t_ktile x (0.65 + 0.35 x fill^1.5) + t_fixed)
+// with t_ktile the measured time of a 32-deep part of the contraction of a resident workgroup on a full chip
 // (microseconds, from 8192^3 runs per operand layout), fill the fraction of the round's slots in use
 // (a partly filled chip leaves each workgroup more L2 and fabric bandwidth) and t_fixed the prologue +
-// epilogue of a tile.  Against measured times of the layer's GEMM shapes the estimate is within
-// 6 % on average and picks the fastest tile or one within 1 % of it.
+// epilogue of a tile.  Over 33 shapes of 256 .. 6144 tokens in three layouts the tile it picks is the fastest or within 1 %
+// of it (three launches of 8 us: within 7 %).
 // The 192 x 256 tile exists for 6144-token activations: 32 tile rows x (N / 256) columns fill the 256 CUs in
 // whole rounds where the 256 x 256 tile leaves a quarter to a half of them idle; alone on the GPU it is the
 // fastest tile for seven of the layer's eight token-major shapes (3-12 %).  When other streams run beside
@@ -848,11 +864,11 @@ int launch_cfg(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t 
 struct TileChoice { int bm, bn; };
 inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool shared_gpu) {
   struct Cfg { int bm, bn, per_cu; double t_ktile[4]; };   // t_ktile index: 2 * a_kc + b_kc; 0 = layout not built
-  static const Cfg cfgs[5] = {{256, 256, 1, {0.761, 0.766, 0.756, 0.766}},
-                              {192, 256, 1, {0.0, 0.0, 0.567, 0.617}},
-                              {128, 256, 1, {0.432, 0.467, 0.428, 0.492}},
-                              {256, 128, 1, {0.449, 0.451, 0.517, 0.496}},
-                              {128, 128, 2, {0.240, 0.278, 0.251, 0.285}}};
+  static const Cfg cfgs[5] = {{256, 256, 1, {0.779, 0.766, 0.782, 0.760}},
+                              {192, 256, 1, {0.0, 0.0, 0.584, 0.583}},
+                              {128, 256, 1, {0.445, 0.440, 0.430, 0.432}},
+                              {256, 128, 1, {0.460, 0.440, 0.432, 0.434}},
+                              {128, 128, 2, {0.244, 0.240, 0.235, 0.235}}};
   if (shared_gpu) {
     // Beside other streams' kernels the rounds of the estimate below mean nothing (what a round leaves idle the
     // other streams use), and what counts is the work a tile costs the compute units: the biggest tile, which
@@ -865,7 +881,7 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool s
       if (((M + o[0] - 1) / o[0]) * ((N + o[1] - 1) / o[1]) >= 96) return TileChoice{o[0], o[1]};
     return TileChoice{128, 128};
   }
-  const double kt = (double)((K + DK - 1) / DK);
+  const double kt = (double)((K + 31) / 32);
   TileChoice best{256, 256};
   double best_t = 1e30;
   for (const Cfg &c : cfgs) {
@@ -879,7 +895,7 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool s
       // a partial round of the two-per-CU tile runs one workgroup per CU if it fits the 256 CUs
       const bool paired = c.per_cu == 2 && rem > 256;
       const double fill = paired ? rem / 512.0 : (rem < 256 ? rem / 256.0 : 1.0);
-      t += (paired ? 2.0 : 1.0) * (tk * (0.8 + 0.2 * fill) + t_fixed);
+      t += (paired ? 2.0 : 1.0) * (tk * (0.65 + 0.35 * fill * sqrt(fill)) + t_fixed);
     }
     if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn}; }
   }
@@ -898,12 +914,17 @@ template <bool A_KC, bool B_KC, int EPI, bool KTAIL>
 int launch_dma_tile(stp_ctx *ctx, const stp_gemm_args *a, TileChoice c, const Epi &ep, hipStream_t s) {
   if constexpr (A_KC) {
     // 192 rows: 6144 tokens are 32 such tiles, and 32 x (N / 256) fills the 256 compute units in whole rounds
-    if (c.bm == 192 && c.bn == 256) return launch_dma<192, 256, 2, 4, DSTAGES, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+    if (c.bm == 192 && c.bn == 256) return launch_dma<192, 256, 2, 4, 3, 2, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
   }
-  if (c.bm == 256 && c.bn == 128) return launch_dma<256, 128, 2, 4, DSTAGES, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
-  if (c.bm == 128 && c.bn == 256) return launch_dma<128, 256, 2, 4, DSTAGES, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
-  if (c.bm == 128 && c.bn == 128) return launch_dma<128, 128, 2, 4, DSTAGES, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
-  return launch_dma<256, 256, 2, 4, DSTAGES, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+  if (c.bm == 256 && c.bn == 128) return launch_dma<256, 128, 2, 4, 3, 3, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+  if (c.bm == 128 && c.bn == 256) return launch_dma<128, 256, 2, 4, 3, 3, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+  if (c.bm == 128 && c.bn == 128) {
+    // up to one workgroup per compute unit: all of the LDS for loads in flight (a ring of two leaves 42 instead of 29 us for
+    // [6144, 512] K = 4096); with more, two workgroups share it (8192^3: 968 against 1143 us)
+    if (((a->M + 127) / 128) * ((a->N + 127) / 128) <= 256) return launch_dma<128, 128, 2, 4, 4, 4, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+    return launch_dma<128, 128, 2, 4, 3, 2, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+  }
+  return launch_dma<256, 256, 2, 4, 3, 2, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
 }
 
 template <bool A_KC, bool B_KC, int EPI>

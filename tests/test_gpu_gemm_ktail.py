@@ -47,3 +47,23 @@ def test_k_tail(ctx, M, N, K, a_trans, b_trans):
     torch.cuda.synchronize()
     assert rel_err(to_host(C), to_host(ref)) < 4e-3
     assert rel_err(to_host(acc), to_host(ref) + 1.0) < 1e-5
+
+
+# every workgroup tile, fewer K-tiles than its rings hold, as many, and more, with and without a half-empty last one; also
+# just more tiles of 128 x 128 than compute units (another ring length)
+@pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("tile", [(256, 256), (192, 256), (128, 256), (256, 128), (128, 128)])
+@pytest.mark.parametrize("M,N,K", [(264, 520, 32), (264, 520, 64), (264, 520, 128), (264, 520, 192), (264, 520, 224), (264, 520, 256), (264, 520, 544),
+                                   (2056, 2056, 352)])
+def test_rings(ctx, M, N, K, tile, a_trans, b_trans):
+    if a_trans and tile[0] == 192:
+        return
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, lda, a = operand(g, M, K, 1.0, a_trans)
+    B, ldb, b = operand(g, N, K, 0.05, not b_trans)
+    ref = a @ b.t()
+    out = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ctx.gemm(stp.GemmArgs(dtype=stp.BF16, M=M, N=N, K=K, A=A.data_ptr(), lda=lda, a_trans=a_trans, B=B.data_ptr(), ldb=ldb, b_trans=b_trans,
+                          C=out.data_ptr(), ldc=N, bias_scale=1.0, resid_scale=1.0, tile_m=tile[0], tile_n=tile[1]))
+    torch.cuda.synchronize()
+    assert rel_err(to_host(out), to_host(ref)) < 6e-3      # as above: the bf16 rounding of an fp32 sum
