@@ -9,7 +9,8 @@
 // the end of the launch - come from a host-side plan that simulates the dispatch over the 256 compute units.
 // Inside a workgroup 8 waves run as 4 query sub-tiles (32 rows) x 2 key halves: per 128-key step
 // waves 0-3 (group A) take keys 0..63 and waves 4-7 (group B) keys 64..127; a SIMD holds one wave of
-// each group.  The two halves are merged through LDS at the end.
+// each group.  The two halves are merged through LDS at the end.  At head dimension 64 many short blocks go to workgroups of
+// four waves (HALVES = 1), which take every key themselves, 64 a step, as group A does: see four_wave_us.
 //
 // Grouped-query attention: query head i reads key / value head i / (n / nk); only the tile addresses change.
 //
@@ -46,16 +47,19 @@
 namespace {
 
 constexpr int QB = 128;    // query rows per workgroup
-constexpr int KSTEP = 128; // keys per step (64 per wave half)
+constexpr int KSTEP = 128; // keys per step of the plan
 constexpr float LN2 = 0.69314718055994531f;
 
-template <int D> struct AttnGeom {
+struct AttnCost { double fixed, step; };
+
+template <int D, int HALVES = 2> struct AttnGeom {
+  static constexpr int KS = 64 * HALVES;         // keys per tile: 64 per wave
   static constexpr int RB = D * 2;               // bytes per tile row
   static constexpr int CPR = D / 8;              // 16-byte chunks per row
   static constexpr int RPB = 256 / RB;           // rows per 256 bytes (one pass over the 64 banks)
   static constexpr int RPI = 64 / CPR;           // tile rows covered by one direct-to-LDS wave instruction
-  static constexpr int NLD = KSTEP / RPI / 8;    // such instructions per wave per tile
-  static constexpr int TILE = KSTEP * RB;        // bytes of a K or V tile
+  static constexpr int NLD = KS / RPI / (4 * HALVES);    // such instructions per wave per tile
+  static constexpr int TILE = KS * RB;        // bytes of a K or V tile
   static constexpr int piece_floats = QB * D + 2 * QB;   // partial O, then m, then l
 };
 
@@ -99,8 +103,8 @@ __device__ __forceinline__ void mfma_pv(f32x16_t (&o)[D / 32], const u32x4_t (&b
     o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[db]), pf, o[db], 0, 0, 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__restrict__ qkv, float *__restrict__ part,
+template <int D, int HALVES>
+__global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf16_t *__restrict__ qkv, float *__restrict__ part,
                                                             bf16_t *__restrict__ out, float *__restrict__ lse_out, int seq,
                                                             int n, int nk, int causal, int max_chunks, int chunk_steps, float scale_log2,
                                                             int n_items, stp_attn_order ord
@@ -108,18 +112,21 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
                                                             , long long *trace
 #endif
                                                             ) {
-  using G = AttnGeom<D>;
+  using G = AttnGeom<D, HALVES>;
   static_assert(D == 64 || D == 128, "head dimension");
 #ifdef STP_ATTN_TRACE
   const long long tr0 = wall_clock64();
 #endif
-  constexpr int RB = G::RB, CPR = G::CPR, RPB = G::RPB, RPI = G::RPI, NLD = G::NLD, TILE = G::TILE;
+  constexpr int RB = G::RB, CPR = G::CPR, RPB = G::RPB, RPI = G::RPI, NLD = G::NLD, TILE = G::TILE, KS = G::KS;
   constexpr int KREADS = 4, VREADS = 2 * (D / 32);   // LDS operations of one fragment group
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];   // K ring [2][TILE], V ring [2][TILE]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 31, lg = lane >> 5;
-  const int qsub = wave & 3, half = wave >> 2;
+  const int qsub = wave & 3;
+  int half = wave >> 2;
+  // opaque to the compiler: folded away, it rotates the main loop and needs 70 more registers (at D = 128 it spills)
+  if (HALVES == 1) { half = 0; asm volatile("" : "+s"(half)); }
   const int nqb = (seq + QB - 1) / QB;
   // the workgroup's (query block, chunk): from the launch's work order (grid = heads x items), or, without
   // one, from a grid of blocks x chunks x heads with the late query blocks, which own the most chunks, first
@@ -129,8 +136,11 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
   const int bz = n_items ? blockIdx.x : blockIdx.z;
   const int head = bz % n, b = bz / n;
   const int nsteps = attn_steps(qb, seq, causal);
-  const int s_begin = chunk * chunk_steps, s_end = min(nsteps, s_begin + chunk_steps);
-  if (s_begin >= nsteps) return;
+  if (chunk * chunk_steps >= nsteps) return;
+  // the chunk in tiles of KS keys
+  constexpr int TPS = KSTEP / KS;
+  const int s_begin = chunk * chunk_steps * TPS;
+  const int s_end = min(((causal ? min(seq, qb * QB + QB) : seq) + KS - 1) / KS, s_begin + chunk_steps * TPS);
   const int ns = s_end - s_begin;
 
   const int a = n * D;
@@ -167,7 +177,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
   // sequence read its last row
   auto issue_one = [&](int k, bool is_v, int j) {
     char *dst = smem_raw + (is_v ? 2 * TILE : 0) + (k & 1) * TILE + (wave_s * NLD + j) * 1024;
-    const unsigned uni = (unsigned)((s_begin + k) * KSTEP + j * RPI) * row_bytes;
+    const unsigned uni = (unsigned)((s_begin + k) * KS + j * RPI) * row_bytes;
     const unsigned rowoff = min(ld_rowoff0 + uni, max_rowoff);
     dma_load16(rs, dst, rowoff + (is_v ? ld_vcol[j] : ld_kcol[j]), 0);
   };
@@ -205,7 +215,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
 
   // wave-uniform: does local step k hold a key this wave's queries may attend to?
   auto active = [&](int k) {
-    const int kv0 = (s_begin + k) * KSTEP + half * 64;
+    const int kv0 = (s_begin + k) * KS + half * 64;
     return kv0 < seq && (!causal || kv0 <= q_wave0 + 31);
   };
 
@@ -277,7 +287,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
   // kv0 + 32*jb + 8*(v/4) + 4*(l/32) + v%4, query l%32
   auto softmax_impl = [&](int k, auto masked) {
     constexpr bool MASK = decltype(masked)::value;
-    const int kv0 = (s_begin + k) * KSTEP + half * 64;
+    const int kv0 = (s_begin + k) * KS + half * 64;
     // raw scores are kept; the 1/sqrt(d) log2(e) factor is folded into the exponent's FMA
     auto mask_max = [&](f32x16_t &sc, int jb, float mx) {
       if constexpr (MASK) {
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
   };
   // only a step that touches the causal diagonal or the end of the sequence needs the mask
   auto softmax = [&](int k) {
-    const int kv0 = (s_begin + k) * KSTEP + half * 64;
+    const int kv0 = (s_begin + k) * KS + half * 64;
     if ((causal && kv0 + 63 > q_wave0) || (kv0 + 64 > seq)) softmax_impl(k, std::true_type{});
     else softmax_impl(k, std::false_type{});
   };
@@ -380,20 +390,29 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
   // O (un-normalised, relative to m), m (log2 domain), l.
   float *red = reinterpret_cast<float *>(smem_raw);            // [4][D/2][64] accumulators, then [4][2][32] m, l
   float *red_ml = red + 4 * (D / 2) * 64;
-  if (half == 1) {
+  if (HALVES == 2) {
+    if (half == 1) {
 #pragma unroll
-    for (int i = 0; i < D / 32; i++)
+      for (int i = 0; i < D / 32; i++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] = o[i][v];
-    if (lg == 0) { red_ml[(qsub * 2 + 0) * 32 + lr] = m; red_ml[(qsub * 2 + 1) * 32 + lr] = l; }
+        for (int v = 0; v < 16; v++) red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] = o[i][v];
+      if (lg == 0) { red_ml[(qsub * 2 + 0) * 32 + lr] = m; red_ml[(qsub * 2 + 1) * 32 + lr] = l; }
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (half == 0) {
-    const float m_b = red_ml[(qsub * 2 + 0) * 32 + lr], l_b = red_ml[(qsub * 2 + 1) * 32 + lr];
-    const float M = fmaxf(m, m_b);
-    const float m_ref = M == -INFINITY ? 0.f : M;
-    const float ea = __builtin_amdgcn_exp2f(m - m_ref), eb = __builtin_amdgcn_exp2f(m_b - m_ref);
-    l = l * ea + l_b * eb;
+    float M = m;
+    if (HALVES == 2) {
+      const float m_b = red_ml[(qsub * 2 + 0) * 32 + lr], l_b = red_ml[(qsub * 2 + 1) * 32 + lr];
+      M = fmaxf(m, m_b);
+      const float m_ref = M == -INFINITY ? 0.f : M;
+      const float ea = __builtin_amdgcn_exp2f(m - m_ref), eb = __builtin_amdgcn_exp2f(m_b - m_ref);
+      l = l * ea + l_b * eb;
+#pragma unroll
+      for (int i = 0; i < D / 32; i++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) o[i][v] = o[i][v] * ea + red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] * eb;
+    }
     if (qg < seq && nsteps <= chunk_steps) {
       // the query block has this one chunk: its rows are final, so they go to the output (and the log-sum-exp)
       // directly and the combine kernel leaves them alone
@@ -408,7 +427,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const int v = 4 * j + r;
-            w[r] = (bf16_t)((o[i][v] * ea + red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] * eb) * inv);
+            w[r] = (bf16_t)(o[i][v] * inv);
           }
           *reinterpret_cast<bf16x4_t *>(op + 32 * i + 8 * j + 4 * lg) = w;
         }
@@ -425,7 +444,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const int v = 4 * j + r;
-            w[r] = o[i][v] * ea + red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] * eb;
+            w[r] = o[i][v];
           }
           *reinterpret_cast<f32x4_t *>(po + (size_t)qloc * D + 32 * i + 8 * j + 4 * lg) = w;
         }
@@ -448,64 +467,68 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_kernel(const bf16_t *__rest
 #endif
 }
 
-// out[q, :] = sum_c O_c e^{m_c - M} / sum_c l_c e^{m_c - M}; lse = (M + log2 L) ln 2.  One wave per (token, head).
+// out[q, :] = sum_c O_c e^{m_c - M} / sum_c l_c e^{m_c - M}; lse = (M + log2 L) ln 2.  One thread per 8 columns of a query
+// row, the loads of all its chunks in flight together (a wave per row, which went through the chunks one after the other:
+// 7.9 against 4.4 us for 16 heads x 1024 rows of 64 in two chunks).
 template <int D>
 __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float *__restrict__ part, bf16_t *__restrict__ out,
                                                                float *__restrict__ lse, int seq, int n, int mbsz, int causal,
                                                                int max_chunks, int chunk_steps, int q_first) {
   using G = AttnGeom<D>;
-  const int lane = threadIdx.x & 63;
-  const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
+  constexpr int CPR = D / 8;
+  const size_t idx = blockIdx.x * (size_t)256 + threadIdx.x;
   const int rows = seq - q_first;             // rows below q_first belong to one-chunk blocks, which the main kernel finished
-  if (w >= (size_t)mbsz * n * rows) return;
+  if (idx >= (size_t)mbsz * n * rows * CPR) return;
+  const int c8 = (idx % CPR) * 8;
+  const size_t w = idx / CPR;
   const int q = q_first + w % rows, head = (w / rows) % n, b = w / ((size_t)rows * n);
   const int nqb = (seq + QB - 1) / QB, qb = q / QB, qloc = q % QB;
   const int nch = (attn_steps(qb, seq, causal) + chunk_steps - 1) / chunk_steps;
   if (nch <= 1) return;
   const float *p0 = part + ((((size_t)b * n + head) * nqb + qb) * max_chunks) * G::piece_floats;
-  float M = -INFINITY;
-  for (int c = 0; c < nch; c++) M = fmaxf(M, p0[(size_t)c * G::piece_floats + QB * D + qloc]);
-  float L = 0.f, acc0 = 0.f, acc1 = 0.f;
-  for (int c = 0; c < nch; c++) {
-    const float *pc = p0 + (size_t)c * G::piece_floats;
-    const float e = __builtin_amdgcn_exp2f(pc[QB * D + qloc] - M);
-    L += pc[QB * D + QB + qloc] * e;
-    if (D == 128) {
-      const float2 v = *reinterpret_cast<const float2 *>(pc + (size_t)qloc * D + 2 * lane);
-      acc0 += v.x * e; acc1 += v.y * e;
-    } else {
-      acc0 += pc[(size_t)qloc * D + lane] * e;
+  float m[8], l[8], v[8][8];
+#pragma unroll
+  for (int c = 0; c < 8; c++) {               // a block has at most 8 chunks
+    m[c] = -INFINITY;
+    l[c] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) v[c][e] = 0.f;
+    if (c < nch) {
+      const float *pc = p0 + (size_t)c * G::piece_floats;
+      m[c] = pc[QB * D + qloc];
+      l[c] = pc[QB * D + QB + qloc];
+      Vec8<float>::load(pc + (size_t)qloc * D + c8, v[c]);
     }
   }
-  const float inv = 1.0f / L;
-  bf16_t *op = out + ((size_t)b * seq + q) * (n * D) + head * D;
-  if (D == 128) {
-    typedef bf16_t bf16x2_t __attribute__((ext_vector_type(2)));
-    bf16x2_t o2;
-    o2[0] = (bf16_t)(acc0 * inv); o2[1] = (bf16_t)(acc1 * inv);
-    *reinterpret_cast<bf16x2_t *>(op + 2 * lane) = o2;
-  } else {
-    op[lane] = (bf16_t)(acc0 * inv);
+  float M = -INFINITY;
+#pragma unroll
+  for (int c = 0; c < 8; c++) M = fmaxf(M, m[c]);
+  float L = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 8; c++) {
+    const float e = __builtin_amdgcn_exp2f(m[c] - M);
+    L += l[c] * e;
+#pragma unroll
+    for (int i = 0; i < 8; i++) acc[i] += v[c][i] * e;
   }
-  if (lane == 0) lse[((size_t)b * n + head) * seq + q] = (M + log2f(L)) * LN2;
+  const float inv = 1.0f / L;
+#pragma unroll
+  for (int i = 0; i < 8; i++) acc[i] *= inv;
+  Vec8<bf16_t>::store(out + ((size_t)b * seq + q) * (n * D) + head * D + c8, acc);
+  if (c8 == 0) lse[((size_t)b * n + head) * seq + q] = (M + log2f(L)) * LN2;
 }
 
 // the plan of the forward kernel for this shape (block x = query block x)
-inline const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d) {
-  const int nqb = (d->seq + QB - 1) / QB;
-  std::vector<int> steps(nqb);
-  for (int x = 0; x < nqb; x++) steps[x] = attn_steps(x, d->seq, d->causal);
-  return stp_attn_plan_get(ctx, 0, d, nqb, steps.data(), d->heads_local * d->mbsz);
-}
+const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d);
 
-template <int D>
+template <int D, int HALVES>
 int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, float *ws, size_t ws_bytes,
                hipStream_t s) {
-  using G = AttnGeom<D>;
+  using G = AttnGeom<D, HALVES>;
   constexpr size_t smem = (size_t)4 * G::TILE;   // K ring and V ring of two tiles each
-  static_assert(smem >= (size_t)(4 * (D / 2) * 64 + 4 * 2 * 32) * sizeof(float), "merge area fits");
+  static_assert(HALVES == 1 || smem >= (size_t)(4 * (D / 2) * 64 + 4 * 2 * 32) * sizeof(float), "merge area fits");
   static_assert(smem <= 160 * 1024, "LDS budget");
-  auto kern = attn_fwd_bf16_kernel<D>;
+  auto kern = attn_fwd_bf16_kernel<D, HALVES>;
   static bool attr_set = false;
   if (!attr_set) {
     STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -520,7 +543,7 @@ int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out
   if (!ws || ws_bytes < need)
     return stp_fail(ctx, STP_ENOSPACE, "attention forward: workspace lane too small%s (need %ld bytes)", "", (long)need);
   const dim3 grid = plan->n_items ? dim3(d->heads_local * d->mbsz, plan->n_items) : dim3(nqb, max_chunks, d->heads_local * d->mbsz);
-  const dim3 block(512);
+  const dim3 block(256 * HALVES);
   float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   hipLaunchKernelGGL(kern, grid, block, smem, s, (const bf16_t *)qkv, ws, (bf16_t *)out, lse, d->seq, d->heads_local, stp_kv_heads(d), d->causal, max_chunks, chunk_steps,
                      scale_log2, plan->n_items, plan->order
@@ -534,8 +557,8 @@ int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out
   while (qb_first < nqb && attn_steps(qb_first, d->seq, d->causal) <= chunk_steps) qb_first++;
   if (qb_first < nqb) {
     const int q_first = qb_first * QB;
-    size_t waves = (size_t)d->mbsz * d->heads_local * (d->seq - q_first);
-    hipLaunchKernelGGL(attn_fwd_combine_kernel<D>, dim3((waves + 3) / 4), dim3(256), 0, s, ws, (bf16_t *)out, lse, d->seq,
+    const size_t r8 = (size_t)d->mbsz * d->heads_local * (d->seq - q_first) * (D / 8);
+    hipLaunchKernelGGL(attn_fwd_combine_kernel<D>, dim3((r8 + 255) / 256), dim3(256), 0, s, ws, (bf16_t *)out, lse, d->seq,
                        d->heads_local, d->mbsz, d->causal, max_chunks, chunk_steps, q_first);
     STP_LAUNCH_CHECK(ctx);
   }
@@ -556,84 +579,175 @@ size_t stp_attn_fwd_ws_bytes(const stp_layer_desc *d) {
 
 int stp_launch_attn_fwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, float *ws,
                              size_t ws_bytes, hipStream_t s) {
-  if (d->head_dim == 128) return launch_fwd<128>(ctx, d, qkv, out, lse, ws, ws_bytes, s);
-  if (d->head_dim == 64) return launch_fwd<64>(ctx, d, qkv, out, lse, ws, ws_bytes, s);
+  if (d->head_dim == 128) return launch_fwd<128, 2>(ctx, d, qkv, out, lse, ws, ws_bytes, s);
+  if (d->head_dim == 64 && fwd_plan(ctx, d)->halves == 1) return launch_fwd<64, 1>(ctx, d, qkv, out, lse, ws, ws_bytes, s);
+  if (d->head_dim == 64) return launch_fwd<64, 2>(ctx, d, qkv, out, lse, ws, ws_bytes, s);
   return stp_fail(ctx, STP_ESHAPE, "bf16 attention needs head_dim 64 or 128%s");
 }
 
-// Cost of a workgroup of the chunked kernels in microseconds (index: 0 forward, 1 dkv, 2 dq): start and end of a
-// workgroup (first tiles, the merge of the wave halves, the partial result) and one step of its main loop; fitted
-// to measured kernel times over chunk lengths 8 .. 32 (16 .. 64 for dkv) at 4 and 10 heads x 128, seq 4096 and
-// 6144, causal, and 16 heads, seq 1024, not causal: the estimate is within 6 - 8 % (rms) and its choice is the
-// fastest chunk length measured, or within 3 % of it.
-static const double kFixedUs[3] = {11.5, 12.0, 12.0}, kStepUs[3] = {1.75, 1.90, 2.65};
+// Cost of a workgroup of the chunked kernels in microseconds (0 forward, 1 dkv, 2 dq): start and end of a workgroup
+// (first tiles, the merge of the wave halves, the partial result) and one step of its main loop, fitted to measured
+// kernel times.  Head dimension 128: chunk lengths 8 .. 32 (16 .. 64 for dkv) at 4 and 10 heads, seq 4096 and 6144, causal,
+// within 6 - 8 % (rms).  Head dimension 64: 256 .. 4096 tokens, 2 .. 32 heads, within 10 %.
+static AttnCost attn_cost(int kind, int head_dim) {
+  static const AttnCost c128[3] = {{11.5, 1.75}, {12.0, 1.90}, {12.0, 2.65}}, c64[3] = {{6.5, 1.30}, {4.5, 1.20}, {4.5, 1.70}};
+  return head_dim == 128 ? c128[kind] : c64[kind];
+}
 // compute units a chunked attention launch counts on inside a braided block (measured: 96 gives the fastest block on
 // the 4-head and 10-head workloads, 0.3 - 2.5 % ahead of planning for all 256; 32 is 4 - 8 % behind)
 #define STP_ATTN_SHARED_CUS 96
 
 namespace {
 
-// Time of a launch whose workgroups, in the given order, each go to the compute unit that is free first
-// (256 of them, one workgroup each): fixed + per_step * steps per workgroup, every length `zcount` times.
-double plan_makespan(const std::vector<int> &lens, int zcount, double fixed, double per_step, int cus) {
-  // many (head, sequence) pairs: 16 of them on a proportionally smaller machine give the same picture
-  // and keep the planning time bounded
-  if (zcount > 16) { cus = std::max(1, cus * 16 / zcount); zcount = 16; }
+// One kind of work item of a launch: the steps of its blocks, each repeated for z (head, sequence) pairs, cut into chunks of c
+// steps; partial: bytes of a chunk's partial result.
+struct PlanPart {
+  AttnCost cost;
+  int nblocks, z, max_steps, c;
+  const int *steps;
+  size_t partial;
+};
+
+template <typename F>
+void for_chunks(const PlanPart &p, F f) {
+  for (int x = 0; x < p.nblocks; x++)
+    for (int k = 0; k < p.steps[x]; k += p.c) f(p.cost.fixed + p.cost.step * std::min(p.c, p.steps[x] - k));
+}
+
+// The combine kernel of a launch with blocks of several chunks: a launch of its own (about 4 us) that reads the partials at
+// about 3 TB/s.
+double combine_us(const PlanPart &p) {
+  if (p.max_steps <= p.c) return 0.0;
+  size_t pieces = 0;
+  for (int x = 0; x < p.nblocks; x++)
+    if (p.steps[x] > p.c) pieces += (p.steps[x] + p.c - 1) / p.c;
+  return 4.0 + (double)pieces * p.z * p.partial / 3e6;
+}
+
+// no schedule of these chunks over `cus` compute units is shorter
+double plan_bound(const PlanPart *part, int n, int cus) {
+  double sum = 0.0, longest = 0.0, combine = 0.0;
+  for (int i = 0; i < n; i++) {
+    double s = 0.0;
+    for_chunks(part[i], [&](double t) { s += t; longest = std::max(longest, t); });
+    sum += s * part[i].z;
+    combine += combine_us(part[i]);
+  }
+  return std::max(longest, sum / cus) + combine;
+}
+
+// Time of a launch whose workgroups, longest first, each go to the compute unit that is free first (one workgroup each).
+double plan_makespan(const PlanPart *part, int n, int cus) {
+  // many (head, sequence) pairs: a smaller machine with proportionally fewer of them gives the same picture and keeps the
+  // planning time bounded
+  int zmin = part[0].z, zmax = part[0].z;
+  for (int i = 1; i < n; i++) { zmin = std::min(zmin, part[i].z); zmax = std::max(zmax, part[i].z); }
+  const int keep = std::max(1, std::min(zmin, 16 * zmin / zmax));       // of the zmin pairs of the part with the fewest
+  cus = std::max(1, cus * keep / zmin);
+  std::vector<std::pair<double, int>> items;
+  double combine = 0.0;
+  for (int i = 0; i < n; i++) {
+    const int z = std::max(1, (int)((long)part[i].z * keep / zmin));
+    for_chunks(part[i], [&](double t) { items.push_back({t, z}); });
+    combine += combine_us(part[i]);
+  }
+  std::sort(items.begin(), items.end(), [](const std::pair<double, int> &u, const std::pair<double, int> &v) { return u.first > v.first; });
   std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
   for (int i = 0; i < cus; i++) cu.push(0.0);
   double end = 0.0;
-  for (int len : lens)
-    for (int z = 0; z < zcount; z++) {
-      const double t = cu.top() + fixed + per_step * len;
+  for (auto &it : items)
+    for (int z = 0; z < it.second; z++) {
+      const double t = cu.top() + it.first;
       cu.pop();
       cu.push(t);
       end = std::max(end, t);
     }
-  return end;
+  return end + combine;
 }
 
-// cus: the compute units the launch can count on (all 256 when it has the GPU to itself; fewer inside a braided
-// block, where longer chunks, i.e. fewer workgroups with their fixed cost, win because the other streams' kernels
-// fill what an uneven end of the launch leaves idle); min_chunk: never shorter than this
-void plan_make(int kind, int nblocks, const int *steps, int zcount, stp_attn_plan *plan, int cus = 256, int min_chunk = 0) {
-  const double *fixed_us = kFixedUs, *step_us = kStepUs;
-  int max_steps = 1;
-  for (int x = 0; x < nblocks; x++) max_steps = std::max(max_steps, steps[x]);
-  // a block is never cut into more than 8 pieces (bounds the workspace and fits the table's 3 chunk bits)
-  const int lo = std::max((max_steps + 7) / 8, std::min(max_steps, 4));
-  int best_c = max_steps;
-  double best_t = 1e30;
-  std::vector<int> lens;
-  const int stride = std::max(1, (max_steps - lo) / 48);      // at most about 48 candidates
-  for (int c = lo; c <= max_steps; c += stride) {
-    if (c < min_chunk) continue;
-    lens.clear();
-    for (int x = 0; x < nblocks; x++) {
-      for (int k = 0; k < steps[x] / c; k++) lens.push_back(c);
-      if (steps[x] % c) lens.push_back(steps[x] % c);
-    }
-    std::sort(lens.begin(), lens.end(), std::greater<int>());
-    const double t = plan_makespan(lens, zcount, fixed_us[kind], step_us[kind], cus);
-    if (t < best_t * 0.995) { best_t = t; best_c = c; }      // a longer chunk has to win by half a percent
+// Chunk lengths (part[i].c) with the shortest simulated launch on `cus` compute units: all 256 when it has the GPU to itself;
+// fewer inside a braided block, where longer chunks, i.e. fewer workgroups with their fixed cost, win because the other
+// streams' kernels fill what an uneven end of the launch leaves idle.  min_c[i]: never shorter than this.  Two kinds of item
+// share a launch in the backward pass: the second's chunk is as long as the first's in time (or whole blocks).
+// A block is never cut into more than 8 pieces (bounds the workspace and fits the table's 3 chunk bits).
+double plan_chunks(PlanPart *part, int n, int cus, const int *min_c) {
+  auto least = [&](int i) { return std::max(min_c[i], std::max((part[i].max_steps + 7) / 8, std::min(part[i].max_steps, 4))); };
+  struct Cand { double bound; int c[2]; };
+  std::vector<Cand> cand;
+  auto add = [&](int c0, int c1) {
+    part[0].c = c0;
+    if (n > 1) part[1].c = c1;
+    cand.push_back({plan_bound(part, n, cus), {c0, c1}});
+  };
+  const int lo = least(0), hi = std::max(lo, part[0].max_steps), stride = std::max(1, (hi - lo) / 40);
+  auto first = [&](int c) {
+    if (n == 1) { add(c, 0); return; }
+    const double t = part[0].cost.fixed + part[0].cost.step * c;
+    const int lo1 = least(1), hi1 = std::max(lo1, part[1].max_steps);
+    const int c1 = std::max(lo1, std::min(hi1, (int)((t - part[1].cost.fixed) / part[1].cost.step)));
+    add(c, c1);
+    const int even = std::max(lo1, (part[1].max_steps + (part[1].max_steps + c1 - 1) / c1 - 1) / ((part[1].max_steps + c1 - 1) / c1));
+    if (even != c1) add(c, even);
+    if (hi1 != c1) add(c, hi1);
+  };
+  for (int c = lo; c < hi; c += stride) first(c);
+  for (int j = 1; j <= 8; j++)                                       // equal pieces of the longest block
+    if ((part[0].max_steps + j - 1) / j >= lo) first((part[0].max_steps + j - 1) / j);
+  if (cand.empty()) first(hi);
+  // the most promising first; the rest is simulated only while its bound leaves room for a gain of half a percent
+  std::stable_sort(cand.begin(), cand.end(), [](const Cand &u, const Cand &v) { return u.bound < v.bound; });
+  double best = 1e30;
+  int bc[2] = {hi, n > 1 ? part[1].max_steps : 0}, tries = 0;
+  for (auto &k : cand) {
+    if (k.bound >= best * 0.995 || tries >= 24) break;
+    part[0].c = k.c[0];
+    if (n > 1) part[1].c = k.c[1];
+    const double t = plan_makespan(part, n, cus);
+    tries++;
+    if (t < best * 0.995) { best = t; bc[0] = k.c[0]; bc[1] = k.c[1]; }
   }
-  plan->chunk_steps = best_c;
-  plan->max_chunks = (max_steps + best_c - 1) / best_c;
-  // the (block, chunk) pairs, longest first; equal lengths keep the later blocks first
+  part[0].c = bc[0];
+  if (n > 1) part[1].c = bc[1];
+  return best;
+}
+
+// the (block, chunk) pairs of a part, longest first; equal lengths keep the later blocks first
+void plan_fill(const PlanPart &p, stp_attn_plan *plan) {
+  plan->halves = 2;
+  plan->chunk_steps = p.c;
+  plan->max_chunks = (p.max_steps + p.c - 1) / p.c;
   struct Item { int len, block, chunk; };
   std::vector<Item> items;
-  for (int x = nblocks - 1; x >= 0; x--)
-    for (int k = 0; k * best_c < steps[x]; k++) items.push_back({std::min(best_c, steps[x] - k * best_c), x, k});
+  for (int x = p.nblocks - 1; x >= 0; x--)
+    for (int k = 0; k * p.c < p.steps[x]; k++) items.push_back({std::min(p.c, p.steps[x] - k * p.c), x, k});
   std::stable_sort(items.begin(), items.end(), [](const Item &u, const Item &v) { return u.len > v.len; });
   plan->n_items = 0;
-  if (items.size() <= STP_ATTN_ORDER_CAP && nblocks <= 4096 && plan->max_chunks <= 8) {
+  if (items.size() <= STP_ATTN_ORDER_CAP && p.nblocks <= 4096 && plan->max_chunks <= 8) {
     plan->n_items = (int)items.size();
     for (size_t i = 0; i < items.size(); i++) plan->order.item[i] = (uint16_t)(items[i].block | (items[i].chunk << 12));
   }
 }
 
+// Head dimension 64, forward: four waves a workgroup, which take all the keys of a step in turn instead of sharing them with
+// four others, have no halves to merge and sit three to a compute unit.  A workgroup with a compute unit of its own is slower
+// that way (1.8 us a step), three together are faster (1.2 us a step of one of them): one chunk per block, and the longest
+// block or the sum of all bounds the launch.  Measured (us, eight waves / four): 8 x 8 heads, 520 tokens 16.6 / 14.4; 2 x 16
+// heads, 4096 tokens 112 / 90; 10 heads on 2 x 3000 tokens 46 / 51; 16 heads, 1024 tokens, no mask 16.4 / 19.3.  At head dimension 128
+// (two workgroups a compute unit) it is the slower one wherever there is work for the whole chip (281 / 308 at 16384 tokens).
+double four_wave_us(const PlanPart &p, int cus) {
+  double sum = 0.0;
+  for (int x = 0; x < p.nblocks; x++) sum += 2.0 + 1.2 * p.steps[x];
+  return std::max(6.0 + 1.8 * p.max_steps, sum * p.z / cus);
+}
+
+int max_of(const int *v, int n) { return *std::max_element(v, v + n); }
+
 }  // namespace
 
-double stp_attn_item_cost(int kind, int len) { return kFixedUs[kind] + kStepUs[kind] * len; }
+double stp_attn_item_cost(int kind, int head_dim, int len) {
+  const AttnCost c = attn_cost(kind, head_dim);
+  return c.fixed + c.step * len;
+}
 
 stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit) {
   static thread_local stp_attn_plan scratch_of_kind[4];
@@ -652,17 +766,49 @@ stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit) {
   return p;
 }
 
-const stp_attn_plan *stp_attn_plan_get(stp_ctx *ctx, int kind, const stp_layer_desc *d, int nblocks, const int *steps, int zcount) {
-  const bool shared = ctx && ctx->concurrent;
-  const int key[8] = {kind + 1 + (shared ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nblocks};
-  bool hit;
-  stp_attn_plan *p = stp_attn_plan_slot(ctx, key, &hit);
-  if (hit) return p;
-  if (!shared) { plan_make(kind, nblocks, steps, zcount, p); return p; }
-  // inside a block: plan for a share of the machine, never with shorter chunks than alone (the workspace is sized
-  // by the lone plan's chunk count)
-  stp_attn_plan alone;
-  plan_make(kind, nblocks, steps, zcount, &alone);
-  plan_make(kind, nblocks, steps, zcount, p, STP_ATTN_SHARED_CUS, alone.chunk_steps);
-  return p;
+void stp_attn_bwd_chunks(bool shared, const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]) {
+  const int nk = stp_kv_heads(d), D = d->head_dim;
+  PlanPart part[2] = {{attn_cost(1, D), nkv, nk * d->mbsz, max_of(steps_kv, nkv), 0, steps_kv, (size_t)2 * 128 * D * sizeof(float)},
+                      {attn_cost(2, D), nq, d->heads_local * d->mbsz, max_of(steps_q, nq), 0, steps_q, (size_t)128 * D * sizeof(float)}};
+  int min_c[2] = {0, 0};
+  plan_chunks(part, 2, 256, min_c);
+  if (shared) {     // never shorter chunks than alone: the workspace is sized by the lone plan's chunk count
+    min_c[0] = part[0].c;
+    min_c[1] = part[1].c;
+    plan_chunks(part, 2, STP_ATTN_SHARED_CUS, min_c);
+  }
+  chunk[0] = part[0].c;
+  chunk[1] = part[1].c;
 }
+
+void stp_attn_plan_fill(stp_attn_plan *plan, int chunk, int nblocks, const int *steps) {
+  plan_fill(PlanPart{AttnCost{}, nblocks, 1, max_of(steps, nblocks), chunk, steps, 0}, plan);
+}
+
+namespace {
+
+const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d) {
+  const bool shared = ctx && ctx->concurrent;
+  const int nqb = (d->seq + QB - 1) / QB;
+  const int key[8] = {1 + (shared ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nqb};
+  bool hit;
+  stp_attn_plan *plan = stp_attn_plan_slot(ctx, key, &hit);
+  if (hit) return plan;
+  std::vector<int> steps(nqb);
+  for (int x = 0; x < nqb; x++) steps[x] = attn_steps(x, d->seq, d->causal);
+  PlanPart part = {attn_cost(0, d->head_dim), nqb, d->heads_local * d->mbsz, max_of(steps.data(), nqb), 0, steps.data(),
+                   (size_t)(QB * d->head_dim + 2 * QB) * sizeof(float)};
+  int min_c = 0;
+  double t = plan_chunks(&part, 1, 256, &min_c);
+  if (shared) {     // never shorter chunks than alone: the workspace is sized by the lone plan's chunk count
+    min_c = part.c;
+    t = plan_chunks(&part, 1, STP_ATTN_SHARED_CUS, &min_c);
+  }
+  const bool four = d->head_dim == 64 && four_wave_us(part, shared ? STP_ATTN_SHARED_CUS : 256) < t;
+  if (four) part.c = part.max_steps;
+  plan_fill(part, plan);
+  if (four) plan->halves = 1;
+  return plan;
+}
+
+}  // namespace

@@ -4,8 +4,8 @@
 // Given Q, K, V, the forward's log-sum-exp L and delta = rowsum(dO o O):
 //     P = exp(S - L),  S = Q K^T / sqrt(d)  (causal: key > query masked)
 //     dV = P^T dO,  dP = dO V^T,  dS = P o (dP - delta),  dQ = dS K / sqrt(d),  dK = dS^T Q / sqrt(d)
-// Two kernel bodies, both deterministic (no atomics), run by one launch when the query and key / value head
-// counts are equal (their workgroups then fill each other's idle compute units) and by two launches otherwise:
+// Two kernel bodies, both deterministic (no atomics), run by one launch (their workgroups fill each other's idle compute
+// units; by two where the work order has more than its 1024 entries):
 //   * dkv: a workgroup owns 128 keys and one CHUNK of steps of 64 queries; 8 waves = 4 key sub-tiles
 //     (32 keys) x 2 halves of each 64-query step.  S and dP are formed with the keys as MFMA columns,
 //     so the accumulator layout of P / dS is already the B-operand layout of dV^T += dO^T P and
@@ -346,38 +346,6 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(const bf16_t *__restr
   dkv_body<D>(qkv, dout, lse, delta, part, dqkv, seq, n, nk, causal, max_chunks, chunk_steps, scale, kvb, chunk, bz);
 }
 
-// dK = scale * sum_c, dV = sum_c over the chunks of a key block (fixed order).  One thread per 8 columns of a key row.
-template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_combine_kernel(const float *__restrict__ part, bf16_t *__restrict__ dqkv,
-                                                                   int seq, int n, int nk, int mbsz, int causal, int max_chunks,
-                                                                   int chunk_steps, float scale, int kv_end) {
-  const size_t idx = blockIdx.x * (size_t)256 + threadIdx.x;
-  constexpr int CPR = D / 8;
-  // key rows from kv_end on belong to one-chunk blocks, which the main kernel finished
-  if (idx >= (size_t)mbsz * nk * kv_end * CPR) return;
-  const int c8 = (idx % CPR) * 8;
-  const size_t row = idx / CPR;
-  const int kv = row % kv_end, kh = (row / kv_end) % nk, b = row / ((size_t)kv_end * nk);
-  const int kvb = kv / KVB, kloc = kv % KVB;
-  const int nkvb = (seq + KVB - 1) / KVB, nq = (seq + QSTEP - 1) / QSTEP;
-  const int nch = ((n / nk) * (nq - dkv_first_step(kvb, causal)) + chunk_steps - 1) / chunk_steps;
-  if (nch <= 1) return;
-  const float *p0 = part + ((((size_t)b * nk + kh) * nkvb + kvb) * max_chunks) * (size_t)(2 * KVB * D) + (size_t)kloc * D + c8;
-  float sk[8] = {0, 0, 0, 0, 0, 0, 0, 0}, sv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int c = 0; c < nch; c++) {
-    float a8[8], b8[8];
-    Vec8<float>::load(p0 + (size_t)c * (2 * KVB * D), a8);
-    Vec8<float>::load(p0 + (size_t)c * (2 * KVB * D) + (size_t)KVB * D, b8);
-#pragma unroll
-    for (int e = 0; e < 8; e++) { sk[e] += a8[e]; sv[e] += b8[e]; }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; e++) sk[e] *= scale;
-  bf16_t *dkp = dqkv + ((size_t)b * seq + kv) * ((size_t)(n + 2 * nk) * D) + (n + kh) * D + c8;
-  Vec8<bf16_t>::store(dkp, sk);
-  Vec8<bf16_t>::store(dkp + nk * D, sv);
-}
-
 // ---------------------------------------------------------------------------------------------
 // dQ partials.  piece layout: dQ [128][D] fp32 (unscaled)
 // ---------------------------------------------------------------------------------------------
@@ -573,9 +541,11 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(const bf16_t *__restri
   dq_body<D>(qkv, dout, lse, delta, part, dqkv, seq, n, nk, causal, max_chunks, chunk_steps, scale, qb, chunk, bz);
 }
 
-// Both kernels in one launch (same number of query and key / value heads): a work item is a dkv or a dq
-// (block, chunk) pair, item = block | chunk << 12 | (1 << 15 for dq), sorted by estimated time, longest first.
-// The two kinds fill each other's idle compute units: their workgroups are few and of unequal length.
+// Both kernels in one launch: a work item is a dkv or a dq (block, chunk) pair, item = block | chunk << 12 | (1 << 15 for dq),
+// sorted by estimated time, longest first, and the grid key / value heads x items: a dq item occurs once per query head of the
+// group, one row after the other.  The two kinds fill each other's idle compute units: their workgroups are few
+// and of unequal length, the dkv ones fewer and longer still under grouped-query attention (5 query heads on one, 3072 tokens:
+// 101 us in two launches, 77 in one).
 template <int D>
 __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ dout,
                                                              const float *__restrict__ lse, const float *__restrict__ delta,
@@ -590,10 +560,15 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16_t *__res
 #ifdef STP_ATTN_TRACE
   const long long tr0 = wall_clock64();
 #endif
-  const int item = ord.item[blockIdx.y];
-  const int block = item & 0xfff, chunk = (item >> 12) & 7, bz = blockIdx.x;
-  if (item & 0x8000) dq_body<D>(qkv, dout, lse, delta, part_q, dqkv, seq, n, nk, causal, mc_q, ch_q, scale, block, chunk, bz);
-  else dkv_body<D>(qkv, dout, lse, delta, part_kv, dqkv, seq, n, nk, causal, mc_kv, ch_kv, scale, block, chunk, bz);
+  const int item = ord.item[blockIdx.y], group = n / nk;
+  const int block = item & 0xfff, chunk = (item >> 12) & 7;
+  if (item & 0x8000) {
+    int g = 0;                                     // which query head of the group: how often the row occurred before
+    while (g < group - 1 && g < (int)blockIdx.y && ord.item[blockIdx.y - 1 - g] == item) g++;
+    dq_body<D>(qkv, dout, lse, delta, part_q, dqkv, seq, n, nk, causal, mc_q, ch_q, scale, block, chunk, (int)blockIdx.x * group + g);
+  } else {
+    dkv_body<D>(qkv, dout, lse, delta, part_kv, dqkv, seq, n, nk, causal, mc_kv, ch_kv, scale, block, chunk, blockIdx.x);
+  }
 #ifdef STP_ATTN_TRACE
   if (trace) {   // per-workgroup life time: start, end, work item
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -607,47 +582,92 @@ __global__ __launch_bounds__(512) void attn_bwd_fused_kernel(const bf16_t *__res
 #endif
 }
 
+// Adds the chunks of a block in a fixed order, dK and dQ scaled: one thread per 8 columns of a key row (the first kv_blocks
+// workgroups) or of a query row, the loads of all chunks (at most 8) in flight together.
 template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dq_combine_kernel(const float *__restrict__ part, bf16_t *__restrict__ dqkv,
-                                                                  int seq, int n, int nk, int mbsz, int causal, int max_chunks,
-                                                                  int chunk_steps, float scale, int q_first) {
-  const size_t idx = blockIdx.x * (size_t)256 + threadIdx.x;
+__global__ __launch_bounds__(256) void attn_bwd_combine_kernel(const float *__restrict__ part_kv, const float *__restrict__ part_q,
+                                                               bf16_t *__restrict__ dqkv, int seq, int n, int nk, int mbsz, int causal,
+                                                               int mc_kv, int ch_kv, int mc_q, int ch_q, float scale, int kv_end, int q_first,
+                                                               int kv_blocks) {
   constexpr int CPR = D / 8;
-  const int rows = seq - q_first;           // query rows below q_first belong to one-chunk blocks, which the main kernel finished
-  if (idx >= (size_t)mbsz * n * rows * CPR) return;
-  const int c8 = (idx % CPR) * 8;
-  const size_t row = idx / CPR;
-  const int q = q_first + row % rows, head = (row / rows) % n, b = row / ((size_t)rows * n);
-  const int qb = q / 128, qloc = q % 128;
-  const int nqblk = (seq + 127) / 128;
-  const int nch = (dq_steps(qb, seq, causal) + chunk_steps - 1) / chunk_steps;
-  if (nch <= 1) return;
-  const float *p0 = part + ((((size_t)b * n + head) * nqblk + qb) * max_chunks) * (size_t)(128 * D) + (size_t)qloc * D + c8;
-  float sq[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int c = 0; c < nch; c++) {
-    float a8[8];
-    Vec8<float>::load(p0 + (size_t)c * (128 * D), a8);
+  const int nb = (seq + 127) / 128;
+  const size_t ld = (size_t)(n + 2 * nk) * D;
+  auto add_chunks = [](const float *p, size_t stride, int nch, float (&sum)[8]) {
+    float v[8][8];
 #pragma unroll
-    for (int e = 0; e < 8; e++) sq[e] += a8[e];
+    for (int c = 0; c < 8; c++) {
+#pragma unroll
+      for (int e = 0; e < 8; e++) v[c][e] = 0.f;
+      if (c < nch) Vec8<float>::load(p + c * stride, v[c]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum[e] = v[0][e];
+#pragma unroll
+    for (int c = 1; c < 8; c++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) sum[e] += v[c][e];
+  };
+  if ((int)blockIdx.x < kv_blocks) {
+    const size_t idx = blockIdx.x * (size_t)256 + threadIdx.x;
+    // key rows from kv_end on belong to one-chunk blocks, which the main kernel finished
+    if (idx >= (size_t)mbsz * nk * kv_end * CPR) return;
+    const int c8 = (idx % CPR) * 8;
+    const size_t row = idx / CPR;
+    const int kv = row % kv_end, kh = (row / kv_end) % nk, b = row / ((size_t)kv_end * nk);
+    const int kvb = kv / KVB, nq = (seq + QSTEP - 1) / QSTEP;
+    const int nch = ((n / nk) * (nq - dkv_first_step(kvb, causal)) + ch_kv - 1) / ch_kv;
+    if (nch <= 1) return;
+    constexpr size_t PIECE = (size_t)2 * KVB * D;
+    const float *p0 = part_kv + ((((size_t)b * nk + kh) * nb + kvb) * mc_kv) * PIECE + (size_t)(kv % KVB) * D + c8;
+    bf16_t *dkp = dqkv + ((size_t)b * seq + kv) * ld + (n + kh) * D + c8;
+    float sum[8];
+    add_chunks(p0, PIECE, nch, sum);
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum[e] *= scale;
+    Vec8<bf16_t>::store(dkp, sum);
+    add_chunks(p0 + (size_t)KVB * D, PIECE, nch, sum);
+    Vec8<bf16_t>::store(dkp + nk * D, sum);
+  } else {
+    const size_t idx = (blockIdx.x - kv_blocks) * (size_t)256 + threadIdx.x;
+    const int rows = seq - q_first;           // query rows below q_first belong to one-chunk blocks, which the main kernel finished
+    if (idx >= (size_t)mbsz * n * rows * CPR) return;
+    const int c8 = (idx % CPR) * 8;
+    const size_t row = idx / CPR;
+    const int q = q_first + row % rows, head = (row / rows) % n, b = row / ((size_t)rows * n);
+    const int qb = q / 128;
+    const int nch = (dq_steps(qb, seq, causal) + ch_q - 1) / ch_q;
+    if (nch <= 1) return;
+    constexpr size_t PIECE = (size_t)128 * D;
+    float sum[8];
+    add_chunks(part_q + ((((size_t)b * n + head) * nb + qb) * mc_q) * PIECE + (size_t)(q % 128) * D + c8, PIECE, nch, sum);
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum[e] *= scale;
+    Vec8<bf16_t>::store(dqkv + ((size_t)b * seq + q) * ld + head * D + c8, sum);
   }
-#pragma unroll
-  for (int e = 0; e < 8; e++) sq[e] *= scale;
-  Vec8<bf16_t>::store(dqkv + ((size_t)b * seq + q) * ((size_t)(n + 2 * nk) * D) + head * D + c8, sq);
 }
 
-// the plans of the two kernels for this shape (dkv: block x = key block x; dq: block x = query block x)
-inline const stp_attn_plan *dkv_plan(stp_ctx *ctx, const stp_layer_desc *d) {
-  const int nkvb = (d->seq + KVB - 1) / KVB, nq = (d->seq + QSTEP - 1) / QSTEP;
-  std::vector<int> steps(nkvb);
+// the plan of one of the two kernels (kind 1 dkv: block x = key block x; 2 dq: block x = query block x) for this shape; they
+// are made together
+const stp_attn_plan *bwd_plan(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
+  const bool shared = ctx && ctx->concurrent;
+  const int nb = (d->seq + 127) / 128, nq = (d->seq + QSTEP - 1) / QSTEP;
+  int key[8] = {kind + 1 + (shared ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nb};
+  bool hit;
+  stp_attn_plan *plan = stp_attn_plan_slot(ctx, key, &hit);
+  if (hit) return plan;
+  std::vector<int> steps[2] = {std::vector<int>(nb), std::vector<int>(nb)};
   const int group = d->heads_local / stp_kv_heads(d);     // a key block runs over the steps of its whole head group
-  for (int x = 0; x < nkvb; x++) steps[x] = group * (nq - dkv_first_step(x, d->causal));
-  return stp_attn_plan_get(ctx, 1, d, nkvb, steps.data(), stp_kv_heads(d) * d->mbsz);
-}
-inline const stp_attn_plan *dq_plan(stp_ctx *ctx, const stp_layer_desc *d) {
-  const int nqb = (d->seq + 127) / 128;
-  std::vector<int> steps(nqb);
-  for (int x = 0; x < nqb; x++) steps[x] = dq_steps(x, d->seq, d->causal);
-  return stp_attn_plan_get(ctx, 2, d, nqb, steps.data(), d->heads_local * d->mbsz);
+  for (int x = 0; x < nb; x++) {
+    steps[0][x] = group * (nq - dkv_first_step(x, d->causal));
+    steps[1][x] = dq_steps(x, d->seq, d->causal);
+  }
+  int chunk[2];
+  stp_attn_bwd_chunks(shared, d, nb, steps[0].data(), nb, steps[1].data(), chunk);
+  stp_attn_plan_fill(plan, chunk[kind - 1], nb, steps[kind - 1].data());
+  key[0] += kind == 1 ? 1 : -1;
+  stp_attn_plan *other = stp_attn_plan_slot(ctx, key, &hit);
+  if (!hit) stp_attn_plan_fill(other, chunk[2 - kind], nb, steps[2 - kind].data());
+  return plan;
 }
 
 // The merged work order of the fused launch: the (block, chunk) pairs of both kernels, sorted by the plan's
@@ -663,12 +683,13 @@ const stp_attn_plan *fused_plan(stp_ctx *ctx, const stp_layer_desc *d, const stp
   for (int i = 0; i < pkv.n_items; i++) {
     const int x = pkv.order.item[i] & 0xfff, k = pkv.order.item[i] >> 12;
     const int steps = group * (nq - dkv_first_step(x, d->causal));
-    items.push_back({stp_attn_item_cost(1, std::min(pkv.chunk_steps, steps - k * pkv.chunk_steps)), pkv.order.item[i]});
+    items.push_back({stp_attn_item_cost(1, d->head_dim, std::min(pkv.chunk_steps, steps - k * pkv.chunk_steps)), pkv.order.item[i]});
   }
   for (int i = 0; i < pq.n_items; i++) {
     const int x = pq.order.item[i] & 0xfff, k = pq.order.item[i] >> 12;
     const int steps = dq_steps(x, d->seq, d->causal);
-    items.push_back({stp_attn_item_cost(2, std::min(pq.chunk_steps, steps - k * pq.chunk_steps)), (uint16_t)(pq.order.item[i] | 0x8000)});
+    for (int g = 0; g < group; g++)
+      items.push_back({stp_attn_item_cost(2, d->head_dim, std::min(pq.chunk_steps, steps - k * pq.chunk_steps)), (uint16_t)(pq.order.item[i] | 0x8000)});
   }
   std::stable_sort(items.begin(), items.end(), [](const Item &u, const Item &v) { return u.cost > v.cost; });
   p->chunk_steps = 0;
@@ -703,19 +724,19 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
   const int nkvb = (d->seq + KVB - 1) / KVB, nqb = (d->seq + 127) / 128;
   const int nk = stp_kv_heads(d);
   // copies: a later lookup may evict an earlier plan from the context's cache
-  const stp_attn_plan pkv = *dkv_plan(ctx, d), pq = *dq_plan(ctx, d);
+  const stp_attn_plan pkv = *bwd_plan(ctx, d, 1), pq = *bwd_plan(ctx, d, 2);
   const int ch_kv = pkv.chunk_steps, ch_q = pq.chunk_steps, mc_kv = pkv.max_chunks, mc_q = pq.max_chunks;
   const size_t bh = (size_t)d->mbsz * d->heads_local, bk = (size_t)d->mbsz * nk;
-  // the partials of the two kernels lie one behind the other: with equal head counts both run in one launch
+  // the partials of the two kernels lie one behind the other: both run in one launch
   const size_t need_kv = stp_align_up(bk * nkvb * mc_kv * 2 * KVB * D * sizeof(float), 256), need_q = bh * nqb * mc_q * 128 * D * sizeof(float);
   const size_t need = need_kv + need_q;
   if (!ws || ws_bytes < need)
     return stp_fail(ctx, STP_ENOSPACE, "attention backward: workspace lane too small%s (need %ld bytes)", "", (long)need);
   float *ws_kv = ws, *ws_q = ws + need_kv / sizeof(float);
-  const bool fused = bk == bh && pkv.n_items && pq.n_items && pkv.n_items + pq.n_items <= STP_ATTN_ORDER_CAP;
+  const bool fused = pkv.n_items && pq.n_items && pkv.n_items + (int)(bh / bk) * pq.n_items <= STP_ATTN_ORDER_CAP;
   if (fused) {
     const stp_attn_plan *pf = fused_plan(ctx, d, pkv, pq);
-    hipLaunchKernelGGL(kf, dim3((unsigned)bh, pf->n_items), dim3(512), smem_f, s, (const bf16_t *)qkv, (const bf16_t *)dout, lse, delta,
+    hipLaunchKernelGGL(kf, dim3((unsigned)bk, pf->n_items), dim3(512), smem_f, s, (const bf16_t *)qkv, (const bf16_t *)dout, lse, delta,
                        ws_kv, ws_q, (bf16_t *)dqkv, d->seq, d->heads_local, nk, d->causal, mc_kv, ch_kv, mc_q, ch_q, scale, pf->order
 #ifdef STP_ATTN_TRACE
                        , getenv("STP_TRACE_PTR") ? (long long *)strtoull(getenv("STP_TRACE_PTR"), nullptr, 0) : (long long *)nullptr
@@ -738,18 +759,11 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
   int kvb_end = nkvb, qb_first = 0;
   while (kvb_end > 0 && group * (nq64 - dkv_first_step(kvb_end - 1, d->causal)) <= ch_kv) kvb_end--;
   while (qb_first < nqb && dq_steps(qb_first, d->seq, d->causal) <= ch_q) qb_first++;
-  if (kvb_end > 0) {
-    const int kv_end = std::min(d->seq, kvb_end * KVB);
-    const size_t r8 = bk * kv_end * (D / 8);
-    hipLaunchKernelGGL(attn_bwd_dkv_combine_kernel<D>, dim3((r8 + 255) / 256), dim3(256), 0, s, ws_kv, (bf16_t *)dqkv, d->seq,
-                       d->heads_local, nk, d->mbsz, d->causal, mc_kv, ch_kv, scale, kv_end);
-    STP_LAUNCH_CHECK(ctx);
-  }
-  if (qb_first < nqb) {
-    const int q_first = qb_first * 128;
-    const size_t r8 = bh * (d->seq - q_first) * (D / 8);
-    hipLaunchKernelGGL(attn_bwd_dq_combine_kernel<D>, dim3((r8 + 255) / 256), dim3(256), 0, s, ws_q, (bf16_t *)dqkv, d->seq,
-                       d->heads_local, nk, d->mbsz, d->causal, mc_q, ch_q, scale, q_first);
+  const int kv_end = std::min(d->seq, kvb_end * KVB), q_first = std::min(d->seq, qb_first * 128);
+  const size_t kv_blocks = (bk * kv_end * (D / 8) + 255) / 256, q_blocks = (bh * (d->seq - q_first) * (D / 8) + 255) / 256;
+  if (kv_blocks + q_blocks > 0) {
+    hipLaunchKernelGGL(attn_bwd_combine_kernel<D>, dim3((unsigned)(kv_blocks + q_blocks)), dim3(256), 0, s, ws_kv, ws_q, (bf16_t *)dqkv, d->seq,
+                       d->heads_local, nk, d->mbsz, d->causal, mc_kv, ch_kv, mc_q, ch_q, scale, kv_end, q_first, (int)kv_blocks);
     STP_LAUNCH_CHECK(ctx);
   }
   return STP_OK;
@@ -758,15 +772,15 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
 }  // namespace
 
 const stp_attn_plan *stp_attn_bwd_plan_for(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
-  return kind == 1 ? dkv_plan(ctx, d) : dq_plan(ctx, d);
+  return bwd_plan(ctx, d, kind);
 }
 
 size_t stp_attn_bwd_ws_bytes(const stp_layer_desc *d) {
   const int nkvb = (d->seq + KVB - 1) / KVB, nqb = (d->seq + 127) / 128;
   const int nk = stp_kv_heads(d);
   const size_t bh = (size_t)d->mbsz * d->heads_local, bk = (size_t)d->mbsz * nk;
-  const size_t need_kv = stp_align_up(bk * nkvb * dkv_plan(nullptr, d)->max_chunks * 2 * KVB * d->head_dim * sizeof(float), 256);
-  const size_t need_q = bh * nqb * dq_plan(nullptr, d)->max_chunks * 128 * d->head_dim * sizeof(float);
+  const size_t need_kv = stp_align_up(bk * nkvb * bwd_plan(nullptr, d, 1)->max_chunks * 2 * KVB * d->head_dim * sizeof(float), 256);
+  const size_t need_q = bh * nqb * bwd_plan(nullptr, d, 2)->max_chunks * 128 * d->head_dim * sizeof(float);
   return need_kv + need_q;
 }
 

@@ -26,6 +26,7 @@ struct stp_attn_order { uint16_t item[STP_ATTN_ORDER_CAP]; };
 struct stp_attn_plan {
   int key[8];          // what the plan was made for (cache tag)
   int chunk_steps, max_chunks, n_items;
+  int halves;          // forward: 2 = eight waves share a step's keys, 1 = four waves take all of them
   stp_attn_order order;
 };
 #define STP_ATTN_PLAN_CACHE 12
@@ -209,14 +210,15 @@ int stp_launch_attn_bwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *
 static inline int stp_kv_heads(const stp_layer_desc *d) { return d->kv_heads_local > 0 ? d->kv_heads_local : d->heads_local; }
 static inline int stp_qkv_width(const stp_layer_desc *d) { return (d->heads_local + 2 * stp_kv_heads(d)) * d->head_dim; }
 
-// The plan for one attention kernel.  kind: 0 forward, 1 dkv, 2 dq; steps[x] is the number of steps of block
-// x; zcount the number of (head, sequence) pairs that repeat the same blocks.  With a context the plan is
-// cached there (tag: kind and the layer's attention shape); without one it lives in a thread-local slot.
-const stp_attn_plan *stp_attn_plan_get(stp_ctx *ctx, int kind, const stp_layer_desc *d, int nblocks, const int *steps, int zcount);
+// Chunk lengths {dkv, dq} of the backward kernels, planned together because one launch runs both; steps_*[x] is the number of
+// steps of block x.
+void stp_attn_bwd_chunks(bool shared, const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]);
+// fills in the work order of blocks cut into chunks of `chunk` steps
+void stp_attn_plan_fill(stp_attn_plan *plan, int chunk, int nblocks, const int *steps);
 // the context's (or, without one, the thread's) cache slot for a plan with this tag; *hit says whether it is filled
 stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit);
 // the plan's estimate of a workgroup's time in microseconds: `len` steps of a kernel of this kind
-double stp_attn_item_cost(int kind, int len);
+double stp_attn_item_cost(int kind, int head_dim, int len);
 // the plan of one kernel for a layer shape (kind as above); bf16 shapes only
 const stp_attn_plan *stp_attn_plan_for(stp_ctx *ctx, const stp_layer_desc *d, int kind);
 const stp_attn_plan *stp_attn_bwd_plan_for(stp_ctx *ctx, const stp_layer_desc *d, int kind);
