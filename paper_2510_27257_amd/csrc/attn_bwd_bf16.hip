@@ -129,7 +129,7 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
   constexpr int OFF_K = 0, OFF_V = KV_TILE, OFF_RING = 2 * KV_TILE, OFF_STAT = OFF_RING + 2 * STAGE;
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform control flow
   const int lr = lane & 31, lg = lane >> 5;
   const int ksub = wave & 3, qhalf = wave >> 2;
   const int kh = bz % nk, b = bz / nk;                     // key / value head
@@ -183,6 +183,10 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
   unsigned trl_lo, trl_hi;
   tr_lane<D>(lane, trl_lo, trl_hi);
   const unsigned k_base = lds0 + OFF_K + ksub * 32 * RB + kcl, v_base = lds0 + OFF_V + ksub * 32 * RB + kcl;
+  // Head dimension 64: the wave's K and V fragments stay in registers, where there is room for them; the formation of S and
+  // dP, whose fragments feed one MFMA each, is bound by LDS reads.  (At 128, K alone costs 61 spilled registers.)
+  constexpr bool REG = D == 64;
+  u32x4_t kf[REG ? D / 16 : 1], vf[REG ? D / 16 : 1];
 
   f32x16_t dk[D / 32], dv[D / 32];
 #pragma unroll
@@ -195,6 +199,18 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
     STP_SB();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     STP_SB();
+    if constexpr (REG) {
+      if (k == 0) {
+#pragma unroll
+        for (int i = 0; i < D / 16; i++) {
+          kf[i] = lds_read_b128<0>(k_base ^ (32 * i));
+          vf[i] = lds_read_b128<0>(v_base ^ (32 * i));
+        }
+        lds_wait<0>();
+        lds_tie(kf);
+        lds_tie(vf);
+      }
+    }
     if (k + 1 < ns) issue_step(k + 1);
     const int q0 = (first + (s_begin + k) % nq_k) * QSTEP;
     const int qs0 = q0 + 32 * qhalf;                        // this wave's 32 queries of the step
@@ -212,29 +228,34 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
 #pragma unroll
     for (int v = 0; v < 16; v++) { sacc[v] = 0.f; pacc[v] = 0.f; }
     u32x4_t fa[4], fb[4];
-#define STP_SP(buf, acc) do {                                                                                                   \
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[0]), __builtin_bit_cast(bf16x8_t, buf[2]), acc, 0, 0, 0); \
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[1]), __builtin_bit_cast(bf16x8_t, buf[3]), acc, 0, 0, 0); \
+#define STP_MM(acc, x, y) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, y), acc, 0, 0, 0)
+#define STP_SP(buf, acc, reg, SP) do {                                                                       \
+      if constexpr (REG) { STP_MM(acc, buf[0], reg[2 * SP]); STP_MM(acc, buf[1], reg[2 * SP + 1]); }         \
+      else { STP_MM(acc, buf[0], buf[2]); STP_MM(acc, buf[1], buf[3]); }                                     \
       STP_SB(); } while (0)
-#define STP_RD_S(buf, SP) do { read_kc2<D, 0, SP>(buf[0], buf[1], q_kc); read_kc2<D, 0, SP>(buf[2], buf[3], k_base); } while (0)
-#define STP_RD_P(buf, SP) do { read_kc2<D, 0, SP>(buf[0], buf[1], o_kc); read_kc2<D, 0, SP>(buf[2], buf[3], v_base); } while (0)
+#define STP_S(buf, SP) STP_SP(buf, sacc, kf, SP)
+#define STP_P(buf, SP) STP_SP(buf, pacc, vf, SP)
+#define STP_RD_S(buf, SP) do { read_kc2<D, 0, SP>(buf[0], buf[1], q_kc); if constexpr (!REG) read_kc2<D, 0, SP>(buf[2], buf[3], k_base); } while (0)
+#define STP_RD_P(buf, SP) do { read_kc2<D, 0, SP>(buf[0], buf[1], o_kc); if constexpr (!REG) read_kc2<D, 0, SP>(buf[2], buf[3], v_base); } while (0)
 #define STP_RD_T(buf, lo, hi, T) do {                                                                        \
       buf[0] = read_tr<D, 16 * T>(lo, hi, 0); buf[1] = read_tr<D, 16 * T>(lo, hi, 1);                        \
       if constexpr (D == 128) { buf[2] = read_tr<D, 16 * T>(lo, hi, 2); buf[3] = read_tr<D, 16 * T>(lo, hi, 3); } } while (0)
     constexpr int TR_READS = 2 * (D / 32);
+    constexpr int RD = REG ? 2 : 4;       // LDS reads of a group
     STP_RD_S(fa, 0);
-    STP_RD_P(fb, 0); lds_wait<4>(); lds_tie(fa); STP_SP(fa, sacc);
-    STP_RD_S(fa, 1); lds_wait<4>(); lds_tie(fb); STP_SP(fb, pacc);
+    STP_RD_P(fb, 0); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 0);
+    STP_RD_S(fa, 1); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 0);
     if constexpr (D == 128) {
-      STP_RD_P(fb, 1); lds_wait<4>(); lds_tie(fa); STP_SP(fa, sacc);
-      STP_RD_S(fa, 2); lds_wait<4>(); lds_tie(fb); STP_SP(fb, pacc);
-      STP_RD_P(fb, 2); lds_wait<4>(); lds_tie(fa); STP_SP(fa, sacc);
-      STP_RD_S(fa, 3); lds_wait<4>(); lds_tie(fb); STP_SP(fb, pacc);
-      STP_RD_P(fb, 3); lds_wait<4>(); lds_tie(fa); STP_SP(fa, sacc);
+      STP_RD_P(fb, 1); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 1);
+      STP_RD_S(fa, 2); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 1);
+      STP_RD_P(fb, 2); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 2);
+      STP_RD_S(fa, 3); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 2);
+      STP_RD_P(fb, 3); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 3);
+      STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_P(fb, 3);   // first dO^T fragments ride through the vector phase
     } else {
-      STP_RD_P(fb, 1); lds_wait<4>(); lds_tie(fa); STP_SP(fa, sacc);
+      STP_RD_P(fb, 1); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 1);
+      STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_P(fb, 1);
     }
-    STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_SP(fb, pacc);   // first dO^T fragments ride through the vector phase
 
     // ---- P = exp(S - L), dS = P o (dP - delta); accumulator v of lane l: query qs0 + 8*(v/4) + 4*(l/32) + v%4, key kv_wave0 + l%32
     bf16x8_t pf[2], sf[2];
@@ -271,7 +292,10 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
     STP_RD_T(fa, o_lo, o_hi, 1); lds_wait<TR_READS>(); lds_tie(fb); STP_ACC(fb, dk, sf[0]);
     STP_RD_T(fb, q_lo, q_hi, 1); lds_wait<TR_READS>(); lds_tie(fa); STP_ACC(fa, dv, pf[1]);
     lds_wait<0>(); lds_tie(fb); STP_ACC(fb, dk, sf[1]);
+#undef STP_MM
 #undef STP_SP
+#undef STP_S
+#undef STP_P
 #undef STP_RD_S
 #undef STP_RD_P
 #undef STP_RD_T
@@ -359,7 +383,7 @@ __device__ __forceinline__ void dq_body(const bf16_t *__restrict__ qkv, const bf
   constexpr int KV_TILE = KVB * RB, STAGE = 2 * KV_TILE;      // LDS: ring of two stages { K [128][D], V [128][D] }
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform control flow
   const int lr = lane & 31, lg = lane >> 5;
   const int qsub = wave & 3, half = wave >> 2;
   const int nqblk = (seq + 127) / 128;
