@@ -121,20 +121,21 @@ enum { EPI_STORE = 0, EPI_GELU_DUAL = 1, EPI_GELU_BWD = 2, EPI_F32_ACCUM = 3 };
 // XCD-aware tile map: workgroups are dealt round-robin to the 8 XCDs, so XCD x (= blockIdx % 8) is given
 // the contiguous band [x*total/8, (x+1)*total/8) of a tile order that walks groups of 4 tile-rows
 // column by column: tiles resident on one XCD share their A / B panels in that XCD's L2.
-__device__ __forceinline__ void map_tile(int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int total = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  {
-    const int base = total >> 3, rem = total & 7;
-    const int x = pid & 7, j = pid >> 3;
-    pid = x * base + min(x, rem) + j;
-  }
+__device__ __forceinline__ int xcd_order(int total) {
+  const int base = total >> 3, rem = total & 7;
+  const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+  return x * base + min(x, rem) + j;
+}
+__device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int &tm, int &tn) {
   constexpr int GROUP_M = 4;
   int group = pid / (GROUP_M * tiles_n);
   int first_m = group * GROUP_M;
   int gsize = min(tiles_m - first_m, GROUP_M);
   tm = first_m + (pid % (GROUP_M * tiles_n)) % gsize;
   tn = (pid % (GROUP_M * tiles_n)) / gsize;
+}
+__device__ __forceinline__ void map_tile(int tiles_m, int tiles_n, int &tm, int &tn) {
+  tile_of(xcd_order(tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
 }
 
 // What the epilogue of 8 consecutive columns of one row reads from global memory: residual / aux in lo (8 bf16), the fp32
@@ -440,9 +441,8 @@ struct DmaOp {
 };
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTA, int NSTB, bool A_KC, bool B_KC, int EPI, bool KTAIL>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(const bf16_t *__restrict__ A, int lda, int a_bytes,
-                                                            const bf16_t *__restrict__ B, int ldb, int b_bytes, int M, int N, int K,
-                                                            int tiles_m, int tiles_n, Epi ep) {
+__device__ __forceinline__ void gemm_dma_tile(const bf16_t *__restrict__ A, int lda, int a_bytes, const bf16_t *__restrict__ B, int ldb, int b_bytes,
+                                              int M, int N, int K, int tm, int tn, const Epi &ep) {
   constexpr int NWAVES = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 32, NI = WN / 32;
   using OA = DmaOp<BM, A_KC, NWAVES, DK>;
@@ -464,8 +464,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
 #endif
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);   // same value, known wave-uniform: LDS targets of the loads stay scalar
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  int tm, tn;
-  map_tile(tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A), 0, a_bytes, 0x00020000);
@@ -617,6 +615,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(c
     }
   }
 #endif
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTA, int NSTB, bool A_KC, bool B_KC, int EPI, bool KTAIL>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(const bf16_t *__restrict__ A, int lda, int a_bytes,
+                                                            const bf16_t *__restrict__ B, int ldb, int b_bytes, int M, int N, int K,
+                                                            int tiles_m, int tiles_n, Epi ep) {
+  int tm, tn;
+  map_tile(tiles_m, tiles_n, tm, tn);
+  gemm_dma_tile<BM, BN, WAVES_M, WAVES_N, NSTA, NSTB, A_KC, B_KC, EPI, KTAIL>(A, lda, a_bytes, B, ldb, b_bytes, M, N, K, tm, tn, ep);
+}
+
+// Several products with one contraction length in one launch: the weight gradients of a unit.  Alone each of them ends in
+// a round of workgroups that fills a part of the chip.
+struct Problem { const bf16_t *A, *B; float *C; int lda, a_bytes, ldb, b_bytes, ldc, M, N, tiles_m, tiles_n, first; };
+struct ProblemSet { int n, tiles; Problem p[3]; };
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NSTA, int NSTB, bool A_KC, bool B_KC, bool KTAIL>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_set_kernel(ProblemSet set, int K) {
+  int pid = xcd_order(set.tiles);
+  const int i = set.n > 2 && pid >= set.p[2].first ? 2 : pid >= set.p[1].first ? 1 : 0;
+  const Problem &q = set.p[i];
+  int tm, tn;
+  tile_of(pid - q.first, q.tiles_m, q.tiles_n, tm, tn);
+  Epi ep = {};
+  ep.C = q.C;
+  ep.ldc = q.ldc;
+  gemm_dma_tile<BM, BN, WAVES_M, WAVES_N, NSTA, NSTB, A_KC, B_KC, EPI_F32_ACCUM, KTAIL>(q.A, q.lda, q.a_bytes, q.B, q.ldb, q.b_bytes, q.M, q.N, K,
+                                                                                     tm, tn, ep);
 }
 
 // =====================================================================================================
@@ -862,13 +887,29 @@ int launch_cfg(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t 
 // the GEMM (the braided block) those idle CUs are not idle and a GEMM spread over all of them only takes longer
 // per tile: with `shared_gpu` the choice is made differently (first lines of pick_tile).
 struct TileChoice { int bm, bn; };
-inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool shared_gpu) {
-  struct Cfg { int bm, bn, per_cu; double t_ktile[4]; };   // t_ktile index: 2 * a_kc + b_kc; 0 = layout not built
-  static const Cfg cfgs[5] = {{256, 256, 1, {0.779, 0.766, 0.782, 0.760}},
-                              {192, 256, 1, {0.0, 0.0, 0.584, 0.583}},
-                              {128, 256, 1, {0.445, 0.440, 0.430, 0.432}},
-                              {256, 128, 1, {0.460, 0.440, 0.432, 0.434}},
-                              {128, 128, 2, {0.244, 0.240, 0.235, 0.235}}};
+struct TileCfg { int bm, bn, per_cu; double t_ktile[4]; };   // t_ktile index: 2 * a_kc + b_kc; 0 = layout not built
+static const TileCfg kTiles[5] = {{256, 256, 1, {0.779, 0.766, 0.782, 0.760}},
+                                   {192, 256, 1, {0.0, 0.0, 0.584, 0.583}},
+                                   {128, 256, 1, {0.445, 0.440, 0.430, 0.432}},
+                                   {256, 128, 1, {0.460, 0.440, 0.432, 0.434}},
+                                   {128, 128, 2, {0.244, 0.240, 0.235, 0.235}}};
+inline long tile_count(const TileCfg &c, long M, long N) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); }
+// time of a launch of so many tiles that has the GPU to itself
+inline double launch_us(const TileCfg &c, long tiles, long K, int layout) {
+  const double kt = (double)((K + 31) / 32);
+  const long slots = 256L * c.per_cu;
+  const long full = tiles / slots, rem = tiles % slots;
+  const double tk = kt * c.t_ktile[layout], t_fixed = 1.0 + 3.0 * (c.bm * c.bn / 65536.0);
+  double t = (double)full * c.per_cu * (tk + t_fixed);
+  if (rem) {
+    // a partial round of the two-per-CU tile runs one workgroup per CU if it fits the 256 CUs
+    const bool paired = c.per_cu == 2 && rem > 256;
+    const double fill = paired ? rem / 512.0 : (rem < 256 ? rem / 256.0 : 1.0);
+    t += (paired ? 2.0 : 1.0) * (tk * (0.65 + 0.35 * fill * sqrt(fill)) + t_fixed);
+  }
+  return t;
+}
+inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool shared_gpu, double *us = nullptr) {
   if (shared_gpu) {
     // Beside other streams' kernels the rounds of the estimate below mean nothing (what a round leaves idle the
     // other streams use), and what counts is the work a tile costs the compute units: the biggest tile, which
@@ -881,24 +922,14 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool s
       if (((M + o[0] - 1) / o[0]) * ((N + o[1] - 1) / o[1]) >= 96) return TileChoice{o[0], o[1]};
     return TileChoice{128, 128};
   }
-  const double kt = (double)((K + 31) / 32);
   TileChoice best{256, 256};
   double best_t = 1e30;
-  for (const Cfg &c : cfgs) {
+  for (const TileCfg &c : kTiles) {
     if (c.t_ktile[2 * a_kc + b_kc] == 0.0) continue;
-    const long tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    const long slots = 256L * c.per_cu;
-    const long full = tiles / slots, rem = tiles % slots;
-    const double tk = kt * c.t_ktile[2 * a_kc + b_kc], t_fixed = 1.0 + 3.0 * (c.bm * c.bn / 65536.0);
-    double t = (double)full * c.per_cu * (tk + t_fixed);
-    if (rem) {
-      // a partial round of the two-per-CU tile runs one workgroup per CU if it fits the 256 CUs
-      const bool paired = c.per_cu == 2 && rem > 256;
-      const double fill = paired ? rem / 512.0 : (rem < 256 ? rem / 256.0 : 1.0);
-      t += (paired ? 2.0 : 1.0) * (tk * (0.65 + 0.35 * fill * sqrt(fill)) + t_fixed);
-    }
+    const double t = launch_us(c, tile_count(c, M, N), K, 2 * a_kc + b_kc);
     if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn}; }
   }
+  if (us) *us = best_t;
   return best;
 }
 
@@ -959,6 +990,63 @@ int launch_layout(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s) {
   if (a->epilogue == 1) return launch_tile<A_KC, B_KC, EPI_GELU_DUAL>(ctx, a, ep, s);
   if (a->epilogue == 2) return launch_tile<A_KC, B_KC, EPI_GELU_BWD>(ctx, a, ep, s);
   return launch_tile<A_KC, B_KC, EPI_STORE>(ctx, a, ep, s);
+}
+
+template <int BM, int BN, int NSTA, int NSTB, bool KTAIL>
+int launch_set(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s) {
+  constexpr size_t smem = (size_t)(NSTA * BM + NSTB * BN) * DK * 2;
+  auto kern = gemm_bf16_set_kernel<BM, BN, 2, 4, NSTA, NSTB, false, false, KTAIL>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    attr_set = true;
+  }
+  ProblemSet set;
+  set.n = n;
+  set.tiles = 0;
+  for (int i = 0; i < n; i++) {
+    const int tm = (a[i].M + BM - 1) / BM, tn = (a[i].N + BN - 1) / BN;
+    set.p[i] = {(const bf16_t *)a[i].A, (const bf16_t *)a[i].B, (float *)a[i].C, a[i].lda, (int)operand_bytes(false, a[i].M, a[i].K, a[i].lda), a[i].ldb,
+                (int)operand_bytes(false, a[i].N, a[i].K, a[i].ldb), a[i].ldc, a[i].M, a[i].N, tm, tn, set.tiles};
+    set.tiles += tm * tn;
+  }
+  hipLaunchKernelGGL(kern, dim3(set.tiles), dim3(512), smem, s, set, a[0].K);
+  STP_LAUNCH_CHECK(ctx);
+  return STP_OK;
+}
+
+// A set takes one launch where the estimate of its time is below the sum of the estimates of its products.
+inline bool set_tile(stp_ctx *ctx, const stp_gemm_args *a, int n, TileChoice *choice) {
+  double apart = 0.0, together = 1e30;
+  for (int i = 0; i < n; i++) {
+    if (a[i].K <= 0 || !operand_bytes(false, a[i].M, a[i].K, a[i].lda) || !operand_bytes(false, a[i].N, a[i].K, a[i].ldb) ||
+        wavek_shape(a[i].M, a[i].N, a[i].K)) return false;
+    // accumulators that overlap are added to one after the other
+    const float *c0 = (const float *)a[i].C, *c1 = c0 + (size_t)(a[i].M - 1) * a[i].ldc + a[i].N;
+    for (int j = 0; j < i; j++) {
+      const float *d0 = (const float *)a[j].C, *d1 = d0 + (size_t)(a[j].M - 1) * a[j].ldc + a[j].N;
+      if (c0 < d1 && d0 < c1) return false;
+    }
+    double t;
+    pick_tile(a[i].M, a[i].N, a[i].K, false, false, false, &t);
+    apart += t;
+  }
+  for (const TileCfg &c : kTiles) {
+    if (c.t_ktile[0] == 0.0) continue;
+    long tiles = 0;
+    for (int i = 0; i < n; i++) tiles += tile_count(c, a[i].M, a[i].N);
+    const double t = launch_us(c, tiles, a[0].K, 0);
+    if (t < together) { together = t; *choice = TileChoice{c.bm, c.bn}; }
+  }
+  return together < 0.98 * apart;
+}
+
+template <bool KTAIL>
+int launch_set_tile(stp_ctx *ctx, const stp_gemm_args *a, int n, TileChoice c, hipStream_t s) {
+  if (c.bm == 256 && c.bn == 128) return launch_set<256, 128, 3, 3, KTAIL>(ctx, a, n, s);
+  if (c.bm == 128 && c.bn == 256) return launch_set<128, 256, 3, 3, KTAIL>(ctx, a, n, s);
+  if (c.bm == 128 && c.bn == 128) return launch_set<128, 128, 3, 2, KTAIL>(ctx, a, n, s);
+  return launch_set<256, 256, 3, 2, KTAIL>(ctx, a, n, s);
 }
 
 }  // namespace

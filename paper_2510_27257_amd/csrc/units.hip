@@ -191,8 +191,7 @@ extern "C" int stp_gemm_tile_hints_clear(stp_ctx *ctx) {
   return STP_OK;
 }
 
-extern "C" int stp_gemm(stp_ctx *ctx, const stp_gemm_args *g, void *hip_stream) {
-  if (!ctx) return STP_EINVAL;
+static int check_gemm(stp_ctx *ctx, const stp_gemm_args *g) {
   if (!g || !g->A || !g->B || !g->C) return stp_fail(ctx, STP_EINVAL, "stp_gemm: null pointer%s");
   if (g->dtype != STP_BF16 && g->dtype != STP_F32) return stp_fail(ctx, STP_EINVAL, "stp_gemm: bad dtype%s");
   if (g->M < 0 || g->N < 0 || g->K < 0) return stp_fail(ctx, STP_ESHAPE, "stp_gemm: negative dimension%s");
@@ -216,6 +215,13 @@ extern "C" int stp_gemm(stp_ctx *ctx, const stp_gemm_args *g, void *hip_stream) 
       return stp_fail(ctx, STP_EINVAL, "stp_gemm: tile_m / tile_n must both be 0, or 128 or 256 each, or 192 x 256 with a_trans = 0, "
                                        "for bf16 with K %% 32 == 0%s");
   }
+  return STP_OK;
+}
+
+extern "C" int stp_gemm(stp_ctx *ctx, const stp_gemm_args *g, void *hip_stream) {
+  if (!ctx) return STP_EINVAL;
+  const int rc = check_gemm(ctx, g);
+  if (rc != STP_OK) return rc;
   if (g->M == 0 || g->N == 0) return STP_OK;
   hipStream_t s = (hipStream_t)hip_stream;
   return g->dtype == STP_BF16 ? stp_launch_gemm_bf16(ctx, g, s) : stp_launch_gemm_f32(ctx, g, s);
@@ -479,18 +485,26 @@ extern "C" int stp_backward_weight_unit(stp_ctx *ctx, const stp_layer_desc *d, i
   const int T = d->seq * d->mbsz, h = d->hidden, a = d->heads_local * d->head_dim, ff = d->ffn_local;
   const float inv_t = 1.0f / (float)d->tp;
   // dW[in, out] += act^T grad: both operands are [tokens, features], contraction over tokens
+  stp_gemm_args set[3];
+  int n = 0;
   auto wgemm = [&](const void *act, int in, const void *grad, int out, float *dw) -> int {
     if (!dw) return STP_OK;
-    stp_gemm_args g = gemm_base(d, in, out, T);
+    stp_gemm_args &g = set[n++] = gemm_base(d, in, out, T);
     g.A = act; g.lda = in; g.a_trans = 1;
     g.B = grad; g.ldb = out; g.b_trans = 0;
     g.C = dw; g.ldc = out; g.c_f32_accum = 1;
-    return stp_gemm(ctx, &g, hip_stream);
+    return check_gemm(ctx, &g);
+  };
+  auto issue = [&]() -> int {
+    if (d->dtype == STP_BF16) return stp_launch_gemm_bf16_wgrads(ctx, set, n, (hipStream_t)hip_stream);
+    for (int i = 0; i < n; i++) RET_IF(stp_launch_gemm_f32(ctx, &set[i], (hipStream_t)hip_stream));
+    return STP_OK;
   };
   if (unit == STP_MLP) {
     RET_IF(wgemm(f.p[STP_ST_G], ff, dy, h, wg->w_fc2));
     RET_IF(wgemm(f.p[STP_ST_Z_LN], h, f.p[STP_ST_DH], ff, wg->w_fc1));
     if (d->act == STP_ACT_SWIGLU) RET_IF(wgemm(f.p[STP_ST_Z_LN], h, f.p[STP_ST_DHU], ff, wg->w_up));
+    RET_IF(issue());
     if (d->has_bias) {
       if (wg->b_fc1) RET_IF(stp_colsum(ctx, d->dtype, T, ff, f.p[STP_ST_DH], 1.0f, wg->b_fc1, lane, hip_stream));
       if (wg->b_fc2) RET_IF(stp_colsum(ctx, d->dtype, T, h, dy, inv_t, wg->b_fc2, lane, hip_stream));
@@ -499,6 +513,7 @@ extern "C" int stp_backward_weight_unit(stp_ctx *ctx, const stp_layer_desc *d, i
   }
   RET_IF(wgemm(f.p[STP_ST_CTX], a, dy, h, wg->w_o));
   RET_IF(wgemm(f.p[STP_ST_X_LN], h, f.p[STP_ST_DQKV], stp_qkv_width(d), wg->w_qkv));
+  RET_IF(issue());
   if (d->has_bias) {
     if (wg->b_qkv) RET_IF(stp_colsum(ctx, d->dtype, T, stp_qkv_width(d), f.p[STP_ST_DQKV], 1.0f, wg->b_qkv, lane, hip_stream));
     if (wg->b_o) RET_IF(stp_colsum(ctx, d->dtype, T, h, dy, inv_t, wg->b_o, lane, hip_stream));
