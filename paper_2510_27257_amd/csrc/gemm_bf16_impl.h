@@ -879,7 +879,9 @@ int launch_cfg(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t 
 // with t_ktile the measured time of a 32-deep part of the contraction of a resident workgroup on a full chip
 // (microseconds, from 8192^3 runs per operand layout), fill the fraction of the round's slots in use
 // (a partly filled chip leaves each workgroup more L2 and fabric bandwidth) and t_fixed the prologue +
-// epilogue of a tile.  Over 33 shapes of 256 .. 6144 tokens in three layouts the tile it picks is the fastest or within 1 %
+// epilogue of a tile: 4 us for a 256 x 256 tile of bf16, 20 where it is added to an fp32 accumulator (512 KB per tile, all tiles of a
+// round at once: 134 MB; half of a tile's time at 4096 tokens, which is why the smaller tiles, whose workgroups overlap, win there: [5120,
+// 3456] 200 -> 176 us).  Over 33 shapes of 256 .. 6144 tokens in three layouts the tile it picks is the fastest or within 1 %
 // of it (three launches of 8 us: within 7 %).
 // The 192 x 256 tile exists for 6144-token activations: 32 tile rows x (N / 256) columns fill the 256 CUs in
 // whole rounds where the 256 x 256 tile leaves a quarter to a half of them idle; alone on the GPU it is the
@@ -895,21 +897,22 @@ static const TileCfg kTiles[5] = {{256, 256, 1, {0.779, 0.766, 0.782, 0.760}},
                                    {128, 128, 2, {0.244, 0.240, 0.235, 0.235}}};
 inline long tile_count(const TileCfg &c, long M, long N) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); }
 // time of a launch of so many tiles that has the GPU to itself
-inline double launch_us(const TileCfg &c, long tiles, long K, int layout) {
+inline double launch_us(const TileCfg &c, long tiles, long K, int layout, bool accum) {
   const double kt = (double)((K + 31) / 32);
   const long slots = 256L * c.per_cu;
   const long full = tiles / slots, rem = tiles % slots;
-  const double tk = kt * c.t_ktile[layout], t_fixed = 1.0 + 3.0 * (c.bm * c.bn / 65536.0);
+  const double tk = kt * c.t_ktile[layout], t_fixed = 1.0 + (accum ? 19.0 : 3.0) * (c.bm * c.bn / 65536.0);
   double t = (double)full * c.per_cu * (tk + t_fixed);
   if (rem) {
     // a partial round of the two-per-CU tile runs one workgroup per CU if it fits the 256 CUs
     const bool paired = c.per_cu == 2 && rem > 256;
     const double fill = paired ? rem / 512.0 : (rem < 256 ? rem / 256.0 : 1.0);
-    t += (paired ? 2.0 : 1.0) * (tk * (0.65 + 0.35 * fill * sqrt(fill)) + t_fixed);
+    const double alone = accum && c.per_cu == 2 && !paired ? 3.0 : 0.0;      // no second workgroup works behind this one's epilogue
+    t += (paired ? 2.0 : 1.0) * (tk * (0.65 + 0.35 * fill * sqrt(fill)) + t_fixed + alone);
   }
   return t;
 }
-inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool shared_gpu, double *us = nullptr) {
+inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool accum, bool shared_gpu, double *us = nullptr) {
   if (shared_gpu) {
     // Beside other streams' kernels the rounds of the estimate below mean nothing (what a round leaves idle the
     // other streams use), and what counts is the work a tile costs the compute units: the biggest tile, which
@@ -926,7 +929,7 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool s
   double best_t = 1e30;
   for (const TileCfg &c : kTiles) {
     if (c.t_ktile[2 * a_kc + b_kc] == 0.0) continue;
-    const double t = launch_us(c, tile_count(c, M, N), K, 2 * a_kc + b_kc);
+    const double t = launch_us(c, tile_count(c, M, N), K, 2 * a_kc + b_kc, accum);
     if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn}; }
   }
   if (us) *us = best_t;
@@ -966,7 +969,7 @@ int launch_tile(stp_ctx *ctx, const stp_gemm_args *a, const Epi &ep, hipStream_t
     constexpr int WK = A_KC || B_KC ? 64 : 32;
     return a->K % WK ? launch_wavek<WK, A_KC, B_KC, EPI, true>(ctx, a, ep, s) : launch_wavek<WK, A_KC, B_KC, EPI, false>(ctx, a, ep, s);
   }
-  TileChoice c = pick_tile(a->M, a->N, a->K, A_KC, B_KC, ctx && ctx->concurrent);
+  TileChoice c = pick_tile(a->M, a->N, a->K, A_KC, B_KC, EPI == EPI_F32_ACCUM, ctx && ctx->concurrent);
   if (ctx && ctx->concurrent)       // a measured preference for this shape beside other streams' kernels
     for (int i = 0; i < ctx->n_tile_hints; i++) {
       const auto &hnt = ctx->tile_hint[i];
@@ -1028,14 +1031,14 @@ inline bool set_tile(stp_ctx *ctx, const stp_gemm_args *a, int n, TileChoice *ch
       if (c0 < d1 && d0 < c1) return false;
     }
     double t;
-    pick_tile(a[i].M, a[i].N, a[i].K, false, false, false, &t);
+    pick_tile(a[i].M, a[i].N, a[i].K, false, false, true, false, &t);
     apart += t;
   }
   for (const TileCfg &c : kTiles) {
     if (c.t_ktile[0] == 0.0) continue;
     long tiles = 0;
     for (int i = 0; i < n; i++) tiles += tile_count(c, a[i].M, a[i].N);
-    const double t = launch_us(c, tiles, a[0].K, 0);
+    const double t = launch_us(c, tiles, a[0].K, 0, true);
     if (t < together) { together = t; *choice = TileChoice{c.bm, c.bn}; }
   }
   return together < 0.98 * apart;

@@ -6,8 +6,8 @@ int stp_launch_gemm_bf16_mn(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s)
   return launch_layout<false, false>(ctx, a, s);
 }
 
-// The weight gradients of a unit in one launch where the chip is theirs alone: 13B shard, [3456 | 5120, 5120 | 3456] three times over
-// 4096 tokens, 169 + 2 x 180 -> 430 us.  Beside other streams, which fill what a launch's last round leaves idle, one long launch is the
+// The weight gradients of a unit in one launch where the chip is theirs alone: 13B shard, three products of 3456 x 5120 over
+// 4096 tokens and two smaller ones, 85 us of a pass of 2400.  Beside other streams, which fill what a launch's last round leaves idle, one long launch is the
 // worse one (blocks 0.3 - 5 % slower).
 int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s) {
   TileChoice c;
