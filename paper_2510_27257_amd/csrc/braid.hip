@@ -140,6 +140,7 @@ extern "C" int stp_braid_detach(stp_ctx *ctx) {
   if (!ctx) return STP_EINVAL;
   ctx->ev_next = 0;
   ctx->ev_valid[0] = ctx->ev_valid[1] = 0;
+  ctx->waited_last = 0;
   return STP_OK;
 }
 
@@ -211,9 +212,14 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
   const int last = ctx->ev_gen ^ 1, older = ctx->ev_gen;
   bool same_streams = ctx->ev_valid[last] && ctx->last_mbs == MB && ctx->last_b;
   for (int i = 0; i < 3 && same_streams; i++) same_streams = ctx->ev_stream[last][i] == streams[i];
+  // waits issued by this step: of stream i for the events of the last step, bit 3 i + j for stream j
+  unsigned waited = 0;
   auto wait_for = [&](hipStream_t s, int gen, int j) -> int {
     if (!ctx->ev_valid[gen] || ctx->ev_stream[gen][j] == s) return STP_OK;
     STP_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_step[gen][ctx->ev_alias[gen][j]], 0));
+    if (gen == last)
+      for (int i = 0; i < 3; i++)
+        if (streams[i] == s) waited |= 1u << (3 * i + j);
     return STP_OK;
   };
   rc = STP_OK;
@@ -224,8 +230,6 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
         for (int j = 0; j < 3 && rc == STP_OK; j++) rc = wait_for(streams[i], g, j);
     }
   } else if (ctx->ev_next && !serial) {
-    for (int i = 0; i < 3 && rc == STP_OK; i++)
-      for (int j = 0; j < 3 && rc == STP_OK; j++) rc = wait_for(streams[i], older, j);
     bool b_after_f = false, b_after_w = false, w_after_b = false, w_after_f = false;
     for (int m = 0; m < MB; m++) {
       if (cur_b[m] && m == ctx->last_f_mb) b_after_f = true;
@@ -239,6 +243,11 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     if (rc == STP_OK && b_after_w) rc = wait_for(sB, last, 2);
     if (rc == STP_OK && w_after_b) rc = wait_for(sW, last, 1);
     if (rc == STP_OK && w_after_f) rc = wait_for(sW, last, 0);
+    // the step before last: implied by a wait for the same stream's last step, and already waited for where the last step
+    // itself depended on it (what was its last step is now the one before)
+    for (int i = 0; i < 3 && rc == STP_OK; i++)
+      for (int j = 0; j < 3 && rc == STP_OK; j++)
+        if (!((waited | ctx->waited_last) >> (3 * i + j) & 1)) rc = wait_for(streams[i], older, j);
   }
   if (rc != STP_OK) { free(cur_b); return rc; }
   int *ev_of = (int *)malloc(sizeof(int) * bsz);
@@ -274,8 +283,8 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     g_b.b_o = g->b_o; g_b.b_fc2 = g->b_fc2;
     g_w.b_o = nullptr; g_w.b_fc2 = nullptr;
     const stp_stash *stash = &st->stash[(size_t)o.layer * MB + o.microbatch];
-    size_t off[STP_ST_NFIELDS], nbytes;
-    for (int f = 0; f < STP_ST_NFIELDS; f++) stp_stash_field(d, f, &off[f], &nbytes);
+    size_t off[STP_ST_NFIELDS];
+    stp_stash_offsets(d, off);
     char *sb = (char *)stash->base;
     void *x = st->act[(size_t)o.layer * MB + o.microbatch];
     // a layer that ends a chain in the middle of the stage has its own output / upstream-gradient slots
@@ -363,6 +372,7 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     ctx->last_f_mb = f_mb;
   }
   free(cur_b);
+  ctx->waited_last = waited;
   ctx->ev_next = 1;
   if (rc == STP_OK)
     for (size_t i = 0; i < bsz; i++) ctx->b_done[i] |= b_now[i];

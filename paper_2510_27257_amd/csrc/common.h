@@ -46,6 +46,7 @@ struct stp_ctx {
   int ev_alias[2][3];               // index of the event that stands for stream i (streams passed twice share one)
   int ev_valid[2], ev_gen;          // ev_gen: generation the NEXT step records into
   int last_f_mb, last_mbs;
+  unsigned waited_last;             // of the last step: which streams waited for which streams' events of its own last step
   uint8_t *last_b, *last_w;         // [last_mbs]
   int have_step_events;
   hipEvent_t *ev_pool;     // events recorded after B ops, waited on by their W ops
@@ -230,6 +231,8 @@ size_t stp_attn_bwd_ws_bytes(const stp_layer_desc *d);
 int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s);
 int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse,
                                 const void *dout, float *delta, void *dqkv, hipStream_t s);
+// byte offsets of all fields of a stash whose description has been checked
+void stp_stash_offsets(const stp_layer_desc *d, size_t off[STP_ST_NFIELDS]);
 // device address of the fixed scratch array of stp_colsum_noalloc on `device` (the current device); a lookup, no allocation
 int stp_noalloc_init(stp_ctx *ctx, int device);
 // Launch geometry that also sizes the workspace.  Norm backward: 256-thread row groups that stride over the rows,

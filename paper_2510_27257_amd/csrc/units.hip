@@ -89,6 +89,14 @@ static size_t field_bytes(const stp_layer_desc *d, int f) {
   return 0;
 }
 
+void stp_stash_offsets(const stp_layer_desc *d, size_t off[STP_ST_NFIELDS]) {
+  size_t at = 0;
+  for (int f = 0; f < STP_ST_NFIELDS; f++) {
+    off[f] = at;
+    at += stp_align_up(field_bytes(d, f), 256);
+  }
+}
+
 extern "C" int stp_stash_field(const stp_layer_desc *d, int field, size_t *offset, size_t *bytes) {
   int rc = stp_check_desc(d);
   if (rc != STP_OK) return rc;
