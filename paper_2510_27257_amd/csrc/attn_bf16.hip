@@ -597,9 +597,10 @@ static AttnCost attn_cost(int kind, int head_dim) {
   static const AttnCost c128[3] = {{11.5, 1.75}, {12.0, 1.90}, {12.0, 2.65}}, c64[3] = {{6.5, 1.30}, {4.5, 1.20}, {4.5, 1.70}};
   return head_dim == 128 ? c128[kind] : c64[kind];
 }
-// compute units a chunked attention launch counts on inside a braided block (measured: 96 gives the fastest block on
-// the 4-head and 10-head workloads, 0.3 - 2.5 % ahead of planning for all 256; 32 is 4 - 8 % behind)
-#define STP_ATTN_SHARED_CUS 96
+// The plan is made for the whole chip, also where other streams' kernels take a part of it: chunk lengths and the four-wave rule
+// below decide in which order a row's keys are added up, and a layer's bits may not depend on what runs beside it.  A plan for 96
+// compute units inside a braided block measured the same there (blocks and stages 0.997 - 1.007 x, ViT layers 1.5 % slower).
+constexpr int PLAN_CUS = 256;
 
 namespace {
 
@@ -628,8 +629,8 @@ double combine_us(const PlanPart &p) {
   return 4.0 + (double)pieces * p.z * p.partial / 3e6;
 }
 
-// no schedule of these chunks over `cus` compute units is shorter
-double plan_bound(const PlanPart *part, int n, int cus) {
+// no schedule of these chunks over the chip is shorter
+double plan_bound(const PlanPart *part, int n) {
   double sum = 0.0, longest = 0.0, combine = 0.0;
   for (int i = 0; i < n; i++) {
     double s = 0.0;
@@ -637,17 +638,17 @@ double plan_bound(const PlanPart *part, int n, int cus) {
     sum += s * part[i].z;
     combine += combine_us(part[i]);
   }
-  return std::max(longest, sum / cus) + combine;
+  return std::max(longest, sum / PLAN_CUS) + combine;
 }
 
 // Time of a launch whose workgroups, longest first, each go to the compute unit that is free first (one workgroup each).
-double plan_makespan(const PlanPart *part, int n, int cus) {
+double plan_makespan(const PlanPart *part, int n) {
   // many (head, sequence) pairs: a smaller machine with proportionally fewer of them gives the same picture and keeps the
   // planning time bounded
   int zmin = part[0].z, zmax = part[0].z;
   for (int i = 1; i < n; i++) { zmin = std::min(zmin, part[i].z); zmax = std::max(zmax, part[i].z); }
   const int keep = std::max(1, std::min(zmin, 16 * zmin / zmax));       // of the zmin pairs of the part with the fewest
-  cus = std::max(1, cus * keep / zmin);
+  const int cus = std::max(1, PLAN_CUS * keep / zmin);
   std::vector<std::pair<double, int>> items;
   double combine = 0.0;
   for (int i = 0; i < n; i++) {
@@ -669,19 +670,17 @@ double plan_makespan(const PlanPart *part, int n, int cus) {
   return end + combine;
 }
 
-// Chunk lengths (part[i].c) with the shortest simulated launch on `cus` compute units: all 256 when it has the GPU to itself;
-// fewer inside a braided block, where longer chunks, i.e. fewer workgroups with their fixed cost, win because the other
-// streams' kernels fill what an uneven end of the launch leaves idle.  min_c[i]: never shorter than this.  Two kinds of item
-// share a launch in the backward pass: the second's chunk is as long as the first's in time (or whole blocks).
+// Chunk lengths (part[i].c) with the shortest simulated launch; returns its time.  Two kinds of item share a launch in the
+// backward pass: the second's chunk is as long as the first's in time (or whole blocks).
 // A block is never cut into more than 8 pieces (bounds the workspace and fits the table's 3 chunk bits).
-double plan_chunks(PlanPart *part, int n, int cus, const int *min_c) {
-  auto least = [&](int i) { return std::max(min_c[i], std::max((part[i].max_steps + 7) / 8, std::min(part[i].max_steps, 4))); };
+double plan_chunks(PlanPart *part, int n) {
+  auto least = [&](int i) { return std::max((part[i].max_steps + 7) / 8, std::min(part[i].max_steps, 4)); };
   struct Cand { double bound; int c[2]; };
   std::vector<Cand> cand;
   auto add = [&](int c0, int c1) {
     part[0].c = c0;
     if (n > 1) part[1].c = c1;
-    cand.push_back({plan_bound(part, n, cus), {c0, c1}});
+    cand.push_back({plan_bound(part, n), {c0, c1}});
   };
   const int lo = least(0), hi = std::max(lo, part[0].max_steps), stride = std::max(1, (hi - lo) / 40);
   auto first = [&](int c) {
@@ -706,7 +705,7 @@ double plan_chunks(PlanPart *part, int n, int cus, const int *min_c) {
     if (k.bound >= best * 0.995 || tries >= 24) break;
     part[0].c = k.c[0];
     if (n > 1) part[1].c = k.c[1];
-    const double t = plan_makespan(part, n, cus);
+    const double t = plan_makespan(part, n);
     tries++;
     if (t < best * 0.995) { best = t; bc[0] = k.c[0]; bc[1] = k.c[1]; }
   }
@@ -738,10 +737,10 @@ void plan_fill(const PlanPart &p, stp_attn_plan *plan) {
 // block or the sum of all bounds the launch.  Measured (us, eight waves / four): 8 x 8 heads, 520 tokens 16.6 / 14.4; 2 x 16
 // heads, 4096 tokens 112 / 90; 10 heads on 2 x 3000 tokens 46 / 51; 16 heads, 1024 tokens, no mask 16.4 / 19.3.  At head dimension 128
 // (two workgroups a compute unit) it is the slower one wherever there is work for the whole chip (281 / 308 at 16384 tokens).
-double four_wave_us(const PlanPart &p, int cus) {
+double four_wave_us(const PlanPart &p) {
   double sum = 0.0;
   for (int x = 0; x < p.nblocks; x++) sum += 2.0 + 1.2 * p.steps[x];
-  return std::max(6.0 + 1.8 * p.max_steps, sum * p.z / cus);
+  return std::max(6.0 + 1.8 * p.max_steps, sum * p.z / PLAN_CUS);
 }
 
 int max_of(const int *v, int n) { return *std::max_element(v, v + n); }
@@ -770,17 +769,11 @@ stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit) {
   return p;
 }
 
-void stp_attn_bwd_chunks(bool shared, const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]) {
+void stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]) {
   const int nk = stp_kv_heads(d), D = d->head_dim;
   PlanPart part[2] = {{attn_cost(1, D), nkv, nk * d->mbsz, max_of(steps_kv, nkv), 0, steps_kv, (size_t)2 * 128 * D * sizeof(float)},
                       {attn_cost(2, D), nq, d->heads_local * d->mbsz, max_of(steps_q, nq), 0, steps_q, (size_t)128 * D * sizeof(float)}};
-  int min_c[2] = {0, 0};
-  plan_chunks(part, 2, 256, min_c);
-  if (shared) {     // never shorter chunks than alone: the workspace is sized by the lone plan's chunk count
-    min_c[0] = part[0].c;
-    min_c[1] = part[1].c;
-    plan_chunks(part, 2, STP_ATTN_SHARED_CUS, min_c);
-  }
+  plan_chunks(part, 2);
   chunk[0] = part[0].c;
   chunk[1] = part[1].c;
 }
@@ -792,9 +785,8 @@ void stp_attn_plan_fill(stp_attn_plan *plan, int chunk, int nblocks, const int *
 namespace {
 
 const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d) {
-  const bool shared = ctx && ctx->concurrent;
   const int nqb = (d->seq + QB - 1) / QB;
-  const int key[8] = {1 + (shared ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nqb};
+  const int key[8] = {1, d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nqb};
   bool hit;
   stp_attn_plan *plan = stp_attn_plan_slot(ctx, key, &hit);
   if (hit) return plan;
@@ -802,13 +794,8 @@ const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d) {
   for (int x = 0; x < nqb; x++) steps[x] = attn_steps(x, d->seq, d->causal);
   PlanPart part = {attn_cost(0, d->head_dim), nqb, d->heads_local * d->mbsz, max_of(steps.data(), nqb), 0, steps.data(),
                    (size_t)(QB * d->head_dim + 2 * QB) * sizeof(float)};
-  int min_c = 0;
-  double t = plan_chunks(&part, 1, 256, &min_c);
-  if (shared) {     // never shorter chunks than alone: the workspace is sized by the lone plan's chunk count
-    min_c = part.c;
-    t = plan_chunks(&part, 1, STP_ATTN_SHARED_CUS, &min_c);
-  }
-  const bool four = d->head_dim == 64 && four_wave_us(part, shared ? STP_ATTN_SHARED_CUS : 256) < t;
+  const double t = plan_chunks(&part, 1);
+  const bool four = d->head_dim == 64 && four_wave_us(part) < t;
   if (four) part.c = part.max_steps;
   plan_fill(part, plan);
   if (four) plan->halves = 1;

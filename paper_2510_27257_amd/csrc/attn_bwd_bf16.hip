@@ -673,9 +673,8 @@ __global__ __launch_bounds__(256) void attn_bwd_combine_kernel(const float *__re
 // the plan of one of the two kernels (kind 1 dkv: block x = key block x; 2 dq: block x = query block x) for this shape; they
 // are made together
 const stp_attn_plan *bwd_plan(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
-  const bool shared = ctx && ctx->concurrent;
   const int nb = (d->seq + 127) / 128, nq = (d->seq + QSTEP - 1) / QSTEP;
-  int key[8] = {kind + 1 + (shared ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nb};
+  int key[8] = {kind + 1, d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, nb};
   bool hit;
   stp_attn_plan *plan = stp_attn_plan_slot(ctx, key, &hit);
   if (hit) return plan;
@@ -686,7 +685,7 @@ const stp_attn_plan *bwd_plan(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
     steps[1][x] = dq_steps(x, d->seq, d->causal);
   }
   int chunk[2];
-  stp_attn_bwd_chunks(shared, d, nb, steps[0].data(), nb, steps[1].data(), chunk);
+  stp_attn_bwd_chunks(d, nb, steps[0].data(), nb, steps[1].data(), chunk);
   stp_attn_plan_fill(plan, chunk[kind - 1], nb, steps[kind - 1].data());
   key[0] += kind == 1 ? 1 : -1;
   stp_attn_plan *other = stp_attn_plan_slot(ctx, key, &hit);
@@ -697,7 +696,7 @@ const stp_attn_plan *bwd_plan(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
 // The merged work order of the fused launch: the (block, chunk) pairs of both kernels, sorted by the plan's
 // estimate of their time, longest first (ties keep dkv before dq and each kernel's own order).
 const stp_attn_plan *fused_plan(stp_ctx *ctx, const stp_layer_desc *d, const stp_attn_plan &pkv, const stp_attn_plan &pq) {
-  const int key[8] = {4 + (ctx && ctx->concurrent ? 16 : 0), d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, 0};
+  const int key[8] = {4, d->seq, d->causal, d->heads_local, stp_kv_heads(d), d->mbsz, d->head_dim, 0};
   bool hit;
   stp_attn_plan *p = stp_attn_plan_slot(ctx, key, &hit);
   if (hit) return p;

@@ -215,7 +215,7 @@ static inline int stp_qkv_width(const stp_layer_desc *d) { return (d->heads_loca
 
 // Chunk lengths {dkv, dq} of the backward kernels, planned together because one launch runs both; steps_*[x] is the number of
 // steps of block x.
-void stp_attn_bwd_chunks(bool shared, const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]);
+void stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]);
 // fills in the work order of blocks cut into chunks of `chunk` steps
 void stp_attn_plan_fill(stp_attn_plan *plan, int chunk, int nblocks, const int *steps);
 // the context's (or, without one, the thread's) cache slot for a plan with this tag; *hit says whether it is filled

@@ -1,0 +1,71 @@
+"""fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN; and as many (head, sequence)
+pairs as a description allows."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_2510_27257_amd as stp
+from paper_2510_27257_amd.synth import Workload
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = stp.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def attention(ctx, n, nk, d, seq, mbsz, causal, qkv, dout):
+    desc = stp.make_desc(Workload("w", 64, n, d, 64, seq, 1, dtype="f32", causal=causal, kv_heads=nk), mbsz=mbsz)
+    out, dqkv = torch.zeros_like(dout), torch.zeros_like(qkv)
+    lse, delta = (torch.zeros((mbsz, n, seq), device="cuda") for _ in range(2))
+    ctx.attention_forward(desc, qkv, out, lse)
+    ctx.attention_backward(desc, qkv, out, lse, dout, delta, dqkv)
+    torch.cuda.synchronize()
+    a, ak = n * d, nk * d
+    return {"out": out, "lse": lse[0].t(), "dq": dqkv[:, :a], "dk": dqkv[:, a:a + ak], "dv": dqkv[:, a + ak:]}
+
+
+# one head dimension per kernel instantiation; 168 rows: five blocks of 32 and one of eight; the row before the last block's
+# end, its end, and one in the middle of a block
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("t", [45, 164, 167])
+@pytest.mark.parametrize("n,nk,d", [(2, 2, 24), (4, 2, 64), (2, 1, 104)])
+def test_rows_behind_the_causal_mask_stay_out(ctx, n, nk, d, t, bad):
+    seq = 168
+    g = torch.Generator(device="cuda").manual_seed(d)
+    qkv = torch.randn((seq, (n + 2 * nk) * d), generator=g, device="cuda")
+    dout = torch.randn((seq, n * d), generator=g, device="cuda")
+    clean = attention(ctx, n, nk, d, seq, 1, True, qkv, dout)
+    a, ak = n * d, nk * d
+    before, after, others = slice(0, t), slice(t + 1, seq), [i for i in range(seq) if i != t]
+    # the operand whose row t is replaced -> the rows of each result that do not depend on it
+    untouched = {"q": {"out": others, "lse": others, "dq": others, "dk": after, "dv": after},
+                 "k": {"out": before, "lse": before, "dq": before},
+                 "v": {"out": before, "lse": slice(0, seq), "dq": before, "dv": slice(0, seq)},
+                 "dout": {"out": slice(0, seq), "dq": others, "dk": after, "dv": after}}
+    for operand, rows in untouched.items():
+        x, y = qkv.clone(), dout.clone()
+        if operand == "dout":
+            y[t] = bad
+        else:
+            x[t, {"q": slice(0, a), "k": slice(a, a + ak), "v": slice(a + ak, None)}[operand]] = bad
+        got = attention(ctx, n, nk, d, seq, 1, True, x, y)
+        for name, r in rows.items():
+            assert torch.equal(got[name][r], clean[name][r]), (operand, name)
+
+
+def test_infinite_rows_keep_their_sign(ctx):
+    """Every query sees every key: an infinite value is infinite in each output row, and an infinite upstream gradient
+    in each value gradient, in the last, partly empty block as well."""
+    n, d, seq = 2, 40, 72
+    g = torch.Generator(device="cuda").manual_seed(1)
+    qkv = torch.randn((seq, 3 * n * d), generator=g, device="cuda")
+    dout = torch.randn((seq, n * d), generator=g, device="cuda")
+    x, y = qkv.clone(), dout.clone()
+    x[seq - 1, 2 * n * d:] = float("-inf")
+    y[seq - 1] = float("inf")
+    assert (attention(ctx, n, n, d, seq, 1, False, x, dout)["out"] == float("-inf")).all()
+    assert (attention(ctx, n, n, d, seq, 1, False, qkv, y)["dv"] == float("inf")).all()
