@@ -100,14 +100,29 @@ __device__ __forceinline__ bool merge_waves(const f32x16_t (&acc)[DB], float nan
   return true;
 }
 
+// A launch has a workgroup for every (32-row block, head and sequence) pair, up to tens of millions: block-fastest numbers over a
+// two-dimensional grid, whose second dimension is 1 up to 2^20 of them (a dimension alone holds 2^32 threads, or 65535 workgroups).
+struct Work { int block, pair; };
+__device__ __forceinline__ Work work_of(int nblk) {
+  const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+  return {(int)(id % nblk), (int)(id / nblk)};
+}
+dim3 work_grid(int nblk, size_t pairs) {
+  const size_t total = nblk * pairs, x = total < (1u << 20) ? total : (1u << 20);
+  return dim3((unsigned)x, (unsigned)((total + x - 1) / x));
+}
+
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__restrict__ qkv, float *__restrict__ out, float *__restrict__ lse,
-                                                               int seq, int n, int nk, int d, int causal, float scale) {
+                                                               int seq, int n, int nk, int pairs, int d, int causal, float scale) {
   extern __shared__ __attribute__((aligned(16))) float red[];      // [NW][DB * 16][64], then m [NW][32], l [NW][32], flags [NW]
   float *red_m = red + NW * DB * 1024, *red_l = red_m + NW * 32;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
-  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * RB;        // the late blocks, which see the most keys, first
-  const int head = blockIdx.y % n, b = blockIdx.y / n;
+  const int nblk = (seq + RB - 1) / RB;
+  const Work w = work_of(nblk);
+  if (w.pair >= pairs) return;
+  const int q0 = (nblk - 1 - w.block) * RB;        // the late blocks, which see the most keys, first
+  const int head = w.pair % n, b = w.pair / n;
   const int a = n * d;
   const size_t ld = (size_t)(n + 2 * nk) * d;
   const float *base = qkv + (size_t)b * seq * ld;
@@ -175,12 +190,15 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__re
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
                                                                   const float *__restrict__ dout, const float *__restrict__ delta,
-                                                                  float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal,
+                                                                  float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
                                                                   float scale) {
   extern __shared__ __attribute__((aligned(16))) float red[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
-  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * RB;
-  const int head = blockIdx.y % n, b = blockIdx.y / n;
+  const int nblk = (seq + RB - 1) / RB;
+  const Work w = work_of(nblk);
+  if (w.pair >= pairs) return;
+  const int q0 = (nblk - 1 - w.block) * RB;
+  const int head = w.pair % n, b = w.pair / n;
   const int a = n * d;
   const size_t ld = (size_t)(n + 2 * nk) * d;
   const float *base = qkv + (size_t)b * seq * ld;
@@ -226,12 +244,14 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *_
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
                                                                    const float *__restrict__ dout, const float *__restrict__ delta,
-                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal,
+                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
                                                                    float scale) {
   extern __shared__ __attribute__((aligned(16))) float red[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
-  const int k0 = (int)blockIdx.x * RB;                               // the early blocks, which most queries see, first
-  const int kh = blockIdx.y % nk, b = blockIdx.y / nk;
+  const Work w = work_of((seq + RB - 1) / RB);
+  if (w.pair >= pairs) return;
+  const int k0 = w.block * RB;                               // the early blocks, which most queries see, first
+  const int kh = w.pair % nk, b = w.pair / nk;
   const int a = n * d, group = n / nk;
   const size_t ld = (size_t)(n + 2 * nk) * d;
   const float *base = qkv + (size_t)b * seq * ld;
@@ -295,8 +315,9 @@ int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, float *o
     STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3((d->seq + RB - 1) / RB, d->heads_local * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, out, lse, d->seq,
-                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, 1.0f / sqrtf((float)d->head_dim));
+  const size_t pairs = (size_t)d->heads_local * d->mbsz;
+  hipLaunchKernelGGL(kern, work_grid((d->seq + RB - 1) / RB, pairs), dim3(64 * NW), lds_of<DB>, s, qkv, out, lse, d->seq,
+                     d->heads_local, stp_kv_heads(d), (int)pairs, d->head_dim, d->causal, 1.0f / sqrtf((float)d->head_dim));
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }
@@ -314,12 +335,13 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, const fl
     attr_set = true;
   }
   const int nblk = (d->seq + RB - 1) / RB;
+  const size_t pairs = (size_t)d->heads_local * d->mbsz, pairs_kv = (size_t)stp_kv_heads(d) * d->mbsz;
   const float scale = 1.0f / sqrtf((float)d->head_dim);
-  hipLaunchKernelGGL(kq, dim3(nblk, d->heads_local * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
-                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, scale);
+  hipLaunchKernelGGL(kq, work_grid(nblk, pairs), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
+                     d->heads_local, stp_kv_heads(d), (int)pairs, d->head_dim, d->causal, scale);
   STP_LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL(kkv, dim3(nblk, stp_kv_heads(d) * d->mbsz), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
-                     d->heads_local, stp_kv_heads(d), d->head_dim, d->causal, scale);
+  hipLaunchKernelGGL(kkv, work_grid(nblk, pairs_kv), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
+                     d->heads_local, stp_kv_heads(d), (int)pairs_kv, d->head_dim, d->causal, scale);
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }

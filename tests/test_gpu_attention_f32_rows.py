@@ -1,4 +1,5 @@
-"""fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN."""
+"""fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN; and as many (head, sequence)
+pairs as there may be."""
 import pytest
 import torch
 
@@ -72,3 +73,18 @@ def test_infinite_rows_keep_their_sign(ctx):
     y[seq - 1] = float("inf")
     assert (attention(ctx, n, n, d, seq, 1, False, x, dout)["out"] == float("-inf")).all()
     assert (attention(ctx, n, n, d, seq, 1, False, qkv, y)["dv"] == float("inf")).all()
+
+
+# more pairs than a grid's second or third dimension holds (65535), and more than 2^20
+@pytest.mark.parametrize("n,nk,mbsz", [(8, 8, 8250), (64, 1, 16500)])
+def test_many_pairs(ctx, n, nk, mbsz):
+    d, seq = 8, 32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    qkv = torch.randn((mbsz * seq, (n + 2 * nk) * d), generator=g, device="cuda")
+    dout = torch.randn((mbsz * seq, n * d), generator=g, device="cuda")
+    got = attention(ctx, n, nk, d, seq, mbsz, True, qkv, dout)
+    for first in (0, 8190, mbsz - 4):              # the same sequences by themselves: the same sums, bit for bit
+        rows = slice(first * seq, (first + 4) * seq)
+        few = attention(ctx, n, nk, d, seq, 4, True, qkv[rows].contiguous(), dout[rows].contiguous())
+        for name in ("out", "dq", "dk", "dv"):
+            assert torch.equal(got[name][rows], few[name]), (name, first)
