@@ -16,6 +16,7 @@
 // cross-lane reduction per score was a chain of 128 such reductions: forward / dQ / dK dV 91 / 56 / 46 us against
 // 14 / 11 / 15 us now, the training pass of two microbatches over that layer 554 against 401 us.
 #include "attn_f32_rows.h"
+#include <type_traits>
 
 int stp_launch_rowdot(stp_ctx *ctx, const stp_layer_desc *d, const void *a, const void *b, float *delta, hipStream_t s);
 
@@ -302,48 +303,111 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
                       [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dvp + (size_t)(k0 + r) * ld + col) = s; });
 }
 
-// head dimensions up to 64 run 8 waves per workgroup (64 KB of merge area), wider ones 4
-template <int DB> constexpr int waves_of = DB <= 2 ? 8 : 4;
-template <int DB> constexpr size_t lds_of = (size_t)waves_of<DB> * (DB * 1024 + 65) * sizeof(float);
+// The same for sequences of a few rows, a wave per row: a block of 32 would be mostly empty.
+__global__ __launch_bounds__(256) void attn_fwd_rows_kernel(const float *__restrict__ qkv, float *__restrict__ out, float *__restrict__ lse, int seq,
+                                                            int mbsz, int n, int nk, int d, int causal, float scale) {
+  const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
+  if (w >= (size_t)mbsz * n * seq) return;
+  attn_fwd_row(qkv, out, lse, w / ((size_t)seq * n), (w / seq) % n, w % seq, seq, n, nk, d, causal, scale);
+}
+__global__ __launch_bounds__(256) void attn_bwd_dq_rows_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                               const float *__restrict__ dout, const float *__restrict__ delta,
+                                                               float *__restrict__ dqkv, int seq, int mbsz, int n, int nk, int d, int causal,
+                                                               float scale) {
+  const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
+  if (w >= (size_t)mbsz * n * seq) return;
+  attn_bwd_dq_row(qkv, lse, dout, delta, dqkv, w / ((size_t)seq * n), (w / seq) % n, w % seq, seq, n, nk, d, causal, scale);
+}
+__global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                                const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                float *__restrict__ dqkv, int seq, int mbsz, int n, int nk, int d, int causal,
+                                                                float scale) {
+  const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
+  if (w >= (size_t)mbsz * nk * seq) return;
+  attn_bwd_dkv_row(qkv, lse, dout, delta, dqkv, w / ((size_t)seq * nk), (w / seq) % nk, w % seq, seq, n, nk, d, causal, scale);
+}
 
-template <int DB>
-int launch_fwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, float *out, float *lse, hipStream_t s) {
-  constexpr int NW = waves_of<DB>;
-  auto kern = attn_fwd_f32_kernel<DB, NW>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
-    attr_set = true;
-  }
-  const size_t pairs = (size_t)d->heads_local * d->mbsz;
-  hipLaunchKernelGGL(kern, work_grid((d->seq + RB - 1) / RB, pairs), dim3(64 * NW), lds_of<DB>, s, qkv, out, lse, d->seq,
-                     d->heads_local, stp_kv_heads(d), (int)pairs, d->head_dim, d->causal, 1.0f / sqrtf((float)d->head_dim));
-  STP_LAUNCH_CHECK(ctx);
-  return STP_OK;
+// Waves per workgroup: 8 (4 at head dimensions above 64, whose merge area is twice as large), 1 or 2 where there are only so many
+// 32-row blocks to share out: a workgroup whose other waves have none holds a compute unit's registers and LDS for nothing (4096
+// sequences of 32 rows of dimension 64, forward / backward: 182 / 316 us with 8 waves, 41 / 115 with one; 64 rows 378 / 722, 116 / 448).
+template <int NW, int DB> constexpr size_t lds_of = (size_t)NW * (DB * 1024 + 65) * sizeof(float);
+template <int DB, typename Launch>
+int with_waves(int blocks, Launch launch) {
+  constexpr int MOST = DB <= 2 ? 8 : 4;
+  if (blocks <= 1) return launch(std::integral_constant<int, 1>{});
+  if (blocks <= 2) return launch(std::integral_constant<int, 2>{});
+  return launch(std::integral_constant<int, MOST>{});
+}
+
+struct Shape { int seq, mbsz, n, nk, d, causal, nblk; size_t pairs, pairs_kv; float scale; };
+
+// Up to how many rows a sequence is better off with a wave per row (kind 0 forward, 1 dQ, 2 dK / dV).  With few rows in all both
+// are a chain of latencies: the row's, one reduction per key (dK / dV: per query of each head of the group), against that of a
+// block or, where a wave has several of them, of its blocks; with many, what counts is how much of a block is empty.  Measured over
+// 1 .. 64 rows, 8 .. 4096 (head, sequence) pairs, dimensions 8 .. 128, groups of 1, 4 and 8.  Forward + backward, rows / blocks in us:
+// 8 pairs of 8 rows of 64: 17 / 30; of 128: 19 / 52; of 24 rows of 64: 33 / 32; 4096 pairs of 4 rows of 64: 36 / 91, 12 rows: 148 / 108.
+bool short_rows(const Shape &h, int kind) {
+  static const int few[3][3] = {{8, 12, 16}, {8, 16, 40}, {24, 32, 64}}, many[3][3] = {{4, 4, 8}, {4, 4, 12}, {4, 8, 16}};
+  const int w = h.d <= 32 ? 0 : h.d <= 64 ? 1 : 2;
+  if (h.pairs * h.seq > 4096) return h.seq <= many[kind][w];
+  if (kind < 2) return h.seq <= few[kind][w];
+  const int group = h.n / h.nk, waves = w == 2 ? 4 : 8;
+  return (long)h.seq * group <= (long)few[2][w] * ((h.nblk * group + waves - 1) / waves);
 }
 
 template <int DB>
-int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, const float *lse, const float *dout, const float *delta, float *dqkv,
-               hipStream_t s) {
-  constexpr int NW = waves_of<DB>;
-  auto kq = attn_bwd_dq_f32_kernel<DB, NW>;
-  auto kkv = attn_bwd_dkv_f32_kernel<DB, NW>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kq), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
-    STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<DB>));
-    attr_set = true;
-  }
-  const int nblk = (d->seq + RB - 1) / RB;
-  const size_t pairs = (size_t)d->heads_local * d->mbsz, pairs_kv = (size_t)stp_kv_heads(d) * d->mbsz;
-  const float scale = 1.0f / sqrtf((float)d->head_dim);
-  hipLaunchKernelGGL(kq, work_grid(nblk, pairs), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
-                     d->heads_local, stp_kv_heads(d), (int)pairs, d->head_dim, d->causal, scale);
-  STP_LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL(kkv, work_grid(nblk, pairs_kv), dim3(64 * NW), lds_of<DB>, s, qkv, lse, dout, delta, dqkv, d->seq,
-                     d->heads_local, stp_kv_heads(d), (int)pairs_kv, d->head_dim, d->causal, scale);
-  STP_LAUNCH_CHECK(ctx);
-  return STP_OK;
+int launch_fwd(stp_ctx *ctx, const Shape &h, const float *qkv, float *out, float *lse, hipStream_t s) {
+  return with_waves<DB>(h.nblk, [&](auto nw) -> int {
+    constexpr int NW = decltype(nw)::value;
+    auto kern = attn_fwd_f32_kernel<DB, NW>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<NW, DB>));
+      attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, work_grid(h.nblk, h.pairs), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, out, lse, h.seq, h.n, h.nk, (int)h.pairs, h.d, h.causal,
+                       h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  });
+}
+template <int DB>
+int launch_dq(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *delta, float *dqkv, hipStream_t s) {
+  return with_waves<DB>(h.nblk, [&](auto nw) -> int {
+    constexpr int NW = decltype(nw)::value;
+    auto kern = attn_bwd_dq_f32_kernel<DB, NW>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<NW, DB>));
+      attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, work_grid(h.nblk, h.pairs), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, lse, dout, delta, dqkv, h.seq, h.n, h.nk, (int)h.pairs,
+                       h.d, h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  });
+}
+template <int DB>
+int launch_dkv(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *delta, float *dqkv, hipStream_t s) {
+  return with_waves<DB>(h.nblk * (h.n / h.nk), [&](auto nw) -> int {
+    constexpr int NW = decltype(nw)::value;
+    auto kern = attn_bwd_dkv_f32_kernel<DB, NW>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<NW, DB>));
+      attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, work_grid(h.nblk, h.pairs_kv), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, lse, dout, delta, dqkv, h.seq, h.n, h.nk,
+                       (int)h.pairs_kv, h.d, h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  });
+}
+
+Shape shape_of(const stp_layer_desc *d) {
+  const int nk = stp_kv_heads(d);
+  return {d->seq, d->mbsz, d->heads_local, nk, d->head_dim, d->causal, (d->seq + RB - 1) / RB, (size_t)d->heads_local * d->mbsz, (size_t)nk * d->mbsz,
+          1.0f / sqrtf((float)d->head_dim)};
 }
 
 }  // namespace
@@ -351,9 +415,13 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const float *qkv, const fl
 int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s) {
   const float *x = (const float *)qkv;
   float *o = (float *)out;
-  if (d->head_dim <= 32) return launch_fwd<1>(ctx, d, x, o, lse, s);
-  if (d->head_dim <= 64) return launch_fwd<2>(ctx, d, x, o, lse, s);
-  return launch_fwd<4>(ctx, d, x, o, lse, s);
+  const Shape h = shape_of(d);
+  if (short_rows(h, 0)) {
+    hipLaunchKernelGGL(attn_fwd_rows_kernel, dim3((h.pairs * h.seq + 3) / 4), dim3(256), 0, s, x, o, lse, h.seq, h.mbsz, h.n, h.nk, h.d, h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  }
+  return h.d <= 32 ? launch_fwd<1>(ctx, h, x, o, lse, s) : h.d <= 64 ? launch_fwd<2>(ctx, h, x, o, lse, s) : launch_fwd<4>(ctx, h, x, o, lse, s);
 }
 
 int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse, const void *dout,
@@ -362,7 +430,22 @@ int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *q
   if (rc != STP_OK) return rc;
   const float *x = (const float *)qkv, *g = (const float *)dout;
   float *dx = (float *)dqkv;
-  if (d->head_dim <= 32) return launch_bwd<1>(ctx, d, x, lse, g, delta, dx, s);
-  if (d->head_dim <= 64) return launch_bwd<2>(ctx, d, x, lse, g, delta, dx, s);
-  return launch_bwd<4>(ctx, d, x, lse, g, delta, dx, s);
+  const Shape h = shape_of(d);
+  if (short_rows(h, 1)) {
+    hipLaunchKernelGGL(attn_bwd_dq_rows_kernel, dim3((h.pairs * h.seq + 3) / 4), dim3(256), 0, s, x, lse, g, delta, dx, h.seq, h.mbsz, h.n, h.nk, h.d,
+                       h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+  } else {
+    rc = h.d <= 32 ? launch_dq<1>(ctx, h, x, lse, g, delta, dx, s) : h.d <= 64 ? launch_dq<2>(ctx, h, x, lse, g, delta, dx, s)
+                                                                           : launch_dq<4>(ctx, h, x, lse, g, delta, dx, s);
+    if (rc != STP_OK) return rc;
+  }
+  if (short_rows(h, 2)) {
+    hipLaunchKernelGGL(attn_bwd_dkv_rows_kernel, dim3((h.pairs_kv * h.seq + 3) / 4), dim3(256), 0, s, x, lse, g, delta, dx, h.seq, h.mbsz, h.n, h.nk, h.d,
+                       h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  }
+  return h.d <= 32 ? launch_dkv<1>(ctx, h, x, lse, g, delta, dx, s) : h.d <= 64 ? launch_dkv<2>(ctx, h, x, lse, g, delta, dx, s)
+                                                                         : launch_dkv<4>(ctx, h, x, lse, g, delta, dx, s);
 }

@@ -1,5 +1,5 @@
 """fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN; and as many (head, sequence)
-pairs as there may be."""
+pairs as there may be; and sequences of few rows, which have kernels and workgroups of their own."""
 import pytest
 import torch
 
@@ -88,3 +88,14 @@ def test_many_pairs(ctx, n, nk, mbsz):
         few = attention(ctx, n, nk, d, seq, 4, True, qkv[rows].contiguous(), dout[rows].contiguous())
         for name in ("out", "dq", "dk", "dv"):
             assert torch.equal(got[name][rows], few[name]), (name, first)
+
+
+# a wave per row in all three kernels; in the backward ones, in dK / dV only; blocks with one, two and all waves a workgroup; with a
+# group of heads dK / dV has several blocks where the others have one; the same sequences few and many at a time
+@pytest.mark.parametrize("seq,mbsz,n,d,causal,nk", [(1, 8, 3, 64, True, 0), (5, 8, 2, 24, False, 0), (12, 2, 2, 64, True, 0), (20, 2, 1, 32, True, 0),
+                                                    (24, 1, 2, 128, False, 0), (24, 1, 2, 16, True, 0), (32, 1, 8, 48, True, 1), (40, 1, 2, 64, False, 0),
+                                                    (64, 1, 4, 104, True, 2), (72, 1, 2, 128, True, 0), (4, 130, 8, 64, True, 0), (8, 130, 8, 64, True, 0),
+                                                    (8, 70, 8, 128, False, 1), (16, 40, 8, 40, True, 0)])
+def test_few_rows(ctx, seq, mbsz, n, d, causal, nk):
+    import test_gpu_kernels
+    test_gpu_kernels.test_attention_forward_backward(ctx, "f32", seq, mbsz, n, d, causal, nk)
