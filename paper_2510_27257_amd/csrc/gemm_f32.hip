@@ -93,6 +93,36 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_kernel(const float
     mac(fa[1], fb[1]);
   }
   // accumulator v of lane l: row 8 * (v / 4) + 4 * (l / 32) + v % 4, column l % 32
+  if constexpr (KS == 1) {                             // nothing to add up: straight from the registers, 32 neighbouring columns per store
+#pragma unroll
+    for (int i = 0; i < WT; i++)
+#pragma unroll
+      for (int j = 0; j < WT; j++) {
+        const int col = n0 + (wn * WT + j) * 32 + lr;
+        if (col >= N) continue;
+        const float bias = ep.bias ? ep.bias[col] * ep.bias_scale : 0.f;
+        const int row0 = m0 + (wm * WT + i) * 32 + 4 * lg;
+        float other[16];                               // the old sum or the GELU' argument (never both), read together
+        if (ep.accum || ep.mode == 2) {
+          const float *p = ep.accum ? ep.C : ep.aux;
+          const int ld = ep.accum ? ep.ldc : ep.ld2;
+#pragma unroll
+          for (int v = 0; v < 16; v++) other[v] = p[(size_t)min(row0 + 8 * (v >> 2) + (v & 3), M - 1) * ld + col];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int row = row0 + 8 * (v >> 2) + (v & 3);
+          if (row >= M) continue;
+          float val = acc[i][j][v] + bias;
+          if (ep.resid) val += ep.resid[(size_t)row * ep.ldr + col] * ep.resid_scale;
+          if (ep.mode == 2) val *= gelu_grad_f(other[v]);
+          if (ep.accum) val += other[v];
+          ep.C[(size_t)row * ep.ldc + col] = val;
+          if (ep.mode == 1) ep.C2[(size_t)row * ep.ld2 + col] = gelu_f(val);
+        }
+      }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < WT; i++)
 #pragma unroll
@@ -132,7 +162,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_kernel(const float
 template <int WT, int WM, int WN, int KS, bool A_KC, bool B_KC>
 int launch_f32(stp_ctx *ctx, const stp_gemm_args *a, const EpiF &ep, hipStream_t s) {
   constexpr int TM = 32 * WT * WM, TN = 32 * WT * WN;
-  constexpr size_t smem = (size_t)KS * TM * (TN + 4) * sizeof(float);
+  constexpr size_t smem = KS == 1 ? 0 : (size_t)KS * TM * (TN + 4) * sizeof(float);
   static_assert(smem <= 160 * 1024, "LDS budget");
   auto kern = gemm_f32_kernel<WT, WM, WN, KS, A_KC, B_KC>;
   static bool attr_set = false;
@@ -147,12 +177,22 @@ int launch_f32(stp_ctx *ctx, const stp_gemm_args *a, const EpiF &ep, hipStream_t
 }
 
 // Tile: the largest of the three that still gives most of the 256 compute units a workgroup (a larger wave tile
-// reads fewer operand bytes per product: 32 B per clock and compute unit at 32 x 32, half of that at 64 x 64).
+// reads fewer operand bytes per product: 32 B per clock and compute unit at 32 x 32, half of that at 64 x 64), and that is not
+// mostly past the end of a narrow output.
+// Short contractions of outputs large enough to fill the chip are bound by the output, not by a chain: there the contraction is
+// not split, nothing passes through LDS and 32 x 32 tiles store from the registers.  us, split / not (scalar FMAs on LDS tiles before
+// either): [4096, 4096] K = 8: 33 / 20 (20), added to C 53 / 28 (28), K = 64: 49 / 43 (51); [65536, 32] K = 128: 37 / 14 (31).  Past
+// K = 80 the chain counts again ([1024, 1024] K = 96: 7.8 / 8.5), for narrow outputs of very many tiles past 128.
 template <bool A_KC, bool B_KC>
 int launch_f32_layout(stp_ctx *ctx, const stp_gemm_args *a, const EpiF &ep, hipStream_t s) {
   auto tiles = [&](long t) { return ((a->M + t - 1) / t) * ((a->N + t - 1) / t); };
-  if (tiles(128) >= 192) return launch_f32<2, 2, 2, 2, A_KC, B_KC>(ctx, a, ep, s);
-  if (tiles(64) >= 192) return launch_f32<2, 1, 1, 4, A_KC, B_KC>(ctx, a, ep, s);
+  if (a->K <= 80 || (a->K <= 128 && (a->M <= 64 || a->N <= 64) && tiles(64) >= 512)) {
+    if (tiles(64) >= 192 && a->M > 32 && a->N > 32) return launch_f32<1, 2, 2, 1, A_KC, B_KC>(ctx, a, ep, s);
+    if (tiles(32) >= 512 && a->M <= 32) return launch_f32<1, 1, 4, 1, A_KC, B_KC>(ctx, a, ep, s);
+    if (tiles(32) >= 512 && a->N <= 32) return launch_f32<1, 4, 1, 1, A_KC, B_KC>(ctx, a, ep, s);
+  }
+  if (tiles(128) >= 192 && a->M > 64 && a->N > 64) return launch_f32<2, 2, 2, 2, A_KC, B_KC>(ctx, a, ep, s);
+  if (tiles(64) >= 192 && a->M > 32 && a->N > 32) return launch_f32<2, 1, 1, 4, A_KC, B_KC>(ctx, a, ep, s);
   return launch_f32<1, 1, 1, 8, A_KC, B_KC>(ctx, a, ep, s);
 }
 }  // namespace
