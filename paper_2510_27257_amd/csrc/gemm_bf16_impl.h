@@ -954,8 +954,10 @@ int launch_dma_tile(stp_ctx *ctx, const stp_gemm_args *a, TileChoice c, const Ep
   if (c.bm == 128 && c.bn == 256) return launch_dma<128, 256, 2, 4, 3, 3, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
   if (c.bm == 128 && c.bn == 128) {
     // up to one workgroup per compute unit: all of the LDS for loads in flight (a ring of two leaves 42 instead of 29 us for
-    // [6144, 512] K = 4096); with more, two workgroups share it (8192^3: 968 against 1143 us)
-    if (((a->M + 127) / 128) * ((a->N + 127) / 128) <= 256) return launch_dma<128, 128, 2, 4, 4, 4, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
+    // [6144, 512] K = 4096); with more, two workgroups share it (8192^3: 968 against 1143 us).  One or two K-tiles
+    // need no more than the shorter rings, which are sooner filled (with copies of the last K-tile: [1024, 1024] K = 64 4.4 -> 4.0 us,
+    // [1024, 4096] K = 96 6.1 -> 5.8)
+    if (a->K > 128 && ((a->M + 127) / 128) * ((a->N + 127) / 128) <= 256) return launch_dma<128, 128, 2, 4, 4, 4, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
     return launch_dma<128, 128, 2, 4, 3, 2, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);
   }
   return launch_dma<256, 256, 2, 4, 3, 2, A_KC, B_KC, EPI, KTAIL>(ctx, a, ep, s);

@@ -67,3 +67,31 @@ def test_rings(ctx, M, N, K, tile, a_trans, b_trans):
                           C=out.data_ptr(), ldc=N, bias_scale=1.0, resid_scale=1.0, tile_m=tile[0], tile_n=tile[1]))
     torch.cuda.synchronize()
     assert rel_err(to_host(out), to_host(ref)) < 6e-3      # as above: the bf16 rounding of an fp32 sum
+
+
+# K <= 128 on the 128 x 128 tile is loaded at once: the bits of the ring kernel's 256 x 256 tile, at every count of 16-deep steps, with
+# every epilogue
+@pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [32, 64, 96, 128])
+def test_short_contraction_bits(ctx, K, a_trans, b_trans):
+    M, N = 392, 264
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A, lda, _ = operand(g, M, K, 1.0, a_trans)
+    B, ldb, _ = operand(g, N, K, 0.05, not b_trans)
+    R = torch.randn((M, N), generator=g, device="cuda").to(torch.bfloat16)
+    bias = torch.randn(N, generator=g, device="cuda").to(torch.bfloat16)
+    base = dict(dtype=stp.BF16, M=M, N=N, K=K, A=A.data_ptr(), lda=lda, a_trans=a_trans, B=B.data_ptr(), ldb=ldb, b_trans=b_trans, ldc=N,
+                bias_scale=0.5, resid_scale=0.25)
+    got = []
+    for tile in (128, 256):
+        C, C2, D, E = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4))
+        acc = torch.ones((M, N), device="cuda")
+        t = dict(tile_m=tile, tile_n=tile)
+        ctx.gemm(stp.GemmArgs(**base | t, C=C.data_ptr(), bias=bias.data_ptr(), resid=R.data_ptr(), ldr=N))
+        ctx.gemm(stp.GemmArgs(**base | t, C=D.data_ptr(), epilogue=1, C2=C2.data_ptr(), ld2=N))
+        ctx.gemm(stp.GemmArgs(**base | t, C=E.data_ptr(), epilogue=2, aux=R.data_ptr(), ld2=N))
+        ctx.gemm(stp.GemmArgs(**base | t, C=acc.data_ptr(), c_f32_accum=1))
+        got.append((C, D, C2, E, acc))
+    torch.cuda.synchronize()
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
