@@ -405,18 +405,18 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     __syncthreads();
   }
   if (half == 0) {
-    float M = m;
+    float M = m, ea = 1.f, eb = 0.f;
     if (HALVES == 2) {
       const float m_b = red_ml[(qsub * 2 + 0) * 32 + lr], l_b = red_ml[(qsub * 2 + 1) * 32 + lr];
       M = fmaxf(m, m_b);
       const float m_ref = M == -INFINITY ? 0.f : M;
-      const float ea = __builtin_amdgcn_exp2f(m - m_ref), eb = __builtin_amdgcn_exp2f(m_b - m_ref);
+      ea = __builtin_amdgcn_exp2f(m - m_ref);
+      eb = __builtin_amdgcn_exp2f(m_b - m_ref);
       l = l * ea + l_b * eb;
-#pragma unroll
-      for (int i = 0; i < D / 32; i++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) o[i][v] = o[i][v] * ea + red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] * eb;
     }
+    // the merged accumulator, formed where it is stored, so that the reads from LDS overlap the stores (merging all of it first: 63.5
+    // against 61.4 us for 32 x 21 heads of 128, 176 tokens, 13.2 against 12.9 for 8 heads, 352 tokens)
+    auto merged = [&](int i, int v) { return HALVES == 2 ? o[i][v] * ea + red[(qsub * (D / 2) + i * 16 + v) * 64 + lane] * eb : o[i][v]; };
     if (qg < seq && nsteps <= chunk_steps) {
       // the query block has this one chunk: its rows are final, so they go to the output (and the log-sum-exp)
       // directly and the combine kernel leaves them alone
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const int v = 4 * j + r;
-            w[r] = (bf16_t)(o[i][v] * inv);
+            w[r] = (bf16_t)(merged(i, v) * inv);
           }
           *reinterpret_cast<bf16x4_t *>(op + 32 * i + 8 * j + 4 * lg) = w;
         }
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
 #pragma unroll
           for (int r = 0; r < 4; r++) {
             const int v = 4 * j + r;
-            w[r] = o[i][v];
+            w[r] = merged(i, v);
           }
           *reinterpret_cast<f32x4_t *>(po + (size_t)qloc * D + 32 * i + 8 * j + 4 * lg) = w;
         }
