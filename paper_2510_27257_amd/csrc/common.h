@@ -204,6 +204,8 @@ __device__ __forceinline__ float sigmoid_f(float x) { return 1.0f / (1.0f + __ex
 int stp_launch_gemm_bf16(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s);
 // n <= 3 products C += A^T B in fp32 with one contraction length, as one launch where that is shorter
 int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s);
+// tile (bm << 16 | bn) of that launch, 0 where the products are launched apart; host only, no part of the interface (tests check routes)
+extern "C" int stp_wgrad_set_tile(const stp_gemm_args *a, int n);
 int stp_launch_gemm_f32(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s);
 int stp_launch_attn_fwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, float *ws,
                              size_t ws_bytes, hipStream_t s);

@@ -1021,7 +1021,7 @@ int launch_set(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s) {
 }
 
 // A set takes one launch where the estimate of its time is below the sum of the estimates of its products.
-inline bool set_tile(stp_ctx *ctx, const stp_gemm_args *a, int n, TileChoice *choice) {
+inline bool set_tile(const stp_gemm_args *a, int n, TileChoice *choice) {
   double apart = 0.0, together = 1e30;
   for (int i = 0; i < n; i++) {
     if (a[i].K <= 0 || !operand_bytes(false, a[i].M, a[i].K, a[i].lda) || !operand_bytes(false, a[i].N, a[i].K, a[i].ldb) ||

@@ -11,11 +11,16 @@ int stp_launch_gemm_bf16_mn(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s)
 // worse one (blocks 0.3 - 5 % slower).
 int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s) {
   TileChoice c;
-  if (n > 1 && !(ctx && ctx->concurrent) && set_tile(ctx, a, n, &c))
+  if (n > 1 && !(ctx && ctx->concurrent) && set_tile(a, n, &c))
     return a[0].K % DK ? launch_set_tile<true>(ctx, a, n, c, s) : launch_set_tile<false>(ctx, a, n, c, s);
   for (int i = 0; i < n; i++) {
     const int rc = stp_launch_gemm_bf16_mn(ctx, &a[i], s);
     if (rc != STP_OK) return rc;
   }
   return STP_OK;
+}
+
+extern "C" int stp_wgrad_set_tile(const stp_gemm_args *a, int n) {
+  TileChoice c;
+  return a && n > 1 && n <= 3 && set_tile(a, n, &c) ? c.bm << 16 | c.bn : 0;
 }

@@ -69,7 +69,7 @@ def test_rings(ctx, M, N, K, tile, a_trans, b_trans):
     assert rel_err(to_host(out), to_host(ref)) < 6e-3      # as above: the bf16 rounding of an fp32 sum
 
 
-# K <= 128 on the 128 x 128 tile is loaded at once: the bits of the ring kernel's 256 x 256 tile, at every count of 16-deep steps, with
+# K <= 128 takes shorter rings on the 128 x 128 tile: the bits of the 256 x 256 tile, with a half-empty last K-tile and without, with
 # every epilogue
 @pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("K", [32, 64, 96, 128])
