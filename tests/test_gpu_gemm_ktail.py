@@ -1,4 +1,4 @@
-"""The bf16 GEMM at contraction lengths that are not a multiple of the 32-deep K-tile: the last tile is partly empty.
+"""The bf16 GEMM at contraction lengths that are not a multiple of the 64-deep K-tile: the last tile is partly empty.
 What lies past K in memory (the padding of the rows, the rows after the last one) is NaN and must not reach a result."""
 import pytest
 import torch
@@ -29,7 +29,7 @@ def operand(g, rows, K, std, k_outer):
     return store, store.stride(0), x.float()
 
 
-# (8, 8): one tile, K-tiles 1 .. 5 around the four-stage ring; then shapes that take each of the workgroup tiles
+# (8, 8): one tile and one K-tile, mostly empty; then shapes that take each of the workgroup tiles
 @pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (8, 8, 40), (136, 264, 72), (264, 136, 120), (520, 776, 152), (1032, 2744, 1000), (3000, 1032, 328),
                                    (6144, 2048, 1048), (6144, 4096, 88)])
@@ -51,13 +51,11 @@ def test_k_tail(ctx, M, N, K, a_trans, b_trans):
 
 # every workgroup tile, fewer K-tiles than its rings hold, as many, and more, with and without a half-empty last one; also
 # just more tiles of 128 x 128 than compute units (another ring length)
-@pytest.mark.parametrize("a_trans,b_trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("tile", [(256, 256), (192, 256), (128, 256), (256, 128), (128, 128)])
+@pytest.mark.parametrize("tile,a_trans,b_trans", [(t, a, b) for t in [(256, 256), (192, 256), (128, 256), (256, 128), (128, 128)] for a in (0, 1)
+                                                  for b in (0, 1) if not (a and t[0] == 192)])     # 192 rows: k-contiguous A only
 @pytest.mark.parametrize("M,N,K", [(264, 520, 32), (264, 520, 64), (264, 520, 128), (264, 520, 192), (264, 520, 224), (264, 520, 256), (264, 520, 544),
                                    (2056, 2056, 352)])
 def test_rings(ctx, M, N, K, tile, a_trans, b_trans):
-    if a_trans and tile[0] == 192:
-        return
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, lda, a = operand(g, M, K, 1.0, a_trans)
     B, ldb, b = operand(g, N, K, 0.05, not b_trans)

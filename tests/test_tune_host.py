@@ -89,3 +89,15 @@ def test_stored_tables_are_well_formed_and_apply(tmp_path):
         assert False
     except ValueError:
         pass
+
+
+def test_shapes_that_take_no_preference_are_not_tuned():
+    """The shape rule of the contraction-splitting kernel: the tuner leaves such shapes out, and no stored table names one."""
+    vit = tune.layer_gemm_shapes(synth.WORKLOADS["vit"])
+    assert set(vit) - set(tune.tunable(vit)) == {"out_f", "fc2_f", "fc1_b", "out_b", "qkv_b", "out_w"}      # [1024, 1024] outputs
+    for shape, takes in {(1024, 1024, 256, 0, 0): False, (1024, 1032, 256, 0, 0): True, (1024, 1024, 248, 0, 0): True, (64, 16384, 4096, 0, 1): False}.items():
+        assert tune.takes_preference(shape) is takes
+    for objective in ("block", "stage"):
+        for name, hints in tune.load_hints(objective=objective).items():
+            for key in hints:
+                assert tune.takes_preference(tuple(int(v) for v in key.split(","))), (name, key)
