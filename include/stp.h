@@ -319,7 +319,7 @@ int stp_gemm(stp_ctx *ctx, const stp_gemm_args *args, void *hip_stream);
  * stp_braid_step issues on concurrent streams (Section 3: the units of a block share the GPU).  Which tile is
  * fastest there depends on the kernels of the other streams; the library's own choice models the GEMM alone.
  * Results do not depend on the tile (every element is summed over K in the same order; outputs of at most 256 tiles of
- * 64 x 64, whose contraction is split over the waves of a workgroup, take no preference).  tile_m = tile_n = 0
+ * 64 x 64 with K >= 256, whose contraction is split over the waves of a workgroup, take no preference).  tile_m = tile_n = 0
  * forgets the preference for that shape.  Host only; at most 96 shapes per context (STP_ENOSPACE);
  * STP_EINVAL for a tile stp_gemm_args.tile_m / tile_n would not take. */
 int stp_gemm_tile_hint(stp_ctx *ctx, int32_t M, int32_t N, int32_t K, int a_trans, int b_trans,

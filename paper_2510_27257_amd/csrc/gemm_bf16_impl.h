@@ -937,11 +937,11 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool a
 }
 
 // Outputs of at most 256 tiles of 64 x 64 (one per compute unit) go to the contraction-splitting kernel, measured against
-// the best of the larger tiles (us): [1024, 1024] with K = 1024 / 3072 / 4096: 8.0 -> 6.0, 25.5 -> 12.7, 29 -> 15.5;
-// [1136, 512] K = 2816: 27 -> 11; [384, 1032] K = 3000 (weight gradient): 23 -> 13; [128, 2128] K = 456: 7.1 -> 4.9.  With
-// more tiles a compute unit works through two of them and the gain shrinks to nothing ([1080, 1344] K = 1792: 15.6 ->
-// 14.9, [2608, 576] K = 1664: none), and it costs more compute-unit time, which counts beside other streams; below K = 256
-// the extra reduction outweighs the shorter chain.
+// the best of the larger tiles (us): [1024, 1024] with K = 256 / 1024 / 3072 / 4096: 5.3 -> 4.3, 9.1 -> 6.6, 19.4 -> 13.2,
+// 24.4 -> 16.3; [1136, 512] K = 2816: 17.8 -> 10.3; [384, 1032] K = 3008 (weight gradient): 22.4 -> 13.0; [128, 2128] K = 480:
+// 6.9 -> 5.0.  With more tiles a compute unit works through two of them and nothing is gained ([1080, 1344] K = 1792: 13.2 with the
+// best tile), and it costs more compute-unit time, which counts beside other streams; below K = 256 the extra reduction
+// outweighs the shorter chain.
 inline bool wavek_shape(long M, long N, long K) { return ((M + 63) / 64) * ((N + 63) / 64) <= 256 && K >= 256; }
 
 template <bool A_KC, bool B_KC, int EPI, bool KTAIL>
