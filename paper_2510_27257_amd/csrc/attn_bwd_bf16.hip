@@ -118,6 +118,7 @@ __host__ __device__ inline int dq_steps(int qb, int seq, int causal) {
 // What the kernels need to undo the rotary embedding in dQ and dK: nothing, or the frequencies.
 template <bool ROPE> struct RopeArg {};
 template <> struct RopeArg<true> { stp_rope_tab tab; };
+static_assert(alignof(RopeArg<true>) >= alignof(f32x4_t), "unrotate4 reads the frequencies four at a time");
 // Inverse rotation of four gradients a (columns i .. i+3 of a head) and b (columns i + D/2 ..) of the row at position pos
 __device__ __forceinline__ void unrotate4(f32x4_t &a, f32x4_t &b, float pos, int i, const stp_rope_tab &tab) {
   const f32x4_t hi = *reinterpret_cast<const f32x4_t *>(tab.hi + i), lo = *reinterpret_cast<const f32x4_t *>(tab.lo + i);

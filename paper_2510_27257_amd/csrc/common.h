@@ -31,7 +31,8 @@ struct stp_attn_plan {
 };
 #define STP_ATTN_PLAN_CACHE 12
 
-struct stp_rope_tab { float hi[64], lo[64]; };      // see rope_sincos
+// see rope_sincos.  Kernels read it from their arguments four or eight floats at a time.
+struct alignas(16) stp_rope_tab { float hi[64], lo[64]; };
 
 // What the streams of the braid steps are known to be ordered behind.  Slot = index of the first of the three streams with that
 // handle.  Every slot is marked at the end of a step (by an event; the last two marks are kept); a mark remembers which steps of

@@ -119,6 +119,7 @@ struct Epi {
 };
 // of the kernels that rotate: the epilogue's description and the frequencies
 struct EpiRope : Epi { stp_rope_tab tab; };
+static_assert(alignof(EpiRope) >= 16, "store_rope reads the frequencies eight at a time");
 
 // EPI_SWIGLU_BWD: C, C2 = gradients of gate and up activation from the sums, aux and aux2.  EPI_SWIGLU_FWD (kernels with paired B
 // operands): C = gate, C2 = up, C3 = SiLU(gate) * up.
