@@ -652,11 +652,24 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const T *__restrict__ 
 
 // ======================================================================
 // Rotary embedding, in place on the Q and K heads of qkv [T, (n + 2 n_kv) d] (the first nrot = n + n_kv heads
-// of a row).  One thread rotates 8 pairs (i, i + d/2) of one head of one token.
+// of a row).  One thread rotates 8 pairs (i, i + d/2) of one head of one token.  For bf16 the angles are those of the kernels that
+// rotate in a product's epilogue or undo it in the attention backward (rope_sincos): a layer's forward may come here and its
+// backward not, and the two have to be each other's inverse.
 // ======================================================================
-template <typename T>
-__global__ __launch_bounds__(256) void rope_kernel(T *__restrict__ qkv, int tokens, int seq, int nrot, int row_width, int d,
-                                                   float log2_base, float sign) {
+struct RopeFreqF32 {
+  float log2_base;
+  int d;
+  __device__ __forceinline__ void sincos(int pos, int i, float &sn, float &cs) const {
+    float inv_freq = exp2f(-2.0f * (float)i / (float)d * log2_base);
+    sincosf((float)pos * inv_freq, &sn, &cs);
+  }
+};
+struct RopeFreqTab {
+  stp_rope_tab tab;
+  __device__ __forceinline__ void sincos(int pos, int i, float &sn, float &cs) const { rope_sincos((float)pos, tab.hi[i], tab.lo[i], sn, cs); }
+};
+template <typename T, typename F>
+__global__ __launch_bounds__(256) void rope_kernel(T *__restrict__ qkv, int tokens, int seq, int nrot, int row_width, int d, F freq, float sign) {
   const int half = d / 2, per_head = half / 8;
   size_t total = (size_t)tokens * nrot * per_head;
   size_t idx = blockIdx.x * (size_t)256 + threadIdx.x;
@@ -672,10 +685,8 @@ __global__ __launch_bounds__(256) void rope_kernel(T *__restrict__ qkv, int toke
   Vec8<T>::load(p + half, b);
 #pragma unroll
   for (int i = 0; i < 8; i++) {
-    float inv_freq = exp2f(-2.0f * (float)(c * 8 + i) / (float)d * log2_base);
-    float ang = (float)pos * inv_freq;
     float sn, cs;
-    sincosf(ang, &sn, &cs);
+    freq.sincos(pos, c * 8 + i, sn, cs);
     sn *= sign;
     oa[i] = a[i] * cs - b[i] * sn;
     ob[i] = b[i] * cs + a[i] * sn;
@@ -1015,12 +1026,14 @@ extern "C" int stp_rope(stp_ctx *ctx, const stp_layer_desc *d, void *qkv, int in
   const int nrot = d->heads_local + stp_kv_heads(d);
   size_t total = (size_t)tokens * nrot * (d->head_dim / 16);
   dim3 grid((total + 255) / 256), block(256);
-  float log2_base = log2f(d->rope_base), sign = inverse ? -1.0f : 1.0f;
+  const float sign = inverse ? -1.0f : 1.0f;
   hipStream_t s = (hipStream_t)hip_stream;
   if (d->dtype == STP_BF16)
-    hipLaunchKernelGGL(rope_kernel<bf16_t>, grid, block, 0, s, (bf16_t *)qkv, tokens, d->seq, nrot, stp_qkv_width(d), d->head_dim, log2_base, sign);
+    hipLaunchKernelGGL((rope_kernel<bf16_t, RopeFreqTab>), grid, block, 0, s, (bf16_t *)qkv, tokens, d->seq, nrot, stp_qkv_width(d), d->head_dim,
+                       RopeFreqTab{stp_rope_tab_for(ctx, d)}, sign);
   else
-    hipLaunchKernelGGL(rope_kernel<float>, grid, block, 0, s, (float *)qkv, tokens, d->seq, nrot, stp_qkv_width(d), d->head_dim, log2_base, sign);
+    hipLaunchKernelGGL((rope_kernel<float, RopeFreqF32>), grid, block, 0, s, (float *)qkv, tokens, d->seq, nrot, stp_qkv_width(d), d->head_dim,
+                       RopeFreqF32{log2f(d->rope_base), d->head_dim}, sign);
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }

@@ -46,7 +46,7 @@ def rotate(x, seq, d, rot_heads, sign):
 # sequences shorter than a strip, positions that start again inside one, half-empty tiles, every tile of the product, long positions
 @pytest.mark.parametrize("n,nk,d,seq,mbsz,hidden", [(2, 1, 128, 264, 1, 640), (6, 2, 64, 1000, 3, 1032), (9, 3, 64, 24, 170, 520), (5, 1, 128, 1096, 1, 264),
                                                     (10, 10, 128, 4096, 1, 5120), (14, 2, 128, 2056, 1, 128), (16, 16, 64, 520, 8, 1024),
-                                                    (4, 4, 128, 8, 300, 72), (3, 3, 64, 6144, 1, 2048)])
+                                                    (4, 4, 128, 8, 300, 72), (3, 3, 64, 6144, 1, 2048), (1, 1, 64, 5000, 1, 512)])
 @pytest.mark.parametrize("bias", [False, True])
 def test_attention_unit(ctx, n, nk, d, seq, mbsz, hidden, bias):
     wl = Workload("rope", hidden, n, d, 64, seq, 4, norm="rms", act="swiglu", rope=True, has_bias=bias, kv_heads=nk)
@@ -75,3 +75,28 @@ def test_attention_unit(ctx, n, nk, d, seq, mbsz, hidden, bias):
     for lo, hi in ((0, a), (a, a + nk * d)):                 # both sides rounded once from the same sums
         assert off(unit[:, lo:hi], back[:, lo:hi]) < 1.5 * ROUND
     assert torch.equal(unit[:, a + nk * d:], plain[:, a + nk * d:])
+
+
+# the first two: products of the contraction-splitting kernel, rotated by the kernel of its own; then both head dimensions in the epilogue
+@pytest.mark.parametrize("n,nk,d,seq,mbsz,hidden", [(1, 1, 64, 5000, 1, 512), (1, 1, 128, 2560, 1, 264), (6, 2, 64, 4096, 1, 640), (4, 4, 128, 4104, 2, 520)])
+def test_angles(ctx, n, nk, d, seq, mbsz, hidden):
+    """Both routes of the forward pass and the stand-alone call, either way, on pairs (1, 0): what comes out is the sine and the cosine.  A value near zero
+    is stored to a fraction of 2^-8 of itself, so an angle that is off by more than the 1e-6 of the hardware's sine shows there."""
+    wl = Workload("rope", hidden, n, d, 64, seq, 4, norm="rms", act="swiglu", rope=True, has_bias=False, kv_heads=nk)
+    lay = LayerOnDevice(ctx, wl, seed=2, mbsz=mbsz)
+    T, width = seq * mbsz, (n + 2 * nk) * d
+    lay.field("X_LN").view(T, hidden).zero_()[:, 0] = 1.0
+    pairs = torch.zeros(n + 2 * nk, d, device="cuda")
+    pairs[:, :d // 2] = 1.0
+    lay.w_dev["w_qkv"].zero_()[0] = pairs.flatten()
+    ones = pairs.flatten().to(torch.bfloat16).expand(T, width).contiguous()
+    x, y = lay.new_act().zero_(), lay.new_act()
+    ctx.forward_unit(lay.desc, stp.ATTN, lay.w, lay.stash[0], x_resid=x, y_out=y)
+    alone, back = ones.clone(), ones.clone()
+    ctx.rope(lay.desc, alone)
+    ctx.rope(lay.desc, back, inverse=True)
+    torch.cuda.synchronize()
+    for got, sign in ((lay.field("QKV").view(T, width), 1.0), (alone, 1.0), (back, -1.0)):
+        ref = rotate(ones.double(), seq, d, n + nk, sign)
+        worst = float(((got.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max())
+        assert worst < 4e-6, worst
