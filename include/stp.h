@@ -233,10 +233,10 @@ int stp_backward_weight_unit(stp_ctx *ctx, const stp_layer_desc *desc, int unit,
  * whose work it reads or overwrites (the forward stream for B / W work on the
  * microbatch whose stash it refills, the backward stream for the forward pass of
  * its microbatches and for W work on them, the weight-gradient stream for their
- * B units), and every stream that has work in the step comes after the whole of the
- * step before that: at most two blocks are in flight, and a block's tail overlaps the
- * next one's head.  Waits that others imply are left out, and a W unit whose B unit is
- * in the same step may be enqueued behind other units of the step.
+ * B units), and every stream waits for the whole of the step before that: at
+ * most two blocks are in flight, and a block's tail overlaps the next one's head.
+ * Waits that others imply are left out, and a W unit whose B unit is in the same
+ * step may be enqueued behind other units of the step.
  * (Gradient accumulators and workspace lanes are touched by one stream each;
  * units called directly on other streams are the caller's to order.)  The list is
  * validated first (STP_ESEQ): all F ops belong to one microbatch i, all B / W /

@@ -213,8 +213,9 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
   // only for   F: the B / W streams if they worked on the microbatch this step's F overwrites;
   //            B: the F stream if it produced one of this step's backward microbatches, the W stream if it read one;
   //            W: the B stream if it produced what this step's W units read (and the F stream likewise).
-  // A stream with work in this step is ordered behind the whole of the step before last, which bounds the skew to one
-  // block.  If the caller changed streams, or the stage's extent changed, every stream waits for everything.
+  // All streams are ordered behind the whole of the step before last, which bounds the skew to one block; those without
+  // work in this step too, since a caller may rely on it for work of its own there.  If the caller changed streams, or the
+  // stage's extent changed, every stream waits for everything.
   const bool has[3] = {f_mb >= 0, memchr(cur_b, 1, MB) != nullptr, memchr(cur_w, 1, MB) != nullptr};
   int slot_of[3];
   for (int i = 0; i < 3; i++)
@@ -224,7 +225,7 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
   bool same_streams = ctx->last_mbs == MB && ctx->last_b;
   for (int i = 0; i < 3; i++) same_streams = same_streams && ctx->step_stream[i] == streams[i];
   rc = STP_OK;
-  long need[3][3] = {};        // [slot][other slot]: the step of the other that the slot's work has to come after
+  long need[3][3] = {};        // [slot][other slot]: the step of the other that the slot has to come after
   if (!same_streams) {
     for (int i = 0; i < 3; i++)
       for (int j = 0; j < 3 && slot_of[i] == i; j++)
@@ -242,8 +243,7 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
       n = std::max(n, step);
     };
     for (int i = 0; i < 3; i++)
-      for (int j = 0; j < 3; j++)
-        if (has[i]) after(i, j, now - 2);
+      for (int j = 0; j < 3; j++) after(i, j, now - 2);
     if (f_mb >= 0 && ctx->last_b[f_mb]) after(0, 1, now - 1);
     if (f_mb >= 0 && ctx->last_w[f_mb]) after(0, 2, now - 1);
     for (int m = 0; m < MB; m++) {
@@ -260,9 +260,9 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     });
   };
   // the weight-gradient stream joins behind its first wait for a B unit of this step, which may stand for its other waits
-  bool w_joined = slot_of[2] != 2;
-  for (int i = 0; i < 2 && rc == STP_OK; i++)
-    if (slot_of[i] == i) rc = join(i);
+  bool w_joined = slot_of[2] != 2 || !has[2];
+  for (int i = 0; i < 3 && rc == STP_OK; i++)
+    if (slot_of[i] == i && (i < 2 || !has[2])) rc = join(i);
   if (rc != STP_OK) { free(cur_b); return rc; }
   int *ev_of = (int *)malloc(sizeof(int) * bsz);
   uint8_t *b_now = (uint8_t *)calloc(bsz, 1);      // B units issued by this step; committed to the context when the step is whole
@@ -420,7 +420,7 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
   return rc;
 }
 
-// The waits between steps, for tests on the host.  Per step: has[i] (slot i has work), last[3 i + j] (that work depends on the last
+// The waits between steps, for tests on the host.  Per step: has[i] (slot i has work), last[3 i + j] (its work depends on the last
 // step's of slot j) and through (slot 2 first waits for a unit of slot 1 of this step).  waits[k]: step | i << 16 | j << 20 | mark's step << 24
 // (as 64-bit numbers); returns their number, or -1 if there are more than cap.
 extern "C" int stp_braid_plan_joins(int n_steps, const uint8_t *has, const uint8_t *last, const uint8_t *through, int64_t *waits, int cap) {
@@ -430,9 +430,8 @@ extern "C" int stp_braid_plan_joins(int n_steps, const uint8_t *has, const uint8
   for (int s = 0; s < n_steps; s++) {
     J.now++;
     for (int i = 0; i < 3; i++) {
-      if (!has[3 * s + i]) continue;
       long need[3];
-      for (int j = 0; j < 3; j++) need[j] = J.now - (last[9 * s + 3 * i + j] ? 1 : 2);
+      for (int j = 0; j < 3; j++) need[j] = J.now - (has[3 * s + i] && last[9 * s + 3 * i + j] ? 1 : 2);
       if (i == 2 && through[s]) J.behind(2, 1, J.now - 1, J.known[1]);
       J.join(i, need, [&](int j, int which) -> int {
         if (n < cap) waits[n] = (int64_t)J.now | (int64_t)i << 16 | (int64_t)j << 20 | (int64_t)J.mark[j][which].step << 24;

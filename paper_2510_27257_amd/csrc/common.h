@@ -41,7 +41,7 @@ struct stp_joins {
   struct Mark { long step, known[3]; } mark[3][2];     // [slot][older, latest]; step 0: none
   long known[3][3];                                    // [slot][other slot]: the other's last step that the slot's stream is ordered behind
   long now;                                            // number of the step
-  // the waits of slot i where its work in this step has to come after step need[j] of slot j: wait(j, which mark); the later ones
+  // the waits of slot i where it has to come after step need[j] of slot j: wait(j, which mark); the later ones
   // first, since they may stand for the earlier ones
   template <typename F> int join(int i, const long need[3], F wait) {
     for (long back = 1; back <= 2; back++)

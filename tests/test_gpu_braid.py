@@ -406,3 +406,34 @@ def test_generated_device_program_runs_and_matches_the_two_chunk_sequence(ctx, p
                 dxl = O.backward_input_unit(cfg, O.ATTN, W, st, dxa)
                 dy = O.backward_input_unit(cfg, O.PRE_ATTN, W, st, dxl, d_resid=dxa)
             assert rel_err(to_host(stg.grad_slot(first, mb)), dy) < TOL[lm.dtype], (ci, mb)
+
+
+def test_streams_without_work_come_after_the_step_before_last_too(ctx):
+    """Three blocks of forward passes leave the other two streams without work.  What the caller puts on these then finds the first
+    block's output whole (a spinning kernel holds the first block back until all of it is enqueued)."""
+    layers, n_mb = STAGES["gpt_bf16_x2"]
+    L = len(layers)
+    stg = StageOnDevice(ctx, layers, n_mb, seed=4)
+    stg.load_inputs()
+    s0 = torch.cuda.current_stream()
+    ctx.braid_reset()
+    ctx.braid_step(stg.stage, forward_ops(L, 0), s0, s0, s0)
+    torch.cuda.synchronize()
+    first = stg.act_slot(L, 0)
+    want, got = first.clone(), [torch.empty_like(first) for _ in range(2)]
+    streams = tuple(torch.cuda.Stream() for _ in range(3))
+    for step in range(2):      # (the change of streams joins them all: the steps that matter come behind two of their own)
+        ctx.braid_step(stg.stage, forward_ops(L, 4), *streams)
+    torch.cuda.synchronize()
+    first.fill_(float("nan"))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[0]):
+        torch.cuda._sleep(20_000_000)
+    for mb in range(3):
+        ctx.braid_step(stg.stage, forward_ops(L, mb), *streams)
+    for s, out in zip(streams[1:], got):
+        with torch.cuda.stream(s):
+            out.copy_(first)
+    torch.cuda.synchronize()
+    for out in got:
+        assert torch.equal(out, want)
