@@ -125,6 +125,18 @@ int ensure_events(stp_ctx *ctx, int want) {
   return STP_OK;
 }
 
+// Asked in relaxed mode: in the others the query invalidates a capture that is under way on any other stream of the thread (or, in
+// global mode, of the process), which the calls of a step otherwise leave alone.
+int event_passed(stp_ctx *ctx, hipEvent_t ev, bool *passed) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  STP_HIP(ctx, hipThreadExchangeStreamCaptureMode(&mode));
+  const hipError_t e = hipEventQuery(ev);
+  STP_HIP(ctx, hipThreadExchangeStreamCaptureMode(&mode));
+  if (e != hipSuccess) (void)hipGetLastError();
+  *passed = e == hipSuccess;
+  return STP_OK;
+}
+
 }  // namespace
 
 extern "C" int stp_validate_ops(const stp_stage *stage, const stp_op *ops, size_t n_ops, size_t *bad_index) {
@@ -289,7 +301,11 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
       const stp_stash *stash = &st->stash[(size_t)o.layer * MB + o.microbatch];
       const int ev = ev_of[((size_t)o.layer * MB + o.microbatch) * 2 + (o.unit == STP_MLP ? 1 : 0)];
       if (ev >= 0) {
-        if (!all && hipEventQuery(ctx->ev_pool[ev]) != hipSuccess) { (void)hipGetLastError(); return STP_OK; }
+        if (!all) {
+          bool passed = false;
+          const int r = event_passed(ctx, ctx->ev_pool[ev], &passed);
+          if (r != STP_OK || !passed) return r;
+        }
         STP_HIP(ctx, hipStreamWaitEvent(sW, ctx->ev_pool[ev], 0));
         // the B stream has made this step's waits, so behind its event are the steps before and what those waits stand for
         J.behind(slot_of[2], slot_of[1], now - 1, J.known[slot_of[1]]);

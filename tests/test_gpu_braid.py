@@ -437,3 +437,37 @@ def test_streams_without_work_come_after_the_step_before_last_too(ctx):
     torch.cuda.synchronize()
     for out in got:
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_steps_run_while_another_stream_is_being_captured(ctx, mode):
+    """Steps on three streams of their own, with weight-gradient units put off behind their B units, between the beginning and the end of
+    a capture on a fourth: both are whole afterwards."""
+    layers, n_mb = STAGES["gpt_bf16_x2"]
+    stg = StageOnDevice(ctx, layers, n_mb, seed=2)
+    stg.load_inputs()
+    s0 = torch.cuda.current_stream()
+    streams = tuple(torch.cuda.Stream() for _ in range(3))
+    run_sequence(ctx, stg, (s0, s0, s0))
+    want = snapshot(stg)
+    run_sequence(ctx, stg, streams)                     # events and kernel attributes are made here
+    ctx.braid_reset()
+    stg.zero_grads()
+    x = torch.ones(1 << 16, device="cuda")
+    x.mul_(1.0)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[1]):
+        torch.cuda._sleep(2_000_000)                    # so that B units are pending when their W units are looked at
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream(), capture_error_mode=mode):
+        x.mul_(2.0)
+        for step in stage_sequence(len(stg.layers), stg.n_mb):
+            ctx.braid_step(stg.stage, step, *streams)
+        x.add_(1.0)
+    torch.cuda.synchronize()
+    for a, b in zip(want, snapshot(stg)):
+        assert torch.equal(a, b)
+    for value in (3.0, 7.0, 15.0):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((x == value).all())
