@@ -132,7 +132,8 @@ int event_passed(stp_ctx *ctx, hipEvent_t ev, bool *passed) {
   STP_HIP(ctx, hipThreadExchangeStreamCaptureMode(&mode));
   const hipError_t e = hipEventQuery(ev);
   STP_HIP(ctx, hipThreadExchangeStreamCaptureMode(&mode));
-  if (e != hipSuccess) (void)hipGetLastError();
+  if (e != hipSuccess && e != hipErrorNotReady) return stp_fail(ctx, STP_EHIP, "stp_braid_step: hipEventQuery failed: %s", hipGetErrorString(e));
+  if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();      // no error of the caller's
   *passed = e == hipSuccess;
   return STP_OK;
 }
