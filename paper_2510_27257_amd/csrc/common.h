@@ -262,7 +262,7 @@ int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hip
 // tile (bm << 16 | bn) of that launch, 0 where the products are launched apart; host only, no part of the interface (tests check routes)
 extern "C" int stp_wgrad_set_tile(const stp_gemm_args *a, int n);
 // The products of a SwiGLU MLP with the activation in the epilogue or both operands in one contraction.  `g` describes one of the two
-// products; STP_EUNSUPPORTED where the operands are beyond the direct-to-LDS kernels (the caller then launches them apart).
+// products; STP_EUNSUPPORTED where the operands are beyond the direct-to-LDS kernels or the first takes longer so (the caller then launches them apart).
 //   up: C = A B (+ bias), up = A B2, act = SiLU(C) * up
 int stp_launch_gemm_bf16_swiglu(stp_ctx *ctx, const stp_gemm_args *g, const void *B2, void *up, void *act, hipStream_t s);
 //   C, dup = gradients of gate and up activation from their values and the product's sums

@@ -1105,8 +1105,9 @@ inline double launch_us(const TileCfg &c, long tiles, long K, int layout, bool a
   }
   return t;
 }
-// pair: two products side by side (MM_PAIR), whose half-width B tiles cost the 128-wide tiles more ([4096, 2 x 5120] K = 7168: 0.50 instead of
-// the 0.43 us below per 32-deep part; the MLP unit 805 us with it, 739 with 256 x 256)
+// pair: two products side by side (MM_PAIR).  Tiles other than 256 x 256 take 6 % longer than the estimate for one product says (fitted to
+// the five tiles at 607 shapes of 136 .. 6144 tokens, hidden 520 .. 7168, f 520 .. 14336: the tile it picks is on average 0.4 % behind the
+// fastest one; with 15 % on the 128-wide tiles, the figure of one shape, 0.8 %, [136, 2 x 14336] K = 5120 106 us instead of 83).
 inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool accum, bool shared_gpu, double *us = nullptr, bool pair = false) {
   if (shared_gpu) {
     // Beside other streams' kernels the rounds of the estimate below mean nothing (what a round leaves idle the
@@ -1124,7 +1125,7 @@ inline TileChoice pick_tile(long M, long N, long K, bool a_kc, bool b_kc, bool a
   double best_t = 1e30;
   for (const TileCfg &c : kTiles) {
     if (c.t_ktile[2 * a_kc + b_kc] == 0.0) continue;
-    const double t = launch_us(c, tile_count(c, M, N), K, 2 * a_kc + b_kc, accum) * (pair && c.bm * c.bn < 192 * 256 ? 1.15 : 1.0);
+    const double t = launch_us(c, tile_count(c, M, N), K, 2 * a_kc + b_kc, accum) * (pair && c.bm * c.bn < 256 * 256 ? 1.06 : 1.0);
     if (t < best_t) { best_t = t; best = TileChoice{c.bm, c.bn}; }
   }
   if (us) *us = best_t;

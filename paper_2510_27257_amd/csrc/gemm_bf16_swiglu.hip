@@ -47,16 +47,37 @@ inline bool addressable(const stp_gemm_args *a, bool b_kc) {
   return a->K > 0 && operand_bytes(true, a->M, a->K, a->lda) > 0 && operand_bytes(b_kc, a->N, a->K, a->ldb) > 0;
 }
 
+// Whether the two projections, alone on the GPU, take longer together than apart, activation kernel included: for few tokens and long
+// contractions, where a tile of both is slower by more than one launch saves.  The MLP unit (us, together / apart): 520 tokens, f = 14336, hidden
+// 4096 261 / 256, 7168 442 / 431; 1032 tokens, 5120, 8192 301 / 290.  Beyond 1152 tokens the estimates are close where it is said to
+// pay, and it does not: [1544, 2 x 5120] K = 7168 345 / 373, [2568, 2 x 3456] 363 / 383.  Both ways store the same bits.
+inline bool longer_together(const stp_gemm_args *a, TileChoice *c) {
+  double together, one;
+  *c = pick_tile(a->M, 2L * a->N, a->K, true, false, false, false, &together, true);
+  pick_tile(a->M, a->N, a->K, true, false, false, false, &one);
+  return a->M <= 1152 && together > 2.0 * one + 1.33e-6 * (double)a->M * a->N;      // the kernel moves three tensors at 4.5 TB/s
+}
+
 }  // namespace
+
+// tile (bm << 16 | bn) of the projections' launch alone on the GPU, 0 where they are launched apart; host only, no part of the interface
+extern "C" int stp_swiglu_pair_tile(int M, int N, int K) {
+  stp_gemm_args a = {};
+  a.M = M; a.N = N; a.K = K;
+  TileChoice c;
+  return wavek_shape(M, N, K) || longer_together(&a, &c) ? 0 : c.bm << 16 | c.bn;
+}
 
 int stp_launch_gemm_bf16_swiglu(stp_ctx *ctx, const stp_gemm_args *a, const void *B2, void *up, void *act, hipStream_t s) {
   // products small enough for the contraction-splitting kernel stay apart
   if (!addressable(a, false) || wavek_shape(a->M, a->N, a->K)) return STP_EUNSUPPORTED;
+  TileChoice c;
+  if (!ctx->concurrent && !a->tile_m && longer_together(a, &c)) return STP_EUNSUPPORTED;
   Epi ep = make_epi(a);
   ep.C2 = (bf16_t *)up;
   ep.C3 = (bf16_t *)act;
   ep.ld2 = a->ldc;
-  const TileChoice c = tile_for(ctx, a, true, false, false, 2L * a->N, a->K, true);
+  c = tile_for(ctx, a, true, false, false, 2L * a->N, a->K, true);
   return a->K % DK ? launch_two_tile<false, EPI_SWIGLU_FWD, true, MM_PAIR>(ctx, a, c, ep, nullptr, B2, s)
                    : launch_two_tile<false, EPI_SWIGLU_FWD, false, MM_PAIR>(ctx, a, c, ep, nullptr, B2, s);
 }

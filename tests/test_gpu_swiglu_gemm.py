@@ -30,7 +30,7 @@ def off(got, ref):
 # that the contraction-splitting kernel takes (the first two), with and without a gate bias
 @pytest.mark.parametrize("T,h,f,bias", [(264, 640, 712, False), (8, 520, 1032, True), (1096, 520, 1096, True), (1032, 1032, 2056, False),
                                         (3000, 1032, 2744, False), (640, 64, 4104, False), (2048, 2048, 40, True), (776, 56, 4168, False),
-                                        (4096, 5120, 3456, False)])
+                                        (4096, 5120, 3456, False), (520, 4096, 13064, False)])      # the last: apart
 def test_mlp_unit_forward_and_input_gradient(ctx, T, h, f, bias):
     wl = Workload("mlp", h, 1, 64, f, T, 2, norm="rms", act="swiglu", has_bias=bias)
     lay = LayerOnDevice(ctx, wl, seed=1)
@@ -50,3 +50,14 @@ def test_mlp_unit_forward_and_input_gradient(ctx, T, h, f, bias):
     assert off(du, d * gate * sig) < ROUND
     assert off(dg, d * up * sig * (1.0 + gate * (1.0 - sig))) < ROUND
     assert off(dz, dg @ w["w_fc1"].T + du @ w["w_up"].T) < ROUND
+    # the projections apart store the same bits: which way they are launched is a question of time alone
+    args = lambda b, c, bias: stp.GemmArgs(dtype=stp.BF16, M=T, N=f, K=h, A=zb.data_ptr(), lda=h, B=b.data_ptr(), ldb=f, C=c.data_ptr(), ldc=f,
+                                           bias=bias, bias_scale=1.0, resid_scale=1.0)
+    zb = lay.field("Z_LN")
+    g1, u1, a1 = (torch.empty((T, f), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    ctx.gemm(args(lay.w_dev["w_fc1"], g1, lay.w_dev["b_fc1"].data_ptr() if bias else None))
+    ctx.gemm(args(lay.w_dev["w_up"], u1, None))
+    ctx.swiglu_forward(stp.BF16, T * f, g1, u1, a1)
+    torch.cuda.synchronize()
+    for one, field in ((g1, "H"), (u1, "HU"), (a1, "G")):
+        assert torch.equal(one, lay.field(field).view(T, f))
