@@ -834,10 +834,15 @@ static int norm_bwd_short_dispatch(stp_ctx *ctx, int norm, int rows, int h, cons
   return STP_OK;
 }
 
-// us, two launches -> one (LayerNorm with residual sum): [128, 256] fp32 9.3 -> 6.8, [1024, 512] 10.0 -> 6.7, [1024, 1024] 10.2 -> 6.6, [1024, 2048]
-// 14.6 -> 10.3, [512, 4096] 20.6 -> 7.4, [1024, 4096] 19.8 -> 14.6; beyond, where the second reading no longer comes from the caches:
-// [2048, 1024] 12.2 -> 16.0, [3000, 1032] 16.1 -> 21.4
-static bool norm_bwd_short(int rows, int h, size_t bytes) { return rows <= 1024 && h <= 4096 && bytes <= (8u << 20); }
+// Two launches -> one (LayerNorm with residual sum, us, inputs from HBM; from the last-level cache nearly the same): bf16 [1024, 512] 8.7 -> 9.4, [1024,
+// 1024] 11.0 -> 10.2, [1024, 4096] 21.3 -> 15.5, [768, 256] 7.4 -> 6.8; fp32 [256, 256] 5.8 -> 4.8, [512, 512] 7.8 -> 7.3, [768, 512] 8.5 -> 9.9, [704, 1024]
+// 10.6 -> 10.1, [1024, 1024] 11.8 -> 14.9, [1024, 256] 7.6 -> 12.2; without the residual's sum a tensor less is summed: fp32 [896, 1032] 9.9 ->
+// 9.7, [1024, 1032] 10.3 -> 11.2.  A column group takes its rows in batches one after the other, so what counts is their number, and
+// for fp32 twice.  Beyond 8 MB the second reading costs too much: [2048, 1024] 12.2 -> 16.0, [3000, 1032] 16.1 -> 21.4.
+static bool norm_bwd_short(int rows, int h, int dtype, bool rsum) {
+  const int most = dtype == STP_BF16 ? (rsum && h < 768 ? 896 : 1024) : !rsum ? 896 : h < 1024 ? 512 : 704;
+  return rows <= most && h <= 4096 && (size_t)rows * h * stp_elem_size(dtype) <= (8u << 20);
+}
 static bool overlaps(const void *a, const void *b, size_t bytes) {
   return b && (const char *)a < (const char *)b + bytes && (const char *)b < (const char *)a + bytes;
 }
@@ -871,7 +876,7 @@ extern "C" int stp_norm_backward(stp_ctx *ctx, int dtype, int norm, int32_t T, i
   }
   const size_t bytes = (size_t)T * h * stp_elem_size(dtype);
   // (dx written over one of its inputs is fine a row at a time, not where another group reads the column)
-  if (partial && norm_bwd_short(T, h, bytes) && !overlaps(dx, x, bytes) && !overlaps(dx, dy, bytes) && !overlaps(dx, d_resid, bytes)) {
+  if (partial && norm_bwd_short(T, h, dtype, rsum) && !overlaps(dx, x, bytes) && !overlaps(dx, dy, bytes) && !overlaps(dx, d_resid, bytes)) {
     const NormSums so = {{dgamma, want_beta ? dbeta : nullptr, d_resid_sum}, {1.0f, 1.0f, d_resid_sum_scale}};
     return dtype == STP_BF16 ? norm_bwd_short_dispatch<bf16_t>(ctx, norm, T, h, x, gamma, stats, dy, d_resid, dx, so, s)
                              : norm_bwd_short_dispatch<float>(ctx, norm, T, h, x, gamma, stats, dy, d_resid, dx, so, s);

@@ -21,7 +21,7 @@ def ctx():
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("norm", ["ln", "rms"])
-@pytest.mark.parametrize("T,h", [(1, 8), (3, 264), (5, 40), (257, 1032), (1023, 2048), (1024, 2056), (1024, 4096), (1025, 1024), (600, 4104), (37, 6152), (1026, 8192)])
+@pytest.mark.parametrize("T,h", [(1, 8), (3, 264), (5, 40), (257, 1032), (512, 264), (513, 264), (704, 1032), (705, 1032), (896, 520), (897, 520), (1023, 2048), (1024, 2056), (1024, 4096), (1025, 1024), (600, 4104), (37, 6152), (1026, 8192)])
 @pytest.mark.parametrize("rsum,over", [(True, None), (False, None), (True, "dy"), (True, "d_resid")])
 def test_against_64_bits(ctx, T, h, norm, dtype, rsum, over):
     td, code = (torch.float32, stp.F32) if dtype == "f32" else (torch.bfloat16, stp.BF16)
