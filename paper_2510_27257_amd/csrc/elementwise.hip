@@ -893,11 +893,14 @@ extern "C" int stp_norm_backward(stp_ctx *ctx, int dtype, int norm, int32_t T, i
   return STP_OK;
 }
 
-// us, two launches -> one: [128, 768] fp32 5.9 -> 4.0, [1024, 4096] 6.5 -> 3.6, [2048, 4096] 6.5 -> 4.6, [3000, 1032] 6.4 -> 6.5, [4096, 1536] 6.4 -> 6.9
-constexpr int COLSUM_SHORT_ROWS = 2048;
+// Two launches -> one (us, inputs from HBM): bf16 [1024, 4096] 9.9 -> 5.9, [2048, 1024] 9.5 -> 9.1, [2048, 5120] 10.8 -> 11.6 (from the last-level cache
+// 9.1 -> 7.6), beyond 2048 rows [3000, 1032] 6.4 -> 6.5 and [4096, 1536] 6.4 -> 6.9 from L2; fp32 [384, 256] 5.9 -> 4.1, [768, 1024] 6.9 -> 7.0, [1024, 1024]
+// 7.0 -> 8.7, [2048, 1024] 7.6 -> 15.0, but [2048, 8192] 18.7 -> 17.8: a row-lane's batches follow one another, twice as many bytes each for fp32, and
+// only 128 groups or more draw what two launches do.
+static bool colsum_short(int rows, int n, int dtype) { return rows <= (dtype == STP_BF16 || n >= 8192 ? 2048 : 768); }
 // a column sum, in one launch or in two with the partial sums at `partial` (slabs x N floats)
 static int colsum_launch(stp_ctx *ctx, int dtype, int T, int N, const void *x, float scale, float *out, float *partial, hipStream_t s) {
-  if (T <= COLSUM_SHORT_ROWS) {
+  if (colsum_short(T, N, dtype)) {
     const dim3 grid((N + 63) / 64), block(1024);
     if (dtype == STP_BF16) hipLaunchKernelGGL(colsum_short_kernel<bf16_t>, grid, block, 0, s, (const bf16_t *)x, T, N, scale, out);
     else hipLaunchKernelGGL(colsum_short_kernel<float>, grid, block, 0, s, (const float *)x, T, N, scale, out);

@@ -1,4 +1,4 @@
-"""The column sum in one launch (up to 2048 rows) and in two, around the row-lanes', batches' and column groups' edges."""
+"""The column sum in one launch (up to 768 rows of fp32, 2048 of bf16 and of wide fp32) and in two, around the row-lanes', batches' and column groups' edges."""
 import pytest
 import torch
 
@@ -8,8 +8,8 @@ import paper_2510_27257_amd as stp
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("N", [8, 64, 72, 1032])
-@pytest.mark.parametrize("T", [1, 7, 128, 129, 1024, 1031, 2048, 2049])
+@pytest.mark.parametrize("N", [8, 64, 72, 1032, 8192])
+@pytest.mark.parametrize("T", [1, 7, 128, 129, 768, 769, 1024, 1031, 2048, 2049])
 def test_column_sum(T, N, dtype):
     ctx = stp.Context(0)
     g = torch.Generator(device="cuda").manual_seed(T * N)
