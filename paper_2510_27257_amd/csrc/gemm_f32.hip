@@ -41,15 +41,39 @@ __device__ __forceinline__ void load_chunk(float (&f)[8], const float *__restric
   for (int i = 0; i < 8; i++) f[i] = ok ? f[i] : 0.f;
 }
 
+// The weight gradients of a unit that take 32 x 32 tiles, in one launch: two or three of these short kernels one after the other are mostly
+// starts and ends.
+struct F32Problem { const float *A, *B; float *C; int lda, ldb, ldc, M, N, tiles_n, first; };
+struct F32Set { int n, K, tiles; F32Problem p[3]; };
+// the workgroup's product of the set and its tile there
+__device__ __forceinline__ void pick_problem(const F32Set &set, const float *&A, int &lda, const float *&B, int &ldb, int &M, int &N, int &K, EpiF &ep, int &tm, int &tn) {
+  const int pid = blockIdx.x, i = set.n > 2 && pid >= set.p[2].first ? 2 : pid >= set.p[1].first ? 1 : 0;
+  const F32Problem &q = set.p[i];
+  A = q.A; lda = q.lda; B = q.B; ldb = q.ldb; M = q.M; N = q.N; K = set.K;
+  ep = EpiF{};      // known here, so the epilogue is the short one
+  ep.C = q.C; ep.ldc = q.ldc; ep.accum = 1;
+  tm = (pid - q.first) / q.tiles_n;
+  tn = (pid - q.first) % q.tiles_n;
+}
+
 // WT: a wave's tile is (32 WT)^2; WM x WN such tiles make the workgroup's tile; KS waves share each of them.
-template <int WT, int WM, int WN, int KS, bool A_KC, bool B_KC>
-__device__ __forceinline__ void gemm_f32_tile(const float *__restrict__ A, int lda, const float *__restrict__ B, int ldb, int M, int N, int K,
-                                              int tm, int tn, const EpiF &ep) {
+// Set: nothing, or the set that the product is taken from (first, so that its start comes with the first cache line of the arguments).  (One kernel for both: as a function called by two, the plain products' epilogues were
+// scheduled differently, [520, 2744] K = 1032 with a row-contiguous A 62.4 -> 67.9 us, [4096, 4096] K = 512 with a transposed B 196 -> 204.)
+template <int WT, int WM, int WN, int KS, bool A_KC, bool B_KC, typename... Set>
+__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_kernel(Set... set, const float *__restrict__ A, int lda,
+                                                                     const float *__restrict__ B, int ldb, int M, int N, int K, EpiF ep) {
   constexpr int TM = 32 * WT * WM, TN = 32 * WT * WN, NTH = 64 * WM * WN * KS;
   constexpr int RP = TN + 4;                          // pitch of a staged row
   extern __shared__ __attribute__((aligned(16))) float red[];   // [KS][TM][RP]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lg = lane >> 5;
   const int ks = wave % KS, wt = wave / KS, wm = wt / WN, wn = wt % WN;
+  int tm = blockIdx.y, tn = blockIdx.x;
+  if constexpr (sizeof...(Set) > 0) {
+    const float *a, *b;
+    pick_problem(set..., a, lda, b, ldb, M, N, K, ep, tm, tn);
+    A = a;
+    B = b;
+  }
   const int m0 = tm * TM, n0 = tn * TN;
   int ra[WT], rb[WT];                                 // this lane's operand rows; past the end: the last row, never stored
 #pragma unroll
@@ -160,26 +184,6 @@ __device__ __forceinline__ void gemm_f32_tile(const float *__restrict__ A, int l
 }
 
 template <int WT, int WM, int WN, int KS, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_kernel(const float *__restrict__ A, int lda, const float *__restrict__ B,
-                                                                     int ldb, int M, int N, int K, EpiF ep) {
-  gemm_f32_tile<WT, WM, WN, KS, A_KC, B_KC>(A, lda, B, ldb, M, N, K, blockIdx.y, blockIdx.x, ep);
-}
-
-// The weight gradients of a unit that take 32 x 32 tiles, in one launch: two or three of these short kernels one after the other are mostly
-// starts and ends.
-struct F32Problem { const float *A, *B; float *C; int lda, ldb, ldc, M, N, tiles_n, first; };
-struct F32Set { int n, K, tiles; F32Problem p[3]; };
-__global__ __launch_bounds__(512) void gemm_f32_set_kernel(F32Set set) {
-  const int pid = blockIdx.x, i = set.n > 2 && pid >= set.p[2].first ? 2 : pid >= set.p[1].first ? 1 : 0;
-  const F32Problem &q = set.p[i];
-  EpiF ep = {};
-  ep.C = q.C;
-  ep.ldc = q.ldc;
-  ep.accum = 1;
-  gemm_f32_tile<1, 1, 1, 8, false, false>(q.A, q.lda, q.B, q.ldb, q.M, q.N, set.K, (pid - q.first) / q.tiles_n, (pid - q.first) % q.tiles_n, ep);
-}
-
-template <int WT, int WM, int WN, int KS, bool A_KC, bool B_KC>
 int launch_f32(stp_ctx *ctx, const stp_gemm_args *a, const EpiF &ep, hipStream_t s) {
   constexpr int TM = 32 * WT * WM, TN = 32 * WT * WN;
   constexpr size_t smem = KS == 1 ? 0 : (size_t)KS * TM * (TN + 4) * sizeof(float);
@@ -254,7 +258,8 @@ int stp_launch_gemm_f32_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipS
     f.p[i] = {(const float *)a[i].A, (const float *)a[i].B, (float *)a[i].C, a[i].lda, a[i].ldb, a[i].ldc, a[i].M, a[i].N, (a[i].N + 31) / 32, f.tiles};
     f.tiles += (int)f32_tiles(&a[i], 32);
   }
-  hipLaunchKernelGGL(gemm_f32_set_kernel, dim3(f.tiles), dim3(512), (size_t)8 * 32 * 36 * sizeof(float), s, f);
+  hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 1, 8, false, false, F32Set>), dim3(f.tiles), dim3(512), (size_t)8 * 32 * 36 * sizeof(float), s, f, nullptr, 0, nullptr, 0, 0, 0, 0,
+                     EpiF{});
   STP_LAUNCH_CHECK(ctx);
   return STP_OK;
 }
