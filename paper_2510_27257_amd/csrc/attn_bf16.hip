@@ -770,7 +770,7 @@ stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit) {
 }
 
 // The same for the backward kernels, two workgroups of four waves to a compute unit.  Alone on one a workgroup takes 5 + 2.0 (dq: 2.8) us a
-// step, beside another 3 + 1.3 (1.85): less than eight waves where blocks are short and many, since one workgroup's first
+// step, beside another 3 + 1.3 (1.85) of the unit's time: less than eight waves where blocks are short and many, since one workgroup's first
 // tiles and results overlap the other's steps; long blocks gain nothing, and few of them leave waves idle.  Measured (us, row dot
 // included, eight waves / four): 8 x 8 heads, 520 tokens, causal 32.3 / 28.9; 8 x 16 heads, 256 tokens 20.2 / 17.3; 16 x 16 heads, 512 tokens, no
 // mask 114 / 95; 2 x 16 heads, 4096 tokens 290 / 290; 16 heads, 1024 tokens, no mask 27 / 36; 4 heads, 512 tokens 16.4 / 21.1.
@@ -784,13 +784,67 @@ static double four_wave_bwd_us(const PlanPart *p) {
   return std::max(longest, sum / PLAN_CUS);
 }
 
+// That bound is blind to a last round of few workgroups: of 691 shapes it would give to four waves (128 .. 8192 tokens, 2 .. 32 heads) they were slower
+// than eight at 51, by up to 18 %, equal long blocks above all (6 heads, 6144 tokens, no mask 250 / 296; 10 heads, 4096 tokens 180 / 202; 6 x 8 heads on 4, 1024
+// tokens 60 / 69).  So the launch is simulated too: longest first, each workgroup to the compute unit that has room first, two of a unit sharing
+// its time.  With costs fitted for this choice none is more than 1.7 % slower, 561 stay, and on average they are where the bound alone had them.
+static double four_wave_bwd_end(const PlanPart *p) {
+  const double fixed = 2.2, step[2] = {1.15, 2.0}, fixed1 = 4.8, step1[2] = {1.5, 2.45};
+  double sum = 0.0, longest = 0.0;
+  for (int i = 0; i < 2; i++) {
+    for (int x = 0; x < p[i].nblocks; x++) sum += p[i].z * (fixed + step[i] * p[i].steps[x]);
+    longest = std::max(longest, fixed + step[i] * p[i].max_steps);
+  }
+  if (sum / PLAN_CUS > 16.0 * longest) return sum / PLAN_CUS;      // the last round is a small part of the whole (and this bounds the planning time)
+  struct Work { double paired, alone; };
+  std::vector<Work> items;
+  for (int i = 0; i < 2; i++)
+    for (int x = 0; x < p[i].nblocks; x++)
+      for (int z = 0; z < p[i].z; z++) items.push_back({fixed + step[i] * p[i].steps[x], fixed1 + step1[i] * p[i].steps[x]});
+  std::sort(items.begin(), items.end(), [](const Work &u, const Work &v) { return u.paired > v.paired; });
+  // two workgroups of a unit share its time, one alone goes at its own rate
+  struct Unit { Work w[2]; double left[2], at; int n; };
+  std::vector<Unit> cu(PLAN_CUS, Unit{{}, {}, 0.0, 0});
+  size_t next = 0;
+  for (int r = 0; r < 2; r++)
+    for (Unit &u : cu)
+      if (next < items.size()) { u.w[u.n] = items[next++]; u.left[u.n++] = 1.0; }
+  auto rate = [](const Unit &u, int k) { return u.n == 1 ? 1.0 / u.w[k].alone : 0.5 / u.w[k].paired; };
+  std::priority_queue<std::pair<double, int>, std::vector<std::pair<double, int>>, std::greater<std::pair<double, int>>> events;
+  auto schedule = [&](int c) {
+    const Unit &u = cu[c];
+    if (!u.n) return;
+    double first = u.left[0] / rate(u, 0);
+    if (u.n == 2) first = std::min(first, u.left[1] / rate(u, 1));
+    events.push({u.at + first, c});
+  };
+  for (int c = 0; c < PLAN_CUS; c++) schedule(c);
+  double end = 0.0;
+  while (!events.empty()) {
+    const int c = events.top().second;
+    end = events.top().first;
+    events.pop();
+    Unit &u = cu[c];
+    const double dt = end - u.at, r[2] = {rate(u, 0), u.n == 2 ? rate(u, 1) : 0.0};
+    u.at = end;
+    int kept = 0;
+    for (int k = 0; k < u.n; k++) {
+      const double left = u.left[k] - dt * r[k];
+      if (left > 1e-9) { u.w[kept] = u.w[k]; u.left[kept++] = left; }
+    }
+    for (u.n = kept; u.n < 2 && next < items.size(); u.n++) { u.w[u.n] = items[next++]; u.left[u.n] = 1.0; }
+    schedule(c);
+  }
+  return end;
+}
+
 int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]) {
   const int nk = stp_kv_heads(d), D = d->head_dim;
   PlanPart part[2] = {{attn_cost(1, D), nkv, nk * d->mbsz, max_of(steps_kv, nkv), 0, steps_kv, (size_t)2 * 128 * D * sizeof(float)},
                       {attn_cost(2, D), nq, d->heads_local * d->mbsz, max_of(steps_q, nq), 0, steps_q, (size_t)128 * D * sizeof(float)}};
   const double t = plan_chunks(part, 2);
   const bool fits = nkv + d->heads_local / nk * nq <= STP_ATTN_ORDER_CAP;        // one launch for both kinds
-  const bool four = D == 64 && fits && four_wave_bwd_us(part) < 0.97 * t;
+  const bool four = D == 64 && fits && four_wave_bwd_us(part) < 0.97 * t && four_wave_bwd_end(part) < 1.01 * t;
   chunk[0] = four ? part[0].max_steps : part[0].c;
   chunk[1] = four ? part[1].max_steps : part[1].c;
   return four ? 1 : 2;

@@ -120,3 +120,15 @@ def test_plan_invariants_on_random_shapes():
             assert len(items) == len(want) and set(items) == want
             lens = [min(c, steps[x] - k * c) for x, k in items]
             assert lens == sorted(lens, reverse=True) and sum(lens) == sum(steps)
+
+
+# heads, kv heads, tokens, sequences, mask: many short blocks; few workgroups; equal long blocks whose last round is nearly empty (four waves took up to
+# 18 % longer there); a sum of many rounds
+@pytest.mark.parametrize("n,nk,seq,mbsz,causal,four", [(8, 8, 520, 8, True, True), (16, 16, 512, 16, False, True), (12, 12, 128, 16, True, True),
+                                                       (32, 32, 384, 16, True, True), (16, 16, 1024, 1, False, False), (4, 4, 512, 1, True, False),
+                                                       (6, 6, 6144, 1, False, False), (10, 10, 4096, 1, False, False), (8, 4, 1024, 6, False, False),
+                                                       (10, 10, 2048, 4, False, False), (20, 20, 4096, 1, False, False)])
+def test_backward_workgroups_of_four_waves(n, nk, seq, mbsz, causal, four):
+    import ctypes as C
+    desc = stp.make_desc(Workload("w", 1024, n, 64, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)
+    assert stp.lib().stp_attn_bwd_halves(C.byref(desc)) == (1 if four else 2)
