@@ -85,7 +85,8 @@ static size_t field_bytes(const stp_layer_desc *d, int f) {
     case STP_ST_CTX: case STP_ST_DCTX: return T * a * es;
     case STP_ST_LSE: case STP_ST_DELTA: return (size_t)d->mbsz * d->heads_local * d->seq * sizeof(float);
     case STP_ST_H: case STP_ST_G: case STP_ST_DH: return T * ff * es;
-    case STP_ST_HU: case STP_ST_DHU: case STP_ST_DG: return sw ? T * ff * es : 0;
+    case STP_ST_HU: case STP_ST_DHU: return sw ? T * ff * es : 0;
+    case STP_ST_DG: return sw && d->dtype == STP_F32 ? T * ff * es : 0;
   }
   return 0;
 }

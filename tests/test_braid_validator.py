@@ -57,6 +57,22 @@ def test_desc_checks_and_sizes_need_no_gpu():
     assert L.stp_check_desc(None) == 1
 
 
+@pytest.mark.parametrize("dtype,act,bytes_per_token", [("bf16", "swiglu", 0), ("bf16", "gelu", 0), ("f32", "swiglu", 712 * 4), ("f32", "gelu", 0)])
+def test_stash_holds_the_product_gradient_only_where_it_is_written(dtype, act, bytes_per_token):
+    """The gradient of the SwiGLU product (DG) passes through memory in the fp32 layers; in bf16 it stays in the accumulators."""
+    d = stp.make_desc(synth.Workload("s", 256, 2, 64, 712, 136, 2, dtype=dtype, act=act))
+    off, sz, total = C.c_size_t(), C.c_size_t(), C.c_size_t()
+    L = stp.lib()
+    assert L.stp_stash_field(C.byref(d), stp.STASH_FIELDS.index("DG"), C.byref(off), C.byref(sz)) == 0
+    assert sz.value == 136 * bytes_per_token
+    sizes = []
+    for i in range(len(stp.STASH_FIELDS)):
+        assert L.stp_stash_field(C.byref(d), i, C.byref(off), C.byref(sz)) == 0
+        assert off.value == sum(sizes)
+        sizes.append(-(-sz.value // 256) * 256)
+    assert L.stp_stash_bytes(C.byref(d), C.byref(total)) == 0 and total.value == sum(sizes)
+
+
 def _stage(n_layers, n_mb, chain_break=None):
     descs = (stp.LayerDesc * n_layers)(*[stp.make_desc(synth.WORKLOADS["tiny"]) for _ in range(n_layers)])
     cb = (C.c_int32 * (n_layers + 1))(*chain_break) if chain_break else None
