@@ -220,30 +220,26 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     if (o.kind == STP_OP_B || o.kind == STP_OP_BW) cur_b[o.microbatch] = 1;
     if (o.kind == STP_OP_W || o.kind == STP_OP_BW) cur_w[o.microbatch] = 1;
   }
-  // Joins with the steps before.  Data of a (layer, microbatch) is written by that microbatch's F units (forward
-  // stream), read and extended by its B units (backward stream), read by its W units (weight-gradient stream);
-  // gradient accumulators and workspace lanes belong to one stream each.  So, of the last step, a stream waits
-  // only for   F: the B / W streams if they worked on the microbatch this step's F overwrites;
-  //            B: the F stream if it produced one of this step's backward microbatches, the W stream if it read one;
-  //            W: the B stream if it produced what this step's W units read (and the F stream likewise).
-  // All streams are ordered behind the whole of the step before last, which bounds the skew to one block; those without
-  // work in this step too, since a caller may rely on it for work of its own there.  If the caller changed streams, or the
-  // stage's extent changed, every stream waits for everything.
+  // Joins with the steps before (see stp_step_joins).  If the caller changed streams, or the stage's extent changed, every stream waits for
+  // everything.
   const bool has[3] = {f_mb >= 0, memchr(cur_b, 1, MB) != nullptr, memchr(cur_w, 1, MB) != nullptr};
-  int slot_of[3];
+  stp_joins &J = ctx->joins;
+  stp_step_joins joins = {J, {}};
+  int (&slot_of)[3] = joins.slot_of;
   for (int i = 0; i < 3; i++)
     for (slot_of[i] = 0; streams[slot_of[i]] != streams[i];) slot_of[i]++;
-  stp_joins &J = ctx->joins;
   const long now = ++J.now;
   bool same_streams = ctx->last_mbs == MB && ctx->last_b;
   for (int i = 0; i < 3; i++) same_streams = same_streams && ctx->step_stream[i] == streams[i];
+  auto wait_mark = [&](int i, int j, int which) -> int {
+    STP_HIP(ctx, hipStreamWaitEvent(streams[i], ctx->mark_ev[j][which], 0));
+    return STP_OK;
+  };
   rc = STP_OK;
-  long need[3][3] = {};        // [slot][other slot]: the step of the other that the slot has to come after
   if (!same_streams) {
     for (int i = 0; i < 3; i++)
       for (int j = 0; j < 3 && slot_of[i] == i; j++)
-        if (J.mark[j][1].step && ctx->step_stream[j] != streams[i] && rc == STP_OK && hipStreamWaitEvent(streams[i], ctx->mark_ev[j][1], 0) != hipSuccess)
-          rc = stp_fail(ctx, STP_EHIP, "stp_braid_step: hipStreamWaitEvent failed%s");
+        if (J.mark[j][1].step && ctx->step_stream[j] != streams[i] && rc == STP_OK) rc = wait_mark(i, j, 1);
     if (rc != STP_OK) { free(cur_b); return rc; }
     J.drop_marks();
     for (int i = 0; i < 3; i++) {
@@ -251,31 +247,9 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
       for (int k = 0; k < 3; k++) J.known[i][k] = now - 1;
     }
   } else {
-    auto after = [&](int i, int j, long step) {
-      long &n = need[slot_of[i]][slot_of[j]];
-      n = std::max(n, step);
-    };
-    for (int i = 0; i < 3; i++)
-      for (int j = 0; j < 3; j++) after(i, j, now - 2);
-    if (f_mb >= 0 && ctx->last_b[f_mb]) after(0, 1, now - 1);
-    if (f_mb >= 0 && ctx->last_w[f_mb]) after(0, 2, now - 1);
-    for (int m = 0; m < MB; m++) {
-      if (cur_b[m] && m == ctx->last_f_mb) after(1, 0, now - 1);
-      if (cur_b[m] && ctx->last_w[m]) after(1, 2, now - 1);
-      if (cur_w[m] && ctx->last_b[m]) after(2, 1, now - 1);
-      if (cur_w[m] && m == ctx->last_f_mb) after(2, 0, now - 1);
-    }
+    joins.needs(MB, {f_mb, cur_b, cur_w}, {ctx->last_f_mb, ctx->last_b, ctx->last_w});
+    rc = joins.begin(has[2], wait_mark);
   }
-  auto join = [&](int i) -> int {
-    return J.join(i, need[i], [&](int j, int which) -> int {
-      STP_HIP(ctx, hipStreamWaitEvent(streams[i], ctx->mark_ev[j][which], 0));
-      return STP_OK;
-    });
-  };
-  // the weight-gradient stream joins behind its first wait for a B unit of this step, which may stand for its other waits
-  bool w_joined = slot_of[2] != 2 || !has[2];
-  for (int i = 0; i < 3 && rc == STP_OK; i++)
-    if (slot_of[i] == i && (i < 2 || !has[2])) rc = join(i);
   if (rc != STP_OK) { free(cur_b); return rc; }
   int *ev_of = (int *)malloc(sizeof(int) * bsz);
   uint8_t *b_now = (uint8_t *)calloc(bsz, 1);      // B units issued by this step; committed to the context when the step is whole
@@ -308,14 +282,9 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
           if (r != STP_OK || !passed) return r;
         }
         STP_HIP(ctx, hipStreamWaitEvent(sW, ctx->ev_pool[ev], 0));
-        // the B stream has made this step's waits, so behind its event are the steps before and what those waits stand for
-        J.behind(slot_of[2], slot_of[1], now - 1, J.known[slot_of[1]]);
       }
-      if (!w_joined) {
-        const int r = join(2);
-        if (r != STP_OK) return r;
-        w_joined = true;
-      }
+      const int j = joins.before_w(ev >= 0, wait_mark);
+      if (j != STP_OK) return j;
       const bool tail = o.layer + 1 < L && st->chain_break && st->chain_break[o.layer + 1];
       const void *dx_out = tail ? st->tail_grad[(size_t)o.layer * MB + o.microbatch] : st->grad[(size_t)(o.layer + 1) * MB + o.microbatch];
       size_t off[STP_ST_NFIELDS];
@@ -437,26 +406,34 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
   return rc;
 }
 
-// The waits between steps, for tests on the host.  Per step: has[i] (slot i has work), last[3 i + j] (its work depends on the last
-// step's of slot j) and through (slot 2 first waits for a unit of slot 1 of this step).  waits[k]: step | i << 16 | j << 20 | mark's step << 24
-// (as 64-bit numbers); returns their number, or -1 if there are more than cap.
-extern "C" int stp_braid_plan_joins(int n_steps, const uint8_t *has, const uint8_t *last, const uint8_t *through, int64_t *waits, int cap) {
+// The waits between steps, for tests on the host (no part of the interface).  Per step: its forward microbatch, b / w[mbs s + m] (B / W work on
+// microbatch m) and through (1: its first W unit waits for a unit of slot_of[1] of this step, 2: a later one does, 0: none).  waits[k]:
+// step | i << 16 | j << 20 | mark's step << 24 (as 64-bit numbers), slot i waits for that mark of slot j; returns their number, or -1 if there are more than cap.
+extern "C" int stp_braid_plan_joins(int n_steps, int mbs, const int32_t *f_mb, const uint8_t *b, const uint8_t *w, const uint8_t *through,
+                                    const int32_t *slot_of, int64_t *waits, int cap) {
   stp_joins J;
   memset(&J, 0, sizeof(J));
+  const uint8_t none[64] = {};
+  if (mbs < 1 || mbs > 64) return -1;
+  stp_step_work last = {-1, none, none};
   int n = 0;
   for (int s = 0; s < n_steps; s++) {
     J.now++;
-    for (int i = 0; i < 3; i++) {
-      long need[3];
-      for (int j = 0; j < 3; j++) need[j] = J.now - (has[3 * s + i] && last[9 * s + 3 * i + j] ? 1 : 2);
-      if (i == 2 && through[s]) J.behind(2, 1, J.now - 1, J.known[1]);
-      J.join(i, need, [&](int j, int which) -> int {
-        if (n < cap) waits[n] = (int64_t)J.now | (int64_t)i << 16 | (int64_t)j << 20 | (int64_t)J.mark[j][which].step << 24;
-        n++;
-        return STP_OK;
-      });
-    }
-    for (int i = 0; i < 3; i++) J.make_mark(i);
+    const stp_step_work cur = {f_mb[s], b + mbs * s, w + mbs * s};
+    stp_step_joins joins = {J, {slot_of[0], slot_of[1], slot_of[2]}};
+    auto wait = [&](int i, int j, int which) -> int {
+      if (n < cap) waits[n] = (int64_t)J.now | (int64_t)i << 16 | (int64_t)j << 20 | (int64_t)J.mark[j][which].step << 24;
+      n++;
+      return STP_OK;
+    };
+    joins.needs(mbs, cur, last);
+    const bool has_w = memchr(cur.w, 1, mbs) != nullptr;
+    joins.begin(has_w, wait);
+    if (has_w) joins.before_w(through[s] == 1, wait);
+    if (has_w && through[s] == 2) joins.before_w(true, wait);
+    for (int i = 0; i < 3; i++)
+      if (slot_of[i] == i) J.make_mark(i);
+    last = cur;
   }
   return n <= cap ? n : -1;
 }

@@ -71,6 +71,61 @@ struct stp_joins {
   }
 };
 
+// What a step works on: its forward microbatch (-1: none) and, per microbatch, whether it holds B / W work.
+struct stp_step_work { int f_mb; const uint8_t *b, *w; };
+
+// The joins of one step with the steps before.  Data of a (layer, microbatch) is written by that microbatch's F units (forward
+// stream), read and extended by its B units (backward stream), read by its W units (weight-gradient stream);
+// gradient accumulators and workspace lanes belong to one stream each.  So, of the last step, a stream waits
+// only for   F: the B / W streams if they worked on the microbatch this step's F overwrites;
+//            B: the F stream if it produced one of this step's backward microbatches, the W stream if it read one;
+//            W: the B stream if it produced what this step's W units read (and the F stream likewise).
+// All streams are ordered behind the whole of the step before last, which bounds the skew to one block; those without
+// work in this step too, since a caller may rely on it for work of its own there.
+struct stp_step_joins {
+  stp_joins &J;
+  int slot_of[3];            // slots of the forward, backward and weight-gradient streams
+  long need[3][3] = {};      // [slot][other slot]: the step of the other that the slot has to come after; 0: none
+  bool w_joined = true;
+
+  void needs(int mbs, const stp_step_work &cur, const stp_step_work &last) {
+    const long now = J.now;
+    auto after = [&](int i, int j, long step) {
+      long &n = need[slot_of[i]][slot_of[j]];
+      if (step > n) n = step;
+    };
+    for (int i = 0; i < 3; i++)
+      for (int j = 0; j < 3; j++) after(i, j, now - 2);
+    if (cur.f_mb >= 0 && last.b[cur.f_mb]) after(0, 1, now - 1);
+    if (cur.f_mb >= 0 && last.w[cur.f_mb]) after(0, 2, now - 1);
+    for (int m = 0; m < mbs; m++) {
+      if (cur.b[m] && m == last.f_mb) after(1, 0, now - 1);
+      if (cur.b[m] && last.w[m]) after(1, 2, now - 1);
+      if (cur.w[m] && last.b[m]) after(2, 1, now - 1);
+      if (cur.w[m] && m == last.f_mb) after(2, 0, now - 1);
+    }
+  }
+  // the waits at the start of the step: wait(i, j, which mark), slot i for slot j.  A weight-gradient stream of its own that has work
+  // joins behind its first wait for a B unit of this step, which may stand for its other waits.
+  template <typename F> int begin(bool has_w, F wait) {
+    w_joined = slot_of[2] != 2 || !has_w;
+    for (int i = 0; i < 3; i++) {
+      if (slot_of[i] != i || (i == 2 && has_w)) continue;
+      const int rc = J.join(i, need[i], [&](int j, int which) { return wait(i, j, which); });
+      if (rc != STP_OK) return rc;
+    }
+    return STP_OK;
+  }
+  // before a W unit is enqueued, behind the wait for its B unit if that is one of this step on another stream
+  template <typename F> int before_w(bool behind_b, F wait) {
+    // the B stream has made this step's waits, so behind its event are the steps before and what those waits stand for
+    if (behind_b) J.behind(slot_of[2], slot_of[1], J.now - 1, J.known[slot_of[1]]);
+    if (w_joined) return STP_OK;
+    w_joined = true;
+    return J.join(2, need[2], [&](int j, int which) { return wait(2, j, which); });
+  }
+};
+
 #define STP_TILE_HINTS 96
 struct stp_ctx {
   int device;

@@ -471,3 +471,32 @@ def test_steps_run_while_another_stream_is_being_captured(ctx, mode):
         graph.replay()
         torch.cuda.synchronize()
         assert bool((x == value).all())
+
+
+@pytest.mark.parametrize("name", ["gpt_bf16_x2", "llama_bf16_x1"])
+def test_streams_shared_by_two_kinds_of_work_give_the_serialized_bits(ctx, name):
+    """Two streams for the three kinds of work, each way; the stage's sequence, the same block again and again, and another choice at every step."""
+    layers, n_mb = STAGES[name]
+    L = len(layers)
+    stg = StageOnDevice(ctx, layers, n_mb, seed=9)
+    stg.load_inputs()
+    s0, a, b = torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()
+    block = braid(forward_ops(L, n_mb - 1), backward_ops(L, 0, OP_BW))
+
+    def run(choices, steps, first=()):
+        ctx.braid_reset()
+        stg.zero_grads()
+        for step in first:
+            ctx.braid_step(stg.stage, step, s0, s0, s0)
+        torch.cuda.synchronize()
+        for i, step in enumerate(steps):
+            ctx.braid_step(stg.stage, step, *choices[i % len(choices)])
+        torch.cuda.synchronize()
+        return snapshot(stg) + [m.clone() for m in stg.stash_mem]
+
+    triples = [(a, a, b), (a, b, a), (a, b, b)]
+    for steps, first in ((stage_sequence(L, n_mb), ()), ([block] * 8, (forward_ops(L, 0),))):
+        serial = run([(s0, s0, s0)], steps, first)
+        for choices in [[t] for t in triples] + [triples, [(b, a, b), (a, a, a), (a, b, a)]]:
+            for u, v in zip(serial, run(choices, steps, first)):
+                assert torch.equal(u, v), f"{name}: {[[a, b].index(s) for t in choices for s in t]} differs from the serialized order"
