@@ -25,6 +25,8 @@ LAYERS = {
     "bidirectional_d64": Workload("v", 1024, 16, 64, 4096, 1024, 1, causal=False, has_bias=True),
     # several chunks in all three attention kernels, grouped heads, tokens no multiple of a tile
     "grouped_d128": Workload("g", 1032, 8, 128, 2064, 1104, 4, norm="rms", act="swiglu", rope=True, has_bias=False, kv_heads=2),
+    # the same with rotated heads of dimension 64: every tile of the QKV product's rotating kernel, contractions that end inside a K-tile
+    "rotated_d64": Workload("r", 1032, 16, 64, 2064, 1104, 4, norm="rms", act="swiglu", rope=True, has_bias=False, kv_heads=4),
     # many key blocks of one long group
     "one_kv_head": Workload("k", 520, 5, 128, 1096, 3072, 8, norm="rms", act="swiglu", rope=True, has_bias=False, kv_heads=1),
 }
@@ -34,7 +36,7 @@ LAYERS = {
 def test_braided_and_hinted_equal_serialized_bitwise(ctx, name):
     wl = LAYERS[name]
     shapes = list(tune.layer_gemm_shapes(wl).values())
-    if name == "grouped_d128":      # every product takes a tile, so the hints below apply to all twelve
+    if name in ("grouped_d128", "rotated_d64"):      # every product takes a tile, so the hints below apply to all twelve
         assert all(-(-M // 64) * -(-N // 64) > 256 for M, N, *_ in shapes)
     stg = StageOnDevice(ctx, [wl], 3, seed=5, tuned_tiles=False)
     stg.load_inputs()

@@ -43,7 +43,8 @@ def rotate(x, seq, d, rot_heads, sign):
 
 
 # heads, kv heads, head dimension, sequence, sequences, hidden: the contraction-splitting kernel's shapes (rotated by a kernel of their own),
-# sequences shorter than a strip, positions that start again inside one, half-empty tiles, every tile of the product, long positions
+# sequences shorter than a strip, positions that start again inside one, half-empty tiles, long positions.  (The tiles that the rule picks here
+# are 128 x 128, 128 x 256 and 256 x 256; the bitwise test of hinted blocks runs the others.)
 @pytest.mark.parametrize("n,nk,d,seq,mbsz,hidden", [(2, 1, 128, 264, 1, 640), (6, 2, 64, 1000, 3, 1032), (9, 3, 64, 24, 170, 520), (5, 1, 128, 1096, 1, 264),
                                                     (10, 10, 128, 4096, 1, 5120), (14, 2, 128, 2056, 1, 128), (16, 16, 64, 520, 8, 1024),
                                                     (4, 4, 128, 8, 300, 72), (3, 3, 64, 6144, 1, 2048), (1, 1, 64, 5000, 1, 512)])
