@@ -787,7 +787,7 @@ static double four_wave_bwd_us(const PlanPart *p) {
 // That bound is blind to a last round of few workgroups: of 691 shapes it would give to four waves (128 .. 8192 tokens, 2 .. 32 heads) they were slower
 // than eight at 51, by up to 18 %, equal long blocks above all (6 heads, 6144 tokens, no mask 250 / 296; 10 heads, 4096 tokens 180 / 202; 6 x 8 heads on 4, 1024
 // tokens 60 / 69).  So the launch is simulated too: longest first, each workgroup to the compute unit that has room first, two of a unit sharing
-// its time.  With costs fitted for this choice none is more than 1.7 % slower, 561 stay, and on average they are where the bound alone had them.
+// its time.  With costs fitted for this choice none is more than 1.7 % slower, 567 stay, and on average they are where the bound alone had them.
 static double four_wave_bwd_end(const PlanPart *p) {
   const double fixed = 2.2, step[2] = {1.15, 2.0}, fixed1 = 4.8, step1[2] = {1.5, 2.45};
   double sum = 0.0, longest = 0.0;
@@ -796,19 +796,25 @@ static double four_wave_bwd_end(const PlanPart *p) {
     longest = std::max(longest, fixed + step[i] * p[i].max_steps);
   }
   if (sum / PLAN_CUS > 16.0 * longest) return sum / PLAN_CUS;      // the last round is a small part of the whole (and this bounds the planning time)
-  struct Work { double paired, alone; };
+  struct Work { double paired, alone; int count; };
   std::vector<Work> items;
+  const int share = (p[0].z | p[1].z | PLAN_CUS) & -(p[0].z | p[1].z | PLAN_CUS);      // equal parts of the chip that get equal shares of each kind: one is simulated
+  const int cus = PLAN_CUS / share;
   for (int i = 0; i < 2; i++)
-    for (int x = 0; x < p[i].nblocks; x++)
-      for (int z = 0; z < p[i].z; z++) items.push_back({fixed + step[i] * p[i].steps[x], fixed1 + step1[i] * p[i].steps[x]});
+    for (int x = 0; x < p[i].nblocks; x++) items.push_back({fixed + step[i] * p[i].steps[x], fixed1 + step1[i] * p[i].steps[x], p[i].z / share});
   std::sort(items.begin(), items.end(), [](const Work &u, const Work &v) { return u.paired > v.paired; });
   // two workgroups of a unit share its time, one alone goes at its own rate
   struct Unit { Work w[2]; double left[2], at; int n; };
-  std::vector<Unit> cu(PLAN_CUS, Unit{{}, {}, 0.0, 0});
+  std::vector<Unit> cu(cus, Unit{{}, {}, 0.0, 0});
   size_t next = 0;
+  auto start = [&](Unit &u) {
+    u.w[u.n] = items[next];
+    u.left[u.n++] = 1.0;
+    if (--items[next].count == 0) next++;
+  };
   for (int r = 0; r < 2; r++)
     for (Unit &u : cu)
-      if (next < items.size()) { u.w[u.n] = items[next++]; u.left[u.n++] = 1.0; }
+      if (next < items.size()) start(u);
   auto rate = [](const Unit &u, int k) { return u.n == 1 ? 1.0 / u.w[k].alone : 0.5 / u.w[k].paired; };
   std::priority_queue<std::pair<double, int>, std::vector<std::pair<double, int>>, std::greater<std::pair<double, int>>> events;
   auto schedule = [&](int c) {
@@ -818,7 +824,7 @@ static double four_wave_bwd_end(const PlanPart *p) {
     if (u.n == 2) first = std::min(first, u.left[1] / rate(u, 1));
     events.push({u.at + first, c});
   };
-  for (int c = 0; c < PLAN_CUS; c++) schedule(c);
+  for (int c = 0; c < cus; c++) schedule(c);
   double end = 0.0;
   while (!events.empty()) {
     const int c = events.top().second;
@@ -832,7 +838,8 @@ static double four_wave_bwd_end(const PlanPart *p) {
       const double left = u.left[k] - dt * r[k];
       if (left > 1e-9) { u.w[kept] = u.w[k]; u.left[kept++] = left; }
     }
-    for (u.n = kept; u.n < 2 && next < items.size(); u.n++) { u.w[u.n] = items[next++]; u.left[u.n] = 1.0; }
+    u.n = kept;
+    while (u.n < 2 && next < items.size()) start(u);
     schedule(c);
   }
   return end;
