@@ -248,7 +248,7 @@ extern "C" int stp_braid_step(stp_ctx *ctx, const stp_stage *st, const stp_op *o
     }
   } else {
     joins.needs(MB, {f_mb, cur_b, cur_w}, {ctx->last_f_mb, ctx->last_b, ctx->last_w});
-    rc = joins.begin(has[2], wait_mark);
+    rc = joins.begin(has, wait_mark);
   }
   if (rc != STP_OK) { free(cur_b); return rc; }
   int *ev_of = (int *)malloc(sizeof(int) * bsz);
@@ -427,10 +427,10 @@ extern "C" int stp_braid_plan_joins(int n_steps, int mbs, const int32_t *f_mb, c
       return STP_OK;
     };
     joins.needs(mbs, cur, last);
-    const bool has_w = memchr(cur.w, 1, mbs) != nullptr;
-    joins.begin(has_w, wait);
-    if (has_w) joins.before_w(through[s] == 1, wait);
-    if (has_w && through[s] == 2) joins.before_w(true, wait);
+    const bool has[3] = {f_mb[s] >= 0, memchr(cur.b, 1, mbs) != nullptr, memchr(cur.w, 1, mbs) != nullptr};
+    joins.begin(has, wait);
+    if (has[2]) joins.before_w(through[s] == 1, wait);
+    if (has[2] && through[s] == 2) joins.before_w(true, wait);
     for (int i = 0; i < 3; i++)
       if (slot_of[i] == i) J.make_mark(i);
     last = cur;

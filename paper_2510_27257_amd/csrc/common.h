@@ -42,13 +42,13 @@ struct stp_joins {
   long known[3][3];                                    // [slot][other slot]: the other's last step that the slot's stream is ordered behind
   long now;                                            // number of the step
   // the waits of slot i where it has to come after step need[j] of slot j: wait(j, which mark); the later ones
-  // first, since they may stand for the earlier ones
-  template <typename F> int join(int i, const long need[3], F wait) {
+  // first, since they may stand for the earlier ones.  latest: where a wait is needed at all, for the other's latest mark.
+  template <typename F> int join(int i, const long need[3], bool latest, F wait) {
     for (long back = 1; back <= 2; back++)
       for (int j = 0; j < 3; j++) {
         const long step = need[j] < mark[j][1].step ? need[j] : mark[j][1].step;
         if (j == i || need[j] != now - back || known[i][j] >= step) continue;
-        const int which = mark[j][0].step >= step ? 0 : 1;
+        const int which = !latest && mark[j][0].step >= step ? 0 : 1;
         const int rc = wait(j, which);
         if (rc != STP_OK) return rc;
         behind(i, j, mark[j][which].step, mark[j][which].known);
@@ -106,12 +106,16 @@ struct stp_step_joins {
     }
   }
   // the waits at the start of the step: wait(i, j, which mark), slot i for slot j.  A weight-gradient stream of its own that has work
-  // joins behind its first wait for a B unit of this step, which may stand for its other waits.
-  template <typename F> int begin(bool has_w, F wait) {
-    w_joined = slot_of[2] != 2 || !has_w;
+  // joins behind its first wait for a B unit of this step, which may stand for its other waits.  A slot without work waits for
+  // the last step's marks: its work in the next step has to come after those in any case and then finds the wait made (with waits for the
+  // marks before them, of no use later, the fp32 layer of 128 tokens took 351 us a pass, two ViT layers 1749; so 337 and 1726).
+  template <typename F> int begin(const bool has[3], F wait) {
+    bool busy[3] = {};
+    for (int i = 0; i < 3; i++) busy[slot_of[i]] = busy[slot_of[i]] || has[i];
+    w_joined = slot_of[2] != 2 || !has[2];
     for (int i = 0; i < 3; i++) {
-      if (slot_of[i] != i || (i == 2 && has_w)) continue;
-      const int rc = J.join(i, need[i], [&](int j, int which) { return wait(i, j, which); });
+      if (slot_of[i] != i || !(w_joined || i < 2)) continue;
+      const int rc = J.join(i, need[i], !busy[i], [&](int j, int which) { return wait(i, j, which); });
       if (rc != STP_OK) return rc;
     }
     return STP_OK;
@@ -122,7 +126,7 @@ struct stp_step_joins {
     if (behind_b) J.behind(slot_of[2], slot_of[1], J.now - 1, J.known[slot_of[1]]);
     if (w_joined) return STP_OK;
     w_joined = true;
-    return J.join(2, need[2], [&](int j, int which) { return wait(2, j, which); });
+    return J.join(2, need[2], false, [&](int j, int which) { return wait(2, j, which); });
   }
 };
 
