@@ -107,8 +107,9 @@ struct stp_step_joins {
   }
   // the waits at the start of the step: wait(i, j, which mark), slot i for slot j.  A weight-gradient stream of its own that has work
   // joins behind its first wait for a B unit of this step, which may stand for its other waits.  A slot without work waits for
-  // the last step's marks: its work in the next step has to come after those in any case and then finds the wait made (with waits for the
-  // marks before them, of no use later, the fp32 layer of 128 tokens took 351 us a pass, two ViT layers 1749; so 337 and 1726).
+  // the last step's marks: its work in the next step has to come after those in any case and then finds the wait made (two ViT layers 1726 us
+  // a pass, 1749 with waits for the marks before them; the fp32 layer of 128 tokens, which the host bounds, about 350 either way, 335 where
+  // streams without work make no waits).
   template <typename F> int begin(const bool has[3], F wait) {
     bool busy[3] = {};
     for (int i = 0; i < 3; i++) busy[slot_of[i]] = busy[slot_of[i]] || has[i];
