@@ -113,7 +113,7 @@ template <> struct Raw8<bf16_t> {
 };
 
 // TPR threads a row: 256, or 512 where four chunks a thread would need more than half of a SIMD's registers, which leaves one wave on it
-// (h > 6144: [4096, 7168] 64.4 -> 48.4 us, with LayerNorm's and the residual's sums 74.5 -> 57.0).
+// (h > 6144: [4096, 7168] 64.4 -> 48.4 us, with LayerNorm's and the residual's sums 74.5 -> 57.0; 84 shapes of 8 .. 4096 rows, both types, 0.75 - 1.02 of the time).
 template <typename T, int NORM, int NCH, bool RSUM, int TPR>
 __global__ __launch_bounds__(TPR) void norm_bwd_kernel(const T *__restrict__ x, const T *__restrict__ gamma,
                                                        const float *__restrict__ stats, const T *__restrict__ dy,

@@ -8,7 +8,8 @@ int stp_launch_gemm_bf16_mn(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s)
 
 // The weight gradients of a unit in one launch where the chip is theirs alone: 13B shard, three products of 3456 x 5120 over
 // 4096 tokens and two smaller ones, 85 us of a pass of 2400.  Beside other streams, which fill what a launch's last round leaves idle, one long launch is the
-// worse one (blocks 0.3 - 5 % slower).
+// worse one (blocks 0.3 - 5 % slower).  Outputs of the contraction-splitting kernel go together there too: blocks of 36 layers of hidden 128 - 1100 take 4 %
+// longer (median) with a launch each.
 int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s) {
   TileChoice c;
   if (wavek_set(a, n)) return a[0].K % 32 ? launch_wavek_set<true>(ctx, a, n, s) : launch_wavek_set<false>(ctx, a, n, s);
