@@ -14,7 +14,7 @@
 // What bounds it: latency.  At 128 tokens and 4 heads of 64 there are 16 workgroups, and a wave works through one or
 // two 32 x 32 blocks (32 + 32 matrix instructions of 64 clocks each in the forward).  One wave per row with a
 // cross-lane reduction per score was a chain of 128 such reductions: forward / dQ / dK dV 91 / 56 / 46 us against
-// 14 / 11 / 15 us now, the training pass of two microbatches over that layer 554 against 401 us.
+// 14 / 11 / 15 us.  So few workgroups take row dot, dQ and dK / dV in one launch: 27.0 -> 14.3 us (see one_launch).
 #include "attn_f32_rows.h"
 #include <type_traits>
 
@@ -188,16 +188,33 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float *__re
   if (wave == 0 && lg == 0 && qg < seq) lse[((size_t)b * n + head) * seq + qg] = M + logf(L);
 }
 
-template <int DB, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
-                                                                  const float *__restrict__ dout, const float *__restrict__ delta,
-                                                                  float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
-                                                                  float scale) {
-  extern __shared__ __attribute__((aligned(16))) float red[];
+// delta = rowsum(dO o O) of a row from the half of its columns that a lane holds as chunks, in the order of the row dot kernels:
+// 8 columns one after the other, then pairwise.  (Columns past d are zero and add nothing.)
+template <int DB>
+__device__ __forceinline__ float row_delta(const float (&gf)[2 * DB][8], const float *__restrict__ orow, int lg, int d) {
+  float t[2 * DB];
+#pragma unroll
+  for (int c = 0; c < 2 * DB; c++) {
+    float of[8], s = 0.f;
+    row_chunk(of, orow, c, lg, d);
+#pragma unroll
+    for (int e = 0; e < 8; e++) s += gf[c][e] * of[e];
+    t[c] = s + other_half(s);
+  }
+#pragma unroll
+  for (int h = 1; h < 2 * DB; h *= 2)
+#pragma unroll
+    for (int c = 0; c < 2 * DB; c += 2 * h) t[c] += t[c + h];
+  return t[0];
+}
+
+// FROM_OUT: delta is formed from the attention output `out`, and not read
+template <int DB, int NW, bool FROM_OUT>
+__device__ __forceinline__ void attn_bwd_dq_f32_block(Work w, const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                      const float *__restrict__ dout, const float *__restrict__ out, const float *__restrict__ delta,
+                                                      float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal, float scale, float *red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
   const int nblk = (seq + RB - 1) / RB;
-  const Work w = work_of(nblk);
-  if (w.pair >= pairs) return;
   const int q0 = (nblk - 1 - w.block) * RB;
   const int head = w.pair % n, b = w.pair / n;
   const int a = n * d;
@@ -206,10 +223,11 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *_
   const float *kp = base + a + (head / (n / nk)) * d, *vp = kp + nk * d;
   const int qg = q0 + lr, qc = min(qg, seq - 1);
   const float *qrow = base + (size_t)qc * ld + head * d, *grow = dout + ((size_t)b * seq + qc) * a + head * d;
-  const float L = lse[((size_t)b * n + head) * seq + qc], D = delta[((size_t)b * n + head) * seq + qc];
+  const float L = lse[((size_t)b * n + head) * seq + qc];
   float qf[2 * DB][8], gf[2 * DB][8];
 #pragma unroll
   for (int c = 0; c < 2 * DB; c++) { row_chunk(qf[c], qrow, c, lg, d); row_chunk(gf[c], grow, c, lg, d); }
+  const float D = FROM_OUT ? row_delta<DB>(gf, out + ((size_t)b * seq + qc) * a + head * d, lg, d) : delta[((size_t)b * n + head) * seq + qc];
   f32x16_t dq[DB];
 #pragma unroll
   for (int i = 0; i < DB; i++) zero(dq[i]);
@@ -238,19 +256,16 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *_
                            [&](int r, int col, float4 s) {
                              if (q0 + r < seq) *reinterpret_cast<float4 *>(dqkv + ((size_t)b * seq + q0 + r) * ld + head * d + col) = s;
                            }))
-    for (int i = q0 + wave; i < min(q0 + RB, seq); i += NW) attn_bwd_dq_row(qkv, lse, dout, delta, dqkv, b, head, i, seq, n, nk, d, causal, scale);
+    for (int i = q0 + wave; i < min(q0 + RB, seq); i += NW)
+      attn_bwd_dq_row(qkv, lse, dout, FROM_OUT ? out : nullptr, delta, dqkv, b, head, i, seq, n, nk, d, causal, scale);
 }
 
 // sums over the query heads of the key / value head's group
-template <int DB, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
-                                                                   const float *__restrict__ dout, const float *__restrict__ delta,
-                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
-                                                                   float scale) {
-  extern __shared__ __attribute__((aligned(16))) float red[];
+template <int DB, int NW, bool FROM_OUT>
+__device__ __forceinline__ void attn_bwd_dkv_f32_block(Work w, const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                       const float *__restrict__ dout, const float *__restrict__ out, const float *__restrict__ delta,
+                                                       float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal, float scale, float *red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
-  const Work w = work_of((seq + RB - 1) / RB);
-  if (w.pair >= pairs) return;
   const int k0 = w.block * RB;                               // the early blocks, which most queries see, first
   const int kh = w.pair % nk, b = w.pair / nk;
   const int a = n * d, group = n / nk;
@@ -270,6 +285,14 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
     const float *qp = base + head * d, *gp = dout + (size_t)b * seq * a + head * d;
     const size_t row = min(q0 + lr, seq - 1);
     const float *Lr = lse + ((size_t)b * n + head) * seq, *Dr = delta + ((size_t)b * n + head) * seq;
+    float Lrow = 0.f, Drow = 0.f;                            // FROM_OUT: of this lane's query
+    if constexpr (FROM_OUT) {
+      float gf[2 * DB][8];
+#pragma unroll
+      for (int c = 0; c < 2 * DB; c++) row_chunk(gf[c], gp + row * a, c, lg, d);
+      Lrow = Lr[row];
+      Drow = row_delta<DB>(gf, out + ((size_t)b * seq + row) * a + head * d, lg, d);
+    }
     f32x16_t p, ds;
     zero(p);
     zero(ds);
@@ -284,9 +307,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int i = q0 + acc_row(v, lg), ic = min(i, seq - 1);
+      const float Li = FROM_OUT ? __shfl(Lrow, acc_row(v, lg)) : Lr[ic], Di = FROM_OUT ? __shfl(Drow, acc_row(v, lg)) : Dr[ic];
       const bool masked = i >= seq || (causal && key > i);
-      const float e = masked ? 0.f : expf(p[v] * scale - Lr[ic]);
-      ds[v] = masked ? 0.f : e * (ds[v] - Dr[ic]) * scale;
+      const float e = masked ? 0.f : expf(p[v] * scale - Li);
+      ds[v] = masked ? 0.f : e * (ds[v] - Di) * scale;
       p[v] = e;
     }
     add_rows<DB>(dv, gp, a, q0, seq - 1, p, lr, lg, d);
@@ -295,12 +319,48 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
   float *dkp = dqkv + (size_t)b * seq * ld + a + kh * d, *dvp = dkp + nk * d;
   if (!merge_waves<DB, NW>(dk, zero_or_nan(dk) + zero_or_nan(dv), red, wave, lane, d, [](int) { return 1.0f; },
                            [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dkp + (size_t)(k0 + r) * ld + col) = s; })) {
-    for (int j = k0 + wave; j < min(k0 + RB, seq); j += NW) attn_bwd_dkv_row(qkv, lse, dout, delta, dqkv, b, kh, j, seq, n, nk, d, causal, scale);
+    for (int j = k0 + wave; j < min(k0 + RB, seq); j += NW)
+      attn_bwd_dkv_row(qkv, lse, dout, FROM_OUT ? out : nullptr, delta, dqkv, b, kh, j, seq, n, nk, d, causal, scale);
     return;
   }
   __syncthreads();
   merge_waves<DB, NW>(dv, 0.f, red, wave, lane, d, [](int) { return 1.0f; },
                       [&](int r, int col, float4 s) { if (k0 + r < seq) *reinterpret_cast<float4 *>(dvp + (size_t)(k0 + r) * ld + col) = s; });
+}
+
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                                  const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                  float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
+                                                                  float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];
+  const Work w = work_of((seq + RB - 1) / RB);
+  if (w.pair < pairs) attn_bwd_dq_f32_block<DB, NW, false>(w, qkv, lse, dout, nullptr, delta, dqkv, seq, n, nk, d, causal, scale, red);
+}
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                                   const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
+                                                                   float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];
+  const Work w = work_of((seq + RB - 1) / RB);
+  if (w.pair < pairs) attn_bwd_dkv_f32_block<DB, NW, false>(w, qkv, lse, dout, nullptr, delta, dqkv, seq, n, nk, d, causal, scale, red);
+}
+// Row dot, dK / dV and dQ in one launch, for so few workgroups that they are all resident at once: see one_launch.
+// nblk * pairs_kv workgroups for dK / dV, then nblk * pairs for dQ.
+template <int DB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
+                                                               const float *__restrict__ dout, const float *__restrict__ out,
+                                                               float *__restrict__ dqkv, int seq, int n, int nk, int pairs_kv, int d, int causal,
+                                                               float scale) {
+  extern __shared__ __attribute__((aligned(16))) float red[];
+  const int nblk = (seq + RB - 1) / RB, first_dq = nblk * pairs_kv, id = blockIdx.x;
+  if (id < first_dq) {
+    attn_bwd_dkv_f32_block<DB, NW, true>({id % nblk, id / nblk}, qkv, lse, dout, out, nullptr, dqkv, seq, n, nk, d, causal, scale, red);
+  } else {
+    const int i = id - first_dq;
+    attn_bwd_dq_f32_block<DB, NW, true>({i % nblk, i / nblk}, qkv, lse, dout, out, nullptr, dqkv, seq, n, nk, d, causal, scale, red);
+  }
 }
 
 // The same for sequences of a few rows, a wave per row: a block of 32 would be mostly empty.
@@ -316,7 +376,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_rows_kernel(const float *__re
                                                                float scale) {
   const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
   if (w >= (size_t)mbsz * n * seq) return;
-  attn_bwd_dq_row(qkv, lse, dout, delta, dqkv, w / ((size_t)seq * n), (w / seq) % n, w % seq, seq, n, nk, d, causal, scale);
+  attn_bwd_dq_row(qkv, lse, dout, nullptr, delta, dqkv, w / ((size_t)seq * n), (w / seq) % n, w % seq, seq, n, nk, d, causal, scale);
 }
 __global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
                                                                 const float *__restrict__ dout, const float *__restrict__ delta,
@@ -324,7 +384,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(const float *__r
                                                                 float scale) {
   const size_t w = blockIdx.x * (size_t)4 + (threadIdx.x >> 6);
   if (w >= (size_t)mbsz * nk * seq) return;
-  attn_bwd_dkv_row(qkv, lse, dout, delta, dqkv, w / ((size_t)seq * nk), (w / seq) % nk, w % seq, seq, n, nk, d, causal, scale);
+  attn_bwd_dkv_row(qkv, lse, dout, nullptr, delta, dqkv, w / ((size_t)seq * nk), (w / seq) % nk, w % seq, seq, n, nk, d, causal, scale);
 }
 
 // Waves per workgroup: 8 (4 at head dimensions above 64, whose merge area is twice as large), 1 or 2 where there are only so many
@@ -404,6 +464,31 @@ int launch_dkv(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse,
   });
 }
 
+// Up to 256 workgroups in all, one for a compute unit, the backward pass is a chain of latencies, and one launch has one of them where
+// row dot, dQ and dK / dV have three: 4 heads of 64, 128 rows 27.0 -> 14.3 us; 4 heads of 32 on 2, 200 rows 37.0 -> 23.9; 8 heads of 128,
+// 256 rows 97.8 -> 52.4.  More of them fill the chip with either body, and delta formed once more by every key block would cost what the
+// launch saves.  The bits are the same either way.
+bool one_launch(const Shape &h) {
+  auto waves = [](long blocks) { return blocks <= 2 ? blocks : 3; };       // as with_waves groups them
+  return !short_rows(h, 1) && !short_rows(h, 2) && h.nblk * (h.pairs + h.pairs_kv) <= 256 && waves(h.nblk) == waves((long)h.nblk * (h.n / h.nk));
+}
+template <int DB>
+int launch_bwd(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *out, float *dqkv, hipStream_t s) {
+  return with_waves<DB>(h.nblk, [&](auto nw) -> int {
+    constexpr int NW = decltype(nw)::value;
+    auto kern = attn_bwd_f32_kernel<DB, NW>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<NW, DB>));
+      attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(h.nblk * (h.pairs + h.pairs_kv))), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, lse, dout, out, dqkv, h.seq,
+                       h.n, h.nk, (int)h.pairs_kv, h.d, h.causal, h.scale);
+    STP_LAUNCH_CHECK(ctx);
+    return STP_OK;
+  });
+}
+
 Shape shape_of(const stp_layer_desc *d) {
   const int nk = stp_kv_heads(d);
   return {d->seq, d->mbsz, d->heads_local, nk, d->head_dim, d->causal, (d->seq + RB - 1) / RB, (size_t)d->heads_local * d->mbsz, (size_t)nk * d->mbsz,
@@ -426,11 +511,16 @@ int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *q
 
 int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const void *out, const float *lse, const void *dout,
                             float *delta, void *dqkv, hipStream_t s) {
-  int rc = stp_launch_rowdot(ctx, d, dout, out, delta, s);
-  if (rc != STP_OK) return rc;
   const float *x = (const float *)qkv, *g = (const float *)dout;
   float *dx = (float *)dqkv;
   const Shape h = shape_of(d);
+  if (one_launch(h)) {
+    const float *o = (const float *)out;
+    return h.d <= 32 ? launch_bwd<1>(ctx, h, x, lse, g, o, dx, s) : h.d <= 64 ? launch_bwd<2>(ctx, h, x, lse, g, o, dx, s)
+                                                                            : launch_bwd<4>(ctx, h, x, lse, g, o, dx, s);
+  }
+  int rc = stp_launch_rowdot(ctx, d, dout, out, delta, s);
+  if (rc != STP_OK) return rc;
   if (short_rows(h, 1)) {
     hipLaunchKernelGGL(attn_bwd_dq_rows_kernel, dim3((h.pairs * h.seq + 3) / 4), dim3(256), 0, s, x, lse, g, delta, dx, h.seq, h.mbsz, h.n, h.nk, h.d,
                        h.causal, h.scale);

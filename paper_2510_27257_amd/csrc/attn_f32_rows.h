@@ -6,6 +6,20 @@
 #pragma once
 #include "common.h"
 
+// delta = rowsum(dO o O) of a row, as the row dot kernels form it
+__device__ __forceinline__ float row_dot_out(const float *__restrict__ g, const float *__restrict__ o, int d) {
+  const int col = (threadIdx.x & 63) * 8;
+  float s = 0.f;
+  if (col < d) {
+    float u[8], v[8];
+    Vec8<float>::load(g + col, u);
+    Vec8<float>::load(o + col, v);
+#pragma unroll
+    for (int i = 0; i < 8; i++) s += u[i] * v[i];
+  }
+  return wave_sum(s);
+}
+
 // query row i of head `head` of sequence b
 __device__ __forceinline__ void attn_fwd_row(const float *__restrict__ qkv, float *__restrict__ out, float *__restrict__ lse, int b, int head,
                                              int i, int seq, int n, int nk, int d, int causal, float scale) {
@@ -36,9 +50,10 @@ __device__ __forceinline__ void attn_fwd_row(const float *__restrict__ qkv, floa
   if (lane == 0) lse[((size_t)b * n + head) * seq + i] = m + logf(l);
 }
 
+// delta from the output `out`, or, without it, from memory
 __device__ __forceinline__ void attn_bwd_dq_row(const float *__restrict__ qkv, const float *__restrict__ lse, const float *__restrict__ dout,
-                                                const float *__restrict__ delta, float *__restrict__ dqkv, int b, int head, int i, int seq,
-                                                int n, int nk, int d, int causal, float scale) {
+                                                const float *__restrict__ out, const float *__restrict__ delta, float *__restrict__ dqkv, int b,
+                                                int head, int i, int seq, int n, int nk, int d, int causal, float scale) {
   const int lane = threadIdx.x & 63;
   const int a = n * d, ak = nk * d;
   const size_t ld = (size_t)a + 2 * ak;
@@ -48,7 +63,8 @@ __device__ __forceinline__ void attn_bwd_dq_row(const float *__restrict__ qkv, c
   const float *dop = dout + ((size_t)b * seq + i) * a + head * d;
   float q0 = h0 ? qp[lane] : 0.f, q1 = h1 ? qp[lane + 64] : 0.f;
   float g0 = h0 ? dop[lane] : 0.f, g1 = h1 ? dop[lane + 64] : 0.f;
-  const float L = lse[((size_t)b * n + head) * seq + i], D = delta[((size_t)b * n + head) * seq + i];
+  const float L = lse[((size_t)b * n + head) * seq + i];
+  const float D = out ? row_dot_out(dop, out + ((size_t)b * seq + i) * a + head * d, d) : delta[((size_t)b * n + head) * seq + i];
   const int jend = causal ? i + 1 : seq;
   float dq0 = 0.f, dq1 = 0.f;
   for (int j = 0; j < jend; j++) {
@@ -69,8 +85,8 @@ __device__ __forceinline__ void attn_bwd_dq_row(const float *__restrict__ qkv, c
 
 // key row j of key / value head kh; sums over the query heads of its group in a fixed order
 __device__ __forceinline__ void attn_bwd_dkv_row(const float *__restrict__ qkv, const float *__restrict__ lse, const float *__restrict__ dout,
-                                                 const float *__restrict__ delta, float *__restrict__ dqkv, int b, int kh, int j, int seq,
-                                                 int n, int nk, int d, int causal, float scale) {
+                                                 const float *__restrict__ out, const float *__restrict__ delta, float *__restrict__ dqkv, int b,
+                                                 int kh, int j, int seq, int n, int nk, int d, int causal, float scale) {
   const int lane = threadIdx.x & 63;
   const int a = n * d, ak = nk * d, group = n / nk;
   const size_t ld = (size_t)a + 2 * ak;
@@ -91,8 +107,9 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const float *__restrict__ qkv, 
       float g0 = h0 ? dop[lane] : 0.f, g1 = h1 ? dop[lane + 64] : 0.f;
       float sc = wave_sum(q0 * k0 + q1 * k1) * scale;
       float dp = wave_sum(g0 * v0 + g1 * v1);
+      const float D = out ? row_dot_out(dop, out + ((size_t)b * seq + i) * a + head * d, d) : Dr[i];
       float p = expf(sc - Lr[i]);
-      float ds = p * (dp - Dr[i]) * scale;
+      float ds = p * (dp - D) * scale;
       dv0 += p * g0; dv1 += p * g1;
       dk0 += ds * q0; dk1 += ds * q1;
     }

@@ -99,3 +99,18 @@ def test_many_pairs(ctx, n, nk, mbsz):
 def test_few_rows(ctx, seq, mbsz, n, d, causal, nk):
     import test_gpu_kernels
     test_gpu_kernels.test_attention_forward_backward(ctx, "f32", seq, mbsz, n, d, causal, nk)
+
+
+# few workgroups take row dot, dQ and dK / dV in one launch: at its limit of 256 of them (two blocks of a sequence, 2 * 64 heads), and the same
+# sequences among more, where each has a launch of its own
+@pytest.mark.parametrize("seq,n,nk,d,causal,mbsz", [(64, 64, 64, 64, True, 1), (128, 4, 4, 64, True, 1), (104, 2, 2, 24, False, 2), (200, 4, 2, 32, True, 1),
+                                                    (96, 6, 2, 104, False, 1), (256, 8, 8, 128, True, 1), (48, 4, 4, 16, True, 1)])
+def test_one_launch_has_the_bits_of_three(ctx, seq, n, nk, d, causal, mbsz):
+    g = torch.Generator(device="cuda").manual_seed(seq)
+    many = mbsz + 256 // (n + nk)
+    qkv = torch.randn((many * seq, (n + 2 * nk) * d), generator=g, device="cuda")
+    dout = torch.randn((many * seq, n * d), generator=g, device="cuda")
+    few = attention(ctx, n, nk, d, seq, mbsz, causal, qkv[:mbsz * seq].contiguous(), dout[:mbsz * seq].contiguous())
+    got = attention(ctx, n, nk, d, seq, many, causal, qkv, dout)
+    for name in ("out", "dq", "dk", "dv"):
+        assert torch.equal(got[name][:mbsz * seq], few[name]), name
