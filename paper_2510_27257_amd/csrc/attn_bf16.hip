@@ -21,7 +21,7 @@
 // its B operand (O^T += V^T P^T), so P never touches LDS.  V^T fragments come from the V tile as it
 // lies in memory ([kv][d]) through the transposing LDS read.
 //
-// Schedule.  A step of a wave is a matrix phase M(k) = { S(k+1) = K(k+1) Q^T ; O += V(k)^T P(k) } and
+// Schedule (head dimension 64 with eight waves: see qk_pv_exps).  A step of a wave is a matrix phase M(k) = { S(k+1) = K(k+1) Q^T ; O += V(k)^T P(k) } and
 // a vector phase V(k) = { P(k) = online softmax of S(k) }, of about equal length.  In iteration k group
 // A runs M(k) then V(k+1) and group B V(k) then M(k), so on every SIMD one wave feeds the matrix pipe
 // while the other does the exponentials; there is one s_barrier per iteration, none between the phases.
@@ -119,6 +119,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
 #endif
   constexpr int RB = G::RB, CPR = G::CPR, RPB = G::RPB, RPI = G::RPI, NLD = G::NLD, TILE = G::TILE, KS = G::KS;
   constexpr int KREADS = 4, VREADS = 2 * (D / 32);   // LDS operations of one fragment group
+  constexpr bool IN_PHASE = D == 64 && HALVES == 2;
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];   // K ring [2][TILE], V ring [2][TILE]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -284,19 +285,24 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
   };
 
   // P(k) = online softmax of S(k) in the log2 domain; accumulator v of lane l is key
-  // kv0 + 32*jb + 8*(v/4) + 4*(l/32) + v%4, query l%32
-  auto softmax_impl = [&](int k, auto masked) {
-    constexpr bool MASK = decltype(masked)::value;
+  // kv0 + 32*jb + 8*(v/4) + 4*(l/32) + v%4, query l%32.
+  // Raw scores are kept; the 1/sqrt(d) log2(e) factor is folded into the exponent's FMA.
+  // First half: the reference of the step.  Only a step that touches the causal diagonal or the end of the sequence needs the mask.
+  auto touches_edge = [&](int k) {
     const int kv0 = (s_begin + k) * KS + half * 64;
-    // raw scores are kept; the 1/sqrt(d) log2(e) factor is folded into the exponent's FMA
-    auto mask_max = [&](f32x16_t &sc, int jb, float mx) {
-      if constexpr (MASK) {
+    return (causal && kv0 + 63 > q_wave0) || (kv0 + 64 > seq);
+  };
+  auto mask_scores = [&](int k, f32x16_t &sc, int jb) {
+    const int kv0 = (s_begin + k) * KS + half * 64;
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const int kv = kv0 + 32 * jb + 8 * (v >> 2) + 4 * lg + (v & 3);
-          sc[v] = ((causal && kv > qg) || kv >= seq) ? -INFINITY : sc[v];
-        }
-      }
+    for (int v = 0; v < 16; v++) {
+      const int kv = kv0 + 32 * jb + 8 * (v >> 2) + 4 * lg + (v & 3);
+      sc[v] = ((causal && kv > qg) || kv >= seq) ? -INFINITY : sc[v];
+    }
+  };
+  auto reference = [&](int k, auto masked) {
+    auto mask_max = [&](f32x16_t &sc, int jb, float mx) {
+      if constexpr (decltype(masked)::value) mask_scores(k, sc, jb);
 #pragma unroll
       for (int v = 0; v < 16; v++) mx = fmaxf(mx, sc[v]);
       return mx;
@@ -312,7 +318,10 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     // error of the output against 64 bits, 16 heads of 64, 1024 keys: two chunks 2.28e-3, one chunk 2.31e-3, with this
     // 2.24e-3; 4 heads of 128, 2048 tokens, causal 2.05e-3, with this 2.00e-3.  Following it all the way takes 2 - 8 % longer.
     // A query row that has seen no admissible key keeps m = -inf.
-    const float m_new = (mx > m + (k * KS < 512 ? 0.0f : 8.0f)) ? mx : m;
+    return (mx > m + (k * KS < 512 ? 0.0f : 8.0f)) ? mx : m;
+  };
+  // l and O to the new reference
+  auto rescale = [&](float m_new) {
     if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
       const float corr = __builtin_amdgcn_exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
       l *= corr;
@@ -322,9 +331,25 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
         for (int v = 0; v < 16; v++) o[i][v] *= corr;
       m = m_new;
     }
+  };
+  // k-slot i of lane-half g in the PV step (jb, t) is key 32*jb + 16*t + 8*(i/4) + 4*g + i%4: elements 8*t .. +7 of sc0 / sc1 (jb) are
+  // the fragment of (jb, t).  Elements v0 .. v0 + c - 1 of sc: exponentials in place / their sum / their fragment p
+  auto exps = [&](f32x16_t &sc, int v0, int c, float neg_ref) {
+#pragma unroll
+    for (int v = v0; v < v0 + c; v++) sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], scale_log2, neg_ref));
+  };
+  auto sums = [&](const f32x16_t &sc, int v0, int c, float &rs) {
+#pragma unroll
+    for (int v = v0; v < v0 + c; v++) rs += sc[v];
+  };
+  auto pack = [&](const f32x16_t &sc, int v0, int c, bf16x8_t &p) {
+#pragma unroll
+    for (int v = v0; v < v0 + c; v++) p[v & 7] = (bf16_t)sc[v];
+  };
+  auto softmax = [&](float m_new) {
+    rescale(m_new);
     const float neg_ref = m == -INFINITY ? 0.f : -m;
     float rs = 0.f;
-    // k-slot i of lane-half g in the PV step (jb, t) is key 32*jb + 16*t + 8*(i/4) + 4*g + i%4
     auto exp_pack = [&](const f32x16_t &sc, bf16x8_t &p0, bf16x8_t &p1) {
 #pragma unroll
       for (int v = 0; v < 16; v++) {
@@ -335,14 +360,52 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     };
     exp_pack(sc0, pf00, pf01);
     exp_pack(sc1, pf10, pf11);
-    rs += other_half(rs);
-    l += rs;
+    l += rs + other_half(rs);
   };
-  // only a step that touches the causal diagonal or the end of the sequence needs the mask
-  auto softmax = [&](int k) {
-    const int kv0 = (s_begin + k) * KS + half * 64;
-    if ((causal && kv0 + 63 > q_wave0) || (kv0 + 64 > seq)) softmax_impl(k, std::true_type{});
-    else softmax_impl(k, std::false_type{});
+
+  // Head dimension 64, eight waves: S(k+1), then O += V(k)^T P(k) with the exponentials of step k+1 between its MFMAs, which take the
+  // probabilities of the step before; both groups at once, so that neither ends a phase after the other.  Alone a wave takes M, then V,
+  // as a chain of latencies, and with 16 MFMAs a step instead of 32 the other wave's phase does not cover them.  Measured (us): 16 heads, 1024
+  // tokens, no mask 16.4 -> 15.4; 8 heads, 4096 tokens, causal 39.9 -> 36.6, 8192 104 -> 97; 4 heads, 12288 124 -> 114; a wave's M | V apart stay where
+  // they are the faster: at dimension 128 (16384 tokens 277 us, in phase 290 - 309; group B half an iteration behind, 303) and for four waves, three
+  // workgroups to a compute unit (16384 tokens 328, in phase 347).  Loads one at a time between the MFMA groups: 0 - 2 % slower than behind the barrier.
+  constexpr int C = 256 / D;           // elements per MFMA of O
+  auto qk_pv_exps = [&](int k) {
+    const unsigned kt = ((k + 1) & 1) * TILE, vt = (k & 1) * TILE;
+    u32x4_t fa[4], fb[4];
+#pragma unroll
+    for (int v = 0; v < 16; v++) { sc0[v] = 0.f; sc1[v] = 0.f; }
+    float rs = 0.f;
+    // behind each MFMA of fragment P: the exponentials of C elements from V0 of S, and PRE, what is left to do with those before
+#define STP_PV(buf, P, S, V0, PRE)                                                                                                 \
+    do {                                                                                                                           \
+      _Pragma("unroll") for (int db = 0; db < D / 32; db++) {                                                                      \
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[db]), P, o[db], 0, 0, 0);                 \
+        STP_SB();                                                                                                                  \
+        exps(S, V0 + db * C, C, neg_ref);                                                                                          \
+        PRE;                                                                                                                       \
+        STP_SB();                                                                                                                  \
+      }                                                                                                                            \
+    } while (0)
+    read_k<D, 0, 0>(fa, kaddr, kt);
+    read_k<D, 1, 0>(fb, kaddr, kt); lds_wait<KREADS>(); lds_tie(fa); mfma_qk<D, 0>(sc0, fa, qf); STP_SB();
+    read_v<D, 0, 0>(fa, vaddr, vt); lds_wait<VREADS>(); lds_tie(fb); mfma_qk<D, 0>(sc1, fb, qf); STP_SB();
+    if (touches_edge(k + 1)) { mask_scores(k + 1, sc0, 0); mask_scores(k + 1, sc1, 1); }
+    const float m_new = reference(k + 1, std::false_type{}), neg_ref = m_new == -INFINITY ? 0.f : -m_new;
+    STP_SB();
+    read_v<D, 0, 1>(fb, vaddr, vt); lds_wait<VREADS>(); lds_tie(fa);
+    STP_PV(fa, pf00, sc0, 0, if (db > 0) sums(sc0, (db - 1) * C, C, rs));
+    read_v<D, 1, 0>(fa, vaddr, vt); lds_wait<VREADS>(); lds_tie(fb);
+    STP_PV(fb, pf01, sc0, 8, sums(sc0, 8 + (db - 1) * C, C, rs); pack(sc0, db * C, C, pf00));
+    read_v<D, 1, 1>(fb, vaddr, vt); lds_wait<VREADS>(); lds_tie(fa);
+    STP_PV(fa, pf10, sc1, 0, if (db > 0) sums(sc1, (db - 1) * C, C, rs); else sums(sc0, 16 - C, C, rs); pack(sc0, 8 + db * C, C, pf01));
+    lds_wait<0>(); lds_tie(fb);
+    STP_PV(fb, pf11, sc1, 8, sums(sc1, 8 + (db - 1) * C, C, rs); pack(sc1, db * C, C, pf10));
+    sums(sc1, 16 - C, C, rs);
+    pack(sc1, 8, 8, pf11);
+    rescale(m_new);
+    l += rs + other_half(rs);
+#undef STP_PV
   };
 
   // ---- main loop.  Iteration k uses tiles K(k+1) and V(k).  At its top every wave's loads have landed
@@ -351,7 +414,10 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
   // coincides with the vector work of the other without a barrier in between.
   const bool last_active = active(ns - 1);      // only the last step of a chunk can be masked out for a wave
   auto vector_phase = [&](int k) {
-    if (k >= 0 && k < ns && (k < ns - 1 || last_active)) softmax(k);
+    if (k >= 0 && k < ns && (k < ns - 1 || last_active)) {
+      if (touches_edge(k)) softmax(reference(k, std::true_type{}));
+      else softmax(reference(k, std::false_type{}));
+    }
   };
   issue_tile(0, false);
   issue_tile(0, true);
@@ -368,7 +434,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     const bool do_qk = k + 1 < ns && (k + 1 < ns - 1 || last_active), do_pv = k >= 0 && (k < ns - 1 || last_active);
     const bool ld_k = k >= 0 && k + 2 < ns, ld_v = k >= 0 && k + 1 < ns;
     // group A starts with the matrix phase: its loads ride behind the MFMA groups
-    const bool defer = half == 0 && do_qk && do_pv;
+    const bool defer = !IN_PHASE && half == 0 && do_qk && do_pv;
     if (k >= 0) {
       STP_SB();
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -378,11 +444,24 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
         if (ld_v) issue_tile(k + 1, true);
       }
     }
-    if (half == 1) vector_phase(k);
-    if (do_qk && do_pv) qk_pv(k + 1, k, defer && ld_k, defer && ld_v);
-    else if (do_qk) qk_only(k + 1);
-    else if (do_pv) pv_only(k);
-    if (half == 0) vector_phase(k + 1);
+    if constexpr (IN_PHASE) {
+      if (do_qk && do_pv) {
+        qk_pv_exps(k);
+      } else {
+        if (do_pv) pv_only(k);
+        if (do_qk) {
+          qk_only(k + 1);
+          if (touches_edge(k + 1)) { mask_scores(k + 1, sc0, 0); mask_scores(k + 1, sc1, 1); }
+          softmax(reference(k + 1, std::false_type{}));
+        }
+      }
+    } else {
+      if (half == 1) vector_phase(k);
+      if (do_qk && do_pv) qk_pv(k + 1, k, defer && ld_k, defer && ld_v);
+      else if (do_qk) qk_only(k + 1);
+      else if (do_pv) pv_only(k);
+      if (half == 0) vector_phase(k + 1);
+    }
   }
 #undef STP_SB
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -592,9 +671,9 @@ int stp_launch_attn_fwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *
 // Cost of a workgroup of the chunked kernels in microseconds (0 forward, 1 dkv, 2 dq): start and end of a workgroup
 // (first tiles, the merge of the wave halves, the partial result) and one step of its main loop, fitted to measured
 // kernel times.  Head dimension 128: chunk lengths 8 .. 32 (16 .. 64 for dkv) at 4 and 10 heads, seq 4096 and 6144, causal,
-// within 6 - 8 % (rms).  Head dimension 64: 256 .. 4096 tokens, 2 .. 32 heads, within 10 %.
+// within 6 - 8 % (rms).  Head dimension 64: 256 .. 4096 tokens, 2 .. 32 heads, within 10 % (forward: with the exponentials among the MFMAs).
 static AttnCost attn_cost(int kind, int head_dim) {
-  static const AttnCost c128[3] = {{11.5, 1.75}, {12.0, 1.90}, {12.0, 2.65}}, c64[3] = {{6.5, 1.30}, {4.5, 1.20}, {4.5, 1.70}};
+  static const AttnCost c128[3] = {{11.5, 1.75}, {12.0, 1.90}, {12.0, 2.65}}, c64[3] = {{5.0, 1.22}, {4.5, 1.20}, {4.5, 1.70}};
   return head_dim == 128 ? c128[kind] : c64[kind];
 }
 // The plan is made for the whole chip, also where other streams' kernels take a part of it: chunk lengths and the four-wave rule
@@ -734,13 +813,23 @@ void plan_fill(const PlanPart &p, stp_attn_plan *plan) {
 // Head dimension 64, forward: four waves a workgroup, which take all the keys of a step in turn instead of sharing them with
 // four others, have no halves to merge and sit three to a compute unit.  A workgroup with a compute unit of its own is slower
 // that way (1.8 us a step), three together are faster (1.2 us a step of one of them): one chunk per block, and the longest
-// block or the sum of all bounds the launch.  Measured (us, eight waves / four): 8 x 8 heads, 520 tokens 16.6 / 14.4; 2 x 16
-// heads, 4096 tokens 112 / 90; 10 heads on 2 x 3000 tokens 46 / 51; 16 heads, 1024 tokens, no mask 16.4 / 19.3.  At head dimension 128
-// (two workgroups a compute unit) it is the slower one wherever there is work for the whole chip (281 / 308 at 16384 tokens).
+// block, the sum of all or what shares a compute unit bounds the launch.  Measured (us, eight waves / four): 2 x 16 heads, 4096 tokens 104 / 92;
+// 14 heads on 2, 8 x 912 tokens, no mask 58 / 47; 8 heads, 16384 tokens 360 / 326; but 8 x 8 heads, 520 tokens 13.9 / 14.4; 8 heads, 5120 tokens, no
+// mask 87 / 101; 6 heads on 3, 13568 tokens 198 / 223.  At head dimension 128 (two workgroups a compute unit) it is the slower one wherever there
+// is work for the whole chip (281 / 308 at 16384 tokens).
 double four_wave_us(const PlanPart &p) {
   double sum = 0.0;
-  for (int x = 0; x < p.nblocks; x++) sum += 2.0 + 1.2 * p.steps[x];
-  return std::max(6.0 + 1.8 * p.max_steps, sum * p.z / PLAN_CUS);
+  std::vector<int> len(p.steps, p.steps + p.nblocks);
+  std::sort(len.begin(), len.end(), std::greater<int>());
+  for (int x : len) sum += 2.0 + 1.2 * x;
+  double t = std::max(6.0 + 1.8 * len[0], sum * p.z / PLAN_CUS);
+  // longest first, a workgroup to the emptiest compute unit: the 257th is the second on one, the 513th the third, the 769th waits
+  const double step[3] = {2.45, 3.25, 4.85};
+  for (int r = 0; r < 3; r++) {
+    const long x = (long)PLAN_CUS * (r + 1) / p.z;      // the block that it belongs to
+    if (x < p.nblocks) t = std::max(t, 6.0 + step[r] * len[x]);
+  }
+  return t;
 }
 
 int max_of(const int *v, int n) { return *std::max_element(v, v + n); }
