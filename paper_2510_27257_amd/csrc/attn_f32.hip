@@ -514,7 +514,9 @@ int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *q
   const float *x = (const float *)qkv, *g = (const float *)dout;
   float *dx = (float *)dqkv;
   const Shape h = shape_of(d);
-  if (one_launch(h)) {
+  // (gradients written over the output are fine behind the row dot, not where other workgroups still read it)
+  const size_t row = (size_t)h.mbsz * h.seq * h.d * sizeof(float), out_end = (size_t)out + row * h.n, dx_end = (size_t)dqkv + row * (h.n + 2 * h.nk);
+  if (one_launch(h) && ((size_t)out >= dx_end || (size_t)dqkv >= out_end)) {
     const float *o = (const float *)out;
     return h.d <= 32 ? launch_bwd<1>(ctx, h, x, lse, g, o, dx, s) : h.d <= 64 ? launch_bwd<2>(ctx, h, x, lse, g, o, dx, s)
                                                                             : launch_bwd<4>(ctx, h, x, lse, g, o, dx, s);

@@ -114,3 +114,18 @@ def test_one_launch_has_the_bits_of_three(ctx, seq, n, nk, d, causal, mbsz):
     got = attention(ctx, n, nk, d, seq, many, causal, qkv, dout)
     for name in ("out", "dq", "dk", "dv"):
         assert torch.equal(got[name][:mbsz * seq], few[name]), name
+
+
+def test_gradients_over_the_output(ctx):
+    n, d, seq = 4, 64, 128
+    g = torch.Generator(device="cuda").manual_seed(2)
+    qkv, dout = (torch.randn((seq, w * n * d), generator=g, device="cuda") for w in (3, 1))
+    want = attention(ctx, n, n, d, seq, 1, True, qkv, dout)
+    desc = stp.make_desc(Workload("w", 64, n, d, 64, seq, 1, dtype="f32", causal=True, kv_heads=n))
+    buf = torch.zeros((seq, 3 * n * d), device="cuda")
+    out = buf.view(-1)[:seq * n * d].view(seq, n * d)
+    lse, delta = (torch.zeros((1, n, seq), device="cuda") for _ in range(2))
+    ctx.attention_forward(desc, qkv, out, lse)
+    ctx.attention_backward(desc, qkv, out, lse, dout, delta, buf)
+    torch.cuda.synchronize()
+    assert torch.equal(buf, torch.cat([want[k] for k in ("dq", "dk", "dv")], 1))
