@@ -355,7 +355,7 @@ int stp_attention_plan(const stp_layer_desc *desc, int kind, int32_t *chunk_step
  * rows with 32-bit byte offsets: seq * (n + 2 n_kv) * d * 2 bytes must stay below 2 GiB (STP_ESHAPE). */
 int stp_attention_forward(stp_ctx *ctx, const stp_layer_desc *desc, const void *qkv, void *ctx_out,
                           float *lse, int lane, void *hip_stream);
-/* dqkv [T, (n + 2 n_kv) d] from dctx [T, n d]; delta is fp32 scratch [mbsz,n,seq]. */
+/* dqkv [T, (n + 2 n_kv) d] from dctx [T, n d]; delta, fp32 [mbsz,n,seq], receives rowsum(dctx * ctx). */
 int stp_attention_backward(stp_ctx *ctx, const stp_layer_desc *desc, const void *qkv, const void *ctx_in,
                            const float *lse, const void *dctx, float *delta, void *dqkv, int lane,
                            void *hip_stream);

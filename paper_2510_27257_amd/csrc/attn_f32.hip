@@ -208,10 +208,10 @@ __device__ __forceinline__ float row_delta(const float (&gf)[2 * DB][8], const f
   return t[0];
 }
 
-// FROM_OUT: delta is formed from the attention output `out`, and not read
+// FROM_OUT: delta is formed from the attention output `out`, and written where it is read otherwise
 template <int DB, int NW, bool FROM_OUT>
 __device__ __forceinline__ void attn_bwd_dq_f32_block(Work w, const float *__restrict__ qkv, const float *__restrict__ lse,
-                                                      const float *__restrict__ dout, const float *__restrict__ out, const float *__restrict__ delta,
+                                                      const float *__restrict__ dout, const float *__restrict__ out, float *__restrict__ delta,
                                                       float *__restrict__ dqkv, int seq, int n, int nk, int d, int causal, float scale, float *red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, lg = lane >> 5;
   const int nblk = (seq + RB - 1) / RB;
@@ -228,6 +228,7 @@ __device__ __forceinline__ void attn_bwd_dq_f32_block(Work w, const float *__res
 #pragma unroll
   for (int c = 0; c < 2 * DB; c++) { row_chunk(qf[c], qrow, c, lg, d); row_chunk(gf[c], grow, c, lg, d); }
   const float D = FROM_OUT ? row_delta<DB>(gf, out + ((size_t)b * seq + qc) * a + head * d, lg, d) : delta[((size_t)b * n + head) * seq + qc];
+  if (FROM_OUT && wave == 0 && lg == 0 && qg < seq) delta[((size_t)b * n + head) * seq + qg] = D;
   f32x16_t dq[DB];
 #pragma unroll
   for (int i = 0; i < DB; i++) zero(dq[i]);
@@ -284,7 +285,8 @@ __device__ __forceinline__ void attn_bwd_dkv_f32_block(Work w, const float *__re
     const int head = kh * group + u / nblk, q0 = (first + u % nblk) * RB;
     const float *qp = base + head * d, *gp = dout + (size_t)b * seq * a + head * d;
     const size_t row = min(q0 + lr, seq - 1);
-    const float *Lr = lse + ((size_t)b * n + head) * seq, *Dr = delta + ((size_t)b * n + head) * seq;
+    const float *Lr = lse + ((size_t)b * n + head) * seq;
+    [[maybe_unused]] const float *Dr = FROM_OUT ? nullptr : delta + ((size_t)b * n + head) * seq;
     float Lrow = 0.f, Drow = 0.f;                            // FROM_OUT: of this lane's query
     if constexpr (FROM_OUT) {
       float gf[2 * DB][8];
@@ -330,7 +332,7 @@ __device__ __forceinline__ void attn_bwd_dkv_f32_block(Work w, const float *__re
 
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
-                                                                  const float *__restrict__ dout, const float *__restrict__ delta,
+                                                                  const float *__restrict__ dout, float *__restrict__ delta,
                                                                   float *__restrict__ dqkv, int seq, int n, int nk, int pairs, int d, int causal,
                                                                   float scale) {
   extern __shared__ __attribute__((aligned(16))) float red[];
@@ -351,15 +353,15 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_f32_kernel(const float *
 template <int DB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_kernel(const float *__restrict__ qkv, const float *__restrict__ lse,
                                                                const float *__restrict__ dout, const float *__restrict__ out,
-                                                               float *__restrict__ dqkv, int seq, int n, int nk, int pairs_kv, int d, int causal,
-                                                               float scale) {
+                                                               float *__restrict__ delta, float *__restrict__ dqkv, int seq, int n, int nk,
+                                                               int pairs_kv, int d, int causal, float scale) {
   extern __shared__ __attribute__((aligned(16))) float red[];
   const int nblk = (seq + RB - 1) / RB, first_dq = nblk * pairs_kv, id = blockIdx.x;
   if (id < first_dq) {
     attn_bwd_dkv_f32_block<DB, NW, true>({id % nblk, id / nblk}, qkv, lse, dout, out, nullptr, dqkv, seq, n, nk, d, causal, scale, red);
   } else {
     const int i = id - first_dq;
-    attn_bwd_dq_f32_block<DB, NW, true>({i % nblk, i / nblk}, qkv, lse, dout, out, nullptr, dqkv, seq, n, nk, d, causal, scale, red);
+    attn_bwd_dq_f32_block<DB, NW, true>({i % nblk, i / nblk}, qkv, lse, dout, out, delta, dqkv, seq, n, nk, d, causal, scale, red);
   }
 }
 
@@ -432,7 +434,7 @@ int launch_fwd(stp_ctx *ctx, const Shape &h, const float *qkv, float *out, float
   });
 }
 template <int DB>
-int launch_dq(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *delta, float *dqkv, hipStream_t s) {
+int launch_dq(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, float *delta, float *dqkv, hipStream_t s) {
   return with_waves<DB>(h.nblk, [&](auto nw) -> int {
     constexpr int NW = decltype(nw)::value;
     auto kern = attn_bwd_dq_f32_kernel<DB, NW>;
@@ -473,7 +475,8 @@ bool one_launch(const Shape &h) {
   return !short_rows(h, 1) && !short_rows(h, 2) && h.nblk * (h.pairs + h.pairs_kv) <= 256 && waves(h.nblk) == waves((long)h.nblk * (h.n / h.nk));
 }
 template <int DB>
-int launch_bwd(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *out, float *dqkv, hipStream_t s) {
+int launch_bwd(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *out, float *delta, float *dqkv,
+               hipStream_t s) {
   return with_waves<DB>(h.nblk, [&](auto nw) -> int {
     constexpr int NW = decltype(nw)::value;
     auto kern = attn_bwd_f32_kernel<DB, NW>;
@@ -482,8 +485,8 @@ int launch_bwd(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse,
       STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of<NW, DB>));
       attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(h.nblk * (h.pairs + h.pairs_kv))), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, lse, dout, out, dqkv, h.seq,
-                       h.n, h.nk, (int)h.pairs_kv, h.d, h.causal, h.scale);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(h.nblk * (h.pairs + h.pairs_kv))), dim3(64 * NW), (lds_of<NW, DB>), s, qkv, lse, dout, out, delta, dqkv,
+                       h.seq, h.n, h.nk, (int)h.pairs_kv, h.d, h.causal, h.scale);
     STP_LAUNCH_CHECK(ctx);
     return STP_OK;
   });
@@ -496,6 +499,8 @@ Shape shape_of(const stp_layer_desc *d) {
 }
 
 }  // namespace
+
+extern "C" int stp_attn_bwd_f32_launches(const stp_layer_desc *d) { return one_launch(shape_of(d)) ? 1 : 3; }
 
 int stp_launch_attn_fwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, void *out, float *lse, hipStream_t s) {
   const float *x = (const float *)qkv;
@@ -518,8 +523,8 @@ int stp_launch_attn_bwd_f32(stp_ctx *ctx, const stp_layer_desc *d, const void *q
   const size_t row = (size_t)h.mbsz * h.seq * h.d * sizeof(float), out_end = (size_t)out + row * h.n, dx_end = (size_t)dqkv + row * (h.n + 2 * h.nk);
   if (one_launch(h) && ((size_t)out >= dx_end || (size_t)dqkv >= out_end)) {
     const float *o = (const float *)out;
-    return h.d <= 32 ? launch_bwd<1>(ctx, h, x, lse, g, o, dx, s) : h.d <= 64 ? launch_bwd<2>(ctx, h, x, lse, g, o, dx, s)
-                                                                            : launch_bwd<4>(ctx, h, x, lse, g, o, dx, s);
+    return h.d <= 32 ? launch_bwd<1>(ctx, h, x, lse, g, o, delta, dx, s) : h.d <= 64 ? launch_bwd<2>(ctx, h, x, lse, g, o, delta, dx, s)
+                                                                                   : launch_bwd<4>(ctx, h, x, lse, g, o, delta, dx, s);
   }
   int rc = stp_launch_rowdot(ctx, d, dout, out, delta, s);
   if (rc != STP_OK) return rc;

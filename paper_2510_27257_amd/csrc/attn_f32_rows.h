@@ -99,7 +99,7 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const float *__restrict__ qkv, 
   float dk0 = 0.f, dk1 = 0.f, dv0 = 0.f, dv1 = 0.f;
   for (int g = 0; g < group; g++) {
     const int head = kh * group + g;
-    const float *Lr = lse + ((size_t)b * n + head) * seq, *Dr = delta + ((size_t)b * n + head) * seq;
+    const float *Lr = lse + ((size_t)b * n + head) * seq, *Dr = out ? nullptr : delta + ((size_t)b * n + head) * seq;
     for (int i = causal ? j : 0; i < seq; i++) {
       const float *qp = base + (size_t)i * ld + head * d;
       const float *dop = dout + ((size_t)b * seq + i) * a + head * d;

@@ -129,3 +129,24 @@ def test_gradients_over_the_output(ctx):
     ctx.attention_backward(desc, qkv, out, lse, dout, delta, buf)
     torch.cuda.synchronize()
     assert torch.equal(buf, torch.cat([want[k] for k in ("dq", "dk", "dv")], 1))
+
+
+# one launch (to the limit of it, a partly empty block, groups of heads, rows computed one by one) and three
+@pytest.mark.parametrize("seq,n,nk,d,causal,mbsz,bad", [(128, 4, 4, 64, True, 1, 0.0), (64, 64, 64, 64, True, 1, 0.0), (168, 2, 1, 104, False, 2, 0.0), (72, 8, 2, 24, True, 1, 0.0),
+                                                        (128, 4, 4, 64, True, 1, float("nan")), (128, 64, 64, 32, True, 2, 0.0), (8, 4, 4, 64, True, 1, 0.0)])
+def test_delta_is_the_row_sum(ctx, seq, n, nk, d, causal, mbsz, bad):
+    g = torch.Generator(device="cuda").manual_seed(seq * n)
+    qkv = torch.randn((mbsz * seq, (n + 2 * nk) * d), generator=g, device="cuda")
+    dout = torch.randn((mbsz * seq, n * d), generator=g, device="cuda")
+    if bad:
+        dout[seq - 1] = bad
+    desc = stp.make_desc(Workload("w", 64, n, d, 64, seq, 1, dtype="f32", causal=causal, kv_heads=nk), mbsz=mbsz)
+    out, dqkv, lse, delta = torch.zeros_like(dout), torch.zeros_like(qkv), torch.zeros((mbsz, n, seq), device="cuda"), torch.full((mbsz, n, seq), 1e9, device="cuda")
+    ctx.attention_forward(desc, qkv, out, lse)
+    ctx.attention_backward(desc, qkv, out, lse, dout, delta, dqkv)
+    torch.cuda.synchronize()
+    terms = (dout.double() * out.double()).view(mbsz, seq, n, d).transpose(1, 2)
+    want = terms.sum(-1)
+    assert torch.equal(want.isnan(), delta.isnan())
+    # d products and sums of 32 bits: at most d roundings of the sum of the terms' sizes
+    assert ((delta.double() - want).abs() <= d * 2.0 ** -24 * terms.abs().sum(-1))[~want.isnan()].all()
