@@ -287,28 +287,23 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
   // P(k) = online softmax of S(k) in the log2 domain; accumulator v of lane l is key
   // kv0 + 32*jb + 8*(v/4) + 4*(l/32) + v%4, query l%32.
   // Raw scores are kept; the 1/sqrt(d) log2(e) factor is folded into the exponent's FMA.
-  // First half: the reference of the step.  Only a step that touches the causal diagonal or the end of the sequence needs the mask.
-  auto touches_edge = [&](int k) {
-    const int kv0 = (s_begin + k) * KS + half * 64;
-    return (causal && kv0 + 63 > q_wave0) || (kv0 + 64 > seq);
-  };
-  auto mask_scores = [&](int k, f32x16_t &sc, int jb) {
-    const int kv0 = (s_begin + k) * KS + half * 64;
+  // Only a step that touches the causal diagonal or the end of the sequence needs the mask.
+  auto first_key = [&](int k) { return (s_begin + k) * KS + half * 64; };
+  auto touches_edge = [&](int k) { return (causal && first_key(k) + 63 > q_wave0) || first_key(k) + 64 > seq; };
+  auto mask = [&](int kv0, f32x16_t &sc, int jb) {
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int kv = kv0 + 32 * jb + 8 * (v >> 2) + 4 * lg + (v & 3);
       sc[v] = ((causal && kv > qg) || kv >= seq) ? -INFINITY : sc[v];
     }
   };
-  auto reference = [&](int k, auto masked) {
-    auto mask_max = [&](f32x16_t &sc, int jb, float mx) {
-      if constexpr (decltype(masked)::value) mask_scores(k, sc, jb);
+  auto largest = [&](const f32x16_t &sc, float mx) {
 #pragma unroll
-      for (int v = 0; v < 16; v++) mx = fmaxf(mx, sc[v]);
-      return mx;
-    };
-    float mx = mask_max(sc0, 0, -INFINITY);
-    mx = mask_max(sc1, 1, mx);
+    for (int v = 0; v < 16; v++) mx = fmaxf(mx, sc[v]);
+    return mx;
+  };
+  // the reference of step k, whose largest score (of this lane's keys) is mx
+  auto reference = [&](int k, float mx) {
     mx = fmaxf(mx, other_half(mx)) * scale_log2;      // scale > 0: max and scaling commute
     // Lazy rescaling: the reference m only moves when the block maximum exceeds it by more than 2^8,
     // so exponentials stay below 256 (harmless in fp32 / bf16) and the O rescale is skipped on almost
@@ -346,8 +341,14 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
 #pragma unroll
     for (int v = v0; v < v0 + c; v++) p[v & 7] = (bf16_t)sc[v];
   };
-  auto softmax = [&](float m_new) {
-    rescale(m_new);
+  // Written so, with the mask beside the search for the maximum, and not built from the pieces above, the kernels whose phases stay apart are compiled
+  // as before the others had them; otherwise four waves a workgroup lose 2 - 4 % here and there (16 heads, 8 x 392 tokens, no mask 16.0 / 16.4 us).
+  auto softmax_impl = [&](int k, auto masked) {
+    constexpr bool MASK = decltype(masked)::value;
+    if constexpr (MASK) mask(first_key(k), sc0, 0);
+    float mx = largest(sc0, -INFINITY);
+    if constexpr (MASK) mask(first_key(k), sc1, 1);
+    rescale(reference(k, largest(sc1, mx)));
     const float neg_ref = m == -INFINITY ? 0.f : -m;
     float rs = 0.f;
     auto exp_pack = [&](const f32x16_t &sc, bf16x8_t &p0, bf16x8_t &p1) {
@@ -362,6 +363,10 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     exp_pack(sc1, pf10, pf11);
     l += rs + other_half(rs);
   };
+  auto softmax = [&](int k) {
+    if (touches_edge(k)) softmax_impl(k, std::true_type{});
+    else softmax_impl(k, std::false_type{});
+  };
 
   // Head dimension 64, eight waves: S(k+1), then O += V(k)^T P(k) with the exponentials of step k+1 between its MFMAs, which take the
   // probabilities of the step before; both groups at once, so that neither ends a phase after the other.  Alone a wave takes M, then V,
@@ -369,8 +374,8 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
   // tokens, no mask 16.4 -> 15.4; 8 heads, 4096 tokens, causal 39.9 -> 36.6, 8192 104 -> 97; 4 heads, 12288 124 -> 114; a wave's M | V apart stay where
   // they are the faster: at dimension 128 (16384 tokens 277 us, in phase 290 - 309; group B half an iteration behind, 303) and for four waves, three
   // workgroups to a compute unit (16384 tokens 328, in phase 347).  Loads one at a time between the MFMA groups: 0 - 2 % slower than behind the barrier.
-  constexpr int C = 256 / D;           // elements per MFMA of O
   auto qk_pv_exps = [&](int k) {
+    constexpr int C = 4;               // scores per MFMA of O: the 8 of a fragment over its two MFMAs
     const unsigned kt = ((k + 1) & 1) * TILE, vt = (k & 1) * TILE;
     u32x4_t fa[4], fb[4];
 #pragma unroll
@@ -379,7 +384,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     // behind each MFMA of fragment P: the exponentials of C elements from V0 of S, and PRE, what is left to do with those before
 #define STP_PV(buf, P, S, V0, PRE)                                                                                                 \
     do {                                                                                                                           \
-      _Pragma("unroll") for (int db = 0; db < D / 32; db++) {                                                                      \
+      _Pragma("unroll") for (int db = 0; db < 2; db++) {                                                                           \
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[db]), P, o[db], 0, 0, 0);                 \
         STP_SB();                                                                                                                  \
         exps(S, V0 + db * C, C, neg_ref);                                                                                          \
@@ -390,8 +395,8 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
     read_k<D, 0, 0>(fa, kaddr, kt);
     read_k<D, 1, 0>(fb, kaddr, kt); lds_wait<KREADS>(); lds_tie(fa); mfma_qk<D, 0>(sc0, fa, qf); STP_SB();
     read_v<D, 0, 0>(fa, vaddr, vt); lds_wait<VREADS>(); lds_tie(fb); mfma_qk<D, 0>(sc1, fb, qf); STP_SB();
-    if (touches_edge(k + 1)) { mask_scores(k + 1, sc0, 0); mask_scores(k + 1, sc1, 1); }
-    const float m_new = reference(k + 1, std::false_type{}), neg_ref = m_new == -INFINITY ? 0.f : -m_new;
+    if (touches_edge(k + 1)) { mask(first_key(k + 1), sc0, 0); mask(first_key(k + 1), sc1, 1); }
+    const float m_new = reference(k + 1, largest(sc1, largest(sc0, -INFINITY))), neg_ref = m_new == -INFINITY ? 0.f : -m_new;
     STP_SB();
     read_v<D, 0, 1>(fb, vaddr, vt); lds_wait<VREADS>(); lds_tie(fa);
     STP_PV(fa, pf00, sc0, 0, if (db > 0) sums(sc0, (db - 1) * C, C, rs));
@@ -414,10 +419,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
   // coincides with the vector work of the other without a barrier in between.
   const bool last_active = active(ns - 1);      // only the last step of a chunk can be masked out for a wave
   auto vector_phase = [&](int k) {
-    if (k >= 0 && k < ns && (k < ns - 1 || last_active)) {
-      if (touches_edge(k)) softmax(reference(k, std::true_type{}));
-      else softmax(reference(k, std::false_type{}));
-    }
+    if (k >= 0 && k < ns && (k < ns - 1 || last_active)) softmax(k);
   };
   issue_tile(0, false);
   issue_tile(0, true);
@@ -451,8 +453,8 @@ __global__ __launch_bounds__(256 * HALVES, 2) void attn_fwd_bf16_kernel(const bf
         if (do_pv) pv_only(k);
         if (do_qk) {
           qk_only(k + 1);
-          if (touches_edge(k + 1)) { mask_scores(k + 1, sc0, 0); mask_scores(k + 1, sc1, 1); }
-          softmax(reference(k + 1, std::false_type{}));
+          if (touches_edge(k + 1)) { mask(first_key(k + 1), sc0, 0); mask(first_key(k + 1), sc1, 1); }
+          softmax_impl(k + 1, std::false_type{});
         }
       }
     } else {
