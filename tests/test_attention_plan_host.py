@@ -132,3 +132,15 @@ def test_backward_workgroups_of_four_waves(n, nk, seq, mbsz, causal, four):
     import ctypes as C
     desc = stp.make_desc(Workload("w", 1024, n, 64, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)
     assert stp.lib().stp_attn_bwd_halves(C.byref(desc)) == (1 if four else 2)
+
+
+# heads, kv heads, head dimension, tokens, sequences, mask -> 0: four waves, 1: eight, phases apart, 2: eight, in phase.  Without a mask two or three steps
+# keep their phases apart where one half of the waves sees a part of the last and the other nothing (129 .. 191 and 257 .. 319 tokens).
+@pytest.mark.parametrize("n,nk,d,seq,mbsz,causal,route", [
+    (4, 4, 64, 128, 1, False, 2), (4, 4, 64, 136, 1, False, 1), (4, 4, 64, 184, 1, False, 1), (4, 4, 64, 192, 1, False, 2), (4, 4, 64, 200, 1, False, 2), (4, 4, 64, 256, 1, False, 2),
+    (4, 4, 64, 264, 1, False, 1), (4, 2, 64, 312, 1, False, 1), (4, 2, 64, 320, 1, False, 2), (4, 4, 64, 328, 1, False, 2), (4, 4, 64, 392, 1, False, 2), (4, 4, 64, 136, 1, True, 2),
+    (4, 4, 128, 136, 1, False, 1), (4, 4, 128, 4096, 1, True, 1), (16, 16, 64, 1024, 1, False, 2), (16, 4, 64, 1000, 4, True, 0), (16, 16, 64, 520, 8, True, 0)])
+def test_forward_route(n, nk, d, seq, mbsz, causal, route):
+    import ctypes as C
+    desc = stp.make_desc(Workload("w", 1024, n, d, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)
+    assert stp.lib().stp_attn_fwd_route(C.byref(desc)) == route
