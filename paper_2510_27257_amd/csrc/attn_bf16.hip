@@ -696,7 +696,7 @@ static AttnCost attn_cost(int kind, int head_dim) {
 // The plan is made for the whole chip, also where other streams' kernels take a part of it: chunk lengths and the four-wave rule
 // below decide in which order a row's keys are added up, and a layer's bits may not depend on what runs beside it.  A plan for 96
 // compute units inside a braided block is 0 - 1 % faster there for the larger layers, 0.8 - 1.5 % slower for ViT layers.
-constexpr int PLAN_CUS = 256;
+constexpr int PLAN_CUS = STP_CUS;
 
 namespace {
 

@@ -143,7 +143,7 @@ __device__ __forceinline__ void store_bf16x4(bf16_t *p, f32x4_t v) {
 // LDS: K [128][D], V [128][D] (resident), then a ring of two stages { Q [64][D], dO [64][D] }, then the
 // ring of { lse [64], delta [64] } (fp32).
 // ---------------------------------------------------------------------------------------------
-template <int D, bool ROPE, int HALVES>
+template <int D, bool ROPE, int HALVES, bool BETWEEN>
 __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ dout,
                                          const float *__restrict__ lse, const float *__restrict__ delta,
                                          float *__restrict__ part, bf16_t *__restrict__ dqkv, int seq, int n, int nk, int causal,
@@ -247,8 +247,6 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
     const unsigned q_kc = stage + qhalf * 32 * RB + kcl, o_kc = q_kc + Q_TILE;
     const unsigned q_lo = stage + qhalf * 32 * RB + trl_lo, q_hi = stage + qhalf * 32 * RB + trl_hi;
     const unsigned o_lo = q_lo + Q_TILE, o_hi = q_hi + Q_TILE;
-    [[maybe_unused]] const float *s_lse = reinterpret_cast<const float *>(smem_raw + OFF_STAT + (k & 1) * 512) + 32 * qhalf;
-    [[maybe_unused]] const float *s_del = s_lse + 64;
 
     // ---- S = Q K^T and dP = dO V^T for 32 queries x 32 keys
     f32x16_t sacc, pacc;
@@ -269,10 +267,10 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
       if constexpr (D == 128) { buf[2] = read_tr<D, 16 * T>(lo, hi, 2); buf[3] = read_tr<D, 16 * T>(lo, hi, 3); } } while (0)
     constexpr int TR_READS = 2 * (D / 32);
     constexpr int RD = REG ? 2 : 4;       // LDS reads of a group
-    if constexpr (D == 64) {
+    if constexpr (BETWEEN) {
       // The exponentials sit between the MFMAs of dP, which do not need them, and dS between those of dV: a short step's chain of latencies
-      // gets shorter.  8 x 8 heads, 520 tokens, causal 26.5 -> 25.4 us, 16 heads, 1024 tokens, no mask 27.3 -> 26.6; from 4096 tokens on 0.99 - 1.01x.
-      // At head dimension 128 (0.985 - 1.015x) and in dQ (0.98 - 1.01x) the same is worth nothing.
+      // gets shorter.  Eight waves (us): 8 heads, 1024 tokens, no mask 26.8 -> 26.4; 8 heads, 216 tokens, causal 12.6 -> 12.0; 87 drawn shapes 2.3 % in the
+      // mean, from 4096 tokens on 0.3 - 1.5 %.  At head dimension 128 (0.985 - 1.015x) and in dQ (0.98 - 1.01x) the same is worth nothing.
       const bool need_mask = (causal && qs0 < kv_wave0 + 31) || qs0 + 32 > seq;
       const unsigned stat = lds0 + OFF_STAT + (k & 1) * 512 + 128 * qhalf + 16 * lg;     // lse of queries 4 lg .. +3 (+ 8 j), delta 256 bytes on
       u32x4_t st[4];
@@ -326,51 +324,57 @@ __device__ __forceinline__ void dkv_body(const bf16_t *__restrict__ qkv, const b
 #undef STP_P1
 #undef STP_ACC1
     } else {
-    STP_RD_S(fa, 0);
-    STP_RD_P(fb, 0); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 0);
-    STP_RD_S(fa, 1); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 0);
-    STP_RD_P(fb, 1); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 1);
-    STP_RD_S(fa, 2); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 1);
-    STP_RD_P(fb, 2); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 2);
-    STP_RD_S(fa, 3); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 2);
-    STP_RD_P(fb, 3); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 3);
-    STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_P(fb, 3);   // first dO^T fragments ride through the vector phase
-
-    // ---- P = exp(S - L), dS = P o (dP - delta); accumulator v of lane l: query qs0 + 8*(v/4) + 4*(l/32) + v%4, key kv_wave0 + l%32
-    bf16x8_t pf[2], sf[2];
-    auto vector_phase = [&](auto masked) {
-      constexpr bool MASK = decltype(masked)::value;
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const f32x4_t L4 = *reinterpret_cast<const f32x4_t *>(s_lse + 8 * j + 4 * lg);
-        const f32x4_t D4 = *reinterpret_cast<const f32x4_t *>(s_del + 8 * j + 4 * lg);
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int v = 4 * j + r;
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2, -L4[r] * LOG2E));
-          if constexpr (MASK) {
-            const int qi = qs0 + 8 * j + 4 * lg + r;
-            p = ((causal && qi < kvg) || qi >= seq) ? 0.f : p;
-          }
-          const float ds = p * (pacc[v] - D4[r]);
-          pf[j >> 1][4 * (j & 1) + r] = (bf16_t)p;
-          sf[j >> 1][4 * (j & 1) + r] = (bf16_t)ds;
-        }
+      const float *s_lse = reinterpret_cast<const float *>(smem_raw + OFF_STAT + (k & 1) * 512) + 32 * qhalf, *s_del = s_lse + 64;
+      STP_RD_S(fa, 0);
+      STP_RD_P(fb, 0); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 0);
+      STP_RD_S(fa, 1); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 0);
+      if constexpr (D == 128) {
+        STP_RD_P(fb, 1); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 1);
+        STP_RD_S(fa, 2); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 1);
+        STP_RD_P(fb, 2); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 2);
+        STP_RD_S(fa, 3); lds_wait<RD>(); lds_tie(fb); STP_P(fb, 2);
+        STP_RD_P(fb, 3); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 3);
+        STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_P(fb, 3);   // first dO^T fragments ride through the vector phase
+      } else {
+        STP_RD_P(fb, 1); lds_wait<RD>(); lds_tie(fa); STP_S(fa, 1);
+        STP_RD_T(fa, o_lo, o_hi, 0); lds_wait<TR_READS>(); lds_tie(fb); STP_P(fb, 1);
       }
-    };
-    if ((causal && qs0 < kv_wave0 + 31) || qs0 + 32 > seq) vector_phase(std::true_type{});
-    else vector_phase(std::false_type{});
-    STP_SB();
 
-    // ---- dV^T[d, kv] += dO^T P ; dK^T[d, kv] += Q^T dS   (k = the 32 queries, two 16-steps)
+      // ---- P = exp(S - L), dS = P o (dP - delta); accumulator v of lane l: query qs0 + 8*(v/4) + 4*(l/32) + v%4, key kv_wave0 + l%32
+      bf16x8_t pf[2], sf[2];
+      auto vector_phase = [&](auto masked) {
+        constexpr bool MASK = decltype(masked)::value;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          const f32x4_t L4 = *reinterpret_cast<const f32x4_t *>(s_lse + 8 * j + 4 * lg);
+          const f32x4_t D4 = *reinterpret_cast<const f32x4_t *>(s_del + 8 * j + 4 * lg);
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            const int v = 4 * j + r;
+            float p = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2, -L4[r] * LOG2E));
+            if constexpr (MASK) {
+              const int qi = qs0 + 8 * j + 4 * lg + r;
+              p = ((causal && qi < kvg) || qi >= seq) ? 0.f : p;
+            }
+            const float ds = p * (pacc[v] - D4[r]);
+            pf[j >> 1][4 * (j & 1) + r] = (bf16_t)p;
+            sf[j >> 1][4 * (j & 1) + r] = (bf16_t)ds;
+          }
+        }
+      };
+      if ((causal && qs0 < kv_wave0 + 31) || qs0 + 32 > seq) vector_phase(std::true_type{});
+      else vector_phase(std::false_type{});
+      STP_SB();
+
+      // ---- dV^T[d, kv] += dO^T P ; dK^T[d, kv] += Q^T dS   (k = the 32 queries, two 16-steps)
 #define STP_ACC(buf, acc, bop) do {                                                                                             \
-      _Pragma("unroll") for (int db = 0; db < D / 32; db++)                                                                      \
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[db]), bop, acc[db], 0, 0, 0);         \
-      STP_SB(); } while (0)
-    STP_RD_T(fb, q_lo, q_hi, 0); lds_wait<TR_READS>(); lds_tie(fa); STP_ACC(fa, dv, pf[0]);
-    STP_RD_T(fa, o_lo, o_hi, 1); lds_wait<TR_READS>(); lds_tie(fb); STP_ACC(fb, dk, sf[0]);
-    STP_RD_T(fb, q_lo, q_hi, 1); lds_wait<TR_READS>(); lds_tie(fa); STP_ACC(fa, dv, pf[1]);
-    lds_wait<0>(); lds_tie(fb); STP_ACC(fb, dk, sf[1]);
+        _Pragma("unroll") for (int db = 0; db < D / 32; db++)                                                                      \
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, buf[db]), bop, acc[db], 0, 0, 0);         \
+        STP_SB(); } while (0)
+      STP_RD_T(fb, q_lo, q_hi, 0); lds_wait<TR_READS>(); lds_tie(fa); STP_ACC(fa, dv, pf[0]);
+      STP_RD_T(fa, o_lo, o_hi, 1); lds_wait<TR_READS>(); lds_tie(fb); STP_ACC(fb, dk, sf[0]);
+      STP_RD_T(fb, q_lo, q_hi, 1); lds_wait<TR_READS>(); lds_tie(fa); STP_ACC(fa, dv, pf[1]);
+      lds_wait<0>(); lds_tie(fb); STP_ACC(fb, dk, sf[1]);
     }
     };
     if constexpr (HALVES == 2) {
@@ -462,7 +466,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(const bf16_t *__restr
   const int item = n_items ? ord.item[blockIdx.y] : 0;
   const int kvb = n_items ? (item & 0xfff) : (int)blockIdx.x, chunk = n_items ? (item >> 12) : (int)blockIdx.y;
   const int bz = n_items ? blockIdx.x : blockIdx.z;
-  dkv_body<D, ROPE, 2>(qkv, dout, lse, delta, part, dqkv, seq, n, nk, causal, max_chunks, chunk_steps, scale, kvb, chunk, bz, rope);
+  dkv_body<D, ROPE, 2, D == 64>(qkv, dout, lse, delta, part, dqkv, seq, n, nk, causal, max_chunks, chunk_steps, scale, kvb, chunk, bz, rope);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -680,7 +684,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(const bf16_t *__restri
 // group, one row after the other.  The two kinds fill each other's idle compute units: their workgroups are few
 // and of unequal length, the dkv ones fewer and longer still under grouped-query attention (5 query heads on one, 3072 tokens:
 // 101 us in two launches, 77 in one).
-template <int D, bool ROPE, int HALVES>
+template <int D, bool ROPE, int HALVES, bool BETWEEN>
 __global__ __launch_bounds__(256 * HALVES) void attn_bwd_fused_kernel(const bf16_t *__restrict__ qkv, const bf16_t *__restrict__ dout,
                                                              const float *__restrict__ lse, const float *__restrict__ delta,
                                                              float *__restrict__ part_kv, float *__restrict__ part_q,
@@ -701,7 +705,7 @@ __global__ __launch_bounds__(256 * HALVES) void attn_bwd_fused_kernel(const bf16
     while (g < group - 1 && g < (int)blockIdx.y && ord.item[blockIdx.y - 1 - g] == item) g++;
     dq_body<D, ROPE, HALVES>(qkv, dout, lse, delta, part_q, dqkv, seq, n, nk, causal, mc_q, ch_q, scale, block, chunk, (int)blockIdx.x * group + g, rope);
   } else {
-    dkv_body<D, ROPE, HALVES>(qkv, dout, lse, delta, part_kv, dqkv, seq, n, nk, causal, mc_kv, ch_kv, scale, block, chunk, blockIdx.x, rope);
+    dkv_body<D, ROPE, HALVES, BETWEEN>(qkv, dout, lse, delta, part_kv, dqkv, seq, n, nk, causal, mc_kv, ch_kv, scale, block, chunk, blockIdx.x, rope);
   }
 #ifdef STP_ATTN_TRACE
   if (trace) {   // per-workgroup life time: start, end, work item
@@ -851,7 +855,7 @@ const stp_attn_plan *fused_plan(stp_ctx *ctx, const stp_layer_desc *d, const stp
   return p;
 }
 
-template <int D, bool ROPE, int HALVES>
+template <int D, bool ROPE, int HALVES, bool BETWEEN>
 int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const float *lse, const void *dout, const float *delta,
                void *dqkv, float *ws, size_t ws_bytes, hipStream_t s) {
   using G = BG<D>;
@@ -866,7 +870,7 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
     return stp_fail(ctx, STP_ESHAPE, "attention backward: one sequence of QKV must span less than 2 GiB%s");
   auto kkv = attn_bwd_dkv_kernel<D, ROPE>;
   auto kq = attn_bwd_dq_kernel<D, ROPE>;
-  auto kf = attn_bwd_fused_kernel<D, ROPE, HALVES>;
+  auto kf = attn_bwd_fused_kernel<D, ROPE, HALVES, BETWEEN>;
   static bool attr_set = false;
   if (!attr_set) {
     STP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_kv));
@@ -923,10 +927,21 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
   return STP_OK;
 }
 
+// Workgroups of four waves that are all on the chip at once, two to a compute unit, take dK / dV with the exponentials among the MFMAs (BETWEEN).  Where more
+// follow, a compute unit's next workgroup comes when one of dQ is through, and beside a denser one of dK / dV that is later (us, apart / among): 8 x 8 heads, 520
+// tokens, no mask 39.1 / 41.9; 12 heads, 4 x 1000 tokens, causal 40.5 / 42.0; 8 x 8 heads, 520 tokens, causal 26.5 / 25.4.  72 shapes in one
+// round: 2.2 % in the mean, 0.99 - 1.05x, but for the causal ones that fill it to the last place (16 heads, 8 x 256 tokens 16.9 / 17.3), which stay apart; 122 in
+// more: 0.7 %, 0.93 - 1.10x.  The bits are the same.
+bool four_wave_one_round(const stp_layer_desc *d) {
+  const long nb = (d->seq + 127) / 128;
+  return nb * d->mbsz * (d->heads_local + stp_kv_heads(d)) <= 2 * STP_CUS - (d->causal ? 1 : 0);
+}
+
 }  // namespace
 
 // 1 where the backward of this layer runs in workgroups of four waves, else 2; host only, no part of the interface (tests check routes)
 extern "C" int stp_attn_bwd_halves(const stp_layer_desc *d) { return bwd_plan(nullptr, d, 1)->halves; }
+extern "C" int stp_attn_bwd_between(const stp_layer_desc *d) { return d->head_dim == 64 && (stp_attn_bwd_halves(d) == 2 || four_wave_one_round(d)); }
 
 const stp_attn_plan *stp_attn_bwd_plan_for(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
   return bwd_plan(ctx, d, kind);
@@ -945,14 +960,17 @@ int stp_launch_attn_bwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *
                              const void *dout, float *delta, void *dqkv, float *ws, size_t ws_bytes, bool rope, hipStream_t s) {
   int rc = stp_launch_rowdot(ctx, d, dout, out, delta, s);
   if (rc != STP_OK) return rc;
-  if (d->head_dim == 128)
-    return rope ? launch_bwd<128, true, 2>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s)
-                : launch_bwd<128, false, 2>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s);
-  if (d->head_dim == 64 && bwd_plan(ctx, d, 1)->halves == 1)
-    return rope ? launch_bwd<64, true, 1>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s)
-                : launch_bwd<64, false, 1>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s);
-  if (d->head_dim == 64)
-    return rope ? launch_bwd<64, true, 2>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s)
-                : launch_bwd<64, false, 2>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s);
+  auto launch = [&](auto dim, auto halves, auto between) {
+    constexpr int D = decltype(dim)::value, HALVES = decltype(halves)::value;
+    constexpr bool BETWEEN = decltype(between)::value;
+    return rope ? launch_bwd<D, true, HALVES, BETWEEN>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s)
+                : launch_bwd<D, false, HALVES, BETWEEN>(ctx, d, qkv, lse, dout, delta, dqkv, ws, ws_bytes, s);
+  };
+  constexpr std::integral_constant<int, 64> d64;
+  constexpr std::integral_constant<int, 1> four_waves;
+  constexpr std::integral_constant<int, 2> eight_waves;
+  if (d->head_dim == 128) return launch(std::integral_constant<int, 128>{}, eight_waves, std::false_type{});
+  if (d->head_dim == 64 && bwd_plan(ctx, d, 1)->halves == 2) return launch(d64, eight_waves, std::true_type{});
+  if (d->head_dim == 64) return four_wave_one_round(d) ? launch(d64, four_waves, std::true_type{}) : launch(d64, four_waves, std::false_type{});
   return stp_fail(ctx, STP_ESHAPE, "bf16 attention needs head_dim 64 or 128%s");
 }

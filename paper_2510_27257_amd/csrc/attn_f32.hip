@@ -472,7 +472,7 @@ int launch_dkv(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse,
 // launch saves.  The bits are the same either way.
 bool one_launch(const Shape &h) {
   auto waves = [](long blocks) { return blocks <= 2 ? blocks : 3; };       // as with_waves groups them
-  return !short_rows(h, 1) && !short_rows(h, 2) && h.nblk * (h.pairs + h.pairs_kv) <= 256 && waves(h.nblk) == waves((long)h.nblk * (h.n / h.nk));
+  return !short_rows(h, 1) && !short_rows(h, 2) && h.nblk * (h.pairs + h.pairs_kv) <= STP_CUS && waves(h.nblk) == waves((long)h.nblk * (h.n / h.nk));
 }
 template <int DB>
 int launch_bwd(stp_ctx *ctx, const Shape &h, const float *qkv, const float *lse, const float *dout, const float *out, float *delta, float *dqkv,

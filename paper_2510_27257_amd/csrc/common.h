@@ -15,6 +15,8 @@ typedef short s16x8_t __attribute__((ext_vector_type(8)));
 
 #define STP_MAX_LAYER_EVENTS 4096
 
+constexpr int STP_CUS = 256;      // compute units of the chip
+
 // Work plan of a chunked attention kernel (forward, dq, dkv).  A workgroup owns one chunk of up to chunk_steps
 // steps of one block (a query block, or a key block for dkv); `order` lists the (block, chunk) pairs, longest
 // first, and the grid is (heads, n_items) so that the dispatcher, which hands out workgroups in grid order,
@@ -321,11 +323,14 @@ int stp_launch_gemm_bf16(stp_ctx *ctx, const stp_gemm_args *a, hipStream_t s);
 int stp_launch_gemm_bf16_wgrads(stp_ctx *ctx, const stp_gemm_args *a, int n, hipStream_t s);
 // tile (bm << 16 | bn) of that launch, 0 where the products are launched apart; host only, no part of the interface (tests check routes)
 extern "C" int stp_wgrad_set_tile(const stp_gemm_args *a, int n);
-// Further host functions for tests of routes and waits, no part of the interface either: the tile of the SwiGLU projections' launch (0: apart), the
-// workgroups of the bf16 attention forward (0: four waves, 1: eight, matrix and vector phases apart, 2: eight, in phase), the wave halves of the attention backward's workgroups, the launches of the fp32 attention backward (1 or 3), the waits of a sequence of braid steps.
+// Further host functions for tests of routes and waits, no part of the interface either: the tile of the SwiGLU projections' launch (0: apart); the
+// workgroups of the bf16 attention forward (0: four waves, 1: eight, matrix and vector phases apart, 2: eight, in phase); the wave halves of the attention
+// backward's workgroups, and whether dK / dV have the exponentials among the MFMAs; the launches of the fp32 attention backward (1 or 3); the waits of a
+// sequence of braid steps.
 extern "C" int stp_swiglu_pair_tile(int M, int N, int K);
 extern "C" int stp_attn_fwd_route(const stp_layer_desc *d);
 extern "C" int stp_attn_bwd_halves(const stp_layer_desc *d);
+extern "C" int stp_attn_bwd_between(const stp_layer_desc *d);
 extern "C" int stp_attn_bwd_f32_launches(const stp_layer_desc *d);
 extern "C" int stp_braid_plan_joins(int n_steps, int mbs, const int32_t *f_mb, const uint8_t *b, const uint8_t *w, const uint8_t *through, const int32_t *slot_of,
                                     int64_t *waits, int cap);

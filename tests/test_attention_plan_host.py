@@ -145,3 +145,12 @@ def test_forward_route(n, nk, d, seq, mbsz, causal, route):
     import ctypes as C
     desc = stp.make_desc(Workload("w", 1024, n, d, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)
     assert stp.lib().stp_attn_fwd_route(C.byref(desc)) == route
+
+
+# dK / dV with the exponentials among the MFMAs: eight waves at head dimension 64; four waves up to 512 workgroups, with the mask 511
+@pytest.mark.parametrize("n,nk,d,seq,mbsz,causal,among", [(16, 16, 64, 1024, 1, False, 1), (16, 16, 64, 256, 8, True, 0), (16, 16, 64, 256, 8, False, 1), (8, 8, 64, 33, 64, False, 0), (8, 8, 64, 520, 8, False, 0),
+                                                          (16, 16, 64, 264, 8, False, 0), (16, 8, 64, 200, 10, True, 1), (16, 8, 64, 200, 11, True, 0), (4, 4, 128, 1024, 1, True, 0)])
+def test_backward_exponentials_among_the_mfmas(n, nk, d, seq, mbsz, causal, among):
+    import ctypes as C
+    desc = stp.make_desc(Workload("w", 1024, n, d, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)
+    assert stp.lib().stp_attn_bwd_between(C.byref(desc)) == among
