@@ -1,5 +1,7 @@
 """fp32 attention: what a query may not see does not reach it, not even as 0 * inf or 0 * NaN; and as many (head, sequence)
 pairs as there may be; and sequences of few rows, which have kernels and workgroups of their own."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -75,6 +77,52 @@ def test_infinite_rows_keep_their_sign(ctx):
     assert (attention(ctx, n, n, d, seq, 1, False, qkv, y)["dv"] == float("inf")).all()
 
 
+def launches(n, nk, d, seq, mbsz, causal):
+    return stp.lib().stp_attn_bwd_f32_launches(C.byref(stp.make_desc(Workload("w", 64, n, d, 64, seq, 1, dtype="f32", causal=causal, kv_heads=nk), mbsz=mbsz)))
+
+
+# the same among so many workgroups that row dot, dQ and dK / dV have a launch each; the sequences without the value keep their bits
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("t", [45, 167])
+@pytest.mark.parametrize("n,nk,d", [(2, 2, 24), (4, 2, 64), (2, 1, 104)])
+def test_rows_behind_the_causal_mask_stay_out_in_three_launches(ctx, n, nk, d, t, bad):
+    seq = 168
+    mbsz = 256 // (6 * (n + nk)) + 1
+    assert launches(n, nk, d, seq, mbsz, True) == 3 and launches(n, nk, d, seq, 1, True) == 1
+    g = torch.Generator(device="cuda").manual_seed(d)
+    qkv = torch.randn((mbsz * seq, (n + 2 * nk) * d), generator=g, device="cuda")
+    dout = torch.randn((mbsz * seq, n * d), generator=g, device="cuda")
+    clean = attention(ctx, n, nk, d, seq, mbsz, True, qkv, dout)
+    a, ak = n * d, nk * d
+    before, after, others = slice(0, t), slice(t + 1, seq), [i for i in range(seq) if i != t]
+    untouched = {"q": {"dq": others, "dk": after, "dv": after}, "k": {"dq": before}, "v": {"dq": before, "dv": slice(0, seq)},
+                 "dout": {"dq": others, "dk": after, "dv": after}}
+    for operand, rows in untouched.items():
+        x, y = qkv.clone(), dout.clone()
+        if operand == "dout":
+            y[t] = bad
+        else:
+            x[t, {"q": slice(0, a), "k": slice(a, a + ak), "v": slice(a + ak, None)}[operand]] = bad
+        got = attention(ctx, n, nk, d, seq, mbsz, True, x, y)
+        for name in ("out", "dq", "dk", "dv"):
+            assert torch.equal(got[name][seq:], clean[name][seq:]), (operand, name)
+        for name, r in rows.items():
+            if clean[name][:seq][r].numel():
+                # as above: rows computed one by one, or in blocks, each within 3e-6 of the exact value
+                assert rel_err(to_host(got[name][:seq][r]), to_host(clean[name][:seq][r])) < 6e-6, (operand, name)
+
+
+def test_infinite_rows_keep_their_sign_in_three_launches(ctx):
+    n, d, seq, mbsz = 2, 40, 72, 24
+    assert launches(n, n, d, seq, mbsz, False) == 3
+    g = torch.Generator(device="cuda").manual_seed(1)
+    qkv = torch.randn((mbsz * seq, 3 * n * d), generator=g, device="cuda")
+    y = torch.randn((mbsz * seq, n * d), generator=g, device="cuda")
+    y[seq - 1] = float("inf")
+    dv = attention(ctx, n, n, d, seq, mbsz, False, qkv, y)["dv"]
+    assert (dv[:seq] == float("inf")).all() and dv[seq:].isfinite().all()
+
+
 # more pairs than a grid's second or third dimension holds (65535), and more than 2^20
 @pytest.mark.parametrize("n,nk,mbsz", [(8, 8, 8250), (64, 1, 16500)])
 def test_many_pairs(ctx, n, nk, mbsz):
@@ -108,6 +156,7 @@ def test_few_rows(ctx, seq, mbsz, n, d, causal, nk):
 def test_one_launch_has_the_bits_of_three(ctx, seq, n, nk, d, causal, mbsz):
     g = torch.Generator(device="cuda").manual_seed(seq)
     many = mbsz + 256 // (n + nk)
+    assert (launches(n, nk, d, seq, mbsz, causal), launches(n, nk, d, seq, many, causal)) == (1, 3)
     qkv = torch.randn((many * seq, (n + 2 * nk) * d), generator=g, device="cuda")
     dout = torch.randn((many * seq, n * d), generator=g, device="cuda")
     few = attention(ctx, n, nk, d, seq, mbsz, causal, qkv[:mbsz * seq].contiguous(), dout[:mbsz * seq].contiguous())
