@@ -834,11 +834,15 @@ void plan_fill(const PlanPart &p, stp_attn_plan *plan) {
 // 14 heads on 2, 8 x 912 tokens, no mask 58 / 47; 8 heads, 16384 tokens 360 / 326; but 8 x 8 heads, 520 tokens 13.9 / 14.4; 8 heads, 5120 tokens, no
 // mask 87 / 101; 6 heads on 3, 13568 tokens 198 / 223.  At head dimension 128 (two workgroups a compute unit) it is the slower one wherever there
 // is work for the whole chip (281 / 308 at 16384 tokens).
-double four_wave_us(const PlanPart &p) {
+double four_wave_us(const PlanPart &p, int seq) {
   double sum = 0.0;
-  std::vector<int> len(p.steps, p.steps + p.nblocks);
-  std::sort(len.begin(), len.end(), std::greater<int>());
-  for (int x : len) sum += 2.0 + 1.2 * x;
+  std::vector<double> len(p.steps, p.steps + p.nblocks);
+  // their tiles are of 64 keys, half a step: 16 heads, 4 x 784 .. 824 tokens, causal 18.4 us, 888 20.4 (eight waves 19.0 and 19.1)
+  if (seq % KSTEP && seq % KSTEP <= 64)
+    for (int x = 0; x < p.nblocks; x++)
+      if (p.steps[x] == (seq + KSTEP - 1) / KSTEP) len[x] -= 0.5;
+  std::sort(len.begin(), len.end(), std::greater<double>());
+  for (double x : len) sum += 2.0 + 1.2 * x;
   double t = std::max(6.0 + 1.8 * len[0], sum * p.z / PLAN_CUS);
   // longest first, a workgroup to the emptiest compute unit: the 257th is the second on one, the 513th the third, the 769th waits
   const double step[3] = {2.45, 3.25, 4.85};
@@ -980,11 +984,10 @@ const stp_attn_plan *fwd_plan(stp_ctx *ctx, const stp_layer_desc *d) {
   PlanPart part = {attn_cost(0, d->head_dim), nqb, d->heads_local * d->mbsz, max_of(steps.data(), nqb), 0, steps.data(),
                    (size_t)(QB * d->head_dim + 2 * QB) * sizeof(float)};
   const double t = plan_chunks(&part, 1);
-  // Eight waves only where they are expected to be shorter by more than the estimates are off: 1 % (16 heads, 4 x 816 tokens, causal 19.0 us, four waves 18.4),
-  // and 6 % where equal long blocks are cut into several pieces, for which the simulation is up to 12 % low (3 heads, 2 x 8856 tokens 195 / 173; 5 heads,
-  // 15160 tokens 425 / 401; but with the estimates 12 % apart 3 heads, 2 x 7568 tokens 134 / 148).
-  const double margin = !d->causal && part.c < part.max_steps ? 1.06 : 1.01;
-  const bool four = d->head_dim == 64 && four_wave_us(part) < margin * t;
+  // Where equal long blocks are cut into several pieces the simulation is up to 12 % low (3 heads, 2 x 8856 tokens 195 us, four waves 173; 5 heads, 15160 tokens
+  // 425 / 401; 7 heads on one, 7632 tokens 162 / 150): there eight waves have to be expected shorter by 3 % (with 4.6 % 5 heads on one, 2 x 3376 tokens 64 / 69).
+  const double margin = !d->causal && part.c < part.max_steps ? 1.03 : 1.0;
+  const bool four = d->head_dim == 64 && four_wave_us(part, d->seq) < margin * t;
   if (four) part.c = part.max_steps;
   plan_fill(part, plan);
   if (four) plan->halves = 1;

@@ -139,7 +139,7 @@ def test_backward_workgroups_of_four_waves(n, nk, seq, mbsz, causal, four):
 @pytest.mark.parametrize("n,nk,d,seq,mbsz,causal,route", [
     (4, 4, 64, 128, 1, False, 2), (4, 4, 64, 136, 1, False, 1), (4, 4, 64, 184, 1, False, 1), (4, 4, 64, 192, 1, False, 2), (4, 4, 64, 200, 1, False, 2), (4, 4, 64, 256, 1, False, 2),
     (4, 4, 64, 264, 1, False, 1), (4, 2, 64, 312, 1, False, 1), (4, 2, 64, 320, 1, False, 2), (4, 4, 64, 328, 1, False, 2), (4, 4, 64, 392, 1, False, 2), (4, 4, 64, 136, 1, True, 2),
-    (3, 3, 64, 8856, 2, False, 0), (7, 1, 64, 7632, 1, False, 0), (16, 16, 64, 816, 4, True, 0), (8, 8, 64, 5120, 1, False, 2), (8, 8, 64, 9904, 1, True, 2),
+    (3, 3, 64, 8856, 2, False, 0), (7, 1, 64, 7632, 1, False, 0), (16, 16, 64, 816, 4, True, 0), (16, 16, 64, 888, 4, True, 2), (5, 1, 64, 3376, 2, False, 2), (8, 8, 64, 5120, 1, False, 2), (8, 8, 64, 9904, 1, True, 2),
     (4, 4, 128, 136, 1, False, 1), (4, 4, 128, 4096, 1, True, 1), (16, 16, 64, 1024, 1, False, 2), (16, 4, 64, 1000, 4, True, 0), (16, 16, 64, 520, 8, True, 0)])
 def test_forward_route(n, nk, d, seq, mbsz, causal, route):
     import ctypes as C
