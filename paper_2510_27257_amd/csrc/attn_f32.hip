@@ -228,7 +228,6 @@ __device__ __forceinline__ void attn_bwd_dq_f32_block(Work w, const float *__res
 #pragma unroll
   for (int c = 0; c < 2 * DB; c++) { row_chunk(qf[c], qrow, c, lg, d); row_chunk(gf[c], grow, c, lg, d); }
   const float D = FROM_OUT ? row_delta<DB>(gf, out + ((size_t)b * seq + qc) * a + head * d, lg, d) : delta[((size_t)b * n + head) * seq + qc];
-  if (FROM_OUT && wave == 0 && lg == 0 && qg < seq) delta[((size_t)b * n + head) * seq + qg] = D;
   f32x16_t dq[DB];
 #pragma unroll
   for (int i = 0; i < DB; i++) zero(dq[i]);
@@ -259,6 +258,8 @@ __device__ __forceinline__ void attn_bwd_dq_f32_block(Work w, const float *__res
                            }))
     for (int i = q0 + wave; i < min(q0 + RB, seq); i += NW)
       attn_bwd_dq_row(qkv, lse, dout, FROM_OUT ? out : nullptr, delta, dqkv, b, head, i, seq, n, nk, d, causal, scale);
+  // (last: loads behind a store wait for it)
+  if (FROM_OUT && wave == 0 && lg == 0 && qg < seq) delta[((size_t)b * n + head) * seq + qg] = D;
 }
 
 // sums over the query heads of the key / value head's group
