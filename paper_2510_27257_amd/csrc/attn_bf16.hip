@@ -813,6 +813,7 @@ double plan_chunks(PlanPart *part, int n) {
 // the (block, chunk) pairs of a part, longest first; equal lengths keep the later blocks first
 void plan_fill(const PlanPart &p, stp_attn_plan *plan) {
   plan->halves = 2;
+  plan->between = 0;
   plan->chunk_steps = p.c;
   plan->max_chunks = (p.max_steps + p.c - 1) / p.c;
   struct Item { int len, block, chunk; };
@@ -884,14 +885,15 @@ stp_attn_plan *stp_attn_plan_slot(stp_ctx *ctx, const int key[8], bool *hit) {
 // tiles and results overlap the other's steps; long blocks gain nothing, and few of them leave waves idle.  Measured (us, row dot
 // included, eight waves / four): 8 x 8 heads, 520 tokens, causal 32.3 / 28.9; 8 x 16 heads, 256 tokens 20.2 / 17.3; 16 x 16 heads, 512 tokens, no
 // mask 114 / 95; 2 x 16 heads, 4096 tokens 290 / 290; 16 heads, 1024 tokens, no mask 27 / 36; 4 heads, 512 tokens 16.4 / 21.1.
-static double four_wave_bwd_us(const PlanPart *p) {
+struct FourWaveBwd { double longest, all; };      // the longest workgroup alone on its compute unit; all of them, shared out evenly
+static FourWaveBwd four_wave_bwd_us(const PlanPart *p) {
   const double fixed = 3.0, step[2] = {1.3, 1.85}, fixed1 = 5.0, step1[2] = {2.0, 2.8};
   double sum = 0.0, longest = 0.0;
   for (int i = 0; i < 2; i++) {
     for (int x = 0; x < p[i].nblocks; x++) sum += p[i].z * (fixed + step[i] * p[i].steps[x]);
     longest = std::max(longest, fixed1 + step1[i] * p[i].max_steps);
   }
-  return std::max(longest, sum / PLAN_CUS);
+  return {longest, sum / PLAN_CUS};
 }
 
 // That bound is blind to a last round of few workgroups: of 691 shapes it would give to four waves (128 .. 8192 tokens, 2 .. 32 heads) they were slower
@@ -955,13 +957,22 @@ static double four_wave_bwd_end(const PlanPart *p) {
   return end;
 }
 
-int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]) {
+int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2], int *between) {
   const int nk = stp_kv_heads(d), D = d->head_dim;
   PlanPart part[2] = {{attn_cost(1, D), nkv, nk * d->mbsz, max_of(steps_kv, nkv), 0, steps_kv, (size_t)2 * 128 * D * sizeof(float)},
                       {attn_cost(2, D), nq, d->heads_local * d->mbsz, max_of(steps_q, nq), 0, steps_q, (size_t)128 * D * sizeof(float)}};
   const double t = plan_chunks(part, 2);
   const bool fits = nkv + d->heads_local / nk * nq <= STP_ATTN_ORDER_CAP;        // one launch for both kinds
-  const bool four = D == 64 && fits && four_wave_bwd_us(part) < 0.97 * t && four_wave_bwd_end(part) < 1.01 * t;
+  const FourWaveBwd us = four_wave_bwd_us(part);
+  const bool four = D == 64 && fits && std::max(us.longest, us.all) < 0.97 * t && four_wave_bwd_end(part) < 1.01 * t;
+  // dK / dV with the exponentials among the MFMAs (head dimension 64): always with eight waves.  With four, a compute unit's next workgroup comes when one
+  // of dQ is through, and beside a denser one of dK / dV that is later (us, apart / among): 8 x 8 heads, 520 tokens, no mask 39.1 / 41.9; 12 heads, 4 x 1000 tokens, causal
+  // 40.5 / 42.0.  So only where all are on the chip at once, two to a compute unit (90 drawn shapes: 3.6 % in the mean, none slower; but the causal ones that fill it
+  // to the last place, 16 heads, 8 x 256 tokens 16.9 / 17.3, stay apart), or where the longest workgroup bounds the launch and not their sum (110 drawn shapes: 2 - 9 %;
+  // 8 x 8 heads, 520 tokens, causal 26.5 / 25.4; 24 heads on 8, 10 x 168 tokens 25.3 / 24.6).  Among the rest 0.93 - 1.10x, 0.5 % in the mean.  The bits are the same.
+  const long groups = (long)nkv * part[0].z + (long)nq * part[1].z;
+  const bool one_round = groups < 2 * PLAN_CUS + (d->causal ? 0 : 1), by_longest = groups > 2 * PLAN_CUS && us.longest > 1.015 * us.all;
+  *between = D == 64 && (!four || one_round || by_longest);
   chunk[0] = four ? part[0].max_steps : part[0].c;
   chunk[1] = four ? part[1].max_steps : part[1].c;
   return four ? 1 : 2;

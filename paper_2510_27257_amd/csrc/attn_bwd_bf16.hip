@@ -813,15 +813,17 @@ const stp_attn_plan *bwd_plan(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
     steps[0][x] = group * (nq - dkv_first_step(x, d->causal));
     steps[1][x] = dq_steps(x, d->seq, d->causal);
   }
-  int chunk[2];
-  const int halves = stp_attn_bwd_chunks(d, nb, steps[0].data(), nb, steps[1].data(), chunk);
+  int chunk[2], between;
+  const int halves = stp_attn_bwd_chunks(d, nb, steps[0].data(), nb, steps[1].data(), chunk, &between);
   stp_attn_plan_fill(plan, chunk[kind - 1], nb, steps[kind - 1].data());
   plan->halves = halves;
+  plan->between = between;
   key[0] += kind == 1 ? 1 : -1;
   stp_attn_plan *other = stp_attn_plan_slot(ctx, key, &hit);
   if (!hit) {
     stp_attn_plan_fill(other, chunk[2 - kind], nb, steps[2 - kind].data());
     other->halves = halves;
+    other->between = between;
   }
   return plan;
 }
@@ -927,21 +929,11 @@ int launch_bwd(stp_ctx *ctx, const stp_layer_desc *d, const void *qkv, const flo
   return STP_OK;
 }
 
-// Workgroups of four waves that are all on the chip at once, two to a compute unit, take dK / dV with the exponentials among the MFMAs (BETWEEN).  Where more
-// follow, a compute unit's next workgroup comes when one of dQ is through, and beside a denser one of dK / dV that is later (us, apart / among): 8 x 8 heads, 520
-// tokens, no mask 39.1 / 41.9; 12 heads, 4 x 1000 tokens, causal 40.5 / 42.0; 8 x 8 heads, 520 tokens, causal 26.5 / 25.4.  72 shapes in one
-// round: 2.2 % in the mean, 0.99 - 1.05x, but for the causal ones that fill it to the last place (16 heads, 8 x 256 tokens 16.9 / 17.3), which stay apart; 122 in
-// more: 0.7 %, 0.93 - 1.10x.  The bits are the same.
-bool four_wave_one_round(const stp_layer_desc *d) {
-  const long nb = (d->seq + 127) / 128;
-  return nb * d->mbsz * (d->heads_local + stp_kv_heads(d)) <= 2 * STP_CUS - (d->causal ? 1 : 0);
-}
-
 }  // namespace
 
 // 1 where the backward of this layer runs in workgroups of four waves, else 2; host only, no part of the interface (tests check routes)
 extern "C" int stp_attn_bwd_halves(const stp_layer_desc *d) { return bwd_plan(nullptr, d, 1)->halves; }
-extern "C" int stp_attn_bwd_between(const stp_layer_desc *d) { return d->head_dim == 64 && (stp_attn_bwd_halves(d) == 2 || four_wave_one_round(d)); }
+extern "C" int stp_attn_bwd_between(const stp_layer_desc *d) { return bwd_plan(nullptr, d, 1)->between; }
 
 const stp_attn_plan *stp_attn_bwd_plan_for(stp_ctx *ctx, const stp_layer_desc *d, int kind) {
   return bwd_plan(ctx, d, kind);
@@ -970,7 +962,11 @@ int stp_launch_attn_bwd_bf16(stp_ctx *ctx, const stp_layer_desc *d, const void *
   constexpr std::integral_constant<int, 1> four_waves;
   constexpr std::integral_constant<int, 2> eight_waves;
   if (d->head_dim == 128) return launch(std::integral_constant<int, 128>{}, eight_waves, std::false_type{});
-  if (d->head_dim == 64 && bwd_plan(ctx, d, 1)->halves == 2) return launch(d64, eight_waves, std::true_type{});
-  if (d->head_dim == 64) return four_wave_one_round(d) ? launch(d64, four_waves, std::true_type{}) : launch(d64, four_waves, std::false_type{});
+  if (d->head_dim == 64) {
+    const stp_attn_plan *plan = bwd_plan(ctx, d, 1);
+    return plan->halves == 2 ? launch(d64, eight_waves, std::true_type{})
+           : plan->between   ? launch(d64, four_waves, std::true_type{})
+                             : launch(d64, four_waves, std::false_type{});
+  }
   return stp_fail(ctx, STP_ESHAPE, "bf16 attention needs head_dim 64 or 128%s");
 }

@@ -29,6 +29,7 @@ struct stp_attn_plan {
   int key[8];          // what the plan was made for (cache tag)
   int chunk_steps, max_chunks, n_items;
   int halves;          // 2 = eight waves share a step's keys (dkv: queries), 1 = four waves take all of them
+  int between;         // backward: dK / dV with the exponentials among the MFMAs
   stp_attn_order order;
 };
 #define STP_ATTN_PLAN_CACHE 12
@@ -369,7 +370,7 @@ static inline int stp_qkv_width(const stp_layer_desc *d) { return (d->heads_loca
 // Chunk lengths {dkv, dq} of the backward kernels, planned together because one launch runs both; steps_*[x] is the number of
 // steps of block x.
 // Returns the number of key or query halves that a workgroup's waves share: 2, or 1 where it has four waves.
-int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2]);
+int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, int nq, const int *steps_q, int chunk[2], int *between);
 // fills in the work order of blocks cut into chunks of `chunk` steps
 void stp_attn_plan_fill(stp_attn_plan *plan, int chunk, int nblocks, const int *steps);
 // the context's (or, without one, the thread's) cache slot for a plan with this tag; *hit says whether it is filled

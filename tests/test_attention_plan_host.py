@@ -147,9 +147,11 @@ def test_forward_route(n, nk, d, seq, mbsz, causal, route):
     assert stp.lib().stp_attn_fwd_route(C.byref(desc)) == route
 
 
-# dK / dV with the exponentials among the MFMAs: eight waves at head dimension 64; four waves up to 512 workgroups, with the mask 511
-@pytest.mark.parametrize("n,nk,d,seq,mbsz,causal,among", [(16, 16, 64, 1024, 1, False, 1), (16, 16, 64, 256, 8, True, 0), (16, 16, 64, 256, 8, False, 1), (8, 8, 64, 33, 64, False, 0), (8, 8, 64, 520, 8, False, 0),
-                                                          (16, 16, 64, 264, 8, False, 0), (16, 8, 64, 200, 10, True, 1), (16, 8, 64, 200, 11, True, 0), (4, 4, 128, 1024, 1, True, 0)])
+# dK / dV with the exponentials among the MFMAs: eight waves at head dimension 64; four waves up to 512 workgroups, with the mask
+# 511, or where the longest bounds the launch
+@pytest.mark.parametrize("n,nk,d,seq,mbsz,causal,among", [(16, 16, 64, 1024, 1, False, 1), (16, 16, 64, 256, 8, True, 0), (16, 16, 64, 256, 8, False, 1), (8, 8, 64, 33, 64, False, 0), (8, 8, 64, 520, 8, False, 0), (8, 8, 64, 520, 8, True, 1),
+                                                          (12, 12, 64, 1000, 4, True, 0), (12, 12, 64, 776, 4, True, 1),
+                                                          (16, 16, 64, 264, 8, False, 0), (16, 8, 64, 200, 10, True, 1), (16, 8, 64, 200, 11, True, 1), (16, 8, 64, 200, 16, True, 0), (4, 4, 128, 1024, 1, True, 0)])
 def test_backward_exponentials_among_the_mfmas(n, nk, d, seq, mbsz, causal, among):
     import ctypes as C
     desc = stp.make_desc(Workload("w", 1024, n, d, 1024, seq, 1, causal=causal, kv_heads=nk), mbsz=mbsz)

@@ -34,7 +34,7 @@ def test_against_fp32(ctx, n, nk, seq, mbsz, causal):  # noqa: F811
         assert rel_err(to_host(dqkv[:, lo:hi]), to_host(ref[:, lo:hi])) < TOL["bf16"]
 
 
-# the exponentials among the MFMAs of dK / dV where all workgroups are on the chip at once, behind them where more follow: the same sums either way.  Blocks
+# the exponentials among the MFMAs of dK / dV, or behind them where more workgroups follow than the chip holds at once: the same sums either way.  Blocks
 # that end inside a tile, a half and a row, groups of heads, both masks
 @pytest.mark.parametrize("n,nk,seq,few,many,causal", [(16, 16, 40, 16, 24, False), (12, 12, 136, 10, 16, True), (16, 8, 200, 10, 16, False), (8, 8, 264, 10, 16, True),
                                                       (12, 12, 520, 4, 8, False)])
