@@ -968,7 +968,7 @@ int stp_attn_bwd_chunks(const stp_layer_desc *d, int nkv, const int *steps_kv, i
   // dK / dV with the exponentials among the MFMAs (head dimension 64): always with eight waves.  With four, a compute unit's next workgroup comes when one
   // of dQ is through, and beside a denser one of dK / dV that is later (us, apart / among): 8 x 8 heads, 520 tokens, no mask 39.1 / 41.9; 12 heads, 4 x 1000 tokens, causal
   // 40.5 / 42.0.  So only where all are on the chip at once, two to a compute unit (90 drawn shapes: 3.6 % in the mean, none slower; but the causal ones that fill it
-  // to the last place, 16 heads, 8 x 256 tokens 16.9 / 17.3, stay apart), or where the longest workgroup bounds the launch and not their sum (110 drawn shapes: 2 - 9 %;
+  // to the last place, 16 heads, 8 x 256 tokens 16.9 / 17.3, stay apart), or where the longest workgroup bounds the launch and not their sum (110 drawn shapes: 2 - 7 %;
   // 8 x 8 heads, 520 tokens, causal 26.5 / 25.4; 24 heads on 8, 10 x 168 tokens 25.3 / 24.6).  Among the rest 0.93 - 1.10x, 0.5 % in the mean.  The bits are the same.
   const long groups = (long)nkv * part[0].z + (long)nq * part[1].z;
   const bool one_round = groups < 2 * PLAN_CUS + (d->causal ? 0 : 1), by_longest = groups > 2 * PLAN_CUS && us.longest > 1.015 * us.all;

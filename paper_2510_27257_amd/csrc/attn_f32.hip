@@ -14,7 +14,7 @@
 // What bounds it: latency.  At 128 tokens and 4 heads of 64 there are 16 workgroups, and a wave works through one or
 // two 32 x 32 blocks (32 + 32 matrix instructions of 64 clocks each in the forward).  One wave per row with a
 // cross-lane reduction per score was a chain of 128 such reductions: forward / dQ / dK dV 91 / 56 / 46 us against
-// 14 / 11 / 15 us.  So few workgroups take row dot, dQ and dK / dV in one launch: 27.0 -> 14.3 us (see one_launch).
+// 10 / 11 / 16 us.  So few workgroups take row dot, dQ and dK / dV in one launch: 27.0 -> 14.3 us (see one_launch).
 #include "attn_f32_rows.h"
 #include <type_traits>
 
