@@ -190,7 +190,8 @@ def test_delta_is_the_row_sum(ctx, seq, n, nk, d, causal, mbsz, bad):
     if bad:
         dout[seq - 1] = bad
     desc = stp.make_desc(Workload("w", 64, n, d, 64, seq, 1, dtype="f32", causal=causal, kv_heads=nk), mbsz=mbsz)
-    out, dqkv, lse, delta = torch.zeros_like(dout), torch.zeros_like(qkv), torch.zeros((mbsz, n, seq), device="cuda"), torch.full((mbsz, n, seq), 1e9, device="cuda")
+    out, dqkv = torch.zeros_like(dout), torch.zeros_like(qkv)
+    lse, delta = torch.zeros((mbsz, n, seq), device="cuda"), torch.full((mbsz, n, seq), 1e9, device="cuda")
     ctx.attention_forward(desc, qkv, out, lse)
     ctx.attention_backward(desc, qkv, out, lse, dout, delta, dqkv)
     torch.cuda.synchronize()
